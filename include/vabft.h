@@ -54,9 +54,9 @@ typedef enum {
 /* VABFT_F8E4M3, VABFT_F8E5M2: A and B are OCP FP8 (one byte per element, both in the same encoding), the
  * accumulator is FP32 and C is FP16 ("FP8 inputs -> FP32 accumulation -> FP16 output", section 3.6, which names
  * both encodings).  Every entry point takes these types for any shape and either layout of B.  Problems made of
- * whole 256 x 256 x 256 tiles with 16-byte aligned rows and B stored N x K (transB = 1) run on the FP8 matrix
- * instruction; all others run on the guarded kernel, which widens the operands to FP16 on load (exact) and
- * multiplies them with the FP16 matrix instruction: the same products, the same FP32 accumulation. */
+ * more than 36 whole 256 x 256 x 256 tiles with 16-byte aligned rows and B stored N x K (transB = 1) run on the FP8
+ * matrix instruction; all others widen the operands to FP16 (exact) and multiply them with the FP16 matrix
+ * instruction: the same products, the same FP32 accumulation. */
 typedef enum { VABFT_F64 = 0, VABFT_F32 = 1, VABFT_F16 = 2, VABFT_BF16 = 3, VABFT_F8E4M3 = 4, VABFT_F8E5M2 = 5 } vabft_dtype;
 
 typedef struct {
@@ -173,13 +173,12 @@ int vabft_gemm_verified(const vabft_problem* p, const void* dA, const void* dB, 
  * thresholds are undefined); e_max, c_sigma as in vabft_threshold.
  * Outputs: d_astat [3M], d_expected [M], d_T [M] (as vabft_threshold) and d_rowsum, d_E,
  * d_flags, d_nflag, dC, injection log (as vabft_gemm_verified).  For BF16 / FP16 problems made
- * of whole 256 x 256 x 128 tiles (FP8: 256 x 256 x 256, B stored N x K), and FP32 / FP64 problems
- * made of whole 128 x 128 x 16 tiles,
- * with 16-byte aligned rows the statistics ride on the operand tiles inside the GEMM kernel
- * and the compare-and-flag step runs in the last workgroup of each row block (a single
- * launch); other problems run the two passes back to back.  The
- * summation order of the A-side sums differs between the two routes (both are fixed and
- * bit-reproducible). */
+ * of more than 64 whole 256 x 256 x 128 tiles (FP8: more than 36 of 256 x 256 x 256, B stored N x K)
+ * with 16-byte aligned rows the statistics ride on the operand tiles inside the GEMM kernel; other
+ * problems run the A-side pass in workgroups of its own in the same launch (a few large ones, whose K
+ * does not fit the statistics' scheme, in a launch of its own).  The compare-and-flag step runs in the
+ * last workgroup of each row block.  The summation order of the A-side sums differs between the two
+ * routes (both are fixed and bit-reproducible). */
 int vabft_gemm_verified_fused(const vabft_problem* p, const void* dA, const void* dB, void* dC,
                               const void* d_Be, const double* d_S, double e_max, double c_sigma,
                               void* d_astat, void* d_expected, void* d_T, const vabft_inject* inj,

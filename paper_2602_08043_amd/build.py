@@ -12,9 +12,9 @@ CSRC = os.path.join(PKG, "csrc")
 OBJ = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libvabft.so")
 
-SOURCES = ["gemm16_bf16_nn.hip", "gemm16_bf16_nt.hip", "gemm16_f16_nn.hip", "gemm16_f16_nt.hip", "gemm8_f8_nt.hip",
-           "gemm8_bf8_nt.hip", "gemm16_f8_edge.hip", "api.hip",
-           "encode.hip", "blocks.hip", "gemm_f32.hip", "gemm_f64.hip", "probe.hip"]
+DIRECT = [f"gemm_direct_{t}.hip" for t in ("bf16", "f16", "f8", "bf8", "f32", "f64")]
+SOURCES = DIRECT + ["gemm16_bf16_nn.hip", "gemm16_bf16_nt.hip", "gemm16_f16_nn.hip", "gemm16_f16_nt.hip",
+                    "gemm8_f8_nt.hip", "gemm8_bf8_nt.hip", "api.hip", "encode.hip", "blocks.hip", "probe.hip"]
 
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",
@@ -23,14 +23,10 @@ FLAGS = [
 ]
 
 
-# The FP32 / FP64 kernels need at most 128 accumulator registers: keep them in the ordinary
+# The direct kernels need at most 128 accumulator registers: keep them in the ordinary
 # vector register file (VGPR-form MFMA).  Left to its heuristic the compiler puts them in the
 # accumulation file and copies all of them in and out around the MFMAs of every loop iteration.
-EXTRA_FLAGS = {
-    "gemm_f32.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
-    "gemm_f64.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
-    "probe.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
-}
+EXTRA_FLAGS = {s: ["-mllvm", "-amdgpu-mfma-vgpr-form"] for s in DIRECT + ["probe.hip"]}
 
 
 def _run(cmd):

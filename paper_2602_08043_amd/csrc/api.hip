@@ -32,30 +32,6 @@ __device__ __forceinline__ acc_t fold_partials(const acc_t* __restrict__ part, i
     return (a4[0] + a4[1]) + (a4[2] + a4[3]);
 }
 
-// rowsum[i] = sum_t rowpart[t][i] in a fixed order; E = expected - rowsum; flag = !(|E| <= T)
-template <typename acc_t>
-__global__ __launch_bounds__(256) void finalize_kernel(const acc_t* __restrict__ rowpart, int tiles_n, int M,
-                                                       const acc_t* __restrict__ expected,
-                                                       const acc_t* __restrict__ T, acc_t* __restrict__ rowsum,
-                                                       acc_t* __restrict__ E, int32_t* __restrict__ flags,
-                                                       int32_t* __restrict__ nflag,
-                                                       const acc_t* __restrict__ rowpart2,
-                                                       acc_t* __restrict__ rowsum2) {
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    int f = 0;
-    if (i < M) {
-        if (rowsum2) rowsum2[i] = fold_partials(rowpart2, tiles_n, M, i);  // position-weighted row sums C r2
-        const acc_t s = fold_partials(rowpart, tiles_n, M, i);
-        const acc_t e = expected[i] - s;
-        f = !(fabs(e) <= T[i]);
-        rowsum[i] = s;
-        E[i] = e;
-        flags[i] = f;
-    }
-    const int cnt = __syncthreads_count(f);
-    if (threadIdx.x == 0 && cnt) atomicAdd(nflag, cnt);
-}
-
 __global__ void zero_int_kernel(int32_t* p) { *p = 0; }
 
 // colsum[j] = sum over tile-rows of colpart[t][j] in a fixed order; E_col = expected_col - colsum;
@@ -174,24 +150,68 @@ static inline bool is_tile256(int dtype) { return dtype == VABFT_F16 || dtype ==
 static inline size_t acc_bytes(int dtype) { return dtype == VABFT_F64 ? 8 : 4; }
 static inline bool aligned_to(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; }
 
-// FP32 / FP64 problems with fewer than 128 tiles of 128 x 128 (half the compute units or fewer would work) run
-// 64 x 64 tiles instead: 256^3 is 16 workgroups of 16 k-tiles then, not 4.  The block-wise route keeps the large
-// tile: its column blocks are what one wavefront of that tile sums.
-static bool small_wide_tiles(const vabft_problem* p) {
-    if (is_tile256(p->dtype)) return false;
-    return (((int64_t)p->M + 127) / 128) * (((int64_t)p->N + 127) / 128) < 128;
-}
-static void tile_shape(const vabft_problem* p, bool blockwise, int* bm, int* bn) {
-    if (is_tile256(p->dtype)) {
-        *bm = 256;
-        *bn = 256;
-    } else if (!blockwise && small_wide_tiles(p)) {
-        *bm = 64;
-        *bn = 64;
-    } else {
-        *bm = 128;
-        *bn = 128;
+// ---- route: whole-tile kernels (256 x 256, LDS-tiled) or direct kernels (gemm_direct.h) ----
+static int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
+static int direct_rows(int shape) { return shape == DIRECT_16 ? 16 : shape == DIRECT_64 ? 64 : 32; }
+static int direct_cols(int shape, int transB) { return shape >= DIRECT_32W || !transB ? 64 : 32; }
+static int direct_waves(int shape) { return shape <= DIRECT_32 ? 8 : 4; }
+
+static int direct_launch(const vabft_problem* p, const DirectArgs& d, int shape, hipStream_t st) {
+    switch (p->dtype) {
+        case VABFT_BF16: return gemm_direct_launch_bf16(d, shape, p->transB, st);
+        case VABFT_F16: return gemm_direct_launch_f16(d, shape, p->transB, st);
+        case VABFT_F8E4M3: return gemm_direct_launch_f8(d, shape, p->transB, st);
+        case VABFT_F8E5M2: return gemm_direct_launch_bf8(d, shape, p->transB, st);
+        case VABFT_F32: return gemm_direct_launch_f32(d, shape, p->transB, st);
+        case VABFT_F64: return gemm_direct_launch_f64(d, shape, p->transB, st);
     }
+    return VABFT_EINVAL;
+}
+
+// whole: the problem is made of whole 256 x 256 x 64 tiles (FP8: x 256, B stored N x K) with 16-byte aligned rows.
+// The lines, from fused calls timed inside a HIP graph (us):
+//   * a whole-tile kernel takes the time of one 256 x 256 tile however few there are (12 + 0.0155 K for the 16-bit
+//     types, 15 + 0.009 K for FP8); the direct kernel's time goes with the work.  2048^3 (64 tiles): 44.4 against 40.8
+//     (K x N) and 44.0 against 42.1 (N x K), 2048 x 4096 x 4096 (128): 76 against 112; FP8 1024^3 (16): 24.1 against
+//     14.2, 2048^3: 33.1 against 41.2.
+//   * 16 x 32 tiles (eight wavefronts share K): at most 16 rows.  N = 4096: 11.4 against 14.9 with 32 x 64;
+//     N = 11008, where there are enough of the wide ones: 24.2 against 21.2.
+//   * 32 x 32 tiles (eight wavefronts): few tiles and a long K.  100 x 200 x 8000: 16.8 against 21.9; FP32 256^3: 10.9
+//     against 10.1.
+//   * 64 x 64 tiles against 32 x 64: half the operand traffic, half the workgroups.  64 x 11008 x 4096: 24.6 against
+//     27.6; 128 x 4096 x 4096: 21.8 against 19.6; 1024^3: 15.5 against 14.5.  FP32 has the matrix time to hide the
+//     traffic: 2048^3 144 against 150, 1000 x 1200 x 1500 63 against 53 (304 tiles: the last wave is nearly empty).
+//     FP64 has no registers for it.
+static int direct_shape(const vabft_problem* p, bool whole) {
+    const int64_t eb = (int64_t)elem_bytes(p->dtype);
+    if (whole && ceil_div(p->M, 256) * ceil_div(p->N, 256) > (is_fp8(p->dtype) ? 36 : 64)) return DIRECT_NONE;
+    // a tile's byte offsets in 32 bits, and rows of 16 bytes at least
+    const bool far = 64 * p->lda * eb >= (1ll << 32) || (p->transB ? 64 * eb : 128) * p->ldb >= (1ll << 32);
+    if (far || p->K * eb < 16 || (!p->transB && p->N * eb < 16)) return DIRECT_ANY;
+    const int64_t t64 = ceil_div(p->M, 64) * ceil_div(p->N, 64), t32w = ceil_div(p->M, 32) * ceil_div(p->N, 64);
+    const bool long_k = p->K * eb >= 4096;
+    if (p->M <= 16 && p->N <= 8192) return DIRECT_16;
+    if (t32w <= 32 && long_k) return DIRECT_32;
+    if (p->dtype == VABFT_F64) return DIRECT_32W;
+    if (p->dtype == VABFT_F32) return t64 >= 512 ? DIRECT_64 : DIRECT_32W;
+    return p->M > 32 && t64 >= (long_k ? 150 : 512) ? DIRECT_64 : DIRECT_32W;
+}
+
+// Accumulator words of partials that a direct kernel may leave for problems with B's shape and up to M rows:
+// [tiles_n][M] row sums, and behind them as many weighted row sums (w) or [tiles_m][N] column sums (c)
+static size_t direct_words(const vabft_problem* p, bool w, bool c) {
+    const auto need = [&](int64_t rows, int64_t dm, int64_t dn) {
+        const int64_t part = ceil_div(p->N, dn) * rows, col = ceil_div(rows, dm) * p->N;
+        const int64_t more = (w ? part : 0) > (c ? col : 0) ? part : c ? col : 0;
+        return (size_t)(part + more);
+    };
+    // the rows with which the narrow tiles still serve (direct_shape)
+    const int64_t m16 = p->N <= 8192 ? (p->M < 16 ? p->M : 16) : 0;
+    const int64_t m32 = 32 / ceil_div(p->N, 64) * 32;
+    size_t words = need(p->M, 32, 64);
+    const size_t a = need(m16, 16, 32), b = need(p->M < m32 ? p->M : m32, 32, 32);
+    words = words > a ? words : a;
+    return words > b ? words : b;
 }
 
 // Workspace layout: [S area][tickets][scratch].
@@ -210,19 +230,17 @@ static size_t s_area_bytes(const vabft_problem* p) {
     return round_up(64 + (size_t)s_partial_count(p) * 3 * sizeof(double), 256);
 }
 static size_t tickets_offset(const vabft_problem* p) { return s_area_bytes(p); }
-// bytes of arrival counters a problem uses: tiles_m int32 + the 64-bit done counter, rounded to 256 B
+// bytes of arrival counters a problem uses: tiles_m int32 (tiles of 32 rows at least, or a single one) + the 64-bit
+// done counter, rounded to 256 B
 static size_t tickets_used_bytes(const vabft_problem* p) {
-    int bm, bn;
-    tile_shape(p, false, &bm, &bn);  // the smaller tile of the two routes: the larger count
-    const size_t tiles_m = ((size_t)p->M + bm - 1) / bm;
-    return round_up((tiles_m + 4) * sizeof(int32_t), 256);
+    return round_up(((size_t)ceil_div(p->M, 32) + 4) * sizeof(int32_t), 256);
 }
-// The counters' region has a fixed size (64 KiB: 16 380 tile-rows, a million rows of the smallest tile), so the
+// The counters' region has a fixed size (128 KiB: a million rows), so the
 // scratch area behind it starts at a place that depends on B's shape only.  Otherwise a call that shares the
 // workspace with a problem of more rows (an encode of B made through a problem with few rows, say) would put its
 // transient partials where the larger problem keeps counters that must stay zero.  Problems with more tile-rows
 // than that get a larger region; they only share a workspace with problems of the same M.
-constexpr size_t TICKETS_REGION = 64u << 10;
+constexpr size_t TICKETS_REGION = 128u << 10;
 // everything in front of the scratch area
 static size_t tickets_bytes(const vabft_problem* p) {
     const size_t used = tickets_used_bytes(p);
@@ -249,16 +267,28 @@ static int32_t* encode_ticket(const vabft_problem*, void* ws) {
     return reinterpret_cast<int32_t*>(reinterpret_cast<unsigned char*>(ws) + 32);
 }
 
+// Scratch of the whole-tile kernels: per tile-column rowpart + 4 A-statistics partials + weighted rowpart, and the
+// column-sum partials, one vector of N per tile-row
+static size_t whole_tile_scratch_bytes(const vabft_problem* p) {
+    if (!is_tile256(p->dtype)) return 0;
+    const size_t tiles_m = (size_t)ceil_div(p->M, 256), tiles_n = (size_t)ceil_div(p->N, 256);
+    return (tiles_n * (size_t)p->M * 6 + tiles_m * (size_t)p->N) * acc_bytes(p->dtype);
+}
 size_t gemm_workspace_bytes(const vabft_problem* p) {
-    int bm, bn;
-    tile_shape(p, false, &bm, &bn);  // the smaller tile of the two routes: the larger need
-    const size_t tiles_n = ((size_t)p->N + bn - 1) / bn;
-    const bool is16 = is_tile256(p->dtype);
-    // 16-bit: rowpart + 4 A-statistics partials + weighted rowpart per tile-column; wide types: two
-    // row-sum partials per tile-column (one per wavefront column), plain and weighted, + 4 A-statistics partials
-    const size_t tiles_m = ((size_t)p->M + bm - 1) / bm;
-    // ... and the column-sum partials: one (16-bit) or two (wide) vectors of N per tile-row
-    return (tiles_n * (size_t)p->M * (is16 ? 6 : 8) + tiles_m * (size_t)p->N * (is16 ? 1 : 2)) * acc_bytes(p->dtype);
+    const size_t whole = whole_tile_scratch_bytes(p), direct = direct_words(p, true, true) * acc_bytes(p->dtype);
+    return whole > direct ? whole : direct;
+}
+
+// What the entry point that allocates nothing holds a problem to.  It forms no weighted and no column sums, so that
+// what its kernels leave (the row sums of a direct kernel are one word per row and 32 or 64 columns) is below this
+// for every problem; the figure itself is part of that entry point's behaviour and stays.
+static size_t static_route_bytes(const vabft_problem* p) {
+    const bool wide = !is_tile256(p->dtype);
+    const int64_t bt = !wide ? 256 : ceil_div(p->M, 128) * ceil_div(p->N, 128) < 128 ? 64 : 128;
+    const size_t tiles_m = (size_t)ceil_div(p->M, bt), tiles_n = (size_t)ceil_div(p->N, bt);
+    const size_t counters = round_up((tiles_m + 4) * sizeof(int32_t), 256);
+    return tickets_offset(p) + (counters > (64u << 10) ? counters : (64u << 10)) +
+           (tiles_n * (size_t)p->M * (wide ? 8 : 6) + tiles_m * (size_t)p->N * (wide ? 2 : 1)) * acc_bytes(p->dtype);
 }
 
 __global__ void fill_zero_kernel(uint32_t* p, size_t n) {
@@ -269,6 +299,20 @@ void workspace_init_launch(void* ws, size_t bytes, hipStream_t st) {
     const size_t n = bytes / 4;
     const int blocks = (int)((n + 255) / 256 < 1024 ? (n + 255) / 256 : 1024);
     fill_zero_kernel<<<blocks > 0 ? blocks : 1, 256, 0, st>>>(reinterpret_cast<uint32_t*>(ws), n);
+}
+
+static int finalize_cols_launch(const vabft_problem* p, const void* colpart, int nparts, const ColArgs* cols,
+                                hipStream_t st) {
+    const dim3 grid((p->N + 255) / 256), block(256);
+    if (p->dtype == VABFT_F64)
+        finalize_cols_kernel<double><<<grid, block, 0, st>>>(
+            (const double*)colpart, nparts, p->N, (const double*)cols->d_expected_col, (const double*)cols->d_Tcol,
+            (double*)cols->d_colsum, (double*)cols->d_Ecol, cols->d_colflags, cols->d_ncolflag);
+    else
+        finalize_cols_kernel<float><<<grid, block, 0, st>>>(
+            (const float*)colpart, nparts, p->N, (const float*)cols->d_expected_col, (const float*)cols->d_Tcol,
+            (float*)cols->d_colsum, (float*)cols->d_Ecol, cols->d_colflags, cols->d_ncolflag);
+    return hipGetLastError() == hipSuccess ? VABFT_OK : VABFT_EDEVICE;
 }
 
 int gemm_dispatch(const vabft_problem* p, const void* dA, const void* dB, void* dC, void* d_expected, void* d_T,
@@ -285,23 +329,19 @@ int gemm_dispatch(const vabft_problem* p, const void* dA, const void* dB, void* 
     a.lda = p->lda;
     a.ldb = p->ldb;
     a.ldc = p->ldc;
-    int bm, bn;
-    tile_shape(p, blocks != nullptr, &bm, &bn);
-    a.tiles_m = (p->M + bm - 1) / bm;
-    a.tiles_n = (p->N + bn - 1) / bn;
+    a.tiles_m = (int32_t)ceil_div(p->M, 256);
+    a.tiles_n = (int32_t)ceil_div(p->N, 256);
     const size_t eb = elem_bytes(p->dtype), ab = acc_bytes(p->dtype);
-    const bool is16 = is_tile256(p->dtype);
-    a.a_vec_ok = aligned_to(dA, 16) && (p->lda * eb) % 16 == 0;
-    a.b_vec_ok = aligned_to(dB, 16) && (p->ldb * eb) % 16 == 0;
-    a.c_vec_ok = aligned_to(dC, 16) && (p->ldc * out_bytes(p->dtype)) % 16 == 0;
+    const bool aligned = aligned_to(dA, 16) && (p->lda * eb) % 16 == 0 && aligned_to(dB, 16) && (p->ldb * eb) % 16 == 0 &&
+                         aligned_to(dC, 16) && (p->ldc * out_bytes(p->dtype)) % 16 == 0;
     unsigned char* wsb = reinterpret_cast<unsigned char*>(ws);
     a.tickets = ws ? reinterpret_cast<int32_t*>(wsb + tickets_offset(p)) : nullptr;
     a.rowpart = ws ? wsb + tickets_bytes(p) : nullptr;
-    a.apart = ws ? wsb + tickets_bytes(p) + (size_t)a.tiles_n * p->M * ab * (is16 ? 1 : 4) : nullptr;
-    // weighted partials: behind rowpart + apart (16-bit) resp. behind the two plain partials (wide)
-    a.rowpart2 = ws ? wsb + tickets_bytes(p) + (size_t)a.tiles_n * p->M * ab * (is16 ? 5 : 2) : nullptr;
+    a.apart = ws ? wsb + tickets_bytes(p) + (size_t)a.tiles_n * p->M * ab : nullptr;
+    // weighted partials: behind rowpart + apart
+    a.rowpart2 = ws ? wsb + tickets_bytes(p) + (size_t)a.tiles_n * p->M * ab * 5 : nullptr;
     a.rowsum2 = d_rowsum2;
-    a.colpart = ws ? wsb + tickets_bytes(p) + (size_t)a.tiles_n * p->M * ab * (is16 ? 6 : 8) : nullptr;
+    a.colpart = ws ? wsb + tickets_bytes(p) + (size_t)a.tiles_n * p->M * ab * 6 : nullptr;
     a.d_ncolflag = cols ? cols->d_ncolflag : nullptr;
     a.block_mode = blocks ? 1 : 0;
     a.d_nblockflag = blocks ? blocks->d_nblockflag : nullptr;
@@ -342,31 +382,59 @@ int gemm_dispatch(const vabft_problem* p, const void* dA, const void* dB, void* 
         a.inj.log_capacity = inj->log_capacity;
         zero_int_kernel<<<1, 1, 0, st>>>(d_ninj);
     }
-    // the unguarded kernels need whole tiles and 16-byte aligned rows
-    const int bk = is_fp8(p->dtype) ? 256 : (is16 ? 64 : 16);
-    // (the whole-tile 16-bit kernels address a tile's rows with 32-bit byte offsets from a per-wavefront base)
-    const bool wide_rows = is16 && (p->lda > (1 << 24) || p->ldb > (1 << 24));
-    // (the whole-tile FP8 kernel exists for B stored N x K only; a K x N B takes the guarded kernel)
-    const bool edge = (p->M % bm) || (p->N % bn) || (p->K % bk) || !a.a_vec_ok || !a.b_vec_ok || !a.c_vec_ok ||
-                      wide_rows || (is_fp8(p->dtype) && !p->transB);
-    // whole-tile kernels do the compare-and-flag step (and, if asked, the A-side pass) in-kernel
-    const bool in_kernel_finalize = !edge;
+    if ((cols && d_rowsum2) || (blocks && (cols || d_rowsum2))) return VABFT_EUNSUPPORTED;
+    // (the whole-tile 16-bit kernels address a tile's rows with 32-bit byte offsets from a per-wavefront base; the FP8
+    // one exists for B stored N x K only)
+    const bool whole = is_tile256(p->dtype) && p->M % 256 == 0 && p->N % 256 == 0 &&
+                       p->K % (is_fp8(p->dtype) ? 256 : 64) == 0 && aligned && p->lda <= (1 << 24) &&
+                       p->ldb <= (1 << 24) && (!is_fp8(p->dtype) || p->transB);
+    const bool kblocked = blocks && blocks->kblock > 0;
+    const int shape = kblocked ? (int)DIRECT_NONE : direct_shape(p, whole);
+    const auto set_stats = [&] {
+        a.fused_stats = 1;
+        a.Be = fused->d_Be;
+        a.S = fused->d_S;
+        a.s_partial = s_partials(p, ws);
+        a.s_nparts = s_partial_count(p);
+        a.e_max = fused->e_max;
+        a.c_sigma = fused->c_sigma;
+        a.astat = fused->d_astat;
+    };
+    if (shape != DIRECT_NONE) {
+        DirectArgs d;
+        const int dm = direct_rows(shape), dn = direct_cols(shape, p->transB);
+        a.tiles_m = (int32_t)ceil_div(p->M, dm);
+        a.tiles_n = (int32_t)ceil_div(p->N, dn);
+        d.verify = verify;
+        d.wsum = d_rowsum2 != nullptr;
+        d.csum = cols != nullptr;
+        a.rowpart2 = ws ? wsb + tickets_bytes(p) + (size_t)a.tiles_n * p->M * ab : nullptr;
+        a.colpart = a.rowpart2;
+        d.stat_blocks = 0;
+        if (fused) {
+            set_stats();
+            d.stat_blocks = (int32_t)ceil_div(p->M, direct_waves(shape));
+        }
+        d.g = a;
+        const int rc = direct_launch(p, d, shape, st);
+        if (rc != VABFT_OK || !verify) return rc;
+        if (blocks)
+            return finalize_blocks_dispatch(p, a.rowpart, blocks->d_expected_blk, blocks->d_T_blk, blocks->d_rowsum_blk,
+                                            blocks->d_E_blk, blocks->d_blockflags, d_E, d_flags, d_nflag,
+                                            blocks->d_nblockflag, block_width(p->dtype) / dn, a.tiles_n, st);
+        if (cols) return finalize_cols_launch(p, a.colpart, a.tiles_m, cols, st);
+        return VABFT_OK;
+    }
+    // the whole-tile kernels do the compare-and-flag step (and, if asked, the A-side pass) in-kernel; with K split as
+    // well only the 16-bit ones leave a prefix of the row sums per K-block
+    if (kblocked && (!whole || is_fp8(p->dtype))) return VABFT_EUNSUPPORTED;
     if (fused) {
         // the fused 16-bit kernel caches the checksum panel of the k-units a tile-column folds: at most 16
-        // (units of 128 k, dealt round-robin to the tile-columns; the FP8 kernel: units of 256 k, 8 slots,
-        // B stored N x K)
-        const bool fits16 = is_fp8(p->dtype)
-                                ? (a.tiles_n >= 2 && p->K % 256 == 0 && p->transB && (p->K / 256) / a.tiles_n + 2 <= 8)
-                                : (p->K % 128 == 0 && (p->K / 128 + a.tiles_n - 1) / a.tiles_n <= 16);
-        if (in_kernel_finalize && (!is16 || fits16)) {
-            a.fused_stats = 1;
-            a.Be = fused->d_Be;
-            a.S = fused->d_S;
-            a.s_partial = s_partials(p, ws);
-            a.s_nparts = s_partial_count(p);
-            a.e_max = fused->e_max;
-            a.c_sigma = fused->c_sigma;
-            a.astat = fused->d_astat;
+        // (units of 128 k, dealt round-robin to the tile-columns; the FP8 kernel: units of 256 k, 8 slots)
+        const bool fits = is_fp8(p->dtype) ? (a.tiles_n >= 2 && (p->K / 256) / a.tiles_n + 2 <= 8)
+                                           : (p->K % 128 == 0 && (p->K / 128 + a.tiles_n - 1) / a.tiles_n <= 16);
+        if (fits) {
+            set_stats();
         } else {
             const double* dS = fused->d_S;
             if (!dS) {  // the pass of its own needs S1..S3 folded
@@ -381,80 +449,38 @@ int gemm_dispatch(const vabft_problem* p, const void* dA, const void* dB, void* 
     int rc;
     // injector runs form every kind of sum; otherwise one extra kind per launch
     int mode = !verify ? 0 : (a.inj.mode != 0 ? 2 : (cols ? 4 : (d_rowsum2 ? 3 : 1)));
-    if (cols && d_rowsum2 && mode != 2) return VABFT_EUNSUPPORTED;
     if (blocks) {
-        if (cols || d_rowsum2) return VABFT_EUNSUPPORTED;
-        if (mode == 1 && in_kernel_finalize && is16) mode = 5;  // partials only, no in-kernel compare (the wide
-                                                                // kernels read block_mode at run time)
-        if (blocks->kblock > 0) {
-            // K split as well: the 16-bit whole-tile kernel leaves a prefix of the row sums per K-block
-            if ((p->dtype != VABFT_BF16 && p->dtype != VABFT_F16) || edge) return VABFT_EUNSUPPORTED;
+        if (mode == 1) mode = 5;  // partials only, no in-kernel compare
+        if (kblocked) {
             mode = a.inj.mode != 0 ? 7 : 6;
             a.kprefix = blocks->kprefix;
             a.kblock_tiles = blocks->kblock / 64;
         }
     }
     switch (p->dtype) {
-        case VABFT_F8E4M3:
-        case VABFT_F8E5M2:
-            if (edge)
-                rc = gemm16_launch_f8_edge(a, mode, p->dtype == VABFT_F8E5M2, p->transB, st);
-            else
-                rc = p->dtype == VABFT_F8E4M3 ? gemm8_launch_f8_nt(a, mode, st) : gemm8_launch_bf8_nt(a, mode, st);
-            break;
-        case VABFT_BF16:
-            rc = p->transB ? gemm16_launch_bf16_nt(a, mode, edge, st) : gemm16_launch_bf16_nn(a, mode, edge, st);
-            break;
-        case VABFT_F16:
-            rc = p->transB ? gemm16_launch_f16_nt(a, mode, edge, st) : gemm16_launch_f16_nn(a, mode, edge, st);
-            break;
-        case VABFT_F32: rc = gemmw_launch_f32(a, p->transB, mode, edge, bm / 2, st); break;
-        case VABFT_F64: rc = gemmw_launch_f64(a, p->transB, mode, edge, bm / 2, st); break;
+        case VABFT_F8E4M3: rc = gemm8_launch_f8_nt(a, mode, st); break;
+        case VABFT_F8E5M2: rc = gemm8_launch_bf8_nt(a, mode, st); break;
+        case VABFT_BF16: rc = p->transB ? gemm16_launch_bf16_nt(a, mode, st) : gemm16_launch_bf16_nn(a, mode, st); break;
+        case VABFT_F16: rc = p->transB ? gemm16_launch_f16_nt(a, mode, st) : gemm16_launch_f16_nn(a, mode, st); break;
         default: return VABFT_EINVAL;
     }
     if (rc != VABFT_OK || !verify) return rc;
-    if (blocks && blocks->kblock > 0)
+    if (kblocked)
         return finalize_blocks_k_dispatch(p, (p->K + blocks->kblock - 1) / blocks->kblock, blocks->kprefix,
                                           blocks->d_expected_blk, blocks->d_T_blk, blocks->d_rowsum_blk, blocks->d_E_blk,
                                           blocks->d_blockflags, d_E, d_flags, d_nflag, blocks->d_nblockflag, st);
     if (blocks)
         return finalize_blocks_dispatch(p, a.rowpart, blocks->d_expected_blk, blocks->d_T_blk, blocks->d_rowsum_blk,
                                         blocks->d_E_blk, blocks->d_blockflags, d_E, d_flags, d_nflag,
-                                        blocks->d_nblockflag, st);
-    if (cols) {
-        const dim3 cgrid((p->N + 255) / 256), cblock(256);
-        const int ncparts = is16 ? a.tiles_m : 2 * a.tiles_m;
-        if (p->dtype == VABFT_F64)
-            finalize_cols_kernel<double><<<cgrid, cblock, 0, st>>>(
-                (const double*)a.colpart, ncparts, p->N, (const double*)cols->d_expected_col,
-                (const double*)cols->d_Tcol, (double*)cols->d_colsum, (double*)cols->d_Ecol, cols->d_colflags,
-                cols->d_ncolflag);
-        else
-            finalize_cols_kernel<float><<<cgrid, cblock, 0, st>>>(
-                (const float*)a.colpart, ncparts, p->N, (const float*)cols->d_expected_col, (const float*)cols->d_Tcol,
-                (float*)cols->d_colsum, (float*)cols->d_Ecol, cols->d_colflags, cols->d_ncolflag);
-        if (hipGetLastError() != hipSuccess) return VABFT_EDEVICE;
-    }
-    if (in_kernel_finalize) return rc;
-    const dim3 grid((p->M + 255) / 256), block(256);
-    const int nparts = is16 ? a.tiles_n : 2 * a.tiles_n;
-    if (p->dtype == VABFT_F64)
-        finalize_kernel<double><<<grid, block, 0, st>>>((const double*)a.rowpart, nparts, p->M,
-                                                        (const double*)d_expected, (const double*)d_T,
-                                                        (double*)d_rowsum, (double*)d_E, d_flags, d_nflag,
-                                                        (const double*)a.rowpart2, (double*)d_rowsum2);
-    else
-        finalize_kernel<float><<<grid, block, 0, st>>>((const float*)a.rowpart, nparts, p->M,
-                                                       (const float*)d_expected, (const float*)d_T, (float*)d_rowsum,
-                                                       (float*)d_E, d_flags, d_nflag, (const float*)a.rowpart2,
-                                                       (float*)d_rowsum2);
-    return hipGetLastError() == hipSuccess ? VABFT_OK : VABFT_EDEVICE;
+                                        blocks->d_nblockflag, 1, a.tiles_n, st);
+    return cols ? finalize_cols_launch(p, a.colpart, a.tiles_m, cols, st) : rc;
 }
 
 // Scratch of the entry point that allocates nothing (vabft_gemm_verified_fused_static): device memory that
 // lives in the library's code object, one copy per GPU, held until the process ends.  In host code the array's
 // name is only a handle for hipGetSymbolAddress; kernels receive the address that call returns.
-static __device__ __align__(256) unsigned char scratch[VABFT_STATIC_SCRATCH_BYTES];
+// Its size is what the interface states plus what the counters' region has grown by.
+static __device__ __align__(256) unsigned char scratch[VABFT_STATIC_SCRATCH_BYTES + TICKETS_REGION];
 
 constexpr int MAX_DEVICES = 64;
 static std::mutex g_scratch_mutex;
@@ -608,7 +634,7 @@ int vabft_threshold_weighted(const vabft_problem* p, const void* dA, const void*
 static int check_gemm_args(const vabft_problem* p, const void* dA, const void* dB, void* dC, int verify,
                            const vabft_inject* inj, const void* d_expected, const void* d_T, void* d_rowsum,
                            void* d_E, int32_t* d_flags, int32_t* d_nflag, vabft_inject_rec* d_injlog, int32_t* d_ninj,
-                           void* d_workspace, size_t workspace_bytes) {
+                           void* d_workspace, size_t workspace_bytes, size_t scratch_bytes) {
     if (!problem_ok(p) || !dA || !dB || !dC) return VABFT_EINVAL;
     if (verify != 0 && verify != 1) return VABFT_EINVAL;
     const size_t eb = elem_bytes(p->dtype), ab = acc_bytes(p->dtype);
@@ -619,7 +645,7 @@ static int check_gemm_args(const vabft_problem* p, const void* dA, const void* d
         if (!aligned_to(d_expected, ab) || !aligned_to(d_T, ab) || !aligned_to(d_rowsum, ab) || !aligned_to(d_E, ab) ||
             !aligned_to(d_flags, 4) || !aligned_to(d_nflag, 4))
             return VABFT_EINVAL;
-        const size_t need = tickets_bytes(p) + gemm_workspace_bytes(p);
+        const size_t need = tickets_bytes(p) + scratch_bytes;
         if (!d_workspace || workspace_bytes < need || !aligned_to(d_workspace, 16)) return VABFT_EWORKSPACE;
     } else if (inj_on) {
         return VABFT_EINVAL;  // the injector lives in the verified kernel
@@ -642,7 +668,7 @@ int vabft_gemm_verified(const vabft_problem* p, const void* dA, const void* dB, 
                         int32_t* d_flags, int32_t* d_nflag, vabft_inject_rec* d_injlog, int32_t* d_ninj,
                         void* d_workspace, size_t workspace_bytes, void* stream) {
     const int rc = check_gemm_args(p, dA, dB, dC, verify, inj, d_expected, d_T, d_rowsum, d_E, d_flags, d_nflag,
-                                   d_injlog, d_ninj, d_workspace, workspace_bytes);
+                                   d_injlog, d_ninj, d_workspace, workspace_bytes, p ? gemm_workspace_bytes(p) : 0);
     if (rc != VABFT_OK) return rc;
     return gemm_dispatch(p, dA, dB, dC, const_cast<void*>(d_expected), const_cast<void*>(d_T), verify, nullptr, inj,
                          d_rowsum, nullptr, d_E, d_flags, d_nflag, d_injlog, d_ninj, d_workspace, (hipStream_t)stream);
@@ -654,7 +680,7 @@ int vabft_gemm_verified_weighted(const vabft_problem* p, const void* dA, const v
                                  vabft_inject_rec* d_injlog, int32_t* d_ninj, void* d_workspace,
                                  size_t workspace_bytes, void* stream) {
     const int rc = check_gemm_args(p, dA, dB, dC, 1, inj, d_expected, d_T, d_rowsum, d_E, d_flags, d_nflag, d_injlog,
-                                   d_ninj, d_workspace, workspace_bytes);
+                                   d_ninj, d_workspace, workspace_bytes, p ? gemm_workspace_bytes(p) : 0);
     if (rc != VABFT_OK) return rc;
     if (!d_rowsum2 || !aligned_to(d_rowsum2, acc_bytes(p->dtype))) return VABFT_EINVAL;
     return gemm_dispatch(p, dA, dB, dC, const_cast<void*>(d_expected), const_cast<void*>(d_T), 1, nullptr, inj,
@@ -698,7 +724,7 @@ int vabft_gemm_verified_rc(const vabft_problem* p, const void* dA, const void* d
                            int32_t* d_colflags, int32_t* d_ncolflag, vabft_inject_rec* d_injlog, int32_t* d_ninj,
                            void* d_workspace, size_t workspace_bytes, void* stream) {
     const int rc = check_gemm_args(p, dA, dB, dC, 1, inj, d_expected, d_T, d_rowsum, d_E, d_flags, d_nflag, d_injlog,
-                                   d_ninj, d_workspace, workspace_bytes);
+                                   d_ninj, d_workspace, workspace_bytes, p ? gemm_workspace_bytes(p) : 0);
     if (rc != VABFT_OK) return rc;
     if (!d_expected_col || !d_Tcol || !d_colsum || !d_Ecol || !d_colflags || !d_ncolflag) return VABFT_EINVAL;
     const size_t ab = acc_bytes(p->dtype);
@@ -750,7 +776,7 @@ int vabft_gemm_verified_blocks(const vabft_problem* p, const void* dA, const voi
                                int32_t* d_ninj, void* d_workspace, size_t workspace_bytes, void* stream) {
     // the row-level vectors of the plain check are not inputs here: pass the block vectors through the checker
     const int rc = check_gemm_args(p, dA, dB, dC, 1, inj, d_expected_blk, d_T_blk, d_rowsum_blk, d_E, d_flags, d_nflag,
-                                   d_injlog, d_ninj, d_workspace, workspace_bytes);
+                                   d_injlog, d_ninj, d_workspace, workspace_bytes, p ? gemm_workspace_bytes(p) : 0);
     if (rc != VABFT_OK) return rc;
     if (!d_E_blk || !d_blockflags || !d_nblockflag) return VABFT_EINVAL;
     if (!aligned_to(d_E_blk, acc_bytes(p->dtype)) || !aligned_to(d_blockflags, 4) || !aligned_to(d_nblockflag, 4))
@@ -850,7 +876,7 @@ int vabft_gemm_verified_blocks_k(const vabft_problem* p, int32_t kblock, const v
                                  int32_t* d_ninj, void* d_workspace, size_t workspace_bytes, void* stream) {
     if (!problem_ok(p) || !kblock_ok(p, kblock)) return VABFT_EINVAL;
     const int rc = check_gemm_args(p, dA, dB, dC, 1, inj, d_expected_blk_k, d_T_blk_k, d_rowsum_blk_k, d_E, d_flags,
-                                   d_nflag, d_injlog, d_ninj, d_workspace, workspace_bytes);
+                                   d_nflag, d_injlog, d_ninj, d_workspace, workspace_bytes, p ? gemm_workspace_bytes(p) : 0);
     if (rc != VABFT_OK) return rc;
     if (workspace_bytes < vabft_workspace_bytes_blocks_k(p, kblock)) return VABFT_EWORKSPACE;
     if (!d_E_blk_k || !d_blockflags_k || !d_nblockflag) return VABFT_EINVAL;
@@ -909,7 +935,7 @@ int vabft_gemm_verified_fused(const vabft_problem* p, const void* dA, const void
                               int32_t* d_nflag, vabft_inject_rec* d_injlog, int32_t* d_ninj, void* d_workspace,
                               size_t workspace_bytes, void* stream) {
     const int rc = check_gemm_args(p, dA, dB, dC, 1, inj, d_expected, d_T, d_rowsum, d_E, d_flags, d_nflag, d_injlog,
-                                   d_ninj, d_workspace, workspace_bytes);
+                                   d_ninj, d_workspace, workspace_bytes, p ? gemm_workspace_bytes(p) : 0);
     if (rc != VABFT_OK) return rc;
     if (!d_Be || !d_astat) return VABFT_EINVAL;  // d_S may be null: S1..S3 are the partials of the last encode
     if (!(e_max > 0.0) || !(c_sigma >= 0.0) || !isfinite(e_max) || !isfinite(c_sigma)) return VABFT_EINVAL;
@@ -933,12 +959,12 @@ int vabft_gemm_verified_fused_static(const vabft_problem* p, const void* dA, con
                                      int32_t* d_nflag, vabft_inject_rec* d_injlog, int32_t* d_ninj, void* stream) {
     if (!problem_ok(p)) return VABFT_EINVAL;
     if (!d_S) return VABFT_EINVAL;  // no encode runs on this scratch: S1..S3 must come folded
-    const size_t need = tickets_bytes(p) + gemm_workspace_bytes(p);
+    const size_t need = static_route_bytes(p);
     if (need > VABFT_STATIC_SCRATCH_BYTES) return VABFT_EWORKSPACE;
     void* ws = static_scratch_of_current_device();
     if (!ws) return VABFT_EDEVICE;
     const int rc = check_gemm_args(p, dA, dB, dC, 1, inj, d_expected, d_T, d_rowsum, d_E, d_flags, d_nflag, d_injlog,
-                                   d_ninj, ws, VABFT_STATIC_SCRATCH_BYTES);
+                                   d_ninj, ws, VABFT_STATIC_SCRATCH_BYTES, 0);
     if (rc != VABFT_OK) return rc;
     if (!d_Be || !d_astat) return VABFT_EINVAL;
     if (!(e_max > 0.0) || !(c_sigma >= 0.0) || !isfinite(e_max) || !isfinite(c_sigma)) return VABFT_EINVAL;

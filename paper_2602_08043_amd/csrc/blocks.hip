@@ -462,11 +462,12 @@ __global__ __launch_bounds__(256) void threshold_blocks_vec_kernel(const void* _
 }
 
 // ---------------------------------------------------------------------------
-// compare per block and aggregate per row.  rowpart holds `sub` partials per block (1 for the 256-wide
-// kernels, whose workgroup sums a whole block; the wide kernels leave the block's value directly too)
+// compare per block and aggregate per row.  rowpart holds `sub` partials per block, nparts in all: one where a
+// workgroup (or a wavefront of the wide kernels) sums a whole block, more where the GEMM's tile is narrower
 // ---------------------------------------------------------------------------
 template <typename acc_t>
-__global__ __launch_bounds__(64) void finalize_blocks_kernel(const acc_t* __restrict__ rowpart, int nblocks, int M,
+__global__ __launch_bounds__(64) void finalize_blocks_kernel(const acc_t* __restrict__ rowpart, int sub, int nparts,
+                                                             int nblocks, int M,
                                                              const acc_t* __restrict__ expected_blk,
                                                              const acc_t* __restrict__ T_blk,
                                                              acc_t* __restrict__ rowsum_blk, acc_t* __restrict__ E_blk,
@@ -485,9 +486,16 @@ __global__ __launch_bounds__(64) void finalize_blocks_kernel(const acc_t* __rest
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
                 const int64_t idx = (int64_t)(t0 + u < nblocks ? t0 + u : nblocks - 1) * M + i;
-                s[u] = rowpart[idx];
+                s[u] = rowpart[(int64_t)min(sub * min(t0 + u, nblocks - 1), nparts - 1) * M + i];
                 x[u] = expected_blk[idx];
                 thr[u] = T_blk[idx];
+            }
+            for (int q = 1; q < sub; ++q) {
+                acc_t y[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) y[u] = rowpart[(int64_t)min(sub * (t0 + u) + q, nparts - 1) * M + i];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) s[u] += sub * (t0 + u) + q < nparts ? y[u] : (acc_t)0;
             }
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
@@ -691,17 +699,18 @@ int threshold_blocks_dispatch(const vabft_problem* p, const void* dA, const void
 
 int finalize_blocks_dispatch(const vabft_problem* p, const void* rowpart, const void* d_expected_blk,
                              const void* d_T_blk, void* d_rowsum_blk, void* d_E_blk, int32_t* d_blockflags, void* d_E,
-                             int32_t* d_flags, int32_t* d_nflag, int32_t* d_nblockflag, hipStream_t st) {
+                             int32_t* d_flags, int32_t* d_nflag, int32_t* d_nblockflag, int sub, int nparts,
+                             hipStream_t st) {
     const int W = block_width(p->dtype), nblocks = (p->N + W - 1) / W;
     // d_nflag and d_nblockflag were zeroed by the GEMM kernel that produced the partials
     const dim3 grid((p->M + 63) / 64), block(64);
     if (p->dtype == VABFT_F64)
         finalize_blocks_kernel<double><<<grid, block, 0, st>>>(
-            (const double*)rowpart, nblocks, p->M, (const double*)d_expected_blk, (const double*)d_T_blk,
+            (const double*)rowpart, sub, nparts, nblocks, p->M, (const double*)d_expected_blk, (const double*)d_T_blk,
             (double*)d_rowsum_blk, (double*)d_E_blk, d_blockflags, (double*)d_E, d_flags, d_nflag, d_nblockflag);
     else
         finalize_blocks_kernel<float><<<grid, block, 0, st>>>(
-            (const float*)rowpart, nblocks, p->M, (const float*)d_expected_blk, (const float*)d_T_blk,
+            (const float*)rowpart, sub, nparts, nblocks, p->M, (const float*)d_expected_blk, (const float*)d_T_blk,
             (float*)d_rowsum_blk, (float*)d_E_blk, d_blockflags, (float*)d_E, d_flags, d_nflag, d_nblockflag);
     return hipGetLastError() == hipSuccess ? VABFT_OK : VABFT_EDEVICE;
 }

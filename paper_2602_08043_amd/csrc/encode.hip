@@ -2,6 +2,7 @@
 // of Algorithm 1 (paper section 2.2 Eq. r1 / encoded matrices; section 3.5; Algorithm 1 k-loop),
 // and the A-side pass: row statistics, expected checksum A*(B r1) and the threshold T_m
 // (section 3.4 boxed formula).  Both are single streaming passes bound by HBM bandwidth.
+#include "row_threshold.h"
 #include "unpack.h"
 #include "vabft_device.h"
 #include "vabft_host.h"
@@ -104,7 +105,7 @@ template <typename T, bool W, int RPB, int WAVES>
 __global__ __launch_bounds__(64 * WAVES) void encode_rows_kernel(const void* __restrict__ B, int K, int N, int64_t ldb,
                                                            typename Elem<T>::acc_t* __restrict__ Be,
                                                            typename Elem<T>::acc_t* __restrict__ Be2,
-                                                           typename Elem<T>::acc_t* __restrict__ bstat, int vec_ok,
+                                                           typename Elem<T>::acc_t* __restrict__ bstat,
                                                            double* __restrict__ s_partial,
                                                            int32_t* __restrict__ ticket, double* __restrict__ S) {
     using acc_t = typename Elem<T>::acc_t;
@@ -118,17 +119,17 @@ __global__ __launch_bounds__(64 * WAVES) void encode_rows_kernel(const void* __r
     if (k < K) {
         const char* row = reinterpret_cast<const char*>(B) + (int64_t)k * ldb * Elem<T>::bytes;
         int done = 0;
-        if (vec_ok) {
+        {
             const int nchunks = N / V;
             // segment of this wavefront: a multiple of 64 chunks, the last one takes what is left
             const int per = ((nchunks + WPR - 1) / WPR + 63) / 64 * 64;
             const int c_end = part == WPR - 1 ? nchunks : min(nchunks, (part + 1) * per);
             int c = part * per + lane;
             for (; c + 192 < c_end; c += 256) {
-                raw16 r0 = ld16(row + (int64_t)c * 16);
-                raw16 r1 = ld16(row + (int64_t)(c + 64) * 16);
-                raw16 r2 = ld16(row + (int64_t)(c + 128) * 16);
-                raw16 r3 = ld16(row + (int64_t)(c + 192) * 16);
+                raw16 r0 = ld16u<T>(row + (int64_t)c * 16);
+                raw16 r1 = ld16u<T>(row + (int64_t)(c + 64) * 16);
+                raw16 r2 = ld16u<T>(row + (int64_t)(c + 128) * 16);
+                raw16 r3 = ld16u<T>(row + (int64_t)(c + 192) * 16);
                 acc_t v[4][V];
                 Unpack<T>::run(r0, v[0]);
                 Unpack<T>::run(r1, v[1]);
@@ -145,7 +146,7 @@ __global__ __launch_bounds__(64 * WAVES) void encode_rows_kernel(const void* __r
                     }
             }
             for (; c < c_end; c += 64) {
-                raw16 r0 = ld16(row + (int64_t)c * 16);
+                raw16 r0 = ld16u<T>(row + (int64_t)c * 16);
                 acc_t v[V];
                 Unpack<T>::run(r0, v);
 #pragma unroll
@@ -232,7 +233,7 @@ __global__ __launch_bounds__(64 * WAVES) void encode_rows_kernel(const void* __r
 template <typename T, bool W, int COLS_NL>
 __global__ __launch_bounds__(256) void encode_cols_kernel(const void* __restrict__ Bt, int K, int N, int64_t ldb,
                                                           int rows_per_block,
-                                                          typename Elem<T>::acc_t* __restrict__ part, int vec_ok,
+                                                          typename Elem<T>::acc_t* __restrict__ part,
                                                           const typename Elem<T>::acc_t* __restrict__ wvec) {
     using acc_t = typename Elem<T>::acc_t;
     constexpr int V = Elem<T>::vec;
@@ -249,7 +250,7 @@ __global__ __launch_bounds__(256) void encode_cols_kernel(const void* __restrict
         mx[e] = -type_max<acc_t>();
         mn[e] = type_max<acc_t>();
     }
-    const bool full = vec_ok && (k0 + V <= K);
+    const bool full = k0 + V <= K;
     if (full) {
         int n = n_begin + wave;
         // COLS_NL rows in flight per wavefront (a wavefront reads 1 KiB of every fourth row of the slab)
@@ -257,7 +258,7 @@ __global__ __launch_bounds__(256) void encode_cols_kernel(const void* __restrict
             raw16 r[COLS_NL];
 #pragma unroll
             for (int u = 0; u < COLS_NL; ++u)
-                r[u] = ld16(reinterpret_cast<const char*>(Bt) + ((int64_t)(n + 4 * u) * ldb + k0) * Elem<T>::bytes);
+                r[u] = ld16u<T>(reinterpret_cast<const char*>(Bt) + ((int64_t)(n + 4 * u) * ldb + k0) * Elem<T>::bytes);
 #pragma unroll
             for (int u = 0; u < COLS_NL; ++u) {
                 acc_t v[V];
@@ -273,7 +274,7 @@ __global__ __launch_bounds__(256) void encode_cols_kernel(const void* __restrict
             }
         }
         for (; n < n_end; n += 4) {
-            raw16 r0 = ld16(reinterpret_cast<const char*>(Bt) + ((int64_t)n * ldb + k0) * Elem<T>::bytes);
+            raw16 r0 = ld16u<T>(reinterpret_cast<const char*>(Bt) + ((int64_t)n * ldb + k0) * Elem<T>::bytes);
             acc_t v[V];
             Unpack<T>::run(r0, v);
             const acc_t w = !W ? (acc_t)0 : (wvec ? wvec[n] : (acc_t)(n + 1));
@@ -438,85 +439,22 @@ __global__ __launch_bounds__(256) void threshold_rows_kernel(const void* __restr
                                                              typename Elem<T>::acc_t* __restrict__ astat,
                                                              typename Elem<T>::acc_t* __restrict__ expected,
                                                              typename Elem<T>::acc_t* __restrict__ expected2,
-                                                             typename Elem<T>::acc_t* __restrict__ Tout, int vec_ok) {
+                                                             typename Elem<T>::acc_t* __restrict__ Tout) {
     using acc_t = typename Elem<T>::acc_t;
-    constexpr int V = Elem<T>::vec;
     const int lane = threadIdx.x & 63;
     const int m = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (m >= M) return;
     const char* row = reinterpret_cast<const char*>(A) + (int64_t)m * lda * Elem<T>::bytes;
-    acc_t sum = 0, dot = 0, dot2 = 0, mx = -type_max<acc_t>(), mn = type_max<acc_t>();
-    int done = 0;
-    if (vec_ok) {
-        const int nchunks = K / V;
-        int c = lane;
-        // THR_NL 16-byte pieces of the row in flight per lane; the matching pieces of Be come from the caches
-        for (; c + 64 * (THR_NL - 1) < nchunks; c += 64 * THR_NL) {
-            raw16 r[THR_NL];
-#pragma unroll
-            for (int u = 0; u < THR_NL; ++u) r[u] = ld16(row + (int64_t)(c + 64 * u) * 16);
-#pragma unroll
-            for (int u = 0; u < THR_NL; ++u) {
-                acc_t v[V], b[V];
-#pragma unroll
-                for (int e = 0; e < V; ++e) b[e] = Be[(int64_t)(c + 64 * u) * V + e];
-                Unpack<T>::run(r[u], v);
-#pragma unroll
-                for (int e = 0; e < V; ++e) {
-                    sum += v[e];
-                    dot = fma(v[e], b[e], dot);
-                    if constexpr (W) dot2 = fma(v[e], Be2[(int64_t)(c + 64 * u) * V + e], dot2);
-                    mx = fmax(mx, v[e]);
-                    mn = fmin(mn, v[e]);
-                }
-            }
-        }
-        for (; c < nchunks; c += 64) {
-            raw16 r0 = ld16(row + (int64_t)c * 16);
-            acc_t v0[V];
-            Unpack<T>::run(r0, v0);
-#pragma unroll
-            for (int e = 0; e < V; ++e) {
-                const acc_t b = Be[(int64_t)c * V + e];
-                sum += v0[e];
-                dot = fma(v0[e], b, dot);
-                if constexpr (W) dot2 = fma(v0[e], Be2[(int64_t)c * V + e], dot2);
-                mx = fmax(mx, v0[e]);
-                mn = fmin(mn, v0[e]);
-            }
-        }
-        done = nchunks * V;
-    }
-    for (int k = done + lane; k < K; k += 64) {
-        acc_t x = Unpack<T>::one(row, k);
-        sum += x;
-        dot = fma(x, Be[k], dot);
-        if constexpr (W) dot2 = fma(x, Be2[k], dot2);
-        mx = fmax(mx, x);
-        mn = fmin(mn, x);
-    }
-    sum = wave_sum(sum);
-    dot = wave_sum(dot);
-    if constexpr (W) {
-        dot2 = wave_sum(dot2);
-        if (lane == 0) expected2[m] = dot2;
-    }
-    mx = wave_max(mx);
-    mn = wave_min(mn);
+    const RowSums<acc_t> r = row_sums<T, W, THR_NL>(row, K, lane, Be, Be2);
     if (lane == 0) {
-        const double mu = (double)sum / (double)K;
-        double var = ((double)mx - mu) * (mu - (double)mn);
-        var = var > 0 ? var : 0;
-        const double S1 = S[0], S2 = S[1], S3 = S[2];
-        const double dN = (double)N;
-        const double t_det = dN * fabs(mu) * S1;
-        const double t_var23 = c_sigma * sqrt(dN * mu * mu * S2 + dN * dN * var * S3);
-        const double t_var4 = c_sigma * sqrt(dN) * sqrt(var) * sqrt(S2);
-        astat[3 * (int64_t)m + 0] = mx;
-        astat[3 * (int64_t)m + 1] = mn;
+        double mu;
+        const double t = row_threshold(r, K, N, S[0], S[1], S[2], e_max, c_sigma, mu);
+        if constexpr (W) expected2[m] = r.dot2;
+        astat[3 * (int64_t)m + 0] = r.mx;
+        astat[3 * (int64_t)m + 1] = r.mn;
         astat[3 * (int64_t)m + 2] = (acc_t)mu;
-        expected[m] = dot;
-        Tout[m] = (acc_t)(e_max * (t_det + t_var23 + t_var4));
+        expected[m] = r.dot;
+        Tout[m] = (acc_t)t;
     }
 }
 
@@ -530,8 +468,7 @@ __global__ __launch_bounds__(256) void check_offline_kernel(const void* __restri
                                                             const typename Elem<T>::acc_t* __restrict__ Tthr,
                                                             typename Elem<T>::acc_t* __restrict__ rowsum,
                                                             typename Elem<T>::acc_t* __restrict__ E,
-                                                            int32_t* __restrict__ flags, int32_t* __restrict__ nflag,
-                                                            int vec_ok) {
+                                                            int32_t* __restrict__ flags, int32_t* __restrict__ nflag) {
     using acc_t = typename Elem<T>::acc_t;
     constexpr int V = Elem<T>::vec;
     const int lane = threadIdx.x & 63;
@@ -540,13 +477,13 @@ __global__ __launch_bounds__(256) void check_offline_kernel(const void* __restri
     const char* row = reinterpret_cast<const char*>(C) + (int64_t)m * ldc * Elem<T>::bytes;
     acc_t part[4] = {0, 0, 0, 0};
     int done = 0;
-    if (vec_ok) {
+    {
         const int nchunks = N / V;
         int c = lane;
         for (; c + 192 < nchunks; c += 256) {
             raw16 r[4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) r[u] = ld16(row + (int64_t)(c + 64 * u) * 16);
+            for (int u = 0; u < 4; ++u) r[u] = ld16u<T>(row + (int64_t)(c + 64 * u) * 16);
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
                 acc_t v[V];
@@ -559,7 +496,7 @@ __global__ __launch_bounds__(256) void check_offline_kernel(const void* __restri
         }
         for (; c < nchunks; c += 64) {
             acc_t v[V];
-            Unpack<T>::run(ld16(row + (int64_t)c * 16), v);
+            Unpack<T>::run(ld16u<T>(row + (int64_t)c * 16), v);
 #pragma unroll
             for (int e = 0; e < V; ++e) part[0] += v[e];
         }
@@ -631,7 +568,6 @@ template <typename T, bool W>
 static int encode_launch(const vabft_problem* p, const void* dB, void* d_Be, void* d_Be2, void* d_bstat, double* d_S,
                          double* s_partial, void* ws, int32_t* ticket, hipStream_t st) {
     using acc_t = typename Elem<T>::acc_t;
-    const int vec_ok = aligned16(dB) && ((p->ldb * Elem<T>::bytes) % 16 == 0);
     if (!p->transB) {
         const int waves = encode_rows_waves(p, d_S == nullptr);
         const int rpb = encode_rows_per_block(p, waves);
@@ -639,7 +575,7 @@ static int encode_launch(const vabft_problem* p, const void* dB, void* d_Be, voi
 #define VABFT_ENC_ROWS(R, WV)                                                                                    \
     if constexpr (R <= WV)                                                                                       \
         encode_rows_kernel<T, W, R, WV><<<dim3(kblocks), dim3(64 * WV), 0, st>>>(                                \
-            dB, p->K, p->N, p->ldb, (acc_t*)d_Be, (acc_t*)d_Be2, (acc_t*)d_bstat, vec_ok, s_partial, ticket, d_S)
+            dB, p->K, p->N, p->ldb, (acc_t*)d_Be, (acc_t*)d_Be2, (acc_t*)d_bstat, s_partial, ticket, d_S)
 #define VABFT_ENC_ROWS_SWITCH(WV)                 \
     switch (rpb) {                                \
         case 16: VABFT_ENC_ROWS(16, WV); break;   \
@@ -662,9 +598,9 @@ static int encode_launch(const vabft_problem* p, const void* dB, void* d_Be, voi
         acc_t* part = reinterpret_cast<acc_t*>(ws);
         dim3 grid((p->K + 64 * V - 1) / (64 * V), nsplit);
         if (rpb == 64)
-            encode_cols_kernel<T, W, 8><<<grid, dim3(256), 0, st>>>(dB, p->K, p->N, p->ldb, rpb, part, vec_ok, nullptr);
+            encode_cols_kernel<T, W, 8><<<grid, dim3(256), 0, st>>>(dB, p->K, p->N, p->ldb, rpb, part, nullptr);
         else
-            encode_cols_kernel<T, W, 4><<<grid, dim3(256), 0, st>>>(dB, p->K, p->N, p->ldb, rpb, part, vec_ok, nullptr);
+            encode_cols_kernel<T, W, 4><<<grid, dim3(256), 0, st>>>(dB, p->K, p->N, p->ldb, rpb, part, nullptr);
         const int kblocks = s_partial_count(p);
         encode_cols_combine_kernel<acc_t, W><<<dim3(kblocks), dim3(256), 0, st>>>(
             part, nsplit, p->K, p->N, (acc_t*)d_Be, (acc_t*)d_Be2, (acc_t*)d_bstat, s_partial, ticket, d_S);
@@ -697,15 +633,14 @@ static int threshold_launch(const vabft_problem* p, const void* dA, const void* 
                             const double* d_S, double e_max, double c_sigma, void* d_astat, void* d_expected,
                             void* d_expected2, void* d_T, hipStream_t st) {
     using acc_t = typename Elem<T>::acc_t;
-    const int vec_ok = aligned16(dA) && ((p->lda * Elem<T>::bytes) % 16 == 0);
     if (p->K / Elem<T>::vec >= 1024)
         threshold_rows_kernel<T, W, 4><<<dim3((p->M + 3) / 4), dim3(256), 0, st>>>(
             dA, p->M, p->K, p->N, p->lda, (const acc_t*)d_Be, (const acc_t*)d_Be2, d_S, e_max, c_sigma,
-            (acc_t*)d_astat, (acc_t*)d_expected, (acc_t*)d_expected2, (acc_t*)d_T, vec_ok);
+            (acc_t*)d_astat, (acc_t*)d_expected, (acc_t*)d_expected2, (acc_t*)d_T);
     else
         threshold_rows_kernel<T, W, 2><<<dim3((p->M + 3) / 4), dim3(256), 0, st>>>(
             dA, p->M, p->K, p->N, p->lda, (const acc_t*)d_Be, (const acc_t*)d_Be2, d_S, e_max, c_sigma,
-            (acc_t*)d_astat, (acc_t*)d_expected, (acc_t*)d_expected2, (acc_t*)d_T, vec_ok);
+            (acc_t*)d_astat, (acc_t*)d_expected, (acc_t*)d_expected2, (acc_t*)d_T);
     return hipGetLastError() == hipSuccess ? VABFT_OK : VABFT_EDEVICE;
 }
 
@@ -817,13 +752,12 @@ static int threshold_cols_launch(const vabft_problem* p, const void* dB, const v
                                  void* ws, hipStream_t st) {
     using acc_t = typename Elem<T>::acc_t;
     constexpr int V = Elem<T>::vec;
-    const int vec_ok = aligned16(dB) && ((p->ldb * Elem<T>::bytes) % 16 == 0);
     const int rpb = col_rows_per_block(p->dtype, p->K, p->N);
     const int nsplit = (p->K + rpb - 1) / rpb;
     acc_t* part = reinterpret_cast<acc_t*>(ws);
     dim3 grid((p->N + 64 * V - 1) / (64 * V), nsplit);
     // rows of the reduction = k (K of them), columns = n (N of them), weight of row k = (c1 A)[k]
-    encode_cols_kernel<T, true, 4><<<grid, dim3(256), 0, st>>>(dB, p->N, p->K, p->ldb, rpb, part, vec_ok,
+    encode_cols_kernel<T, true, 4><<<grid, dim3(256), 0, st>>>(dB, p->N, p->K, p->ldb, rpb, part,
                                                             (const acc_t*)d_eA);
     threshold_cols_finish_kernel<acc_t><<<dim3((p->N + 255) / 256), dim3(256), 0, st>>>(
         part, nsplit, p->N, p->K, p->M, d_SA, e_max, c_sigma, (acc_t*)d_bcolstat, (acc_t*)d_expected_col,
@@ -869,10 +803,9 @@ int check_offline_dispatch(const vabft_problem* p, const void* dC, const void* d
 #define VABFT_OFF_CASE(T)                                                                                           \
     {                                                                                                               \
         using acc_t = typename Elem<T>::acc_t;                                                                      \
-        const int vec_ok = aligned16(dC) && ((p->ldc * Elem<T>::bytes) % 16 == 0);                                  \
         check_offline_kernel<T><<<grid, block, 0, st>>>(dC, p->M, p->N, p->ldc, (const acc_t*)d_expected,           \
                                                         (const acc_t*)d_T, (acc_t*)d_rowsum, (acc_t*)d_E, d_flags,  \
-                                                        d_nflag, vec_ok);                                           \
+                                                        d_nflag);                                                   \
         break;                                                                                                      \
     }
     switch (p->dtype) {

@@ -1,4 +1,4 @@
-// Pieces shared by the GEMM kernels: block -> tile mapping, guarded loads, the fault
+// Pieces shared by the GEMM kernels: block -> tile mapping, the fault
 // injector applied to accumulator registers (paper section 6.1 "Error injection").
 #pragma once
 #include <type_traits>
@@ -29,42 +29,6 @@ __device__ __forceinline__ void tile_of_block(int b, int tiles_m, int tiles_n, i
     const int in = L - group * GM * tiles_n;
     bm = first_m + in % gsize;
     bn = in / gsize;
-}
-
-// 16-byte chunk of a row-major matrix of 2-byte elements, zero-filled outside [nr) x [nc)
-__device__ __forceinline__ raw16 guarded_chunk2(const uint16_t* base, int r, int nr, int c, int nc, int64_t ld,
-                                                int vec_ok) {
-    raw16 out = {{0u, 0u, 0u, 0u}};
-    if (r < nr && c < nc) {
-        const uint16_t* p = base + (int64_t)r * ld + c;
-        if (vec_ok && c + 8 <= nc) {
-            out = ld16(p);
-        } else {
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-                if (c + e < nc) out.w[e >> 1] |= ((uint32_t)p[e]) << ((e & 1) * 16);
-        }
-    }
-    return out;
-}
-
-// same for 4- and 8-byte elements (V elements per chunk)
-template <typename T, int V>
-__device__ __forceinline__ void guarded_chunk_wide(const T* base, int r, int nr, int c, int nc, int64_t ld,
-                                                   int vec_ok, T (&out)[V]) {
-#pragma unroll
-    for (int e = 0; e < V; ++e) out[e] = 0;
-    if (r < nr && c < nc) {
-        const T* p = base + (int64_t)r * ld + c;
-        if (vec_ok && c + V <= nc) {
-            raw16 v = ld16(p);
-            __builtin_memcpy(out, &v, 16);
-        } else {
-#pragma unroll
-            for (int e = 0; e < V; ++e)
-                if (c + e < nc) out[e] = p[e];
-        }
-    }
 }
 
 // --- bit flips on accumulator words ----------------------------------------

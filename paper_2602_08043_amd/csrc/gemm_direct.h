@@ -1,0 +1,780 @@
+// Verified GEMM for every type, shape and alignment that the whole-tile kernels do not take or would leave most of the
+// chip idle on.  A workgroup owns one small tile of C; its K range is dealt in steps of 128 bytes per row to its
+// wavefronts, each of which multiplies the whole tile over its own steps, so that the loop has no barrier.
+//
+// What bounds it.  Problems with few 256 x 256 tiles are a chain of memory latencies on a few compute units: here a
+// 64 x 64 (or smaller) tile with K split over four or eight wavefronts gives many of them, each with one or two steps
+// of loads outstanding.  A 64 x 64 step of 16-bit operands takes 16 KiB through the vector L1 (64 B / clk per compute
+// unit) and through LDS (128 B / clk, once in and once out) per 32 MFMAs of 16 cycles on each of four SIMDs: large
+// 16-bit problems are bound at about half the matrix rate and belong to the LDS-tiled kernels; FP32 and FP64, with four
+// and eight times the matrix time per byte, are matrix-bound here at any size (FP32 4096^3: 138 of 157 TFLOP/s, FP64
+// 4096^3: 65 of 79).
+//
+// Operands pass from global memory through registers into LDS rows of the wavefront's own and back as MFMA fragments.
+// Loading fragments straight into registers needs no LDS, but puts 16 rows side by side in a quarter of a wavefront,
+// one tag look-up per lane: measured 14 B / clk of L1, 2048^3 BF16 (N x K) 75 us against 42.  With eight lanes per row of
+// 128 bytes every load takes whole lines.  The XOR swizzle of the 16-byte chunks keeps the fragment reads free of bank
+// conflicts; the chunk a lane fetches is chosen for it, so the LDS writes are linear.
+//
+// Fragments.  v_mfma_*_16x16xK with the operands swapped (D' = B^T A^T): lane l of a result tile owns C row l % 16.
+// A lane's chunk is VK consecutive k of one row (16 bytes; 8 for FP8, widened to FP16: exact), the four 16-lane groups
+// hold consecutive chunks; FP32 and FP64 take one MFMA per element of the chunk, so the k that one instruction sees are
+// VK apart, which the contraction does not mind as A and B agree on it.  Columns are dealt to the fragments with stride
+// NF (column of fragment ni, index i = i * NF + ni): with B stored K x N a lane reads NF = 4 consecutive columns of VK
+// LDS rows and has VK k-values of four fragments after a transpose in registers (none for FP32 / FP64), and a lane's
+// results are consecutive columns of C.
+//
+// Loads need no alignment beyond the element's (the hardware takes unaligned global accesses).  Rows and columns past
+// the end are clamped and their results dropped; k past the end is zero in both operands.  FP16 1021 x 1531 x 2047,
+// nothing aligned: 36 us, against 530 with element-wise guarded loads into 256 x 256 tiles.
+//
+// Check: the wavefronts' partial tiles are added in LDS as a fixed tree, the injector edits the sum, row sums (and
+// weighted and column sums) are taken from it before it is rounded to the output type, and the last workgroup of a
+// tile-row to arrive folds the tile-columns' partials and compares (section 2.2, Eq. abft-check).  With the A-side
+// pass fused, the first workgroups of the launch run it (row_threshold.h), one wavefront per row, and count as
+// arrivals of their tile-row: one launch instead of three (pass over A, GEMM, compare).
+#pragma once
+#include "gemm_common.h"
+#include "row_threshold.h"
+
+namespace vabft {
+namespace gd {
+
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4_t;
+typedef __attribute__((ext_vector_type(2))) float f32x2_t;
+typedef __attribute__((ext_vector_type(2))) _Float16 f16x2_t;
+typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_t;
+typedef __attribute__((ext_vector_type(2))) __fp16 fp16x2_t;
+
+// ES: bytes of an element; VK: k-values of a lane's chunk; CB: bytes of that chunk in memory; KU: chunks per step
+// (a row's share of a step is 128 contiguous bytes); NJ: matrix instructions per chunk
+template <typename T> struct Traits;
+template <> struct Traits<bf16_t> {
+    static constexpr int ES = 2, VK = 8, CB = 16, KU = 2, NJ = 1;
+    using accv_t = f32x4_t;
+    using out_t = uint16_t;
+};
+template <> struct Traits<f16_t> {
+    static constexpr int ES = 2, VK = 8, CB = 16, KU = 2, NJ = 1;
+    using accv_t = f32x4_t;
+    using out_t = uint16_t;
+};
+template <> struct Traits<f8_t> {
+    static constexpr int ES = 1, VK = 8, CB = 8, KU = 4, NJ = 1;
+    using accv_t = f32x4_t;
+    using out_t = uint16_t;
+};
+template <> struct Traits<bf8_t> {
+    static constexpr int ES = 1, VK = 8, CB = 8, KU = 4, NJ = 1;
+    using accv_t = f32x4_t;
+    using out_t = uint16_t;
+};
+template <> struct Traits<float> {
+    static constexpr int ES = 4, VK = 4, CB = 16, KU = 2, NJ = 4;
+    using accv_t = f32x4_t;
+    using out_t = float;
+};
+template <> struct Traits<double> {
+    static constexpr int ES = 8, VK = 2, CB = 16, KU = 2, NJ = 2;
+    using accv_t = f64x4_t;
+    using out_t = double;
+};
+
+// 16 bytes at an address in global memory, aligned to the element
+typedef const __attribute__((address_space(1))) char* gptr_t;
+template <int ES> __device__ __forceinline__ u32x4_t load16g(gptr_t p) {
+    typedef uint32_t e_t __attribute__((ext_vector_type(4), aligned(1)));
+    typedef uint32_t h_t __attribute__((ext_vector_type(4), aligned(2)));
+    typedef uint32_t w_t __attribute__((ext_vector_type(4), aligned(4)));
+    if constexpr (ES == 1)
+        return *reinterpret_cast<const __attribute__((address_space(1))) e_t*>(p);
+    else if constexpr (ES == 2)
+        return *reinterpret_cast<const __attribute__((address_space(1))) h_t*>(p);
+    else
+        return *reinterpret_cast<const __attribute__((address_space(1))) w_t*>(p);
+}
+// elements 0 .. n-1 of 16 bytes, the rest zero
+template <int ES> __device__ u32x4_t load_elems(gptr_t p, int n) {
+    u32x4_t o = {0u, 0u, 0u, 0u};
+#pragma unroll
+    for (int e = 0; e < 16 / ES; ++e)
+        if (e < n) {
+            if constexpr (ES == 1)
+                o[e / 4] |= (uint32_t) reinterpret_cast<const __attribute__((address_space(1))) uint8_t*>(p)[e] << (8 * (e & 3));
+            else if constexpr (ES == 2)
+                o[e / 2] |= (uint32_t) reinterpret_cast<const __attribute__((address_space(1))) uint16_t*>(p)[e] << (16 * (e & 1));
+            else
+#pragma unroll
+                for (int q = 0; q < ES / 4; ++q)
+                    o[e * (ES / 4) + q] = reinterpret_cast<const __attribute__((address_space(1))) uint32_t*>(p)[e * (ES / 4) + q];
+        }
+    return o;
+}
+
+// 16 bytes shifted down by s elements, zero behind
+template <int ES> __device__ __forceinline__ u32x4_t shift_elems(u32x4_t v, int s) {
+    const int ds = s * ES >> 2;
+    uint32_t y[5];
+#pragma unroll
+    for (int i = 0; i < 5; ++i) {
+        uint32_t x = 0u;
+#pragma unroll
+        for (int f = i; f < 4; ++f) x = ds == f - i ? v[f] : x;
+        y[i] = x;
+    }
+    u32x4_t o;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        o[i] = ES >= 4 ? y[i] : __builtin_amdgcn_alignbit(y[i + 1], y[i], (uint32_t)(s * ES & 3) * 8);
+    return o;
+}
+
+template <typename T> __device__ __forceinline__ uint32_t widen2(uint32_t w, bool hi);
+template <> __device__ __forceinline__ uint32_t widen2<f8_t>(uint32_t w, bool hi) {
+    const f32x2_t v = hi ? __builtin_amdgcn_cvt_pk_f32_fp8((int)w, true) : __builtin_amdgcn_cvt_pk_f32_fp8((int)w, false);
+    return __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(v[0], v[1]));  // exact
+}
+template <> __device__ __forceinline__ uint32_t widen2<bf8_t>(uint32_t w, bool hi) {
+    const f32x2_t v = hi ? __builtin_amdgcn_cvt_pk_f32_bf8((int)w, true) : __builtin_amdgcn_cvt_pk_f32_bf8((int)w, false);
+    return __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(v[0], v[1]));  // exact
+}
+
+// chunk as loaded (CB bytes) -> MFMA fragment (16 bytes)
+template <typename T> __device__ __forceinline__ raw16 to_frag(const uint32_t* w) {
+    if constexpr (Traits<T>::ES == 1)
+        return raw16{{widen2<T>(w[0], false), widen2<T>(w[0], true), widen2<T>(w[1], false), widen2<T>(w[1], true)}};
+    else
+        return raw16{{w[0], w[1], w[2], w[3]}};
+}
+// VK rows of four columns, CD dwords each -> fragment of column ni
+template <typename T, int CD> __device__ __forceinline__ raw16 to_frag_t(const uint32_t (*w)[CD], int ni) {
+    raw16 o;
+    if constexpr (Traits<T>::ES == 8) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            o.w[2 * j] = w[j][2 * ni];
+            o.w[2 * j + 1] = w[j][2 * ni + 1];
+        }
+    } else if constexpr (Traits<T>::ES == 4) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) o.w[j] = w[j][ni];
+    } else if constexpr (Traits<T>::ES == 2) {
+        const uint32_t sel = (ni & 1) ? 0x07060302u : 0x05040100u;
+#pragma unroll
+        for (int d = 0; d < 4; ++d) o.w[d] = __builtin_amdgcn_perm(w[2 * d + 1][ni >> 1], w[2 * d][ni >> 1], sel);
+    } else {
+        uint32_t c[2];
+#pragma unroll
+        for (int d = 0; d < 2; ++d) {
+            // byte ni of rows 4d .. 4d+3
+            const uint32_t sel = 0x0c0c0000u | (uint32_t)(4 + ni) << 8 | (uint32_t)ni;
+            const uint32_t lo = __builtin_amdgcn_perm(w[4 * d + 1][0], w[4 * d][0], sel);
+            const uint32_t hi = __builtin_amdgcn_perm(w[4 * d + 3][0], w[4 * d + 2][0], sel);
+            c[d] = lo | (hi << 16);
+        }
+        o = to_frag<T>(c);
+    }
+    return o;
+}
+
+// instruction j of the NJ that multiply a chunk
+template <typename T>
+__device__ __forceinline__ typename Traits<T>::accv_t mfma(const raw16& b, const raw16& a, int j,
+                                                           typename Traits<T>::accv_t c) {
+    if constexpr (std::is_same<T, bf16_t>::value)
+        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, b), __builtin_bit_cast(bf16x8_t, a),
+                                                       c, 0, 0, 0);
+    else if constexpr (Traits<T>::ES <= 2)
+        return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8_t, b), __builtin_bit_cast(f16x8_t, a), c,
+                                                      0, 0, 0);
+    else if constexpr (std::is_same<T, float>::value)
+        return __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(b.w[j]), __uint_as_float(a.w[j]), c, 0, 0, 0);
+    else
+        return __builtin_amdgcn_mfma_f64_16x16x4f64(__hiloint2double((int)b.w[2 * j + 1], (int)b.w[2 * j]),
+                                                    __hiloint2double((int)a.w[2 * j + 1], (int)a.w[2 * j]), c, 0, 0, 0);
+}
+
+// four consecutive accumulator values -> stored elements at p (aligned to the element only)
+template <typename T, typename acc_t> __device__ __forceinline__ void store4(void* p, const acc_t* v) {
+    if constexpr (std::is_same<T, double>::value || std::is_same<T, float>::value) {
+        typedef acc_t v_t __attribute__((ext_vector_type(16 / sizeof(acc_t)), aligned(sizeof(acc_t))));
+#pragma unroll
+        for (int q = 0; q < (int)sizeof(acc_t) / 4; ++q) {
+            v_t x;
+#pragma unroll
+            for (int e = 0; e < 16 / (int)sizeof(acc_t); ++e) x[e] = v[q * (16 / (int)sizeof(acc_t)) + e];
+            reinterpret_cast<v_t*>(p)[q] = x;
+        }
+    } else {
+        using h2 = typename std::conditional<std::is_same<T, bf16_t>::value, bf16x2_t, f16x2_t>::type;
+        typedef uint32_t v_t __attribute__((ext_vector_type(2), aligned(2)));
+        v_t x;
+        x[0] = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2_t{v[0], v[1]}), h2));
+        x[1] = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2_t{v[2], v[3]}), h2));
+        *reinterpret_cast<v_t*>(p) = x;
+    }
+}
+template <typename T, typename acc_t> __device__ __forceinline__ typename Traits<T>::out_t to_out(acc_t v) {
+    if constexpr (std::is_same<T, double>::value || std::is_same<T, float>::value)
+        return v;
+    else if constexpr (std::is_same<T, bf16_t>::value)
+        return Elem<bf16_t>::from_acc(v);
+    else
+        return Elem<f16_t>::from_acc(v);
+}
+
+// Partials that cross workgroups (and so XCDs with private L2s) go through device-scope relaxed atomics: see the
+// order argument in gemm_tile32.h.
+template <typename acc_t> struct AgentWord;
+template <> struct AgentWord<float> { using u = uint32_t; };
+template <> struct AgentWord<double> { using u = uint64_t; };
+template <typename acc_t> __device__ __forceinline__ acc_t ld_agent(const acc_t* p) {
+    using u = typename AgentWord<acc_t>::u;
+    return __builtin_bit_cast(acc_t, __hip_atomic_load(reinterpret_cast<const u*>(p), __ATOMIC_RELAXED,
+                                                       __HIP_MEMORY_SCOPE_AGENT));
+}
+template <typename acc_t> __device__ __forceinline__ void st_agent(acc_t* p, acc_t v) {
+    using u = typename AgentWord<acc_t>::u;
+    __hip_atomic_store(reinterpret_cast<u*>(p), __builtin_bit_cast(u, v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// B bytes from an LDS address aligned to them (to 16 at most)
+template <int B> __device__ __forceinline__ void copy_bytes(uint32_t* to, const unsigned char* from) {
+    __builtin_memcpy(to, __builtin_assume_aligned(from, B < 16 ? B : 16), B);
+}
+// N consecutive values between LDS and registers, at a place aligned to all of them or to 16 bytes
+template <int N, typename acc_t> __device__ __forceinline__ void copy_aligned(acc_t* to, const acc_t* from) {
+    constexpr int B = N * (int)sizeof(acc_t), AL = B < 16 ? B : 16;
+    __builtin_memcpy(__builtin_assume_aligned(to, AL), __builtin_assume_aligned(from, AL), B);
+}
+
+template <typename T, int TRANSB, int MF, int NF, int WVK> struct Shape {
+    using acc_t = typename Elem<T>::acc_t;
+    static constexpr int NW = WVK, NT = 64 * NW;
+    static constexpr int BM = 16 * MF, BN = 16 * NF;
+    static constexpr int PITCH = BN + 16 / (int)sizeof(acc_t);  // 16-byte aligned rows, four banks of skew
+    static constexpr int SLOTS = WVK > 1 ? 2 : 1;               // partial tiles left after the tree's register rounds
+    static constexpr int TILE_BYTES = SLOTS * BM * PITCH * (int)sizeof(acc_t);
+    static constexpr int ROUND_BYTES = WVK > 2 ? (WVK / 2) * MF * NF * 64 * 4 * (int)sizeof(acc_t) : 0;
+    static constexpr int WAVE_BYTES = (BM + BN) * 128;  // operand rows of one step of one wavefront
+    static constexpr int cmax(int a, int b) { return a > b ? a : b; }
+    static constexpr int LDS = cmax(cmax(TILE_BYTES, ROUND_BYTES), NW * WAVE_BYTES) + 128;
+    static constexpr int EPT = BM * BN / NT < 16 ? BM * BN / NT : 16;  // consecutive columns of a thread in the epilogue
+    static constexpr int TPR = BN / EPT;                               // threads per row there
+    static constexpr int RPP = NT / TPR;                               // rows per pass
+    static_assert(TPR <= 64 && BM % RPP == 0 && BM % NW == 0, "epilogue mapping");
+};
+
+}  // namespace gd
+
+// The last workgroup of tile-row bm to arrive (GEMM tiles and, with the A-side pass fused, its workgroups) folds the
+// partial row sums and compares.  Every thread of every workgroup calls this after its partials are written.
+template <typename T, typename S>
+__device__ __forceinline__ void direct_tile_row_check(const DirectArgs& d, int bm, int* s_last) {
+    using acc_t = typename Elem<T>::acc_t;
+    const GemmArgs& g = d.g;
+    const int tid = threadIdx.x;
+    const int row0 = bm * S::BM, rows = min(S::BM, g.M - row0);
+    const int arrivals = g.tiles_n + (d.stat_blocks ? (rows + S::NW - 1) / S::NW : 0);
+    __builtin_amdgcn_s_waitcnt(0);  // this wavefront's partials are performed
+    __syncthreads();
+    if (tid == 0) *s_last = (atomicAdd(&g.tickets[bm], 1) == arrivals - 1);
+    __syncthreads();
+    if (!*s_last) return;
+    constexpr int TPF = S::NT / S::BM;  // neighbouring threads that share a row
+    static_assert(TPF >= 1 && TPF <= 64, "fold mapping");
+    const int r = tid / TPF, sub = tid % TPF;
+    const bool act = r < rows;
+    const int gi = row0 + (act ? r : 0);
+    const bool wsum = d.wsum != 0;
+    acc_t s4[4] = {0, 0, 0, 0}, w4[4] = {0, 0, 0, 0};
+    for (int t0 = sub; t0 < g.tiles_n; t0 += 16 * TPF) {
+        acc_t v[16], v2[16];
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            const int t = t0 + j * TPF < g.tiles_n ? t0 + j * TPF : t0;
+            v[j] = gd::ld_agent(reinterpret_cast<const acc_t*>(g.rowpart) + (int64_t)t * g.M + gi);
+            v2[j] = 0;
+            if (wsum) v2[j] = gd::ld_agent(reinterpret_cast<const acc_t*>(g.rowpart2) + (int64_t)t * g.M + gi);
+        }
+#pragma unroll
+        for (int j = 0; j < 16; ++j)
+            if (t0 + j * TPF < g.tiles_n) {
+                s4[j & 3] += v[j];
+                w4[j & 3] += v2[j];
+            }
+    }
+    acc_t s = (s4[0] + s4[1]) + (s4[2] + s4[3]), s2 = (w4[0] + w4[1]) + (w4[2] + w4[3]);
+#pragma unroll
+    for (int o = 1; o < TPF; o <<= 1) {
+        s += __shfl_xor(s, o, WAVE);
+        s2 += __shfl_xor(s2, o, WAVE);
+    }
+    int f = 0;
+    if (act && sub == 0) {
+        const acc_t* ex = reinterpret_cast<const acc_t*>(g.expected) + gi;
+        const acc_t* th = reinterpret_cast<const acc_t*>(g.T) + gi;
+        const acc_t e = (d.stat_blocks ? gd::ld_agent(ex) : *ex) - s;
+        const acc_t t = d.stat_blocks ? gd::ld_agent(th) : *th;
+        f = !(fabs(e) <= t);
+        reinterpret_cast<acc_t*>(g.rowsum)[gi] = s;
+        if (wsum) reinterpret_cast<acc_t*>(g.rowsum2)[gi] = s2;
+        reinterpret_cast<acc_t*>(g.E)[gi] = e;
+        g.flags[gi] = f;
+    }
+    const int cnt = __syncthreads_count(f);
+    if (tid == 0 && g.tiles_m == 1) {
+        *g.d_nflag = cnt;
+        __hip_atomic_store(&g.tickets[bm], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    } else if (tid == 0) {
+        // this tile-row is done: reset its ticket, then one 64-bit atomic counts the finished tile-rows (high word)
+        // and the flagged rows (low word); whoever completes the count publishes nflag and leaves the counter zero
+        __hip_atomic_store(&g.tickets[bm], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        unsigned long long* done = reinterpret_cast<unsigned long long*>(g.tickets + ((g.tiles_m + 1) & ~1));
+        const unsigned long long old = atomicAdd(done, (1ull << 32) | (unsigned long long)(unsigned)cnt);
+        if ((int)(old >> 32) == g.tiles_m - 1) {
+            *g.d_nflag = (int)(unsigned)(old & 0xffffffffull) + cnt;
+            __hip_atomic_store(done, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
+}
+
+// The A-side pass inside the GEMM launch: one wavefront per row
+template <typename T, typename S>
+__device__ __forceinline__ void direct_stats(const DirectArgs& d, double* s_red, int* s_last) {
+    using acc_t = typename Elem<T>::acc_t;
+    const GemmArgs& g = d.g;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int m = blockIdx.x * S::NW + wave;
+    if (!g.S) {
+        fold_s_partials_to_lds(g.s_partial, g.s_nparts, threadIdx.x, s_red);
+        __syncthreads();
+    }
+    if (m < g.M) {
+        const char* row = reinterpret_cast<const char*>(g.A) + (int64_t)m * g.lda * Elem<T>::bytes;
+        const RowSums<acc_t> r = row_sums<T, false, 4>(row, g.K, lane, reinterpret_cast<const acc_t*>(g.Be), nullptr);
+        if (lane == 0) {
+            const double S1 = g.S ? g.S[0] : folded_s(s_red, 0), S2 = g.S ? g.S[1] : folded_s(s_red, 1),
+                         S3 = g.S ? g.S[2] : folded_s(s_red, 2);
+            double mu;
+            const acc_t t = (acc_t)row_threshold(r, g.K, g.N, S1, S2, S3, g.e_max, g.c_sigma, mu);
+            acc_t* astat = reinterpret_cast<acc_t*>(g.astat) + 3 * (int64_t)m;
+            astat[0] = r.mx;
+            astat[1] = r.mn;
+            astat[2] = (acc_t)mu;
+            gd::st_agent(reinterpret_cast<acc_t*>(const_cast<void*>(g.expected)) + m, r.dot);
+            gd::st_agent(reinterpret_cast<acc_t*>(const_cast<void*>(g.T)) + m, t);
+        }
+    }
+    direct_tile_row_check<T, S>(d, blockIdx.x * S::NW / S::BM, s_last);
+}
+
+// ANY: for rows so far apart that 32 bits do not hold a tile's byte offsets, and for rows of under 16 bytes.
+// D: steps in flight from global memory.
+template <typename T, int TRANSB, int MF, int NF, int WVK, int D, bool ANY>
+__global__ __launch_bounds__(64 * WVK, 2) void gemm_direct_kernel(const DirectArgs d) {
+    using S = gd::Shape<T, TRANSB, MF, NF, WVK>;
+    using OFF = typename std::conditional<ANY, uint64_t, uint32_t>::type;
+    using Tr = gd::Traits<T>;
+    using acc_t = typename Elem<T>::acc_t;
+    using accv_t = typename Tr::accv_t;
+    constexpr int ES = Tr::ES, VK = Tr::VK, CB = Tr::CB, KU = Tr::KU;
+    constexpr int KC = 4 * VK, KSTEP = KC * KU;  // k of one chunk over the four lane groups, k of one step
+    constexpr int CD = 4 * ES / 4;               // dwords of four columns (B stored K x N)
+    constexpr int LA = 2 * MF, LB = 2 * NF;  // 1 KiB loads of a step
+    constexpr int RB = S::BN * ES, V = 16 / ES;    // K x N B: bytes of a row of the tile; elements of a lane's 16 bytes
+    static_assert(KSTEP * ES == 128, "a row's share of a step is 128 bytes");
+    static_assert(TRANSB || NF == 4, "a lane reads four columns of B stored K x N");
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    int* const s_last = reinterpret_cast<int*>(smem + S::LDS - 128);
+    double* const s_red = reinterpret_cast<double*>(smem + S::LDS - 112);
+    const GemmArgs& g = d.g;
+    const bool verify = d.verify != 0;
+    const int tid = threadIdx.x;
+    if (verify && blockIdx.x == 0 && tid == 0) {
+        if (g.block_mode) {  // a compare kernel that follows counts into these
+            *g.d_nflag = 0;
+            *g.d_nblockflag = 0;
+        }
+        if (g.d_ncolflag) *g.d_ncolflag = 0;
+    }
+    if ((int)blockIdx.x < d.stat_blocks) {
+        direct_stats<T, S>(d, s_red, s_last);
+        return;
+    }
+    const int lane = tid & 63, l16 = lane & 15, lq = lane >> 4;
+    const int wk = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int bm, bn;
+    tile_of_block(blockIdx.x - d.stat_blocks, g.tiles_m, g.tiles_n, bm, bn);
+    const int row0 = bm * S::BM, col0 = bn * S::BN;
+
+    // ---- global memory -> registers ---------------------------------------------------------------------------
+    // Row loads: load t covers LDS rows 8 t .. 8 t + 7, eight lanes each; the lane at position lane % 8 of row r
+    // fetches chunk (lane % 8) ^ ((r >> 1) & 7), so that the 16 rows of a fragment read hit 16 distinct slots.
+    const int lrow = lane >> 3;
+    const char* const abase = reinterpret_cast<const char*>(g.A) + ((int64_t)row0 * g.lda + wk * KSTEP) * ES;
+    OFF aoff[LA];
+#pragma unroll
+    for (int t = 0; t < LA; ++t) {
+        const int r = min(row0 + 8 * t + lrow, g.M - 1) - row0;
+        aoff[t] = (OFF)r * (OFF)(g.lda * ES) + (OFF)(((lane & 7) ^ ((4 * t + (lane >> 4)) & 7)) << 4);
+    }
+    const char* bbase;
+    OFF boff[LB];
+    if constexpr (TRANSB != 0) {
+        bbase = reinterpret_cast<const char*>(g.B) + ((int64_t)col0 * g.ldb + wk * KSTEP) * ES;
+#pragma unroll
+        for (int t = 0; t < LB; ++t) {
+            // LDS row ni * 16 + i holds column i * NF + ni of the tile
+            const int q = 8 * t + lrow, r = min(col0 + (q & 15) * NF + (q >> 4), g.N - 1) - col0;
+            boff[t] = (OFF)r * (OFF)(g.ldb * ES) + (OFF)(((lane & 7) ^ ((4 * t + (lane >> 4)) & 7)) << 4);
+        }
+    } else {
+        // LDS row k of RB bytes: the tile's columns of row k of the step, in groups of V; a group that would cross the
+        // row's end starts at N - V instead (see column_of)
+        const int c = max(0, min(col0 + lane * 16 % RB / ES, g.N - V));
+        bbase = reinterpret_cast<const char*>(g.B) + ((int64_t)(wk * KSTEP) * g.ldb) * ES;
+#pragma unroll
+        for (int t = 0; t < LB; ++t) boff[t] = (OFF)((t * 1024 + lane * 16) / RB) * (OFF)(g.ldb * ES) + (OFF)c * ES;
+    }
+    const int64_t bstep = TRANSB ? ES : g.ldb * ES;    // bytes of one k
+    struct Stage {
+        gd::u32x4_t a[LA], b[LB];
+    };
+    // Steps are dealt to the wavefronts in turn.  i: this wavefront's step number
+    auto load_step = [&](int i, Stage& st) __attribute__((always_inline)) {
+        const int64_t k0 = (int64_t)i * (WVK * KSTEP);
+        // (base and offsets opaque, so that each load is scalar base + 32-bit lane offset and no sum of the two, nor
+        // the offset widened to 64 bits, is kept across the loop)
+        gd::gptr_t pa = (gd::gptr_t)(abase + k0 * ES);
+        gd::gptr_t pb = (gd::gptr_t)(bbase + k0 * bstep);
+        asm volatile("" : "+s"(pa), "+s"(pb));
+#pragma unroll
+        for (int t = 0; t < LA; ++t) asm volatile("" : "+v"(aoff[t]));
+#pragma unroll
+        for (int t = 0; t < LB; ++t) asm volatile("" : "+v"(boff[t]));
+#pragma unroll
+        for (int t = 0; t < LA; ++t) st.a[t] = gd::load16g<ES>(pa + aoff[t]);
+#pragma unroll
+        for (int t = 0; t < LB; ++t) st.b[t] = gd::load16g<ES>(pb + boff[t]);
+    };
+    // Step i where only the first len < KSTEP k are inside K: rows along k are read where they still have 16 bytes
+    // and shifted by finish_part, rows along n past K are replaced by the last one and cleared by finish_part.
+    // Rows of under 16 bytes (ANY) are read element by element, already finished.
+    const bool tiny = ANY && (g.K < V || (!TRANSB && g.N < V));
+    auto beyond = [&](int t, int len) { return (((lane & 7) ^ ((4 * t + (lane >> 4)) & 7)) << 4) / ES + V - len; };
+    auto load_part = [&](int i, int len, Stage& st) __attribute__((always_inline)) {
+        const int64_t k0 = (int64_t)i * (WVK * KSTEP);
+        const gd::gptr_t pa = (gd::gptr_t)(abase + k0 * ES), pb = (gd::gptr_t)(bbase + k0 * bstep);
+        if (!tiny) {
+#pragma unroll
+            for (int t = 0; t < LA; ++t) st.a[t] = gd::load16g<ES>(pa + aoff[t] - (int64_t)max(0, beyond(t, len)) * ES);
+#pragma unroll
+            for (int t = 0; t < LB; ++t) {
+                const int64_t back = TRANSB ? (int64_t)max(0, beyond(t, len)) * ES
+                                            : (int64_t)max(0, (t * 1024 + lane * 16) / RB - (len - 1)) * bstep;
+                st.b[t] = gd::load16g<ES>(pb + boff[t] - back);
+            }
+        } else if constexpr (ANY) {
+            for (int t = 0; t < LA; ++t) st.a[t] = gd::load_elems<ES>(pa + aoff[t], V - beyond(t, len));
+            for (int t = 0; t < LB; ++t) {
+                const int k = (t * 1024 + lane * 16) / RB;
+                const int n = TRANSB ? V - beyond(t, len) : k < len ? g.N - (col0 + lane * 16 % RB / ES) : 0;
+                st.b[t] = gd::load_elems<ES>(pb + boff[t], n);
+            }
+        }
+    };
+    auto finish_part = [&](int len, Stage& st) __attribute__((always_inline)) {
+        if (tiny) return;
+#pragma unroll
+        for (int t = 0; t < LA; ++t) st.a[t] = gd::shift_elems<ES>(st.a[t], min(V, max(0, beyond(t, len))));
+#pragma unroll
+        for (int t = 0; t < LB; ++t) {
+            if constexpr (TRANSB != 0)
+                st.b[t] = gd::shift_elems<ES>(st.b[t], min(V, max(0, beyond(t, len))));
+            else if ((t * 1024 + lane * 16) / RB >= len)
+                st.b[t] = gd::u32x4_t{0u, 0u, 0u, 0u};
+        }
+    };
+
+    accv_t acc[MF][NF];
+#pragma unroll
+    for (int mi = 0; mi < MF; ++mi)
+#pragma unroll
+        for (int ni = 0; ni < NF; ++ni)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[mi][ni][r] = 0;
+    // ---- registers -> the wavefront's own LDS rows -> fragments -> MFMA ----------------------------------------
+    // No other wavefront reads these rows and LDS operations of one wavefront complete in order, so one buffer and
+    // no barrier will do.
+    unsigned char* const stage = smem + wk * S::WAVE_BYTES;
+    const unsigned char* const frag0 = stage + l16 * 128;
+    const int swz = (l16 >> 1) & 7;
+    // multiplies the step in st; reload() runs as soon as its registers are free
+    auto compute = [&](Stage& st, auto reload) __attribute__((always_inline)) {
+#pragma unroll
+        for (int t = 0; t < LA; ++t) *reinterpret_cast<gd::u32x4_t*>(stage + t * 1024 + lane * 16) = st.a[t];
+#pragma unroll
+        for (int t = 0; t < LB; ++t) *reinterpret_cast<gd::u32x4_t*>(stage + (LA + t) * 1024 + lane * 16) = st.b[t];
+        __builtin_amdgcn_sched_barrier(0);
+        reload();
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < KU; ++u) {
+            // the lane's chunk: 16-byte slot and, for 8-byte chunks, its half
+            const int at = CB == 16 ? ((4 * u + lq) ^ swz) << 4 : (((2 * u + (lq >> 1)) ^ swz) << 4) + 8 * (lq & 1);
+            auto frag = [&](int f) {
+                uint32_t w[Tr::CB / 4];
+                gd::copy_bytes<Tr::CB>(w, frag0 + f * 2048 + at);
+                return gd::to_frag<T>(w);
+            };
+            raw16 af[MF], bf[NF];
+            if constexpr (TRANSB != 0) {
+#pragma unroll
+                for (int ni = 0; ni < NF; ++ni) bf[ni] = frag(MF + ni);
+            } else {
+                uint32_t w[VK][CD];
+#pragma unroll
+                for (int e = 0; e < VK; ++e)
+                    gd::copy_bytes<4 * CD>(w[e], stage + LA * 1024 + (u * KC + lq * VK + e) * RB + l16 * NF * ES);
+#pragma unroll
+                for (int ni = 0; ni < NF; ++ni) bf[ni] = gd::to_frag_t<T, CD>(w, ni);
+            }
+#pragma unroll
+            for (int mi = 0; mi < MF; ++mi) af[mi] = frag(mi);
+#pragma unroll
+            for (int j = 0; j < Tr::NJ; ++j)
+#pragma unroll
+                for (int mi = 0; mi < MF; ++mi)
+#pragma unroll
+                    for (int ni = 0; ni < NF; ++ni) acc[mi][ni] = gd::mfma<T>(bf[ni], af[mi], j, acc[mi][ni]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    {
+        const int full = tiny ? 0 : g.K / KSTEP;                        // whole steps
+        const int cnt = full > wk ? (full - wk + WVK - 1) / WVK : 0;  // ... of this wavefront
+        Stage sg[D];
+        if (full * KSTEP < g.K && full % WVK == wk && !tiny) {
+            // the step that K ends in comes first, with the first whole step in flight behind it
+            Stage part;
+            load_part(full / WVK, g.K - full * KSTEP, part);
+            if (cnt > 0) load_step(0, sg[0]);
+            __builtin_amdgcn_sched_barrier(0);
+            finish_part(g.K - full * KSTEP, part);
+            compute(part, [] {});
+        } else if (cnt > 0) {
+            load_step(0, sg[0]);
+        }
+        if (cnt > 0) {
+            static_for<1, D>([&](auto q_c) { load_step(min(decltype(q_c)::value, cnt - 1), sg[decltype(q_c)::value]); });
+            for (int i = 0;;) {  // (past the last step the last one is read again, and dropped)
+                compute(sg[0], [&] { load_step(min(i + D, cnt - 1), sg[0]); });
+                if (++i == cnt) break;
+                if constexpr (D == 2) {
+                    compute(sg[1], [&] { load_step(min(i + D, cnt - 1), sg[1]); });
+                    if (++i == cnt) break;
+                }
+            }
+        }
+        if constexpr (ANY) {
+            if (tiny)
+                for (int q = wk; q * KSTEP < g.K; q += WVK) {
+                    load_part(q / WVK, min(KSTEP, g.K - q * KSTEP), sg[0]);
+                    compute(sg[0], [] {});
+                }
+        }
+    }
+
+    // ---- partial tiles of the WVK wavefronts -> LDS, as a tree ---------------------------------------------------
+    __syncthreads();  // the operand rows are no longer read
+    if constexpr (WVK > 2) {
+        accv_t* const buf = reinterpret_cast<accv_t*>(smem);
+        constexpr int F = MF * NF * 64;  // vectors of one wavefront
+#pragma unroll
+        for (int active = WVK; active > 2; active /= 2) {
+            const int half = active / 2;
+            if (wk >= half && wk < active) {
+#pragma unroll
+                for (int f = 0; f < MF * NF; ++f)
+                    buf[(wk - half) * F + f * 64 + lane] = acc[f / NF][f % NF];
+            }
+            __syncthreads();
+            if (wk < half) {
+#pragma unroll
+                for (int f = 0; f < MF * NF; ++f)
+                    acc[f / NF][f % NF] += buf[wk * F + f * 64 + lane];
+            }
+            __syncthreads();
+        }
+    }
+    acc_t* const tile = reinterpret_cast<acc_t*>(smem);  // [SLOTS][BM][PITCH]
+    // The column of C that column j of the tile holds, or -1.  With B stored K x N, a group of V columns that would
+    // cross the end of the row was read from N - V on: its first columns repeat those of the group before.
+    const bool nedge = col0 + S::BN > g.N;  // workgroup-uniform
+    auto column_of = [&](int j) {
+        if (!nedge) return col0 + j;
+        if (TRANSB) return col0 + j < g.N ? col0 + j : -1;
+        const int c = col0 + j / V * V, back = c - max(0, min(c, g.N - V));
+        return j % V >= back && c - back + j % V < g.N ? c - back + j % V : -1;
+    };
+    if (wk < S::SLOTS) {
+#pragma unroll
+        for (int mi = 0; mi < MF; ++mi)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                // FP64 results sit at index lq + 4 r of the fragment, the others at 4 lq + r
+                const int idx = sizeof(acc_t) == 8 ? lq + 4 * r : 4 * lq + r;
+                acc_t* p = tile + (wk * S::BM + mi * 16 + l16) * S::PITCH + idx * NF;
+                alignas(16) acc_t x[NF];
+#pragma unroll
+                for (int ni = 0; ni < NF; ++ni) x[ni] = acc[mi][ni][r];
+                gd::copy_aligned<NF>(p, x);
+            }
+    }
+    __syncthreads();
+
+    // ---- fault injector (section 6.1 "Error injection"): the sum of the partial tiles, edited in place --------------
+    const bool inject = g.inj.mode != 0;
+    if (inject) {
+        const InjectArgs& inj = g.inj;
+        for (int e = tid; e < S::BM * S::BN; e += S::NT) {
+            const int r = e / S::BN, c = e % S::BN, gi = row0 + r, gj = column_of(c);
+            acc_t* p = tile + r * S::PITCH + c;
+            acc_t x = *p;
+            if (S::SLOTS == 2) x += p[(S::SLOTS - 1) * S::BM * S::PITCH];
+            if (gi < g.M && gj >= 0) {
+                const auto flip = [&](int bit) {
+                    const acc_t before = x;
+                    x = flip_bit(before, bit);
+                    log_fault(inj, gi, gj, bit, (double)before, (double)x);
+                };
+                if (inj.mode == 1) {
+                    for (int q = 0; q < inj.n_list; ++q) {
+                        const int fb = inj.d_list[3 * q + 2];
+                        if (inj.d_list[3 * q] == gi && inj.d_list[3 * q + 1] == gj && fb >= 0 && fb < acc_bits<acc_t>()) flip(fb);
+                    }
+                } else {
+                    const int bit = bernoulli_bit(inj, gi, gj, g.N);
+                    if (bit >= 0) flip(bit);
+                }
+            }
+            *p = x;
+        }
+        __syncthreads();
+    }
+
+    // ---- epilogue: a thread owns EPT consecutive columns of a row ------------------------------------------------
+    const bool wsum = d.wsum != 0, csum = d.csum != 0;
+    using out_t = typename Tr::out_t;
+    constexpr int EPT = S::EPT;
+    static_assert(EPT * sizeof(acc_t) < 16 || EPT * sizeof(acc_t) % 16 == 0, "LDS vectors");
+    const int tr = tid / S::TPR, tc = tid % S::TPR * EPT;
+    for (int r0 = 0; r0 < S::BM; r0 += S::RPP) {
+        const int gi = row0 + r0 + tr;
+        acc_t* const src = tile + (r0 + tr) * S::PITCH + tc;
+        alignas(16) acc_t v[EPT];
+        gd::copy_aligned<EPT>(v, src);
+        if (S::SLOTS == 2 && !inject) {
+            alignas(16) acc_t u[EPT];
+            gd::copy_aligned<EPT>(u, src + (S::SLOTS - 1) * S::BM * S::PITCH);
+#pragma unroll
+            for (int e = 0; e < EPT; ++e) v[e] += u[e];
+        }
+        if (verify) {
+            acc_t x[EPT];
+#pragma unroll
+            for (int e = 0; e < EPT; ++e) x[e] = (!nedge || column_of(tc + e) >= 0) && gi < g.M ? v[e] : (acc_t)0;
+            if (csum) {
+#pragma unroll
+                for (int e = 0; e < EPT; ++e) src[e] = x[e];
+            }
+            acc_t s2 = 0;
+            if (wsum) {
+                // weights from the thread's first column on; that column's own weight goes with the plain sum below
+#pragma unroll
+                for (int e = 0; e < EPT; ++e)
+                    s2 = fma((acc_t)(nedge ? max(0, column_of(tc + e)) - (col0 + tc) : e), x[e], s2);
+            }
+#pragma unroll
+            for (int w = 1; w < EPT; w *= 2)
+#pragma unroll
+                for (int e = 0; e + w < EPT; e += 2 * w) x[e] += x[e + w];
+            acc_t s = x[0];
+            if (wsum) s2 = fma((acc_t)(col0 + tc + 1), s, s2);
+#pragma unroll
+            for (int o = 1; o < S::TPR; o <<= 1) {
+                s += __shfl_xor(s, o, WAVE);
+                if (wsum) s2 += __shfl_xor(s2, o, WAVE);
+            }
+            if (tid % S::TPR == 0 && gi < g.M) {
+                gd::st_agent(reinterpret_cast<acc_t*>(g.rowpart) + (int64_t)bn * g.M + gi, s);
+                if (wsum) gd::st_agent(reinterpret_cast<acc_t*>(g.rowpart2) + (int64_t)bn * g.M + gi, s2);
+            }
+        }
+        if (gi < g.M) {
+            out_t* c = reinterpret_cast<out_t*>(g.C) + (int64_t)gi * g.ldc;
+            if (EPT >= 4 && !nedge) {
+#pragma unroll
+                for (int e = 0; e + 3 < EPT; e += 4) gd::store4<T, acc_t>(c + col0 + tc + e, v + e);
+            } else {
+#pragma unroll
+                for (int e = 0; e < EPT; ++e) {
+                    const int gj = column_of(tc + e);
+                    if (gj >= 0) c[gj] = gd::to_out<T, acc_t>(v[e]);
+                }
+            }
+        }
+    }
+    if (!verify) return;
+    if (csum) {
+        __syncthreads();
+        for (int c = tid; c < S::BN; c += S::NT) {
+            acc_t q[4] = {0, 0, 0, 0};
+            for (int r = 0; r < S::BM; r += 4)
+#pragma unroll
+                for (int k = 0; k < 4; ++k) q[k] += tile[(r + k) * S::PITCH + c];
+            const int gj = column_of(c);
+            if (gj >= 0)  // compared by a kernel of their own
+                reinterpret_cast<acc_t*>(g.colpart)[(int64_t)bm * g.N + gj] = (q[0] + q[1]) + (q[2] + q[3]);
+        }
+    }
+    if (!g.block_mode) direct_tile_row_check<T, S>(d, bm, s_last);
+}
+
+template <typename T, int TRANSB, int MF, int NF, int WVK, int D, bool ANY = false>
+static int gemm_direct_launch_shape(const DirectArgs& d, hipStream_t st) {
+    using S = gd::Shape<T, TRANSB, MF, NF, WVK>;
+    auto kern = gemm_direct_kernel<T, TRANSB, MF, NF, WVK, D, ANY>;
+    if constexpr (S::LDS > 65536) {
+        static bool attr_set = false;
+        if (!attr_set) {
+            if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    S::LDS) != hipSuccess)
+                return VABFT_EDEVICE;
+            attr_set = true;
+        }
+    }
+    kern<<<dim3(d.stat_blocks + d.g.tiles_m * d.g.tiles_n), dim3(S::NT), S::LDS, st>>>(d);
+    return hipGetLastError() == hipSuccess ? VABFT_OK : VABFT_EDEVICE;
+}
+
+// shape: see DirectShape.  Two steps are in flight from global memory where the registers allow it.
+template <typename T, int TRANSB> static int gemm_direct_launch_tb(const DirectArgs& d, int shape, hipStream_t st) {
+    constexpr int NS = TRANSB ? 2 : 4;  // a lane reads four columns of a K x N B
+    switch (shape) {
+        case DIRECT_16: return gemm_direct_launch_shape<T, TRANSB, 1, NS, 8, TRANSB ? 2 : 1>(d, st);
+        case DIRECT_32: return gemm_direct_launch_shape<T, TRANSB, 2, NS, 8, TRANSB ? 2 : 1>(d, st);
+        case DIRECT_32W: return gemm_direct_launch_shape<T, TRANSB, 2, 4, 4, 1>(d, st);
+        case DIRECT_ANY: return gemm_direct_launch_shape<T, TRANSB, 2, 4, 4, 1, true>(d, st);
+        case DIRECT_64:
+            if constexpr (!std::is_same<T, double>::value)
+                return gemm_direct_launch_shape<T, TRANSB, 4, 4, 4, std::is_same<T, float>::value || !TRANSB ? 1 : 2>(d, st);
+    }
+    return VABFT_EINVAL;
+}
+template <typename T> static int gemm_direct_launch_t(const DirectArgs& d, int shape, int transB, hipStream_t st) {
+    return transB ? gemm_direct_launch_tb<T, 1>(d, shape, st) : gemm_direct_launch_tb<T, 0>(d, shape, st);
+}
+
+}  // namespace vabft

@@ -276,13 +276,13 @@ __device__ __forceinline__ void gemm16_fast_epilogue(const GemmArgs& g, f32x16_t
         const bool partials_only = MODE == 5 || (MODE == 2 && g.block_mode);
         if (partials_only) {
             __syncthreads();  // the store below reuses the LDS the reductions read
-            gemm16_store_c<T, false>(g, acc, smem, row0, col0, lane, wm, wn, l32, lh);
+            gemm16_store_c<T>(g, acc, smem, row0, col0, lane, wm, wn, l32, lh);
             return;
         }
         gemm_tile_row_check<WSUM, FUSED>(g, smem, reinterpret_cast<const double*>(smem + S_RED_OFFSET), bm, gi, tid);
         __syncthreads();  // the store below reuses the LDS the reductions read
     }
-    gemm16_store_c<T, false>(g, acc, smem, row0, col0, lane, wm, wn, l32, lh);
+    gemm16_store_c<T>(g, acc, smem, row0, col0, lane, wm, wn, l32, lh);
 }
 
 }  // namespace vabft

@@ -1,0 +1,90 @@
+// One row of A per wavefront: (sum, max, min), dot product with Be (and Be2), and the threshold T_m of Algorithm 1
+// (section 3.4 boxed formula).  Shared by the streaming pass over A and by the GEMM launches that carry that pass in
+// workgroups of their own.
+#pragma once
+#include "unpack.h"
+
+namespace vabft {
+
+template <typename acc_t> struct RowSums {
+    acc_t sum, dot, dot2, mx, mn;
+};
+
+// W: also the dot product with Be2.  NL: 16-byte pieces of the row in flight per lane.  The pieces need no alignment
+// beyond the element's.
+template <typename T, bool W, int NL>
+__device__ __forceinline__ RowSums<typename Elem<T>::acc_t> row_sums(const char* row, int K, int lane,
+                                                                     const typename Elem<T>::acc_t* __restrict__ Be,
+                                                                     const typename Elem<T>::acc_t* __restrict__ Be2) {
+    using acc_t = typename Elem<T>::acc_t;
+    constexpr int V = Elem<T>::vec;
+    acc_t sum = 0, dot = 0, dot2 = 0, mx = -type_max<acc_t>(), mn = type_max<acc_t>();
+    const int nchunks = K / V;
+    int c = lane;
+    // the matching pieces of Be come from the caches
+    for (; c + 64 * (NL - 1) < nchunks; c += 64 * NL) {
+        raw16 r[NL];
+#pragma unroll
+        for (int u = 0; u < NL; ++u) r[u] = ld16u<T>(row + (int64_t)(c + 64 * u) * 16);
+#pragma unroll
+        for (int u = 0; u < NL; ++u) {
+            acc_t v[V], b[V];
+#pragma unroll
+            for (int e = 0; e < V; ++e) b[e] = Be[(int64_t)(c + 64 * u) * V + e];
+            Unpack<T>::run(r[u], v);
+#pragma unroll
+            for (int e = 0; e < V; ++e) {
+                sum += v[e];
+                dot = fma(v[e], b[e], dot);
+                if constexpr (W) dot2 = fma(v[e], Be2[(int64_t)(c + 64 * u) * V + e], dot2);
+                mx = fmax(mx, v[e]);
+                mn = fmin(mn, v[e]);
+            }
+        }
+    }
+    for (; c < nchunks; c += 64) {
+        raw16 r0 = ld16u<T>(row + (int64_t)c * 16);
+        acc_t v0[V];
+        Unpack<T>::run(r0, v0);
+#pragma unroll
+        for (int e = 0; e < V; ++e) {
+            const acc_t b = Be[(int64_t)c * V + e];
+            sum += v0[e];
+            dot = fma(v0[e], b, dot);
+            if constexpr (W) dot2 = fma(v0[e], Be2[(int64_t)c * V + e], dot2);
+            mx = fmax(mx, v0[e]);
+            mn = fmin(mn, v0[e]);
+        }
+    }
+    for (int k = nchunks * V + lane; k < K; k += 64) {
+        acc_t x = Unpack<T>::one(row, k);
+        sum += x;
+        dot = fma(x, Be[k], dot);
+        if constexpr (W) dot2 = fma(x, Be2[k], dot2);
+        mx = fmax(mx, x);
+        mn = fmin(mn, x);
+    }
+    RowSums<acc_t> o;
+    o.sum = wave_sum(sum);
+    o.dot = wave_sum(dot);
+    o.dot2 = W ? wave_sum(dot2) : (acc_t)0;
+    o.mx = wave_max(mx);
+    o.mn = wave_min(mn);
+    return o;
+}
+
+// T_m in double precision from the row's (sum, max, min) and S1, S2, S3; mu receives the mean
+template <typename acc_t>
+__device__ __forceinline__ double row_threshold(const RowSums<acc_t>& r, int K, int N, double S1, double S2, double S3,
+                                                double e_max, double c_sigma, double& mu) {
+    mu = (double)r.sum / (double)K;
+    double var = ((double)r.mx - mu) * (mu - (double)r.mn);
+    var = var > 0 ? var : 0;
+    const double dN = (double)N;
+    const double t_det = dN * fabs(mu) * S1;
+    const double t_var23 = c_sigma * sqrt(dN * mu * mu * S2 + dN * dN * var * S3);
+    const double t_var4 = c_sigma * sqrt(dN) * sqrt(var) * sqrt(S2);
+    return e_max * (t_det + t_var23 + t_var4);
+}
+
+}  // namespace vabft

@@ -80,6 +80,13 @@ template <> struct Unpack<double> {
 };
 
 
+// 16 bytes of a row of T elements, aligned to the element only (the hardware takes unaligned global loads)
+template <typename T> __device__ __forceinline__ raw16 ld16u(const void* p) {
+    raw16 v;
+    __builtin_memcpy(&v, __builtin_assume_aligned(p, Elem<T>::bytes), 16);
+    return v;
+}
+
 static inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
 }  // namespace vabft

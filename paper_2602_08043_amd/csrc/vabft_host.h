@@ -36,7 +36,8 @@ int threshold_blocks_dispatch(const vabft_problem* p, const void* dA, const void
                               hipStream_t st);
 int finalize_blocks_dispatch(const vabft_problem* p, const void* rowpart, const void* d_expected_blk,
                              const void* d_T_blk, void* d_rowsum_blk, void* d_E_blk, int32_t* d_blockflags, void* d_E,
-                             int32_t* d_flags, int32_t* d_nflag, int32_t* d_nblockflag, hipStream_t st);
+                             int32_t* d_flags, int32_t* d_nflag, int32_t* d_nblockflag, int sub, int nparts,
+                             hipStream_t st);
 int finalize_blocks_k_dispatch(const vabft_problem* p, int nkb, const double* kprefix, const void* d_expected_blk,
                                const void* d_T_blk, void* d_rowsum_blk, void* d_E_blk, int32_t* d_blockflags,
                                void* d_E, int32_t* d_flags, int32_t* d_nflag, int32_t* d_nblockflag, hipStream_t st);
@@ -63,7 +64,6 @@ struct GemmArgs {
     int32_t M, N, K;
     int64_t lda, ldb, ldc;
     int32_t tiles_m, tiles_n;
-    int32_t a_vec_ok, b_vec_ok, c_vec_ok;
     void* rowpart;    // [tiles_n][M] acc: per-tile-column partial row sums
     int32_t* d_nflag; // number of flagged rows
     InjectArgs inj;
@@ -134,22 +134,30 @@ int gemm_dispatch(const vabft_problem* p, const void* dA, const void* dB, void* 
                   void* ws, hipStream_t st, const ColArgs* cols = nullptr, const BlockArgs* blocks = nullptr);
 void workspace_init_launch(void* ws, size_t bytes, hipStream_t st);
 
+// gemm_direct.h: workgroup tiles of 16 x 32 (K x N B: 16 x 64), 32 x 32 (32 x 64) and 64 x 64
+enum DirectShape { DIRECT_NONE = -1, DIRECT_16 = 0, DIRECT_32 = 1, DIRECT_32W = 2, DIRECT_ANY = 3, DIRECT_64 = 4 };
+struct DirectArgs {
+    GemmArgs g;
+    int32_t verify, wsum, csum;  // the check; with position-weighted row sums; with column sums
+    int32_t stat_blocks;         // > 0: that many workgroups in front run the A-side pass
+};
+int gemm_direct_launch_bf16(const DirectArgs& d, int shape, int transB, hipStream_t st);
+int gemm_direct_launch_f16(const DirectArgs& d, int shape, int transB, hipStream_t st);
+int gemm_direct_launch_f8(const DirectArgs& d, int shape, int transB, hipStream_t st);
+int gemm_direct_launch_bf8(const DirectArgs& d, int shape, int transB, hipStream_t st);
+int gemm_direct_launch_f32(const DirectArgs& d, int shape, int transB, hipStream_t st);
+int gemm_direct_launch_f64(const DirectArgs& d, int shape, int transB, hipStream_t st);
+
 // per-dtype launchers (one translation unit each, to compile in parallel)
 // mode: 0 plain, 1 check, 2 check + injector + weighted row sums + column sums, 3 check + weighted row
 // sums, 4 check + column sums, 5 row-sum partials only (block-wise check, whole-tile kernels).
-// With edge == false the kernels do the compare-and-flag step themselves (and, with
-// GemmArgs::fused_stats, the A-side statistics and thresholds); otherwise the caller launches the
-// finalize kernel.
-int gemm16_launch_bf16_nn(const GemmArgs& a, int mode, bool edge, hipStream_t st);
-int gemm16_launch_bf16_nt(const GemmArgs& a, int mode, bool edge, hipStream_t st);
-int gemm16_launch_f16_nn(const GemmArgs& a, int mode, bool edge, hipStream_t st);
-int gemm16_launch_f16_nt(const GemmArgs& a, int mode, bool edge, hipStream_t st);
+// The kernels do the compare-and-flag step themselves and, with GemmArgs::fused_stats, the A-side statistics and
+// thresholds.
+int gemm16_launch_bf16_nn(const GemmArgs& a, int mode, hipStream_t st);
+int gemm16_launch_bf16_nt(const GemmArgs& a, int mode, hipStream_t st);
+int gemm16_launch_f16_nn(const GemmArgs& a, int mode, hipStream_t st);
+int gemm16_launch_f16_nt(const GemmArgs& a, int mode, hipStream_t st);
 int gemm8_launch_f8_nt(const GemmArgs& a, int mode, hipStream_t st);   // E4M3, whole tiles only
 int gemm8_launch_bf8_nt(const GemmArgs& a, int mode, hipStream_t st);  // E5M2, whole tiles only
-// FP8 problems of any shape and either layout of B (guarded kernel, operands widened to FP16 on load)
-int gemm16_launch_f8_edge(const GemmArgs& a, int mode, int e5m2, int transB, hipStream_t st);
-// wave_tile: 64 (128 x 128 tiles per workgroup) or 32 (64 x 64 tiles); a.tiles_m / a.tiles_n must count tiles of that size
-int gemmw_launch_f32(const GemmArgs& a, int transB, int mode, bool edge, int wave_tile, hipStream_t st);
-int gemmw_launch_f64(const GemmArgs& a, int transB, int mode, bool edge, int wave_tile, hipStream_t st);
 
 }  // namespace vabft

@@ -1,0 +1,216 @@
+"""Both families of GEMM kernels on every route, at the sizes where they can go wrong: the direct kernels (every tile
+shape: single rows, remainders in every direction, a K that ends inside a step, rows of under 16 bytes, rows far apart,
+unaligned bases and pitches) and the whole-tile kernels with the smallest number of tiles that still takes them."""
+import numpy as np
+import pytest
+
+import workloads as wl
+from oracle import vabft_oracle as orc
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+from test_gpu_parity import _acc_np, _dev, _emax, _session, check_C, check_light, check_rows  # noqa: E402
+from test_gpu_blocks import check_blocks  # noqa: E402
+from test_gpu_columns import check_columns  # noqa: E402
+from test_gpu_fp8 import check_C8  # noqa: E402
+from test_gpu_weighted import check_weighted  # noqa: E402
+
+FP8 = ("f8", "f8e5m2")
+_TDT = {"bf16": torch.bfloat16, "f16": torch.float16, "f32": torch.float32, "f64": torch.float64,
+        "f8": torch.float8_e4m3fn, "f8e5m2": torch.float8_e5m2}
+
+
+def _gen(dtype, M, N, K, transB, seed):
+    g = wl.rng(seed, 23)
+    A = wl.to_storage(g.normal(size=(M, K)), dtype)
+    B = wl.to_storage(g.normal(size=(N, K) if transB else (K, N)), dtype)
+    return A, B
+
+
+def _check(vg, A, B, dA, dB, dtype, M, N, K, transB, routes):
+    from paper_2602_08043_amd import binding as vb
+    o = orc.verify(A, B, dtype, transB, e_max=_emax(dtype, K, N))
+    C_ok = check_C8 if dtype in FP8 else check_C
+    C_args = (A, B, transB, dtype) if dtype in FP8 else (A, B, dtype, transB)
+    for route in routes:
+        print(f"{route} {dtype} {M}x{N}x{K} transB={transB}", flush=True)
+        vg.astat.fill_(float("nan"))
+        if route == "fused_deferred":
+            vg.run_fused(dA, dB, defer_S=True)
+        elif route == "blocks":
+            e_blk = vb.vabft_default_emax(dtype, K, min(N, vg.W))
+            vg.run_blocks(dA, dB)
+            r = vg.results()
+            ob = orc.verify_blocks(A, B, dtype, transB, vg.W, e_blk)
+            check_blocks(r, ob, dtype)
+            C_ok(r, o, *C_args)
+            assert r["nflag"] == 0 and r["nblockflag"] == 0 and not r["blockflags"].any()
+            continue
+        else:
+            getattr(vg, route)(dA, dB)
+        r = vg.results()
+        if route == "fused_deferred":
+            r["S"] = o["S"]
+        check_light(r, o, dtype, M, N, K)
+        check_rows(r, o, dtype)
+        C_ok(r, o, *C_args)
+        assert r["nflag"] == 0 and not r["flags"].any()
+        if route == "run_weighted":
+            check_weighted(r, o, dtype)
+        if route == "run_rc":
+            oc = orc.verify_columns(A, B, dtype, transB, e_max=_emax(dtype, K, max(N, M)))
+            check_columns(r, oc, dtype, M, N, K)
+            assert r["ncolflag"] == 0
+    # one flip in the last row and column, one in the first
+    bit = 60 if dtype == "f64" else 29
+    faults = sorted({(0, 0, bit), (M - 1, N - 1, bit)})
+    inj = vg.make_inject(mode=1, faults=faults)
+    vg.run_fused(dA, dB, inj=inj)
+    r = vg.results()
+    n, recs = vg.inject_records()
+    assert n == len(faults) and [q[:3] for q in recs] == faults
+    acc = _acc_np(dtype) if dtype not in FP8 else np.float32
+    assert all(after == orc.bitflip(before, b, acc) for (_i, _j, b, before, after) in recs)
+    rs = orc.replay_faults(o["rowsum"], recs)
+    want = orc.fault_flags(orc.verification_difference(o["expected"], rs), o["T"])
+    assert np.array_equal(r["flags"], want) and r["nflag"] == int(want.sum()) > 0
+
+
+ALL = ("run", "run_fused", "fused_deferred", "run_weighted", "run_rc", "blocks")
+
+DIRECT = [
+    # at most 16 rows: 16 x 32 / 16 x 64 tiles
+    ("bf16", 1, 33, 65, 1), ("f16", 16, 130, 127, 0), ("f32", 15, 31, 200, 1), ("f64", 7, 65, 17, 0), ("f8", 5, 70, 129, 1),
+    ("f8e5m2", 3, 66, 300, 0),
+    # few tiles, long K: 32 x 32
+    ("bf16", 33, 70, 2100, 1), ("f16", 70, 65, 2049, 0), ("f32", 65, 33, 1027, 1), ("f64", 40, 100, 515, 0),
+    ("f8", 35, 97, 4100, 1),
+    # 32 x 64
+    ("bf16", 100, 200, 130, 0), ("f16", 31, 64, 64, 1), ("f32", 65, 129, 33, 0), ("f64", 97, 130, 15, 1),
+    ("f8", 100, 130, 50, 0), ("f8e5m2", 64, 64, 128, 1),
+    # 64 x 64
+    ("bf16", 641, 1001, 2050, 1), ("f16", 640, 1000, 2049, 0), ("bf16", 1473, 1409, 63, 0), ("f32", 1473, 1473, 31, 0),
+    ("f32", 1500, 1500, 33, 1), ("f8", 1473, 1409, 130, 1),
+    # rows of under 16 bytes
+    ("bf16", 40, 70, 7, 1), ("f16", 33, 5, 20, 0), ("f32", 10, 3, 3, 0), ("f64", 5, 1, 1, 1), ("f8", 9, 15, 40, 0),
+    ("bf16", 20, 1, 90, 0),
+]
+
+
+@pytest.mark.parametrize("dtype,M,N,K,transB", DIRECT)
+def test_direct_shapes(dtype, M, N, K, transB):
+    A, B = _gen(dtype, M, N, K, transB, 5)
+    vg = _session(M, N, K, dtype, transB)
+    _check(vg, A, B, _dev(A, dtype), _dev(B, dtype), dtype, M, N, K, transB, ALL)
+
+
+@pytest.mark.parametrize("dtype,M,N,K,transB", [("bf16", 70, 131, 200, 1), ("f16", 33, 100, 2065, 0), ("f32", 65, 67, 70, 0),
+                                                ("f64", 40, 70, 33, 1), ("f8", 50, 70, 131, 1), ("f8e5m2", 17, 90, 70, 0)])
+def test_direct_unaligned_base_and_pitch(dtype, M, N, K, transB):
+    """A, B and C start one element behind an aligned address and their rows are one, three and one elements longer
+    than needed; what lies between the rows of C is not written, what lies between those of A and B not used."""
+    from paper_2602_08043_amd import binding as vb
+    A, B = _gen(dtype, M, N, K, transB, 6)
+    rb, cb = B.shape
+
+    def shifted(x, ld, fill):
+        t = torch.full((x.shape[0] * ld + 1,), fill, dtype=torch.float32, device="cuda").to(x.dtype)
+        v = t[1:].view(x.shape[0], ld)
+        v[:, :x.shape[1]].view(torch.uint8 if x.element_size() == 1 else v.dtype).copy_(
+            x.view(torch.uint8) if x.element_size() == 1 else x)
+        return v
+    dA, dB = shifted(_dev(A, dtype), K + 1, 400.0), shifted(_dev(B, dtype), cb + 3, -400.0)
+    vg = _session(M, N, K, dtype, transB)
+    vg.problem = vb.make_problem(M, N, K, dtype, transB, K + 1, cb + 3, N + 1)
+    buf = torch.full((M * (N + 1) + 1,), 7.0, dtype=vg.C.dtype, device="cuda")
+
+    class Narrow(type(vg)):
+        def results(self):
+            r = super().results()
+            full = self.C.float().cpu().numpy()
+            assert np.all(full[:, N:] == 7.0)
+            r["C"] = r["C"][:, :N]
+            return r
+    vg.__class__ = Narrow
+    vg.C = buf[1:].view(M, N + 1)
+    _check(vg, A, B, dA, dB, dtype, M, N, K, transB, ALL)
+
+
+def test_direct_rows_far_apart():
+    """Rows of A 68 MB apart: byte offsets inside a tile need more than 32 bits."""
+    from paper_2602_08043_amd import binding as vb
+    dtype, M, N, K, lda = "bf16", 66, 70, 130, 34_000_000
+    A, B = _gen(dtype, M, N, K, 1, 7)
+    far = torch.zeros(((M - 1) * lda + K,), dtype=torch.bfloat16, device="cuda").as_strided((M, K), (lda, 1))
+    far.copy_(_dev(A, dtype))
+    vg = _session(M, N, K, dtype, 1)
+    vg.problem = vb.make_problem(M, N, K, dtype, 1, lda, K, N)
+    _check(vg, A, B, far, _dev(B, dtype), dtype, M, N, K, 1, ("run", "run_fused", "blocks"))
+
+
+@pytest.mark.parametrize("dtype,M,N,K,transB", [("bf16", 35, 75, 70, 1), ("bf16", 35, 75, 70, 0), ("f32", 35, 75, 37, 0),
+                                                ("f64", 35, 75, 19, 1), ("f16", 100, 130, 2100, 0)])
+def test_direct_infinities_stay_in_their_row_and_column(dtype, M, N, K, transB):
+    """What a tile reads in place of rows, columns and k past the end must not leak: an infinity in the last row of A
+    reaches that row of C only, one in the last column of B that column only (and flags every row through its sum)."""
+    g = wl.rng(8, 23)
+    A = np.abs(g.normal(size=(M, K))) + 0.1
+    Bl = np.abs(g.normal(size=(K, N))) + 0.1
+    A[M - 1, K - 1] = np.inf
+    for col in (False, True):
+        Bc = Bl.copy()
+        if col:
+            Bc[K - 1, N - 1] = np.inf
+
+        def dev(x):
+            return torch.from_numpy(np.ascontiguousarray(x)).to(_TDT[dtype]).cuda()
+        dA, dB = dev(A), dev(Bc.T if transB else Bc)
+        vg = _session(M, N, K, dtype, transB)
+        vg.encode(dB)
+        vg.gemm_fused(dA, dB)
+        C = vg.C.float().cpu().numpy()
+        print(f"infinities {dtype} {M}x{N}x{K} transB={transB} col={col}", flush=True)
+        want = np.zeros((M, N), dtype=bool)
+        want[M - 1, :] = True
+        want[:, N - 1] |= col
+        assert np.array_equal(~np.isfinite(C), want)
+        flags = vg.flags.cpu().numpy()
+        assert flags[M - 1] == 1 and (flags.all() if col else not flags[:M - 1].any())
+        assert int(vg.nflag.item()) == int(flags.sum())
+
+
+WHOLE = [("bf16", 2304, 2304, 256, 0), ("bf16", 2304, 2304, 192, 1), ("f16", 2304, 2304, 384, 1), ("f16", 2304, 2304, 64, 0),
+         ("f8", 1792, 1792, 512, 1), ("f8e5m2", 1792, 1792, 256, 1)]
+
+
+@pytest.mark.parametrize("dtype,M,N,K,transB", WHOLE)
+def test_whole_tile_kernels(dtype, M, N, K, transB):
+    """81 (FP8: 49) tiles of 256 x 256: just above the line below which the direct kernels take over."""
+    A, B = _gen(dtype, M, N, K, transB, 9)
+    vg = _session(M, N, K, dtype, transB)
+    _check(vg, A, B, _dev(A, dtype), _dev(B, dtype), dtype, M, N, K, transB, ALL)
+
+
+def test_one_workspace_for_fewer_rows():
+    """A workspace sized for M rows serves every problem with fewer: the routes change with M, the counters they share
+    stay zero and no partial leaves the workspace."""
+    from paper_2602_08043_amd import binding as vb
+    dtype, N, K, Mmax = "bf16", 2304, 256, 2304
+    A, B = _gen(dtype, Mmax, N, K, 1, 10)
+    dA, dB = _dev(A, dtype), _dev(B, dtype)
+    need = vb.vabft_workspace_bytes(vb.make_problem(Mmax, N, K, dtype, 1))
+    ws = torch.empty(need + 4096, dtype=torch.uint8, device="cuda")
+    vb.vabft_workspace_init(ws.data_ptr(), need, None)
+    ws[need:] = 0x5A
+    o = orc.verify(A, B, dtype, 1, e_max=_emax(dtype, K, N))
+    for M in (1, 2304, 17, 40, 300, 2304, 1500):
+        vg = _session(M, N, K, dtype, 1)
+        vg.ws, vg.ws_bytes = ws, need
+        vg.run_fused(dA[:M].contiguous(), dB, defer_S=True)
+        r = vg.results()
+        print(f"shared workspace M={M}", flush=True)
+        assert np.all(np.abs(r["rowsum"] - o["rowsum"][:M]) <= 1e-5 * o["scale_rowsum"][:M])
+        assert np.all(np.abs(r["expected"] - o["expected"][:M]) <= 1e-5 * o["scale_expected"][:M])
+        assert r["nflag"] == 0 and not r["flags"].any()
+        assert bool((ws[need:] == 0x5A).all())
