@@ -86,7 +86,7 @@ template <> struct CElem<double> {
 // integer or outside 0..N-1 (more than one error, or an error too close to the rounding noise of
 // the weighted sums); else the column.  delta[i] = D1 for flagged rows, 0 otherwise.
 template <typename T>
-__global__ __launch_bounds__(256) void locate_correct_kernel(void* __restrict__ Cv, int M, int N, int64_t ldc,
+__global__ __launch_bounds__(1024) void locate_correct_kernel(void* __restrict__ Cv, int M, int N, int64_t ldc,
                                                              const typename Elem<T>::acc_t* __restrict__ expected,
                                                              const typename Elem<T>::acc_t* __restrict__ expected2,
                                                              const typename Elem<T>::acc_t* __restrict__ rowsum,
@@ -97,9 +97,8 @@ __global__ __launch_bounds__(256) void locate_correct_kernel(void* __restrict__ 
                                                              int32_t* __restrict__ ncorrected) {
     using acc_t = typename Elem<T>::acc_t;
     using store_t = typename CElem<T>::store_t;
-    const int i = blockIdx.x * 256 + threadIdx.x;
     int done = 0;
-    if (i < M) {
+    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < M; i += gridDim.x * blockDim.x) {
         int l = -1;
         acc_t d = 0;
         if (flags[i]) {
@@ -115,7 +114,7 @@ __global__ __launch_bounds__(256) void locate_correct_kernel(void* __restrict__ 
                     if (correct) {
                         store_t* c = reinterpret_cast<store_t*>(Cv) + (int64_t)i * ldc + l;
                         CElem<T>::put(c, CElem<T>::get(c) - d);
-                        done = 1;
+                        ++done;
                     }
                 }
             }
@@ -123,8 +122,20 @@ __global__ __launch_bounds__(256) void locate_correct_kernel(void* __restrict__ 
         loc[i] = l;
         delta[i] = d;
     }
-    const int cnt = __syncthreads_count(done);
-    if (threadIdx.x == 0 && cnt) atomicAdd(ncorrected, cnt);
+    if (gridDim.x == 1) {  // the workgroup has seen every row: no counter to clear before, one launch
+        __shared__ int s_done[16];
+        done = wave_sum(done);
+        if (threadIdx.x % WAVE == 0) s_done[threadIdx.x / WAVE] = done;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            int n = 0;
+            for (int w = 0; w < (int)blockDim.x / WAVE; ++w) n += s_done[w];
+            *ncorrected = n;
+        }
+    } else {
+        const int cnt = __syncthreads_count(done);  // one row per thread
+        if (threadIdx.x == 0 && cnt) atomicAdd(ncorrected, cnt);
+    }
 }
 
 static inline size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
@@ -909,8 +920,10 @@ int vabft_locate_correct(const vabft_problem* p, void* dC, const void* d_expecte
         !aligned_to(d_delta, ab) || !aligned_to(d_ncorrected, 4))
         return VABFT_EINVAL;
     hipStream_t st = (hipStream_t)stream;
-    const dim3 grid((p->M + 255) / 256), block(256);
-    zero_int_kernel<<<1, 1, 0, st>>>(d_ncorrected);
+    // up to 4096 rows: one workgroup that counts by itself; more rows: workgroups that count into a cleared word
+    const bool one = p->M <= 4096;
+    const dim3 grid(one ? 1 : (p->M + 255) / 256), block(one ? 1024 : 256);
+    if (!one) zero_int_kernel<<<1, 1, 0, st>>>(d_ncorrected);
 #define VABFT_LOC_CASE(T, A)                                                                                     \
     locate_correct_kernel<T><<<grid, block, 0, st>>>(dC, p->M, p->N, p->ldc, (const A*)d_expected,               \
                                                      (const A*)d_expected2, (const A*)d_rowsum,                  \

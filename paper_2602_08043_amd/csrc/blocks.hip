@@ -85,17 +85,13 @@ __global__ __launch_bounds__(256) void encode_blocks_rows_vec_kernel(const void*
                 }
             }
             if (cpb == 32) {
-                sum += __shfl_xor(sum, 16, WAVE);
-                const acc_t a = __shfl_xor(mx, 16, WAVE), b = __shfl_xor(mn, 16, WAVE);
-                mx = fmax(mx, a);
-                mn = fmin(mn, b);
-            }
-#pragma unroll
-            for (int off = 8; off >= 1; off >>= 1) {
-                sum += __shfl_xor(sum, off, WAVE);
-                const acc_t a = __shfl_xor(mx, off, WAVE), b = __shfl_xor(mn, off, WAVE);
-                mx = fmax(mx, a);
-                mn = fmin(mn, b);
+                sum = group_sum<32>(sum);
+                mx = group_max<32>(mx);
+                mn = group_min<32>(mn);
+            } else {
+                sum = group_sum<16>(sum);
+                mx = group_max<16>(mx);
+                mn = group_min<16>(mn);
             }
             if (ok && lane % cpb == 0) {
                 acc_t* q = part + (int64_t)(c / cpb) * 3 * K;

@@ -445,10 +445,11 @@ __global__ __launch_bounds__(256) void threshold_rows_kernel(const void* __restr
     const int m = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (m >= M) return;
     const char* row = reinterpret_cast<const char*>(A) + (int64_t)m * lda * Elem<T>::bytes;
+    const double S1 = S[0], S2 = S[1], S3 = S[2];  // (ahead of the row: not one more round trip behind it)
     const RowSums<acc_t> r = row_sums<T, W, THR_NL>(row, K, lane, Be, Be2);
     if (lane == 0) {
         double mu;
-        const double t = row_threshold(r, K, N, S[0], S[1], S[2], e_max, c_sigma, mu);
+        const double t = row_threshold(r, K, N, S1, S2, S3, e_max, c_sigma, mu);
         if constexpr (W) expected2[m] = r.dot2;
         astat[3 * (int64_t)m + 0] = r.mx;
         astat[3 * (int64_t)m + 1] = r.mn;
@@ -530,20 +531,22 @@ static int col_rows_per_block(int dtype, int64_t rows, int64_t cols) {
     return (blocks128 < 512 || (blocks128 < 2048 && rows <= 8192)) ? 64 : 128;
 }
 
-// Rows k per block of the finishing kernel: 16, or fewer (K x N layout) when 16 would leave most of the
-// chip's 256 compute units without a block
+// Rows k per block of the finishing kernel: 16, or fewer (K x N layout) where 16 would leave most of the
+// chip's 256 compute units without a block and a wavefront with more than 4 KiB of a row.  (Rows of up to 4 KiB are
+// one batch of loads for one wavefront: splitting them only adds arrivals, 11 ns each on one address, to the fold.)
 static int encode_rows_per_block(const vabft_problem* p, int waves) {
     if (p->transB) return 16;
+    const int64_t eb = p->dtype == VABFT_F64 ? 8 : p->dtype == VABFT_F32 ? 4 : (p->dtype == VABFT_F8E4M3 || p->dtype == VABFT_F8E5M2) ? 1 : 2;
     int rpb = waves;
-    while (rpb > 1 && (p->K + rpb - 1) / rpb < 256) rpb >>= 1;
+    while (rpb > 1 && (p->K + rpb - 1) / rpb < 256 && p->N * eb * rpb > 4096 * waves) rpb >>= 1;
     return rpb;
 }
 constexpr int ENC_WAVES_OWN_FOLD = 16, ENC_WAVES_DEFERRED = 8;
-// Wavefronts per workgroup of the row walk.  The smaller workgroup is only used when both sizes give one
-// wavefront per row (K >= 4096): with several wavefronts per row the split of a row into segments (and with it
+// Wavefronts per workgroup of the row walk.  The smaller workgroup is only used for many rows, where both sizes give
+// one wavefront per row: with several wavefronts per row the split of a row into segments (and with it
 // the rounding of Be) would depend on the workgroup size, and both routes must produce the same bits.
 static int encode_rows_waves(const vabft_problem* p, bool deferred) {
-    if (deferred && encode_rows_per_block(p, ENC_WAVES_OWN_FOLD) == ENC_WAVES_OWN_FOLD) return ENC_WAVES_DEFERRED;
+    if (deferred && p->K > 255 * ENC_WAVES_OWN_FOLD) return ENC_WAVES_DEFERRED;
     return ENC_WAVES_OWN_FOLD;
 }
 // Per-block partials of (S1, S2, S3), [blocks][3] doubles: the number an encode with the fold deferred leaves

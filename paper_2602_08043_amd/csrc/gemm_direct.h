@@ -267,26 +267,15 @@ template <typename T, int TRANSB, int MF, int NF, int WVK> struct Shape {
 
 }  // namespace gd
 
-// The last workgroup of tile-row bm to arrive (GEMM tiles and, with the A-side pass fused, its workgroups) folds the
-// partial row sums and compares.  Every thread of every workgroup calls this after its partials are written.
-template <typename T, typename S>
-__device__ __forceinline__ void direct_tile_row_check(const DirectArgs& d, int bm, int* s_last) {
+// Folds the partial row sums of `rows` rows from row0 on and compares; TPF neighbouring threads share a row.  Returns
+// the number of flagged rows.
+template <typename T, int TPF> __device__ __forceinline__ int direct_compare(const DirectArgs& d, int row0, int rows) {
     using acc_t = typename Elem<T>::acc_t;
-    const GemmArgs& g = d.g;
-    const int tid = threadIdx.x;
-    const int row0 = bm * S::BM, rows = min(S::BM, g.M - row0);
-    const int arrivals = g.tiles_n + (d.stat_blocks ? (rows + S::NW - 1) / S::NW : 0);
-    __builtin_amdgcn_s_waitcnt(0);  // this wavefront's partials are performed
-    __syncthreads();
-    if (tid == 0) *s_last = (atomicAdd(&g.tickets[bm], 1) == arrivals - 1);
-    __syncthreads();
-    if (!*s_last) return;
-    constexpr int TPF = S::NT / S::BM;  // neighbouring threads that share a row
     static_assert(TPF >= 1 && TPF <= 64, "fold mapping");
-    const int r = tid / TPF, sub = tid % TPF;
-    const bool act = r < rows;
+    const GemmArgs& g = d.g;
+    const int r = threadIdx.x / TPF, sub = threadIdx.x % TPF;
+    const bool act = r < rows, wsum = d.wsum != 0;
     const int gi = row0 + (act ? r : 0);
-    const bool wsum = d.wsum != 0;
     acc_t s4[4] = {0, 0, 0, 0}, w4[4] = {0, 0, 0, 0};
     for (int t0 = sub; t0 < g.tiles_n; t0 += 16 * TPF) {
         acc_t v[16], v2[16];
@@ -304,12 +293,9 @@ __device__ __forceinline__ void direct_tile_row_check(const DirectArgs& d, int b
                 w4[j & 3] += v2[j];
             }
     }
-    acc_t s = (s4[0] + s4[1]) + (s4[2] + s4[3]), s2 = (w4[0] + w4[1]) + (w4[2] + w4[3]);
-#pragma unroll
-    for (int o = 1; o < TPF; o <<= 1) {
-        s += __shfl_xor(s, o, WAVE);
-        s2 += __shfl_xor(s2, o, WAVE);
-    }
+    const acc_t s = group_sum<TPF>((s4[0] + s4[1]) + (s4[2] + s4[3]));
+    acc_t s2 = (w4[0] + w4[1]) + (w4[2] + w4[3]);
+    if (wsum) s2 = group_sum<TPF>(s2);
     int f = 0;
     if (act && sub == 0) {
         const acc_t* ex = reinterpret_cast<const acc_t*>(g.expected) + gi;
@@ -322,19 +308,38 @@ __device__ __forceinline__ void direct_tile_row_check(const DirectArgs& d, int b
         reinterpret_cast<acc_t*>(g.E)[gi] = e;
         g.flags[gi] = f;
     }
-    const int cnt = __syncthreads_count(f);
-    if (tid == 0 && g.tiles_m == 1) {
-        *g.d_nflag = cnt;
-        __hip_atomic_store(&g.tickets[bm], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    } else if (tid == 0) {
-        // this tile-row is done: reset its ticket, then one 64-bit atomic counts the finished tile-rows (high word)
-        // and the flagged rows (low word); whoever completes the count publishes nflag and leaves the counter zero
-        __hip_atomic_store(&g.tickets[bm], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        unsigned long long* done = reinterpret_cast<unsigned long long*>(g.tickets + ((g.tiles_m + 1) & ~1));
-        const unsigned long long old = atomicAdd(done, (1ull << 32) | (unsigned long long)(unsigned)cnt);
-        if ((int)(old >> 32) == g.tiles_m - 1) {
-            *g.d_nflag = (int)(unsigned)(old & 0xffffffffull) + cnt;
-            __hip_atomic_store(done, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return __syncthreads_count(f);
+}
+
+// The last workgroup of tile-row bm to arrive (GEMM tiles and, with the A-side pass fused, its workgroups) compares the
+// tile-row.  Problems of a few tiles and no more rows than a workgroup has threads arrive at one counter for all
+// tile-rows: the last workgroup compares every row and knows nflag, one round trip to memory less.
+// Every thread of every workgroup calls this after its partials are written.
+template <typename T, typename S>
+__device__ __forceinline__ void direct_tile_row_check(const DirectArgs& d, int bm, int* s_last) {
+    const GemmArgs& g = d.g;
+    const bool one = g.tiles_m == 1 || (g.tiles_m * g.tiles_n <= 64 && g.M <= S::NT);
+    const int at = one ? 0 : bm, row0 = at * S::BM, rows = one ? g.M : min(S::BM, g.M - row0);
+    const int arrivals = (one ? g.tiles_m : 1) * g.tiles_n + (d.stat_blocks ? (rows + S::NW - 1) / S::NW : 0);
+    __builtin_amdgcn_s_waitcnt(0);  // this wavefront's partials are performed
+    __syncthreads();
+    if (threadIdx.x == 0) *s_last = (atomicAdd(&g.tickets[at], 1) == arrivals - 1);
+    __syncthreads();
+    if (!*s_last) return;
+    const int cnt = one && g.tiles_m > 1 ? direct_compare<T, 1>(d, 0, rows) : direct_compare<T, S::NT / S::BM>(d, row0, rows);
+    if (threadIdx.x == 0) {
+        __hip_atomic_store(&g.tickets[at], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (one) {
+            *g.d_nflag = cnt;
+        } else {
+            // one 64-bit atomic counts the finished tile-rows (high word) and the flagged rows (low word); whoever
+            // completes the count publishes nflag and leaves the counter zero
+            unsigned long long* done = reinterpret_cast<unsigned long long*>(g.tickets + ((g.tiles_m + 1) & ~1));
+            const unsigned long long old = atomicAdd(done, (1ull << 32) | (unsigned long long)(unsigned)cnt);
+            if ((int)(old >> 32) == g.tiles_m - 1) {
+                *g.d_nflag = (int)(unsigned)(old & 0xffffffffull) + cnt;
+                __hip_atomic_store(done, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
         }
     }
 }
@@ -350,12 +355,13 @@ __device__ __forceinline__ void direct_stats(const DirectArgs& d, double* s_red,
         fold_s_partials_to_lds(g.s_partial, g.s_nparts, threadIdx.x, s_red);
         __syncthreads();
     }
+    // (ahead of the row: not one more round trip behind it)
+    const double S1 = g.S ? g.S[0] : folded_s(s_red, 0), S2 = g.S ? g.S[1] : folded_s(s_red, 1),
+                 S3 = g.S ? g.S[2] : folded_s(s_red, 2);
     if (m < g.M) {
         const char* row = reinterpret_cast<const char*>(g.A) + (int64_t)m * g.lda * Elem<T>::bytes;
         const RowSums<acc_t> r = row_sums<T, false, 4>(row, g.K, lane, reinterpret_cast<const acc_t*>(g.Be), nullptr);
         if (lane == 0) {
-            const double S1 = g.S ? g.S[0] : folded_s(s_red, 0), S2 = g.S ? g.S[1] : folded_s(s_red, 1),
-                         S3 = g.S ? g.S[2] : folded_s(s_red, 2);
             double mu;
             const acc_t t = (acc_t)row_threshold(r, g.K, g.N, S1, S2, S3, g.e_max, g.c_sigma, mu);
             acc_t* astat = reinterpret_cast<acc_t*>(g.astat) + 3 * (int64_t)m;
@@ -702,11 +708,8 @@ __global__ __launch_bounds__(64 * WVK, 2) void gemm_direct_kernel(const DirectAr
                 for (int e = 0; e + w < EPT; e += 2 * w) x[e] += x[e + w];
             acc_t s = x[0];
             if (wsum) s2 = fma((acc_t)(col0 + tc + 1), s, s2);
-#pragma unroll
-            for (int o = 1; o < S::TPR; o <<= 1) {
-                s += __shfl_xor(s, o, WAVE);
-                if (wsum) s2 += __shfl_xor(s2, o, WAVE);
-            }
+            s = group_sum<S::TPR>(s);
+            if (wsum) s2 = group_sum<S::TPR>(s2);
             if (tid % S::TPR == 0 && gi < g.M) {
                 gd::st_agent(reinterpret_cast<acc_t*>(g.rowpart) + (int64_t)bn * g.M + gi, s);
                 if (wsum) gd::st_agent(reinterpret_cast<acc_t*>(g.rowpart2) + (int64_t)bn * g.M + gi, s2);

@@ -83,7 +83,7 @@ __device__ __forceinline__ double row_threshold(const RowSums<acc_t>& r, int K, 
     const double dN = (double)N;
     const double t_det = dN * fabs(mu) * S1;
     const double t_var23 = c_sigma * sqrt(dN * mu * mu * S2 + dN * dN * var * S3);
-    const double t_var4 = c_sigma * sqrt(dN) * sqrt(var) * sqrt(S2);
+    const double t_var4 = c_sigma * sqrt(dN * var * S2);  // = c sqrt(N) sigma_A sqrt(S2), one root
     return e_max * (t_det + t_var23 + t_var4);
 }
 

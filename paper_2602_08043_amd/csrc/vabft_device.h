@@ -77,29 +77,76 @@ template <> struct Elem<double> {
 };
 
 // ---------------------------------------------------------------------------
-// wave-level reductions (all 64 lanes end with the result)
+// wave-level reductions (all lanes of the group end with the result)
 // ---------------------------------------------------------------------------
-template <typename T> __device__ __forceinline__ T wave_sum(T v) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, WAVE);
-    return v;
-}
-template <typename T> __device__ __forceinline__ T wave_max(T v) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-        T o = __shfl_xor(v, off, WAVE);
-        v = v > o ? v : o;
+// The partner exchanges of a butterfly (lane ^ 32, 16, 8, 4, 2, 1) as register moves: a lane swap for the halves and
+// the odd and even rows of 16, a rotation inside a row for 8 and 4, a quad permutation for 2 and 1.  Through LDS
+// (ds_bpermute) each of the six steps was a round trip of about 100 cycles, a large part of what a short kernel does
+// after its last load.  TOP is the size of the group, steps run downwards from TOP / 2: after the step at 8 lane i and
+// lane i ^ 8 agree, so rotating by 4 is as good as lane ^ 4; in a group of 8 the first step pairs lane i with lane i ^ 7
+// (a mirror), after which the steps at 2 and 1 complete the group as well.  Every lane must be active.
+template <int OFF, int TOP> __device__ __forceinline__ void lane_exchange(uint32_t v, uint32_t& a, uint32_t& b) {
+    if constexpr (OFF == 32 || OFF == 16) {
+        const auto r = OFF == 32 ? __builtin_amdgcn_permlane32_swap(v, v, false, false)
+                                 : __builtin_amdgcn_permlane16_swap(v, v, false, false);
+        a = r[0];  // the lower lane's value in both lanes of a pair
+        b = r[1];  // the upper lane's
+    } else {
+        constexpr int CTRL = OFF == 8 ? 0x128 : OFF == 4 ? (TOP == 8 ? 0x141 : 0x124) : OFF == 2 ? 0x4E : 0xB1;
+        a = v;
+        b = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xf, 0xf, false);
     }
-    return v;
 }
-template <typename T> __device__ __forceinline__ T wave_min(T v) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-        T o = __shfl_xor(v, off, WAVE);
-        v = v < o ? v : o;
+template <int OFF, int TOP> __device__ __forceinline__ void lane_exchange(float v, float& a, float& b) {
+    uint32_t x, y;
+    lane_exchange<OFF, TOP>(__float_as_uint(v), x, y);
+    a = __uint_as_float(x);
+    b = __uint_as_float(y);
+}
+template <int OFF, int TOP> __device__ __forceinline__ void lane_exchange(int v, int& a, int& b) {
+    uint32_t x, y;
+    lane_exchange<OFF, TOP>((uint32_t)v, x, y);
+    a = (int)x;
+    b = (int)y;
+}
+template <int OFF, int TOP> __device__ __forceinline__ void lane_exchange(double v, double& a, double& b) {
+    uint32_t xl, yl, xh, yh;
+    lane_exchange<OFF, TOP>((uint32_t)__double2loint(v), xl, yl);
+    lane_exchange<OFF, TOP>((uint32_t)__double2hiint(v), xh, yh);
+    a = __hiloint2double((int)xh, (int)xl);
+    b = __hiloint2double((int)yh, (int)yl);
+}
+// sum over aligned groups of W lanes (a power of two)
+template <int W, int TOP = W, typename T> __device__ __forceinline__ T group_sum(T v) {
+    if constexpr (W > 1) {
+        T a, b;
+        lane_exchange<W / 2, TOP>(v, a, b);
+        return group_sum<W / 2, TOP>((T)(a + b));
+    } else {
+        return v;
     }
-    return v;
 }
+template <int W, int TOP = W, typename T> __device__ __forceinline__ T group_max(T v) {
+    if constexpr (W > 1) {
+        T a, b;
+        lane_exchange<W / 2, TOP>(v, a, b);
+        return group_max<W / 2, TOP>(a > b ? a : b);
+    } else {
+        return v;
+    }
+}
+template <int W, int TOP = W, typename T> __device__ __forceinline__ T group_min(T v) {
+    if constexpr (W > 1) {
+        T a, b;
+        lane_exchange<W / 2, TOP>(v, a, b);
+        return group_min<W / 2, TOP>(a < b ? a : b);
+    } else {
+        return v;
+    }
+}
+template <typename T> __device__ __forceinline__ T wave_sum(T v) { return group_sum<WAVE>(v); }
+template <typename T> __device__ __forceinline__ T wave_max(T v) { return group_max<WAVE>(v); }
+template <typename T> __device__ __forceinline__ T wave_min(T v) { return group_min<WAVE>(v); }
 
 // Fold of the per-workgroup partials [count][3] of (S1, S2, S3) (Algorithm 1, k-loop) by the first 256
 // threads of a workgroup, in the order the encode kernels use when they fold them themselves:
