@@ -179,10 +179,11 @@ static int direct_launch(const vabft_problem* p, const DirectArgs& d, int shape,
     return VABFT_EINVAL;
 }
 
-// whole: the problem is made of whole 256 x 256 x 64 tiles (FP8: x 256, B stored N x K) with 16-byte aligned rows.
+// tiled: a kernel with 256 x 256 tiles takes the problem (16-byte aligned rows, see gemm_dispatch).
 // The lines, from fused calls timed inside a HIP graph (us):
-//   * a whole-tile kernel takes the time of one 256 x 256 tile however few there are (12 + 0.0155 K for the 16-bit
-//     types, 15 + 0.009 K for FP8); the direct kernel's time goes with the work.  2048^3 (64 tiles): 44.4 against 40.8
+//   * those kernels take the time of one 256 x 256 tile for every 256 of them, however few there are (12 + 0.0155 K for
+//     the 16-bit types, 15 + 0.009 K for FP8); the direct kernel's time goes with the work, here its 64 x 64 tiles
+//     per round of the others.  2048^3 (64 tiles): 44.4 against 40.8
 //     (K x N) and 44.0 against 42.1 (N x K), 2048 x 4096 x 4096 (128): 76 against 112; FP8 1024^3 (16): 24.1 against
 //     14.2, 2048^3: 33.1 against 41.2.
 //   * 16 x 32 tiles (eight wavefronts share K): at most 16 rows.  N = 4096: 11.4 against 14.9 with 32 x 64;
@@ -193,13 +194,14 @@ static int direct_launch(const vabft_problem* p, const DirectArgs& d, int shape,
 //     27.6; 128 x 4096 x 4096: 21.8 against 19.6; 1024^3: 15.5 against 14.5.  FP32 has the matrix time to hide the
 //     traffic: 2048^3 144 against 150, 1000 x 1200 x 1500 63 against 53 (304 tiles: the last wave is nearly empty).
 //     FP64 has no registers for it.
-static int direct_shape(const vabft_problem* p, bool whole) {
+static int direct_shape(const vabft_problem* p, bool tiled) {
     const int64_t eb = (int64_t)elem_bytes(p->dtype);
-    if (whole && ceil_div(p->M, 256) * ceil_div(p->N, 256) > (is_fp8(p->dtype) ? 36 : 64)) return DIRECT_NONE;
+    const int64_t t64 = ceil_div(p->M, 64) * ceil_div(p->N, 64), t32w = ceil_div(p->M, 32) * ceil_div(p->N, 64);
+    const int64_t rounds = ceil_div(ceil_div(p->M, 256) * ceil_div(p->N, 256), 256);
+    if (tiled && t64 > rounds * (is_fp8(p->dtype) ? 592 : 1040)) return DIRECT_NONE;
     // a tile's byte offsets in 32 bits, and rows of 16 bytes at least
     const bool far = 64 * p->lda * eb >= (1ll << 32) || (p->transB ? 64 * eb : 128) * p->ldb >= (1ll << 32);
     if (far || p->K * eb < 16 || (!p->transB && p->N * eb < 16)) return DIRECT_ANY;
-    const int64_t t64 = ceil_div(p->M, 64) * ceil_div(p->N, 64), t32w = ceil_div(p->M, 32) * ceil_div(p->N, 64);
     const bool long_k = p->K * eb >= 4096;
     if (p->M <= 16 && p->N <= 8192) return DIRECT_16;
     if (t32w <= 32 && long_k) return DIRECT_32;
@@ -399,8 +401,13 @@ int gemm_dispatch(const vabft_problem* p, const void* dA, const void* dB, void* 
     const bool whole = is_tile256(p->dtype) && p->M % 256 == 0 && p->N % 256 == 0 &&
                        p->K % (is_fp8(p->dtype) ? 256 : 64) == 0 && aligned && p->lda <= (1 << 24) &&
                        p->ldb <= (1 << 24) && (!is_fp8(p->dtype) || p->transB);
+    // (the 16-bit kernels also take other sizes for the plain and the checked product; their byte offsets are then
+    // from the tile's first row)
     const bool kblocked = blocks && blocks->kblock > 0;
-    const int shape = kblocked ? (int)DIRECT_NONE : direct_shape(p, whole);
+    const bool ragged = (p->dtype == VABFT_BF16 || p->dtype == VABFT_F16) && !whole && aligned && p->K % 8 == 0 &&
+                        p->K >= 64 && p->N % 8 == 0 && p->lda <= (1 << 22) && p->ldb <= (1 << 22) &&
+                        !d_rowsum2 && !cols && !blocks && a.inj.mode == 0;
+    const int shape = kblocked ? (int)DIRECT_NONE : direct_shape(p, whole || ragged);
     const auto set_stats = [&] {
         a.fused_stats = 1;
         a.Be = fused->d_Be;
@@ -471,8 +478,12 @@ int gemm_dispatch(const vabft_problem* p, const void* dA, const void* dB, void* 
     switch (p->dtype) {
         case VABFT_F8E4M3: rc = gemm8_launch_f8_nt(a, mode, st); break;
         case VABFT_F8E5M2: rc = gemm8_launch_bf8_nt(a, mode, st); break;
-        case VABFT_BF16: rc = p->transB ? gemm16_launch_bf16_nt(a, mode, st) : gemm16_launch_bf16_nn(a, mode, st); break;
-        case VABFT_F16: rc = p->transB ? gemm16_launch_f16_nt(a, mode, st) : gemm16_launch_f16_nn(a, mode, st); break;
+        case VABFT_BF16:
+            rc = p->transB ? gemm16_launch_bf16_nt(a, mode, !whole, st) : gemm16_launch_bf16_nn(a, mode, !whole, st);
+            break;
+        case VABFT_F16:
+            rc = p->transB ? gemm16_launch_f16_nt(a, mode, !whole, st) : gemm16_launch_f16_nn(a, mode, !whole, st);
+            break;
         default: return VABFT_EINVAL;
     }
     if (rc != VABFT_OK || !verify) return rc;

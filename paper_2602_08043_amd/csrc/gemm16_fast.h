@@ -307,7 +307,8 @@ template <> __device__ __forceinline__ uint32_t pack2<f16_t>(float a, float b) {
 // Quantise and store the wavefront's tile of C: each 16 x 128 slab passes through a private LDS buffer so
 // that global stores are 16 bytes per lane and 256 contiguous bytes per row (a lane owns 4 consecutive
 // columns of one row, which alone would give 8-byte pieces scattered over 16 rows).
-template <typename T>
+// EDGE: rows and 16-byte column groups past the end are left out (N is a multiple of 8 then).
+template <typename T, bool EDGE>
 __device__ __forceinline__ void gemm16x_store_c(const GemmArgs& g, const f32x4_t (&acc)[8][8], unsigned char* smem,
                                                 int row0, int col0, int lane, int wm, int wn, int l16, int lq) {
     // row pitch 272 B: the 8-byte writes of 16 rows x 2 column groups hit 32 distinct bank pairs
@@ -337,7 +338,7 @@ __device__ __forceinline__ void gemm16x_store_c(const GemmArgs& g, const f32x4_t
             const int gj = col0 + wn * 128 + schunk * 8;
             // C is not read again by this kernel: non-temporal store
             typedef __attribute__((ext_vector_type(4))) uint32_t u32x4_st;
-            __builtin_nontemporal_store(__builtin_bit_cast(u32x4_st, v),
+            if (!EDGE || (gi < g.M && gj < g.N)) __builtin_nontemporal_store(__builtin_bit_cast(u32x4_st, v),
                                         reinterpret_cast<u32x4_st*>(C + (int64_t)gi * g.ldc + gj));
         }
         asm volatile("" ::: "memory");
@@ -441,8 +442,12 @@ __device__ __forceinline__ void settle_accumulators(f32x4_t (&acc)[8][8]) {
         for (int ni = 0; ni < 8; ++ni) asm volatile("" : "+a"(acc[mi][ni]));
 }
 
-template <typename T, int TRANSB, int MODE, bool FUSED>
+// EDGE: M and N need not be multiples of 256 nor K of 64 (K and N are multiples of 8, K is at least 64).  Rows and columns past the end are read from the last valid ones -- the lane offsets are clamped once,
+// the main loop is the same -- and dropped in the epilogue; the k past the last whole tile are multiplied by a step of
+// their own behind the loop, zero-filled on their way to LDS.
+template <typename T, int TRANSB, int MODE, bool FUSED, bool EDGE>
 __global__ __launch_bounds__(256) void gemm16_fast_kernel(const GemmArgs g) {
+    static_assert(!EDGE || MODE <= 1, "plain and checked products");
     using namespace g16x;
     // MODE 6 / 7: block-wise check with K split as well (7: with the injector).  The kernel leaves the row sums of
     // the accumulator tile at every K-block boundary and at the end, in double; a kernel of its own forms the
@@ -484,19 +489,28 @@ __global__ __launch_bounds__(256) void gemm16_fast_kernel(const GemmArgs g) {
     // chunk (lane%32) ^ f(k) with k&3 = 2*(l&1) + lane/32, (k>>3)&1 = l>>2.
     // Load l of a tile lands at LDS offset l*1024 of the wavefront's area: M0 holds the base of a group of
     // four, the immediate (l&3)*1024 is added to both addresses, so the lane offset carries -(l&3)*1024.
-    const unsigned char* const a_base = uniform_ptr(A + (int64_t)(row0 + wave * 64) * g.lda * 2);
-    const unsigned char* const b_base = uniform_ptr(TRANSB ? B + (int64_t)(col0 + wave * 64) * g.ldb * 2
-                                                           : B + ((int64_t)(wave * 16) * g.ldb + col0) * 2);
+    // (EDGE: offsets are taken from the tile's first row and column; 4096 more on the lane's side than on the base's
+    // keeps them positive where clamped rows no longer outweigh the immediates)
+    constexpr int BIAS = EDGE ? 4096 : 0;
+    const unsigned char* const a_base =
+        uniform_ptr((EDGE ? A + (int64_t)row0 * g.lda * 2 : A + (int64_t)(row0 + wave * 64) * g.lda * 2) - BIAS);
+    const unsigned char* const b_base =
+        uniform_ptr((TRANSB ? (EDGE ? B + (int64_t)col0 * g.ldb * 2 : B + (int64_t)(col0 + wave * 64) * g.ldb * 2)
+                            : B + ((int64_t)(wave * 16) * g.ldb + col0) * 2) - BIAS);
     uint32_t a_voff[8], b_voff[8];
 #pragma unroll
     for (int l = 0; l < 8; ++l) {
         const uint32_t rk = ((lane & 7) ^ (lane >> 4) ^ (4 * (l & 1))) << 4;
-        a_voff[l] = (uint32_t)((lane >> 3) + 8 * l) * (uint32_t)g.lda * 2 + rk - (l & 3) * 1024;
+        const int q = (lane >> 3) + 8 * l;
+        const int ar = EDGE ? min(wave * 64 + q, g.M - 1 - row0) : q;
+        a_voff[l] = (uint32_t)ar * (uint32_t)g.lda * 2 + rk - (l & 3) * 1024 + BIAS;
         if (TRANSB) {
-            b_voff[l] = (uint32_t)((lane >> 3) + 8 * l) * (uint32_t)g.ldb * 2 + rk - (l & 3) * 1024;
+            const int br = EDGE ? min(wave * 64 + q, g.N - 1 - col0) : q;
+            b_voff[l] = (uint32_t)br * (uint32_t)g.ldb * 2 + rk - (l & 3) * 1024 + BIAS;
         } else {
             const int f = 2 * ((2 * (l & 1) + lh) | (4 * (l >> 2)));
-            b_voff[l] = (uint32_t)(lh + 2 * l) * (uint32_t)g.ldb * 2 + ((l32 ^ f) << 4) - (l & 3) * 1024;
+            const int bc = EDGE ? min((l32 ^ f) << 3, g.N - 8 - col0) : (l32 ^ f) << 3;
+            b_voff[l] = (uint32_t)(lh + 2 * l) * (uint32_t)g.ldb * 2 + bc * 2 - (l & 3) * 1024 + BIAS;
         }
     }
     const int64_t b_ktile = TRANSB ? (int64_t)(BK * 2) : (int64_t)BK * g.ldb * 2;
@@ -817,7 +831,66 @@ __global__ __launch_bounds__(256) void gemm16_fast_kernel(const GemmArgs g) {
 #pragma unroll
             for (int ni = 0; ni < 8; ++ni) Mfma16x<T>::acc_a(acc[mi][ni], bf1[ni], af1[mi]);
     }
+    if constexpr (EDGE) {
+        const int kt0 = nk * BK, klen = g.K - kt0;  // the k past the last whole tile: a multiple of 8, below 64
+        if (klen > 0) {
+            // registers -> stage 0 (its last reads completed before the loop's closing barrier), zero past K
+            const raw16 z = {{0u, 0u, 0u, 0u}};
+#pragma unroll
+            for (int l = 0; l < 8; ++l) {
+                const int q = wave * 64 + (lane >> 3) + 8 * l;
+                const int c = (lane & 7) ^ (lane >> 4) ^ (4 * (l & 1));  // chunk of 8 k at LDS position lane % 8
+                const unsigned char* pa = A + ((int64_t)min(row0 + q, g.M - 1) * g.lda + kt0 + c * 8) * 2;
+                const raw16 va = c * 8 < klen ? ld16(pa) : z;
+                raw16 vb;
+                if (TRANSB) {
+                    const unsigned char* pb = B + ((int64_t)min(col0 + q, g.N - 1) * g.ldb + kt0 + c * 8) * 2;
+                    vb = c * 8 < klen ? ld16(pb) : z;
+                } else {
+                    const int k = wave * 16 + 2 * l + lh, f = 2 * ((2 * (l & 1) + lh) | (4 * (l >> 2)));
+                    const unsigned char* pb = B + ((int64_t)(kt0 + k) * g.ldb + col0 + min((l32 ^ f) << 3, g.N - 8 - col0)) * 2;
+                    vb = k < klen ? ld16(pb) : z;
+                }
+                *reinterpret_cast<raw16*>(smem + wave * 8192 + l * 1024 + lane * 16) = va;
+                *reinterpret_cast<raw16*>(smem + B_BASE + wave * 8192 + l * 1024 + lane * 16) = vb;
+            }
+            __builtin_amdgcn_s_waitcnt(0);
+            __syncthreads();
+            static_for<0, 2>([&](auto ks_c) {
+                static_for<0, NRD>([&](auto op_c) { frag_op(I0{}, ks_c, op_c, af1, bf1); });
+                wait_lgkmcnt0();
+                // (the transposing reads are assembly: the fragments are tied behind the wait, and idle slots keep
+                // whatever moved them clear of the MFMAs)
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    u32x4_t x = __builtin_bit_cast(u32x4_t, af1[i]), y = __builtin_bit_cast(u32x4_t, bf1[i]);
+                    asm volatile("" : "+v"(x), "+v"(y));
+                    af1[i] = __builtin_bit_cast(raw16, x);
+                    bf1[i] = __builtin_bit_cast(raw16, y);
+                }
+                asm volatile("s_nop 7\n\ts_nop 7" ::: "memory");
+#pragma unroll
+                for (int mi = 0; mi < 8; ++mi)
+#pragma unroll
+                    for (int ni = 0; ni < 8; ++ni) Mfma16x<T>::acc_a(acc[mi][ni], bf1[ni], af1[mi]);
+                asm volatile("s_nop 7\n\ts_nop 7" ::: "memory");
+            });
+            __syncthreads();  // the epilogue reuses the operand stages
+        }
+    }
     settle_accumulators(acc);
+    if constexpr (EDGE && MODE >= 1) {
+        if (col0 + BN > g.N) {  // columns past the end count as zero in the row sums
+            static_for<0, 8>([&](auto mi_c) {
+                static_for<0, 8>([&](auto ni_c) {
+                    static_for<0, 4>([&](auto r_c) {
+                        constexpr int mi = decltype(mi_c)::value, ni = decltype(ni_c)::value, r = decltype(r_c)::value;
+                        acc[mi][ni][r] = col0 + wn * 128 + ni * 16 + 4 * lq + r < g.N ? acc[mi][ni][r] : 0.f;
+                    });
+                });
+            });
+        }
+    }
 
     // ---- epilogue -------------------------------------------------------------------------------------------
     gemm16x_inject<INJECT>(g, acc, row0, col0, wm, wn, l16, lq);
@@ -861,11 +934,11 @@ __global__ __launch_bounds__(256) void gemm16_fast_kernel(const GemmArgs g) {
         float* rowpart = reinterpret_cast<float*>(g.rowpart);
         float* apart = reinterpret_cast<float*>(g.apart);
         float* rowpart2 = reinterpret_cast<float*>(g.rowpart2);
-        st_agent(rowpart + (int64_t)bn * g.M + gi, red[tid] + red[BM + tid]);
+        if (!EDGE || gi < g.M) st_agent(rowpart + (int64_t)bn * g.M + gi, red[tid] + red[BM + tid]);
         if (WSUM) st_agent(rowpart2 + (int64_t)bn * g.M + gi, red2[tid] + red2[BM + tid]);
         // column-sum partials are compared by a kernel of their own after this one: plain stores
         if (CSUM) reinterpret_cast<float*>(g.colpart)[(int64_t)bm * g.N + col0 + tid] = cred[tid] + cred[BN + tid];
-        if (FUSED) {
+        if (FUSED && (!EDGE || gi < g.M)) {
             float* ap = apart + (int64_t)bn * 4 * g.M + gi;
             st_agent(ap, sred[0 * BM + tid]);
             st_agent(ap + (int64_t)g.M, sred[1 * BM + tid]);
@@ -875,20 +948,20 @@ __global__ __launch_bounds__(256) void gemm16_fast_kernel(const GemmArgs g) {
         // block-wise check: the partials are all this kernel leaves; a later kernel compares them per block
         const bool partials_only = MODE == 5 || (MODE == 2 && g.block_mode);
         if (!partials_only)
-            gemm_tile_row_check<WSUM, FUSED>(g, smem, reinterpret_cast<const double*>(smem + S_RED_X), bm, gi, tid);
+            gemm_tile_row_check<WSUM, FUSED, EDGE>(g, smem, reinterpret_cast<const double*>(smem + S_RED_X), bm, gi, tid);
         __syncthreads();  // the store below reuses the LDS the reductions read
     }
-    gemm16x_store_c<T>(g, acc, smem, row0, col0, lane, wm, wn, l16, lq);
+    gemm16x_store_c<T, EDGE>(g, acc, smem, row0, col0, lane, wm, wn, l16, lq);
 }
 
 template <typename T, int TRANSB>
-static int gemm16_fast_launch_tb(const GemmArgs& a, int mode, hipStream_t st) {
+static int gemm16_fast_launch_tb(const GemmArgs& a, int mode, bool edge, hipStream_t st) {
     const dim3 grid(a.tiles_m * a.tiles_n), block(256);
     const int fused = a.fused_stats ? 1 : 0;
     const size_t lds = fused ? g16x::LDS_BYTES_FUSED_X : g16::LDS_BYTES;
-#define VABFT_G16F_CASE(VF, FU)                                                                            \
-    if (mode == VF && fused == FU) {                                                                       \
-        auto kern = gemm16_fast_kernel<T, TRANSB, VF, FU != 0>;                                            \
+#define VABFT_G16F_CASE(VF, FU, ED)                                                                        \
+    if (mode == VF && fused == FU && edge == ED) {                                                         \
+        auto kern = gemm16_fast_kernel<T, TRANSB, VF, FU != 0, ED>;                                        \
         static bool attr_set = false;                                                                      \
         if (!attr_set) {                                                                                   \
             if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern),                                   \
@@ -899,16 +972,19 @@ static int gemm16_fast_launch_tb(const GemmArgs& a, int mode, hipStream_t st) {
         kern<<<grid, block, lds, st>>>(a);                                                                 \
         return hipGetLastError() == hipSuccess ? VABFT_OK : VABFT_EDEVICE;                                 \
     }
-    VABFT_G16F_CASE(0, 0)
-    VABFT_G16F_CASE(1, 0)
-    VABFT_G16F_CASE(2, 0)
-    VABFT_G16F_CASE(3, 0)
-    VABFT_G16F_CASE(4, 0)
-    VABFT_G16F_CASE(5, 0)
-    VABFT_G16F_CASE(6, 0)
-    VABFT_G16F_CASE(7, 0)
-    VABFT_G16F_CASE(1, 1)
-    VABFT_G16F_CASE(2, 1)
+    VABFT_G16F_CASE(0, 0, false)
+    VABFT_G16F_CASE(1, 0, false)
+    VABFT_G16F_CASE(2, 0, false)
+    VABFT_G16F_CASE(3, 0, false)
+    VABFT_G16F_CASE(4, 0, false)
+    VABFT_G16F_CASE(5, 0, false)
+    VABFT_G16F_CASE(6, 0, false)
+    VABFT_G16F_CASE(7, 0, false)
+    VABFT_G16F_CASE(1, 1, false)
+    VABFT_G16F_CASE(2, 1, false)
+    VABFT_G16F_CASE(0, 0, true)
+    VABFT_G16F_CASE(1, 0, true)
+    VABFT_G16F_CASE(1, 1, true)
 #undef VABFT_G16F_CASE
     return VABFT_EINVAL;
 }

@@ -96,10 +96,13 @@ constexpr int LDS_BYTES_FUSED = S_RED_OFFSET + 128;
 // tile-columns in a fixed order, evaluates Algorithm 1 in double precision (FUSED) and writes rowsum, E, flags
 // (section 2.2, Eq. abft-check); the last row block writes nflag.  gi = the row this thread owns; s_red = the
 // workgroup's fold of the S1..S3 partials in LDS (used when g.S is null).
-template <bool WSUM, bool FUSED>
+template <bool WSUM, bool FUSED, bool EDGE = false>
 __device__ __forceinline__ void gemm_tile_row_check(const GemmArgs& g, unsigned char* smem, const double* s_red, int bm,
-                                                    int gi, int tid) {
+                                                    int gi_in, int tid) {
     using namespace g16f;
+    // EDGE: threads past the last row read it and write nothing
+    const bool act = !EDGE || gi_in < g.M;
+    const int gi = act ? gi_in : g.M - 1;
     int* s_last = reinterpret_cast<int*>(smem + 2048);
     float* rowpart = reinterpret_cast<float*>(g.rowpart);
     float* apart = reinterpret_cast<float*>(g.apart);
@@ -189,22 +192,26 @@ __device__ __forceinline__ void gemm_tile_row_check(const GemmArgs& g, unsigned 
             const double t_var4 = g.c_sigma * sqrt(dN * var * S2);  // = c sqrt(N) sigma_A sqrt(S2), one root
             expv = dot;
             thr = (float)(g.e_max * (t_det + t_var23 + t_var4));
-            float* astat = reinterpret_cast<float*>(g.astat);
-            astat[3 * (int64_t)gi + 0] = mx;
-            astat[3 * (int64_t)gi + 1] = mn;
-            astat[3 * (int64_t)gi + 2] = (float)mu;
-            reinterpret_cast<float*>(const_cast<void*>(g.expected))[gi] = expv;
-            reinterpret_cast<float*>(const_cast<void*>(g.T))[gi] = thr;
+            if (act) {
+                float* astat = reinterpret_cast<float*>(g.astat);
+                astat[3 * (int64_t)gi + 0] = mx;
+                astat[3 * (int64_t)gi + 1] = mn;
+                astat[3 * (int64_t)gi + 2] = (float)mu;
+                reinterpret_cast<float*>(const_cast<void*>(g.expected))[gi] = expv;
+                reinterpret_cast<float*>(const_cast<void*>(g.T))[gi] = thr;
+            }
         } else {
             expv = reinterpret_cast<const float*>(g.expected)[gi];
             thr = reinterpret_cast<const float*>(g.T)[gi];
         }
         const float e = expv - rs;
-        const int f = !(fabsf(e) <= thr);
-        reinterpret_cast<float*>(g.rowsum)[gi] = rs;
-        if (WSUM && g.rowsum2) reinterpret_cast<float*>(g.rowsum2)[gi] = rs2;
-        reinterpret_cast<float*>(g.E)[gi] = e;
-        g.flags[gi] = f;
+        const int f = act && !(fabsf(e) <= thr);
+        if (act) {
+            reinterpret_cast<float*>(g.rowsum)[gi] = rs;
+            if (WSUM && g.rowsum2) reinterpret_cast<float*>(g.rowsum2)[gi] = rs2;
+            reinterpret_cast<float*>(g.E)[gi] = e;
+            g.flags[gi] = f;
+        }
         const int cnt = __syncthreads_count(f);
         if (tid == 0) {
             // this tile-row is done: reset its ticket, then one 64-bit atomic both counts the

@@ -192,6 +192,34 @@ def test_whole_tile_kernels(dtype, M, N, K, transB):
     _check(vg, A, B, _dev(A, dtype), _dev(B, dtype), dtype, M, N, K, transB, ALL)
 
 
+RAGGED = [("bf16", 2049, 2056, 200, 0), ("bf16", 2303, 2296, 72, 1), ("f16", 2100, 2184, 256, 1), ("f16", 2050, 2064, 384, 0),
+          ("bf16", 2175, 2112, 128, 1), ("bf16", 2300, 2200, 64, 0), ("f16", 2111, 2080, 1032, 1), ("f16", 2241, 2312, 120, 0)]
+
+
+@pytest.mark.parametrize("dtype,M,N,K,transB", RAGGED)
+def test_tiled_kernels_at_ragged_sizes(dtype, M, N, K, transB):
+    """Enough 256 x 256 tiles for the tiled kernels, none of the sizes a multiple of theirs: remainders of one row, of
+    one group of eight columns, and of K below and above one step; K a multiple of 128 runs the fused statistics."""
+    A, B = _gen(dtype, M, N, K, transB, 11)
+    vg = _session(M, N, K, dtype, transB)
+    dA, dB = _dev(A, dtype), _dev(B, dtype)
+    _check(vg, A, B, dA, dB, dtype, M, N, K, transB, ("run", "run_fused", "fused_deferred"))
+    vg.gemm(dA, dB, 0)  # plain product
+    check_C(vg.results(), orc.verify(A, B, dtype, transB, e_max=_emax(dtype, K, N)), A, B, dtype, transB)
+
+
+def test_tiled_kernels_leave_padding_of_C():
+    from paper_2602_08043_amd import binding as vb
+    dtype, M, N, K = "bf16", 2100, 2056, 136
+    A, B = _gen(dtype, M, N, K, 0, 12)
+    vg = _session(M, N, K, dtype, 0)
+    vg.problem = vb.make_problem(M, N, K, dtype, 0, K, N, N + 8)
+    vg.C = torch.full((M + 1, N + 8), 7.0, dtype=torch.bfloat16, device="cuda")
+    vg.run_fused(_dev(A, dtype), _dev(B, dtype))
+    C = vg.C.float().cpu().numpy()
+    assert np.all(C[:, N:] == 7.0) and np.all(C[M:] == 7.0) and int(vg.nflag.item()) == 0
+
+
 def test_one_workspace_for_fewer_rows():
     """A workspace sized for M rows serves every problem with fewer: the routes change with M, the counters they share
     stay zero and no partial leaves the workspace."""
