@@ -1,5 +1,6 @@
 // C ABI of libvabft: argument validation, workspace layout, dispatch, and the compare-and-flag
 // step (paper section 2.2 Eq. abft-check, E_i = C^{r1}[i] - C^{r1'}[i]).
+#include <algorithm>
 #include <math.h>
 
 #include <mutex>
@@ -179,13 +180,14 @@ static int direct_launch(const vabft_problem* p, const DirectArgs& d, int shape,
     return VABFT_EINVAL;
 }
 
-// tiled: a kernel with 256 x 256 tiles takes the problem (16-byte aligned rows, see gemm_dispatch).
+// tiled: an LDS-tiled kernel takes the problem (16-byte aligned rows, see gemm_dispatch), in the time that the direct
+// kernel takes for `most` 64 x 64 tiles.
 // The lines, from fused calls timed inside a HIP graph (us):
-//   * those kernels take the time of one 256 x 256 tile for every 256 of them, however few there are (12 + 0.0155 K for
-//     the 16-bit types, 15 + 0.009 K for FP8); the direct kernel's time goes with the work, here its 64 x 64 tiles
-//     per round of the others.  2048^3 (64 tiles): 44.4 against 40.8
-//     (K x N) and 44.0 against 42.1 (N x K), 2048 x 4096 x 4096 (128): 76 against 112; FP8 1024^3 (16): 24.1 against
-//     14.2, 2048^3: 33.1 against 41.2.
+//   * those kernels take the time of one tile for every 256 of them, however few there are (256 x 256: 12 + 0.0155 K for
+//     the 16-bit types, 15 + 0.009 K for FP8); the direct kernel's time goes with the work.  16-bit, the best tile width
+//     (gemm16_columns) against the direct kernel: 1500 x 1500 x 1504 28.9 against 29.1, 1024 x 2560 x 4096 48.2 against
+//     48.2, 1024 x 3072 x 1024 22.1 against 23.7, 2048^3 30.6 against 40.2.  256-wide tiles alone: 2048^3 44.4 against
+//     40.8, 2048 x 4096 x 4096 76 against 112.  FP8 1024^3: 24.1 against 14.2, 2048^3: 33.1 against 41.2.
 //   * 16 x 32 tiles (eight wavefronts share K): at most 16 rows.  N = 4096: 11.4 against 14.9 with 32 x 64;
 //     N = 11008, where there are enough of the wide ones: 24.2 against 21.2.
 //   * 32 x 32 tiles (eight wavefronts): few tiles and a long K.  100 x 200 x 8000: 16.8 against 21.9; FP32 256^3: 10.9
@@ -194,11 +196,10 @@ static int direct_launch(const vabft_problem* p, const DirectArgs& d, int shape,
 //     27.6; 128 x 4096 x 4096: 21.8 against 19.6; 1024^3: 15.5 against 14.5.  FP32 has the matrix time to hide the
 //     traffic: 2048^3 144 against 150, 1000 x 1200 x 1500 63 against 53 (304 tiles: the last wave is nearly empty).
 //     FP64 has no registers for it.
-static int direct_shape(const vabft_problem* p, bool tiled) {
+static int direct_shape(const vabft_problem* p, bool tiled, double most) {
     const int64_t eb = (int64_t)elem_bytes(p->dtype);
     const int64_t t64 = ceil_div(p->M, 64) * ceil_div(p->N, 64), t32w = ceil_div(p->M, 32) * ceil_div(p->N, 64);
-    const int64_t rounds = ceil_div(ceil_div(p->M, 256) * ceil_div(p->N, 256), 256);
-    if (tiled && t64 > rounds * (is_fp8(p->dtype) ? 592 : 1040)) return DIRECT_NONE;
+    if (tiled && (double)t64 > most) return DIRECT_NONE;
     // a tile's byte offsets in 32 bits, and rows of 16 bytes at least
     const bool far = 64 * p->lda * eb >= (1ll << 32) || (p->transB ? 64 * eb : 128) * p->ldb >= (1ll << 32);
     if (far || p->K * eb < 16 || (!p->transB && p->N * eb < 16)) return DIRECT_ANY;
@@ -208,6 +209,33 @@ static int direct_shape(const vabft_problem* p, bool tiled) {
     if (p->dtype == VABFT_F64) return DIRECT_32W;
     if (p->dtype == VABFT_F32) return t64 >= 512 ? DIRECT_64 : DIRECT_32W;
     return p->M > 32 && t64 >= (long_k ? 150 : 512) ? DIRECT_64 : DIRECT_32W;
+}
+
+// Tile width of the 16-bit kernels for the plain and the checked product.  Wide tiles have the best rate, but a round of
+// them takes the time of one tile however many compute units have none.  What a round takes, in full rounds of 256 x 256
+// tiles (98 us at K = 4096), b being the share of the compute units that have a tile: the chip holds a higher clock when
+// it is not full, and narrow tiles pay more operand traffic and shorter k-tiles.
+//   256: 0.66 + 0.34 b   (64 tiles 73 us, 128: 76, 172: 91, 256: 98)
+//   192: 0.54 + 0.28 b   (88 tiles 62 us, 176: 68, 232: 80)
+//   128: 0.46 + 0.15 b   (64 tiles 48 us, 128: 49, 256: 60)
+// 256-wide tiles alone against the choice (us): 1000 x 11008 x 4096 87 / 80, 4096 x 6144 x 4096 175 / 158, 4352 x 4096 x
+// 4096 168 / 140 (192 wide); 2048 x 4096 x 4096 77 / 60, 1280 x 3840 x 1000 39 / 30, 2304 x 2304 x 512 22 / 19 (128 wide).
+// 4096 x 11008 x 4096 (688 wide tiles, 928 of 192: 276 / 292) and 4096^3 (102 / 119 with 128) stay.
+struct Columns16 {
+    int form;  // Form16
+    int64_t tiles_n;
+    double rounds;  // expected time
+};
+static Columns16 gemm16_columns(const vabft_problem* p, bool whole, size_t room) {
+    const int64_t tm = ceil_div(p->M, 256);
+    const auto form = [&](int f, int64_t width, double full, double part) {
+        const int64_t n = ceil_div(p->N, width), before = (tm * n - 1) / 256;  // full rounds before the last one
+        return Columns16{f, n, full * (double)before + part + (full - part) * (double)(tm * n - 256 * before) / 256.0};
+    };
+    Columns16 best = form(whole ? FORM16_WHOLE : FORM16_EDGE, 256, 1.0, 0.66);
+    for (const Columns16& c : {form(FORM16_192, 192, 0.82, 0.54), form(FORM16_128, 128, 0.61, 0.46)})
+        if (c.rounds < 0.97 * best.rounds && (size_t)(5 * c.tiles_n) * (size_t)p->M * sizeof(float) <= room) best = c;
+    return best;
 }
 
 // Accumulator words of partials that a direct kernel may leave for problems with B's shape and up to M rows:
@@ -404,10 +432,22 @@ int gemm_dispatch(const vabft_problem* p, const void* dA, const void* dB, void* 
     // (the 16-bit kernels also take other sizes for the plain and the checked product; their byte offsets are then
     // from the tile's first row)
     const bool kblocked = blocks && blocks->kblock > 0;
-    const bool ragged = (p->dtype == VABFT_BF16 || p->dtype == VABFT_F16) && !whole && aligned && p->K % 8 == 0 &&
-                        p->K >= 64 && p->N % 8 == 0 && p->lda <= (1 << 22) && p->ldb <= (1 << 22) &&
-                        !d_rowsum2 && !cols && !blocks && a.inj.mode == 0;
-    const int shape = kblocked ? (int)DIRECT_NONE : direct_shape(p, whole || ragged);
+    const bool sizes16 = (p->dtype == VABFT_BF16 || p->dtype == VABFT_F16) && p->lda <= (1 << 22) && p->ldb <= (1 << 22) &&
+                         !d_rowsum2 && !cols && !blocks && a.inj.mode == 0;
+    const bool ragged = sizes16 && !whole && aligned && p->K % 8 == 0 && p->K >= 64 && p->N % 8 == 0;
+    // (in 64 x 64 tiles: what a direct kernel has done by the time that the tiled one takes)
+    const double rounds256 = (double)ceil_div((int64_t)a.tiles_m * a.tiles_n, 256);
+    double direct_most = rounds256 * (is_fp8(p->dtype) ? 592 : 1040);
+    Columns16 cols16 = {FORM16_WHOLE, a.tiles_n, rounds256};
+    if (sizes16 && (whole || ragged)) {
+        // room for the partials: what the 256-wide tiles are given, or what every caller's scratch holds anyway (of a
+        // workspace and of the static one)
+        const size_t wide = whole_tile_scratch_bytes(p), all = gemm_workspace_bytes(p), front = tickets_bytes(p);
+        const size_t end = VABFT_STATIC_SCRATCH_BYTES + TICKETS_REGION, rest = end > front ? end - front : 0;
+        cols16 = gemm16_columns(p, whole, std::max(wide, std::min(all, rest)));
+        direct_most = (cols16.rounds - 0.06) / 0.0006;
+    }
+    const int shape = kblocked ? (int)DIRECT_NONE : direct_shape(p, whole || ragged, direct_most);
     const auto set_stats = [&] {
         a.fused_stats = 1;
         a.Be = fused->d_Be;
@@ -443,14 +483,20 @@ int gemm_dispatch(const vabft_problem* p, const void* dA, const void* dB, void* 
         if (cols) return finalize_cols_launch(p, a.colpart, a.tiles_m, cols, st);
         return VABFT_OK;
     }
+    if (cols16.form != FORM16_WHOLE) {
+        a.tiles_n = (int32_t)cols16.tiles_n;
+        a.apart = ws ? wsb + tickets_bytes(p) + (size_t)a.tiles_n * p->M * ab : nullptr;
+    }
     // the whole-tile kernels do the compare-and-flag step (and, if asked, the A-side pass) in-kernel; with K split as
     // well only the 16-bit ones leave a prefix of the row sums per K-block
     if (kblocked && (!whole || is_fp8(p->dtype))) return VABFT_EUNSUPPORTED;
     if (fused) {
-        // the fused 16-bit kernel caches the checksum panel of the k-units a tile-column folds: at most 16
+        // the fused 16-bit kernel caches the checksum panel of the k-units a tile-column folds, a fixed number
         // (units of 128 k, dealt round-robin to the tile-columns; the FP8 kernel: units of 256 k, 8 slots)
+        const int units = cols16.form >= FORM16_192 ? PANEL_UNITS_NARROW : PANEL_UNITS_WIDE;
         const bool fits = is_fp8(p->dtype) ? (a.tiles_n >= 2 && (p->K / 256) / a.tiles_n + 2 <= 8)
-                                           : (p->K % 128 == 0 && (p->K / 128 + a.tiles_n - 1) / a.tiles_n <= 16);
+                                           : (p->K % 128 == 0 && (p->K / 128 + a.tiles_n - 1) / a.tiles_n <= units);
+
         if (fits) {
             set_stats();
         } else {
@@ -479,10 +525,10 @@ int gemm_dispatch(const vabft_problem* p, const void* dA, const void* dB, void* 
         case VABFT_F8E4M3: rc = gemm8_launch_f8_nt(a, mode, st); break;
         case VABFT_F8E5M2: rc = gemm8_launch_bf8_nt(a, mode, st); break;
         case VABFT_BF16:
-            rc = p->transB ? gemm16_launch_bf16_nt(a, mode, !whole, st) : gemm16_launch_bf16_nn(a, mode, !whole, st);
+            rc = p->transB ? gemm16_launch_bf16_nt(a, mode, cols16.form, st) : gemm16_launch_bf16_nn(a, mode, cols16.form, st);
             break;
         case VABFT_F16:
-            rc = p->transB ? gemm16_launch_f16_nt(a, mode, !whole, st) : gemm16_launch_f16_nn(a, mode, !whole, st);
+            rc = p->transB ? gemm16_launch_f16_nt(a, mode, cols16.form, st) : gemm16_launch_f16_nn(a, mode, cols16.form, st);
             break;
         default: return VABFT_EINVAL;
     }

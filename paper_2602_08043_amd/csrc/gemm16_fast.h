@@ -1,6 +1,7 @@
-// BF16 / FP16 GEMM for whole-tile problems (M % 256 == 0, N % 256 == 0, K % 64 == 0, 16-byte aligned rows)
-// on v_mfma_f32_16x16x32: 256 x 256 x 64 tile per workgroup of 4 wavefronts (2 x 2), 128 x 128 per
-// wavefront = 8 x 8 MFMA tiles of 16 x 16, 256 accumulator registers, one wavefront per SIMD.
+// BF16 / FP16 GEMM on v_mfma_f32_16x16x32: 256 x 256 x 64 tile per workgroup of 4 wavefronts (2 x 2), 128 x 128 per
+// wavefront = 8 x 8 MFMA tiles of 16 x 16, 256 accumulator registers, one wavefront per SIMD.  Rows are 16-byte aligned;
+// the plain and the checked product take any M and N (EDGE), and tiles of 192 or 128 columns where those fill the chip
+// better (NF = 6, 4).
 //
 // Why the 16 x 16 x 32 instruction: on N(0,1)-like operands the chip is power-limited, not issue-limited, and
 // this shape moves half the accumulator bytes per flop of the 32 x 32 x 16 one (a register-only loop of it
@@ -18,7 +19,7 @@
 //       c ^ ((r >> 1) & 7); a 16 x 32 fragment is one ds_read_b128 (lane: row l%16, chunk 4*ks + l/16), whose
 //       16 lanes of a row group hit 16 distinct 16-byte slots of a 256-byte window.
 //   B tile when B is stored K x N:  [64 k][32 chunks of 16 B] (n contiguous), chunk c of row k at position
-//       c ^ 2*((k & 3) | 4*((k >> 3) & 1)); a fragment is two ds_read_b64_tr_b16, each handing lane i of a
+//       c ^ 2*((k & 3) | 4*((k >> 3) & 1)) (narrow tiles: see the kernel); a fragment is two ds_read_b64_tr_b16, each handing lane i of a
 //       16-lane block the 4 k-consecutive values of column i of a 4(k) x 16(n) sub-tile.
 // Global memory -> LDS without passing through registers (global_load_lds_dwordx4), issued from inline
 // assembly with a scalar base and a 32-bit lane offset: four loads share one M0 (LDS base) through their
@@ -103,17 +104,25 @@ using namespace g16f;
 // step) 90.0 us, every 5 or 6 the same; every 2 slots 99.0 us (64 lanes x 16 B every 32 cycles from each of four
 // wavefronts is more than the compute unit's vector memory path takes, and the queue stalls the MFMA issue).
 constexpr int LSTRIDE = 4;
-constexpr int LOFF = 1;  // >= 1: the M0 of a group of four rides one slot ahead of its first load
-static_assert(LOFF >= 1 && LOFF + 15 * LSTRIDE < 128, "all 16 loads inside the tile body");
-constexpr int HALF = 32768;       // one operand stage
-constexpr int B_BASE = 2 * HALF;  // B stages behind the two A stages
+constexpr int LOFF = 1;      // >= 1: the M0 of a group of four rides one slot ahead of its first load
+constexpr int HALF = 32768;  // a stage of A, and of a 256-wide B
 // FUSED: behind the operand stages, the panel [1, Be_hi, Be_mid, Be_lo] of every k32-step this tile-column
-// folds: per folded unit (slot) 4 steps x 4 panel rows x 32 k x 2 B = 1 KiB, at most 16 units
-constexpr int PANEL_OFFSET = LDS_BYTES;
-constexpr int PANEL_SLOTS = 16;
-constexpr int S_RED_X = PANEL_OFFSET + PANEL_SLOTS * 1024;  // 12 doubles: fold of the S1..S3 partials
-constexpr int SCALE_X = S_RED_X + 128;                      // 4 floats: per-wavefront max |Be| of the cached slices
-constexpr int LDS_BYTES_FUSED_X = SCALE_X + 64;
+// folds: per folded unit (slot) 4 steps x 4 panel rows x 32 k x 2 B = 1 KiB, at most PANEL_UNITS_* units;
+// behind it 12 doubles for the fold of the S1..S3 partials and 5 floats: per-wavefront max |Be|, the scale
+// LDS of a tile with NF column fragments per wavefront.  A k-tile of a narrow tile has fewer MFMA cycles (1536 and 1024
+// instead of 2048) to hide the way of the next one's operands from memory, about 1700 cycles from the first load's issue
+// to the barrier; a third stage for A (and for a 128-wide B) sends those loads out one k-tile earlier.  With two stages
+// each: 1024 x 4096 x 4096 in 128-wide tiles 60.5 us, now 49; in 192-wide ones 66.7, now 62.
+template <int NF> struct Lds16 {
+    static constexpr bool NARROW = NF < 8;
+    static constexpr int A_STAGES = NARROW ? 3 : 2, B_STAGES = NF == 4 ? 3 : 2;
+    static constexpr int B_STAGE = 4096 * NF;
+    static constexpr int B_AT = A_STAGES * HALF;
+    static constexpr int PANEL = B_AT + B_STAGES * B_STAGE, SLOTS = NARROW ? PANEL_UNITS_NARROW : PANEL_UNITS_WIDE;
+    static constexpr int S_RED = PANEL + SLOTS * 1024, SCALE = S_RED + 128;
+    static constexpr int BYTES = PANEL, BYTES_FUSED = SCALE + 64;
+    static_assert(BYTES_FUSED <= 160 * 1024, "LDS of a compute unit");
+};
 
 // a wave-uniform pointer, made visibly so (the inline assembly below needs it in scalar registers)
 __device__ __forceinline__ const unsigned char* uniform_ptr(const unsigned char* p) {
@@ -192,7 +201,8 @@ __device__ __forceinline__ void gemm16x_inject(const GemmArgs& g, f32x4_t (&acc)
 // Row sums of the wavefront's accumulator tile, taken before quantisation: 31 in-register adds per row,
 // arranged pairwise, plus two cross-lane adds.  Lanes 0..15 leave the sum of row wm*128 + mi*16 + lane over
 // the wavefront's 128 columns in red[wn][row].
-__device__ __forceinline__ void gemm16x_rowsum_to_lds(const f32x4_t (&acc)[8][8], float* red, int wm, int wn, int l16,
+template <int NF>
+__device__ __forceinline__ void gemm16x_rowsum_to_lds(const f32x4_t (&acc)[8][NF], float* red, int wm, int wn, int l16,
                                                       int lq) {
     using namespace g16;
     // the eight row fragments side by side: their cross-lane exchanges are in flight together (one wait per
@@ -200,10 +210,12 @@ __device__ __forceinline__ void gemm16x_rowsum_to_lds(const f32x4_t (&acc)[8][8]
     float s[8];
 #pragma unroll
     for (int mi = 0; mi < 8; ++mi) {
-        float t[8];
+        float t[NF];
 #pragma unroll
-        for (int ni = 0; ni < 8; ++ni) t[ni] = (acc[mi][ni][0] + acc[mi][ni][1]) + (acc[mi][ni][2] + acc[mi][ni][3]);
-        s[mi] = ((t[0] + t[1]) + (t[2] + t[3])) + ((t[4] + t[5]) + (t[6] + t[7]));
+        for (int ni = 0; ni < NF; ++ni) t[ni] = (acc[mi][ni][0] + acc[mi][ni][1]) + (acc[mi][ni][2] + acc[mi][ni][3]);
+        s[mi] = (t[0] + t[1]) + (t[2] + t[3]);
+        if constexpr (NF == 8) s[mi] += (t[4] + t[5]) + (t[6] + t[7]);
+        if constexpr (NF == 6) s[mi] += t[4] + t[5];
     }
     float x[8];
 #pragma unroll
@@ -308,20 +320,23 @@ template <> __device__ __forceinline__ uint32_t pack2<f16_t>(float a, float b) {
 // that global stores are 16 bytes per lane and 256 contiguous bytes per row (a lane owns 4 consecutive
 // columns of one row, which alone would give 8-byte pieces scattered over 16 rows).
 // EDGE: rows and 16-byte column groups past the end are left out (N is a multiple of 8 then).
-template <typename T, bool EDGE>
-__device__ __forceinline__ void gemm16x_store_c(const GemmArgs& g, const f32x4_t (&acc)[8][8], unsigned char* smem,
+template <typename T, bool EDGE, int NF>
+__device__ __forceinline__ void gemm16x_store_c(const GemmArgs& g, const f32x4_t (&acc)[8][NF], unsigned char* smem,
                                                 int row0, int col0, int lane, int wm, int wn, int l16, int lq) {
     // row pitch 272 B: the 8-byte writes of 16 rows x 2 column groups hit 32 distinct bank pairs
     constexpr int PITCH = 272;
     constexpr int SLAB = 16 * PITCH;
     unsigned char* stage = smem + 4096 + (wm * 2 + wn) * (2 * SLAB);
     uint16_t* __restrict__ C = reinterpret_cast<uint16_t*>(g.C);
-    const int srow = lane >> 4, schunk = lane & 15;
+    constexpr int LPR = NF > 4 ? 16 : 8;  // lanes per row (a row of six fragments leaves four of them idle)
+    const int srow = lane / LPR, schunk = lane % LPR;
+    const int gj = col0 + wn * (16 * NF) + schunk * 8;
+    const bool in_row = (2 * NF == LPR || schunk < 2 * NF) && (!EDGE || gj < g.N);
 #pragma unroll
     for (int mi = 0; mi < 8; ++mi) {
         unsigned char* sl = stage + (mi & 1) * SLAB;
 #pragma unroll
-        for (int ni = 0; ni < 8; ++ni) {
+        for (int ni = 0; ni < NF; ++ni) {
             uint2 v;
             v.x = pack2<T>(acc[mi][ni][0], acc[mi][ni][1]);
             v.y = pack2<T>(acc[mi][ni][2], acc[mi][ni][3]);
@@ -331,14 +346,13 @@ __device__ __forceinline__ void gemm16x_store_c(const GemmArgs& g, const f32x4_t
         // above the writes
         asm volatile("" ::: "memory");
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            const int r = srow + 4 * t;
+        for (int t = 0; t < LPR / 4; ++t) {
+            const int r = srow + (64 / LPR) * t;
             const raw16 v = *reinterpret_cast<const raw16*>(sl + r * PITCH + schunk * 16);
             const int gi = row0 + wm * 128 + mi * 16 + r;
-            const int gj = col0 + wn * 128 + schunk * 8;
             // C is not read again by this kernel: non-temporal store
             typedef __attribute__((ext_vector_type(4))) uint32_t u32x4_st;
-            if (!EDGE || (gi < g.M && gj < g.N)) __builtin_nontemporal_store(__builtin_bit_cast(u32x4_st, v),
+            if (in_row && (!EDGE || gi < g.M)) __builtin_nontemporal_store(__builtin_bit_cast(u32x4_st, v),
                                         reinterpret_cast<u32x4_st*>(C + (int64_t)gi * g.ldc + gj));
         }
         asm volatile("" ::: "memory");
@@ -434,20 +448,25 @@ template <> __device__ __forceinline__ uint16_t one16<f16_t>() { return 0x3c00; 
 // slots let the last results land.  The empty statements behind them redefine every accumulator as far as the
 // compiler can tell, so no read of one can be scheduled in front of the idle slots (register reads are not
 // ordered against an assembly statement by its memory clobber).
-__device__ __forceinline__ void settle_accumulators(f32x4_t (&acc)[8][8]) {
+template <int NF> __device__ __forceinline__ void settle_accumulators(f32x4_t (&acc)[8][NF]) {
     asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7" ::: "memory");
 #pragma unroll
     for (int mi = 0; mi < 8; ++mi)
 #pragma unroll
-        for (int ni = 0; ni < 8; ++ni) asm volatile("" : "+a"(acc[mi][ni]));
+        for (int ni = 0; ni < NF; ++ni) asm volatile("" : "+a"(acc[mi][ni]));
 }
 
-// EDGE: M and N need not be multiples of 256 nor K of 64 (K and N are multiples of 8, K is at least 64).  Rows and columns past the end are read from the last valid ones -- the lane offsets are clamped once,
-// the main loop is the same -- and dropped in the epilogue; the k past the last whole tile are multiplied by a step of
-// their own behind the loop, zero-filled on their way to LDS.
-template <typename T, int TRANSB, int MODE, bool FUSED, bool EDGE>
-__global__ __launch_bounds__(256) void gemm16_fast_kernel(const GemmArgs g) {
+// The tile of rows row0 .. row0 + 255 and columns col0 .. col0 + 32 NF - 1; bm, bn: its tile-row and tile-column.
+// NF: column fragments per wavefront.  8 is the 256 x 256 tile; 6 and 4 (256 x 192, 256 x 128) serve the plain and the
+// checked product where wide tiles would leave compute units without work (gemm16_columns in api.hip).
+// EDGE: M and N need not be multiples of the tile nor K of 64 (K and N are multiples of 8, K is at least 64).  Rows and
+// columns past the end are read from the last valid ones -- the lane offsets are clamped once, the main loop is the
+// same -- and dropped in the epilogue; the k past the last whole tile are multiplied by a step of their own behind the
+// loop, zero-filled on their way to LDS.
+template <typename T, int TRANSB, int MODE, bool FUSED, bool EDGE, int NF>
+__device__ __forceinline__ void gemm16_fast_tile(const GemmArgs& g, int bm, int bn, int row0, int col0) {
     static_assert(!EDGE || MODE <= 1, "plain and checked products");
+    static_assert(NF == 8 || (EDGE && (NF == 6 || NF == 4)), "narrow tiles");
     using namespace g16x;
     // MODE 6 / 7: block-wise check with K split as well (7: with the injector).  The kernel leaves the row sums of
     // the accumulator tile at every K-block boundary and at the end, in double; a kernel of its own forms the
@@ -463,30 +482,32 @@ __global__ __launch_bounds__(256) void gemm16_fast_kernel(const GemmArgs g) {
     const int wm = wave >> 1, wn = wave & 1;
     const int l16 = lane & 15, lq = lane >> 4;
     const int l32 = lane & 31, lh = lane >> 5;
-    int bm, bn;
-    tile_of_block(blockIdx.x, g.tiles_m, g.tiles_n, bm, bn);
     if (CSUM && blockIdx.x == 0 && tid == 0 && g.d_ncolflag) *g.d_ncolflag = 0;
     if ((MODE == 5 || MODE == 2 || KSNAP) && blockIdx.x == 0 && tid == 0 && (g.block_mode || KSNAP)) {
         *g.d_nflag = 0;
         *g.d_nblockflag = 0;
     }
-    const int row0 = bm * BM, col0 = bn * BN;
+    constexpr int TN = 32 * NF;               // columns of the tile
+    constexpr int NLOAD = 8 + NF, NSLOT = 8 * NF;
+    using L = Lds16<NF>;
+    constexpr int B_BASE = L::B_AT;
     const unsigned char* __restrict__ A = reinterpret_cast<const unsigned char*>(g.A);
     const unsigned char* __restrict__ B = reinterpret_cast<const unsigned char*>(g.B);
 
-    f32x4_t acc[8][8];
+    f32x4_t acc[8][NF];
 #pragma unroll
     for (int mi = 0; mi < 8; ++mi)
 #pragma unroll
-        for (int ni = 0; ni < 8; ++ni)
+        for (int ni = 0; ni < NF; ++ni)
 #pragma unroll
             for (int r = 0; r < 4; ++r) acc[mi][ni][r] = 0.f;
 
-    // ---- global -> LDS: each wavefront issues 8 + 8 loads of 1 KiB per k-tile -----------------------------
-    // A (and an N x K B): load l covers rows wave*64 + 8l .. +7; lane sits at row lane/8, chunk position lane%8
+    // ---- global -> LDS: each wavefront issues 8 + NF loads of 1 KiB per k-tile ----------------------------
+    // A (and an N x K B): load l covers rows wave*64 (B: wave*8 NF) + 8l .. +7; lane sits at row lane/8, chunk position lane%8
     // and fetches chunk (lane%8) ^ ((row>>1)&7), (row>>1)&7 = 4*(l&1) + lane/16.
-    // K x N B: load l covers k rows wave*16 + 2l, +1; lane sits at row lane/32, position lane%32 and fetches
-    // chunk (lane%32) ^ f(k) with k&3 = 2*(l&1) + lane/32, (k>>3)&1 = l>>2.
+    // K x N B: rows of 4 NF chunks, 16 k rows per wavefront; chunk position pos of row k holds chunk pos ^ f(k).
+    // Rows of 512 or 256 bytes: f = 2*((k&3) | 4*((k>>3)&1)), so that the eight rows of a transposing read hit distinct
+    // slots; rows of 384 bytes start half a window apart by themselves: f = 2*(((k>>1)&1) | 2*((k>>3)&1)).
     // Load l of a tile lands at LDS offset l*1024 of the wavefront's area: M0 holds the base of a group of
     // four, the immediate (l&3)*1024 is added to both addresses, so the lane offset carries -(l&3)*1024.
     // (EDGE: offsets are taken from the tile's first row and column; 4096 more on the lane's side than on the base's
@@ -495,9 +516,12 @@ __global__ __launch_bounds__(256) void gemm16_fast_kernel(const GemmArgs g) {
     const unsigned char* const a_base =
         uniform_ptr((EDGE ? A + (int64_t)row0 * g.lda * 2 : A + (int64_t)(row0 + wave * 64) * g.lda * 2) - BIAS);
     const unsigned char* const b_base =
-        uniform_ptr((TRANSB ? (EDGE ? B + (int64_t)col0 * g.ldb * 2 : B + (int64_t)(col0 + wave * 64) * g.ldb * 2)
+        uniform_ptr((TRANSB ? (EDGE ? B + (int64_t)col0 * g.ldb * 2 : B + (int64_t)(col0 + wave * 8 * NF) * g.ldb * 2)
                             : B + ((int64_t)(wave * 16) * g.ldb + col0) * 2) - BIAS);
-    uint32_t a_voff[8], b_voff[8];
+    uint32_t a_voff[8], b_voff[NF];
+    const auto kn_swz = [](int k) {
+        return NF == 6 ? 2 * (((k >> 1) & 1) | 2 * ((k >> 3) & 1)) : 2 * ((k & 3) | 4 * ((k >> 3) & 1));
+    };
 #pragma unroll
     for (int l = 0; l < 8; ++l) {
         const uint32_t rk = ((lane & 7) ^ (lane >> 4) ^ (4 * (l & 1))) << 4;
@@ -505,65 +529,79 @@ __global__ __launch_bounds__(256) void gemm16_fast_kernel(const GemmArgs g) {
         const int ar = EDGE ? min(wave * 64 + q, g.M - 1 - row0) : q;
         a_voff[l] = (uint32_t)ar * (uint32_t)g.lda * 2 + rk - (l & 3) * 1024 + BIAS;
         if (TRANSB) {
-            const int br = EDGE ? min(wave * 64 + q, g.N - 1 - col0) : q;
-            b_voff[l] = (uint32_t)br * (uint32_t)g.ldb * 2 + rk - (l & 3) * 1024 + BIAS;
+            const int br = EDGE ? min(wave * 8 * NF + q, g.N - 1 - col0) : q;
+            if (l < NF) b_voff[l] = (uint32_t)br * (uint32_t)g.ldb * 2 + rk - (l & 3) * 1024 + BIAS;
         } else {
-            const int f = 2 * ((2 * (l & 1) + lh) | (4 * (l >> 2)));
-            const int bc = EDGE ? min((l32 ^ f) << 3, g.N - 8 - col0) : (l32 ^ f) << 3;
-            b_voff[l] = (uint32_t)(lh + 2 * l) * (uint32_t)g.ldb * 2 + bc * 2 - (l & 3) * 1024 + BIAS;
+            int k = (l * 64 + lane) / (4 * NF), n = ((l * 64 + lane) % (4 * NF) ^ kn_swz(k)) << 3;
+            if (NF == 8) {  // the same, written so that the compiler sees what the loads have in common
+                k = lh + 2 * l;
+                n = (l32 ^ 2 * ((2 * (l & 1) + lh) | (4 * (l >> 2)))) << 3;
+            }
+            const int bc = EDGE ? min(n, g.N - 8 - col0) : n;
+            if (l < NF) b_voff[l] = (uint32_t)k * (uint32_t)g.ldb * 2 + bc * 2 - (l & 3) * 1024 + BIAS;
         }
     }
     const int64_t b_ktile = TRANSB ? (int64_t)(BK * 2) : (int64_t)BK * g.ldb * 2;
     const uint32_t lds0 = (uint32_t)(uintptr_t)lds;
     const uint32_t a_dst = __builtin_amdgcn_readfirstlane(lds0 + wave * 8192);
-    const uint32_t b_dst = __builtin_amdgcn_readfirstlane(lds0 + B_BASE + wave * 8192);
-    // load l (0..7: A, 8..15: B) of the tile whose scalar bases are (ap, bp), into stage LS; M0 must hold the
-    // group's base (set_group)
-    auto set_group = [&](auto ls_c, auto l_c) {
-        constexpr int LS = decltype(ls_c)::value, l = decltype(l_c)::value;
-        set_m0((l < 8 ? a_dst : b_dst) + LS * HALF + ((l & 7) >> 2) * 4096);
+    const uint32_t b_dst = __builtin_amdgcn_readfirstlane(lds0 + B_BASE + wave * NF * 1024);
+    // Load number j of a k-tile; M0 must hold the base of its group of four (set_group).  256-wide tiles load A, then
+    // B, narrow ones B first: the youngest loads are the ones with the longer lead (see Lds16).
+    // The stage they go to: LS, and for narrow tiles wr_a, wr_b (LDS offsets).
+    constexpr int B_FIRST = L::NARROW ? 0 : 8, A_FIRST = L::NARROW ? NF : 0;
+    const auto is_b = [](int j) { return j >= B_FIRST && j < B_FIRST + NF; };
+    const auto in_op = [](int j) { return j >= B_FIRST && j < B_FIRST + NF ? j - B_FIRST : j - A_FIRST; };
+    uint32_t wr_a = 0, wr_b = 0;
+    auto set_group = [&](auto ls_c, auto j_c) {
+        constexpr int LS = decltype(ls_c)::value, j = decltype(j_c)::value, l = in_op(j);
+        if constexpr (L::NARROW)
+            set_m0((is_b(j) ? b_dst + wr_b : a_dst + wr_a) + (l >> 2) * 4096);
+        else
+            set_m0((is_b(j) ? b_dst : a_dst) + LS * HALF + (l >> 2) * 4096);
     };
-    auto issue_load = [&](auto l_c, const unsigned char* ap, const unsigned char* bp) {
-        constexpr int l = decltype(l_c)::value;
-        if constexpr (l < 8)
+    auto issue_load = [&](auto j_c, const unsigned char* ap, const unsigned char* bp) {
+        constexpr int j = decltype(j_c)::value, l = in_op(j);
+        if constexpr (!is_b(j))
             g2l16_m0<(l & 3) * 1024>(a_voff[l], ap);
         else
-            g2l16_m0<(l & 3) * 1024>(b_voff[l - 8], bp);
+            g2l16_m0<(l & 3) * 1024>(b_voff[l], bp);
     };
 
     // ---- LDS -> fragments ---------------------------------------------------------------------------------
     const int f_swz = (l16 >> 1) & 7;
     lds_u8* a_rd[2];  // [k32-step]: row wm*128 + l16, chunk 4*ks + lq; fragment mi and the stage are immediates
-    lds_u8* b_rd[8];  // N x K B: [k32-step] (first two);  K x N B: [ni]
+    lds_u8* b_rd[NF];  // N x K B: [k32-step] (first two);  K x N B: [ni]
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks) a_rd[ks] = lds + (wm * 128 + l16) * 128 + (((ks * 4 + lq) ^ f_swz) << 4);
     if (TRANSB) {
 #pragma unroll
-        for (int q = 0; q < 8; ++q)
-            b_rd[q] = lds + B_BASE + (wn * 128 + l16) * 128 + ((((q & 1) * 4 + lq) ^ f_swz) << 4);
+        for (int q = 0; q < NF; ++q)
+            b_rd[q] = lds + B_BASE + (wn * 16 * NF + l16) * 128 + ((((q & 1) * 4 + lq) ^ f_swz) << 4);
     } else {
         // 16-lane block lq reads the 4(k) x 16(n) sub-tile at k = 8*lq + s/4 (+4 for the second half),
-        // n = 16*ni + 4*(s%4), s = l16; f(k) of those rows is 2*((s/4) | 4*(lq&1))
+        // n = 16*ni + 4*(s%4), s = l16 (f of both is the same)
         const int k_l = 8 * lq + (l16 >> 2);
-        const int f = 2 * ((l16 >> 2) | (4 * (lq & 1)));
+        const int f = kn_swz(k_l);
 #pragma unroll
-        for (int ni = 0; ni < 8; ++ni) {
-            const int chunk = wn * 16 + 2 * ni + ((l16 & 3) >> 1);
-            b_rd[ni] = lds + B_BASE + k_l * 512 + ((chunk ^ f) << 4) + 8 * (l16 & 1);
+        for (int ni = 0; ni < NF; ++ni) {
+            const int chunk = wn * 2 * NF + 2 * ni + ((l16 & 3) >> 1);
+            b_rd[ni] = lds + B_BASE + k_l * (64 * NF) + ((chunk ^ f) << 4) + 8 * (l16 & 1);
         }
     }
-    // Fragment read `op` of k32-step KS of stage S: 8 A fragments, then 8 B fragments (N x K B) or 16
+    // Fragment read `op` of k32-step KS of stage S: 8 A fragments, then NF B fragments (N x K B) or 2 NF
     // transposing 8-byte reads (K x N B: the low halves of all fragments, then the high halves).
-    constexpr int NRD = TRANSB ? 16 : 24;
-    auto frag_op = [&](auto s_c, auto ks_c, auto op_c, raw16 (&af)[8], raw16 (&bf)[8]) {
+    constexpr int NRD = 8 + (TRANSB ? 1 : 2) * NF;
+    static_assert(2 * NRD <= NSLOT, "a read every other slot");
+    auto frag_op = [&](auto s_c, auto ks_c, auto op_c, raw16 (&af)[8], raw16 (&bf)[NF]) {
         constexpr int S = decltype(s_c)::value, KS = decltype(ks_c)::value, op = decltype(op_c)::value;
+        constexpr int SO = L::NARROW ? 0 : S * HALF;  // (narrow tiles move the addresses from stage to stage)
         if constexpr (op < 8) {
-            af[op] = lds_read16(a_rd[KS] + S * HALF + op * 2048);
+            af[op] = lds_read16(a_rd[KS] + SO + op * 2048);
         } else if constexpr (TRANSB != 0) {
-            bf[op - 8] = lds_read16(b_rd[KS] + S * HALF + (op - 8) * 2048);
+            bf[op - 8] = lds_read16(b_rd[KS] + SO + (op - 8) * 2048);
         } else {
-            constexpr int ni = (op - 8) & 7, hi = (op - 8) >> 3;
-            const uint64_t v = lds_read_tr16_b64<S * HALF + KS * 16384 + hi * 2048>(b_rd[ni]);
+            constexpr int ni = (op - 8) % NF, hi = (op - 8) / NF;
+            const uint64_t v = lds_read_tr16_b64<SO + KS * 2048 * NF + hi * 256 * NF>(b_rd[ni]);
             bf[ni].w[2 * hi] = (uint32_t)v;
             bf[ni].w[2 * hi + 1] = (uint32_t)(v >> 32);
         }
@@ -584,14 +622,14 @@ __global__ __launch_bounds__(256) void gemm16_fast_kernel(const GemmArgs g) {
         for (int t = 0; t < 4; ++t) sacc[t][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
         mm[j].init();
     }
-    const lds_u8* const panel_rd = lds + PANEL_OFFSET + (l16 & 3) * 64 + lq * 16;
-    const lds_u8* const a_rd_st[2] = {a_rd[0] + wn * 8192, a_rd[1] + wn * 8192};
+    const lds_u8* const panel_rd = lds + L::PANEL + (l16 & 3) * 64 + lq * 16;
+    const lds_u8* a_rd_st[2] = {a_rd[0] + wn * 8192, a_rd[1] + wn * 8192};
     // The statistics of k32-step KS of the tile in stage S (step t = 2S + KS of folded unit number hj) ride in the
     // slots of the k-step that runs while that tile is in LDS, instead of standing between
     // two k-steps with the matrix cores idle: the wavefront's four fragments and the panel fragment are read once
     // more from LDS in five early slots (the pipeline's own fragment registers are not touched), the panel rows
     // 4..15 are zeroed well ahead of their use (a vector write of an MFMA operand must not sit within a few slots of
-    // the MFMA), the 16 fragment dwords fold into the max / min trackers one per slot in the last 16 slots, when every
+    // the MFMA), the 16 fragment dwords fold into the max / min trackers one per slot (narrow tiles: two) in the last slots, when every
     // read of the step has been issued, and the four statistics MFMAs follow the step's last slot.
     raw16 st_x;
     raw16 st_a[4];
@@ -599,9 +637,14 @@ __global__ __launch_bounds__(256) void gemm16_fast_kernel(const GemmArgs g) {
         constexpr int S = decltype(s_c)::value, KS = decltype(ks_c)::value, slot = decltype(slot_c)::value;
         if constexpr (slot == 3) st_x = lds_read16(panel_rd + hj * 1024 + (2 * S + KS) * 256);
         if constexpr (slot == 7 || slot == 11 || slot == 15 || slot == 19)
-            st_a[(slot - 7) / 4] = lds_read16(a_rd_st[KS] + S * HALF + ((slot - 7) / 4) * 2048);
-        if constexpr (slot >= 24 && slot < 28) st_x.w[slot - 24] = l16 < 4 ? st_x.w[slot - 24] : 0u;
-        if constexpr (slot >= 48) mm[(slot - 48) >> 2].fold(st_a[(slot - 48) >> 2].w[(slot - 48) & 3]);
+            st_a[(slot - 7) / 4] = lds_read16(a_rd_st[KS] + (L::NARROW ? 0 : S * HALF) + ((slot - 7) / 4) * 2048);
+        constexpr int ZERO = NF == 8 ? 24 : 20, FPS = NF == 8 ? 1 : 2, FOLD = NSLOT - 16 / FPS;
+        if constexpr (slot >= ZERO && slot < ZERO + 4) st_x.w[slot - ZERO] = l16 < 4 ? st_x.w[slot - ZERO] : 0u;
+        if constexpr (slot >= FOLD)
+            static_for<FPS * (slot - FOLD), FPS * (slot - FOLD + 1)>([&](auto d_c) {
+                constexpr int d = decltype(d_c)::value;
+                mm[d >> 2].fold(st_a[d >> 2].w[d & 3]);
+            });
     };
     auto stats_mfma = [&](auto s_c, auto ks_c) __attribute__((always_inline)) {
         constexpr int S = decltype(s_c)::value, KS = decltype(ks_c)::value;
@@ -612,17 +655,17 @@ __global__ __launch_bounds__(256) void gemm16_fast_kernel(const GemmArgs g) {
         Mfma16x<T>::acc_v4(sacc[2 * S + KS], st_x, st_a);
     };
 
-    // One k32-step = 64 slots of one MFMA (16 cycles, four issue cycles).  Even slots issue fragment read
+    // One k32-step = 8 NF slots of one MFMA (16 cycles, four issue cycles).  Even slots issue fragment read
     // slot/2 of the NEXT step (stage S, step KS, into the other register set).  LBASE is the step's first slot
-    // within the tile body (0 or 64; negative: no loads): the loads of the next tile go into stage S^1.
-    auto kstep = [&](auto s_c, auto ks_c, auto lbase_c, auto st_c, int hj, const raw16 (&af)[8], const raw16 (&bf)[8],
-                     raw16 (&naf)[8], raw16 (&nbf)[8], const unsigned char* ap, const unsigned char* bp) {
+    // within the tile body (0 or NSLOT): the loads of the next tile go into stage S^1.
+    auto kstep = [&](auto s_c, auto ks_c, auto lbase_c, auto st_c, int hj, const raw16 (&af)[8], const raw16 (&bf)[NF],
+                     raw16 (&naf)[8], raw16 (&nbf)[NF], const unsigned char* ap, const unsigned char* bp) {
         constexpr int S = decltype(s_c)::value, LBASE = decltype(lbase_c)::value;
         constexpr bool STATS = FUSED && decltype(st_c)::value != 0;
         if (!TRANSB) wait_lgkmcnt0();  // the assembly reads of (af, bf) issued during the previous step
-        static_for<0, 64>([&](auto slot_c) {
+        static_for<0, NSLOT>([&](auto slot_c) {
             constexpr int slot = decltype(slot_c)::value;
-            constexpr int mi = slot >> 3, ni = slot & 7;
+            constexpr int mi = slot / NF, ni = slot % NF;
             Mfma16x<T>::acc_a(acc[mi][ni], bf[ni], af[mi]);
             __builtin_amdgcn_sched_barrier(0);  // MFMA first, the rest of the slot in its shadow
             if constexpr ((slot & 1) == 0 && slot / 2 < NRD)
@@ -630,10 +673,12 @@ __global__ __launch_bounds__(256) void gemm16_fast_kernel(const GemmArgs g) {
             // G: slot within the tile body (two steps); load j goes out at G = LOFF + j * LSTRIDE, the M0 of its
             // group of four one slot ahead of the group's first load
             constexpr int G = LBASE + slot;
-            if constexpr (LBASE >= 0 && G + 1 >= LOFF && (G + 1 - LOFF) % (4 * LSTRIDE) == 0 &&
-                          (G + 1 - LOFF) / LSTRIDE < 16)
-                set_group(std::integral_constant<int, S ^ 1>{}, std::integral_constant<int, (G + 1 - LOFF) / LSTRIDE>{});
-            if constexpr (LBASE >= 0 && G >= LOFF && (G - LOFF) % LSTRIDE == 0 && (G - LOFF) / LSTRIDE < 16)
+            static_assert(LOFF >= 1 && LOFF + (NLOAD - 1) * LSTRIDE < 2 * NSLOT, "all loads inside the tile body");
+            if constexpr (G + 1 >= LOFF && (G + 1 - LOFF) % LSTRIDE == 0 && (G + 1 - LOFF) / LSTRIDE < NLOAD) {
+                constexpr int j = (G + 1 - LOFF) / LSTRIDE;
+                if constexpr ((in_op(j) & 3) == 0) set_group(std::integral_constant<int, S ^ 1>{}, std::integral_constant<int, j>{});
+            }
+            if constexpr (G >= LOFF && (G - LOFF) % LSTRIDE == 0 && (G - LOFF) / LSTRIDE < NLOAD)
                 issue_load(std::integral_constant<int, (G - LOFF) / LSTRIDE>{}, ap, bp);
             if constexpr (STATS) stats_slot(s_c, ks_c, slot_c, hj);
             __builtin_amdgcn_sched_barrier(0);
@@ -642,24 +687,30 @@ __global__ __launch_bounds__(256) void gemm16_fast_kernel(const GemmArgs g) {
     };
     using I0 = std::integral_constant<int, 0>;
     using I1 = std::integral_constant<int, 1>;
-    using I64 = std::integral_constant<int, 64>;
+    using IStep = std::integral_constant<int, NSLOT>;
 
     const int nk = g.K / BK;
-    raw16 af0[8], bf0[8], af1[8], bf1[8];
-    // first tile
-    {
-        const unsigned char* ap = a_base;
-        const unsigned char* bp = b_base;
+    raw16 af0[8], bf0[NF], af1[8], bf1[NF];
+    // first tile; narrow tiles: and the second one's A (and B) where there is a stage for it
+    static_for<0, L::A_STAGES - 1>([&](auto t_c) {
+        constexpr int t = decltype(t_c)::value;
+        const unsigned char* ap = uniform_ptr(a_base + (t < nk ? t : nk - 1) * (BK * 2));
+        const unsigned char* bp = uniform_ptr(b_base + (t < nk ? t : nk - 1) * b_ktile);
+        if constexpr (L::NARROW) {
+            wr_a = t * HALF;
+            wr_b = t * L::B_STAGE;
+        }
         settle_bases(ap, bp);
-        static_for<0, 16>([&](auto l_c) {
-            constexpr int l = decltype(l_c)::value;
-            if constexpr ((l & 3) == 0) {
-                set_group(I0{}, l_c);
+        static_for<0, NLOAD>([&](auto j_c) {
+            constexpr int j = decltype(j_c)::value;
+            if constexpr (is_b(j) && t >= L::B_STAGES - 1) return;
+            if constexpr ((in_op(j) & 3) == 0) {
+                set_group(I0{}, j_c);
                 asm volatile("s_nop 0");
             }
-            issue_load(l_c, ap, bp);
+            issue_load(j_c, ap, bp);
         });
-    }
+    });
     int n_slots = 0;  // FUSED: number of k-units this tile-column folds
     if (FUSED) {
         // Panel cache: for slot j (unit u = bn + j*tiles_n), step t, k = 128u + 32t + q: rows
@@ -670,31 +721,31 @@ __global__ __launch_bounds__(256) void gemm16_fast_kernel(const GemmArgs g) {
         const int nunits = nk >> 1;
         if (bn < nunits) {
             n_slots = (nunits - bn + g.tiles_n - 1) / g.tiles_n;
-            n_slots = n_slots < PANEL_SLOTS ? n_slots : PANEL_SLOTS;
+            n_slots = n_slots < L::SLOTS ? n_slots : L::SLOTS;
         }
         // the Be values of this thread (k = 128u + tid of every folded unit), all loads in flight together
-        float bek[PANEL_SLOTS];
+        float bek[L::SLOTS];
 #pragma unroll
-        for (int j = 0; j < PANEL_SLOTS; ++j)
+        for (int j = 0; j < L::SLOTS; ++j)
             bek[j] = (j < n_slots && tid < 128) ? Be[128 * (bn + j * g.tiles_n) + tid] : 0.f;
-        float* const s_scale = reinterpret_cast<float*>(smem + SCALE_X);
+        float* const s_scale = reinterpret_cast<float*>(smem + L::SCALE);
         // S1..S3 still in partials: every workgroup folds them here, under the latency of its first tile
-        if (!g.S) fold_s_partials_to_lds(g.s_partial, g.s_nparts, tid, reinterpret_cast<double*>(smem + S_RED_X));
+        if (!g.S) fold_s_partials_to_lds(g.s_partial, g.s_nparts, tid, reinterpret_cast<double*>(smem + L::S_RED));
         // sigma = 2^(exponent(max |Be|) - 13): |Be / sigma| < 2^14 (BF16 shares FP32's exponent range: sigma = 1)
         float inv_sigma = 1.f;
         if constexpr (std::is_same<T, f16_t>::value) {
             float m = 0.f;
 #pragma unroll
-            for (int j = 0; j < PANEL_SLOTS; ++j) m = fmaxf(m, fabsf(bek[j]));
+            for (int j = 0; j < L::SLOTS; ++j) m = fmaxf(m, fabsf(bek[j]));
             m = wave_max(m);
             if (lane == 0) s_scale[wave] = m;
             __syncthreads();
             m = fmaxf(fmaxf(s_scale[0], s_scale[1]), fmaxf(s_scale[2], s_scale[3]));
             if (m > 0.f && m < 3.0e38f) inv_sigma = ldexpf(1.f, 13 - ilogbf(m));
         }
-        uint16_t* const panel = reinterpret_cast<uint16_t*>(smem + PANEL_OFFSET);
+        uint16_t* const panel = reinterpret_cast<uint16_t*>(smem + L::PANEL);
 #pragma unroll
-        for (int j = 0; j < PANEL_SLOTS; ++j) {
+        for (int j = 0; j < L::SLOTS; ++j) {
             if (j < n_slots && tid < 128) {
                 uint16_t p[3];
                 split3<T>(bek[j] * inv_sigma, p);
@@ -711,7 +762,9 @@ __global__ __launch_bounds__(256) void gemm16_fast_kernel(const GemmArgs g) {
     __syncthreads();
     // the very first step multiplies register set 1 before any tile has been read into it: zeros
 #pragma unroll
-    for (int i = 0; i < 8; ++i) af1[i] = bf1[i] = raw16{{0u, 0u, 0u, 0u}};
+    for (int i = 0; i < 8; ++i) af1[i] = raw16{{0u, 0u, 0u, 0u}};
+#pragma unroll
+    for (int i = 0; i < NF; ++i) bf1[i] = raw16{{0u, 0u, 0u, 0u}};
     asm volatile("s_nop 7\n\ts_nop 7" ::: "memory");  // vector code wrote these operands: see Mfma16x
 
     // KSNAP: prefix row sums of the accumulator tile (section 5.2, K split as well).  Lane l owns C row l % 16 of
@@ -722,6 +775,7 @@ __global__ __launch_bounds__(256) void gemm16_fast_kernel(const GemmArgs g) {
     // code runs between two k-steps.
     int ksnap_idx = 0;
     auto snapshot = [&](int idx) __attribute__((always_inline)) {
+        if constexpr (KSNAP) {
         wait_lgkmcnt0();
         settle_accumulators(acc);
         // (opaque to the optimiser, so that none of the address arithmetic below is hoisted out of this block and
@@ -747,6 +801,7 @@ __global__ __launch_bounds__(256) void gemm16_fast_kernel(const GemmArgs g) {
 #pragma unroll
             for (int mi = 0; mi < 8; ++mi) dst[mi * 16] = tot[mi];
         }
+        }
     };
 
     // Body of k-tile kt (stage kt & 1), from barrier to barrier: step (kt-1, 1) multiplies register set 1 while
@@ -755,16 +810,45 @@ __global__ __launch_bounds__(256) void gemm16_fast_kernel(const GemmArgs g) {
     // whose last reads completed before the barrier that opened this body.  STATS: the tile belongs to a k-unit
     // this tile-column folds (unit u = kt/2, its steps t = 2*(kt&1), +1: the statistics read the tile itself, not
     // the pipeline's registers, so they are not one step behind).
+    // Narrow tiles: A of tile kt+2 (and B, with three stages) goes out here, and the closing barrier leaves those loads in
+    // flight; their stage is the one that tile kt-1 was read from.
+    uint32_t rd_a = 0, rd_b = 0;  // narrow tiles: the stages that tile kt lies in
+    const auto next_stage = [](uint32_t at, uint32_t bytes, uint32_t n) { return at + bytes == n * bytes ? 0u : at + bytes; };
     auto tile_body = [&](auto s_c, auto st_c, int kt, int hj) {
         constexpr bool STATS = decltype(st_c)::value != 0;
-        const int ktn = kt + 1 < nk ? kt + 1 : nk - 1;
-        const unsigned char* ap = uniform_ptr(a_base + (int64_t)ktn * (BK * 2));
-        const unsigned char* bp = uniform_ptr(b_base + ktn * b_ktile);
+        const int kta = kt + L::A_STAGES - 1 < nk ? kt + L::A_STAGES - 1 : nk - 1;
+        const int ktb = kt + L::B_STAGES - 1 < nk ? kt + L::B_STAGES - 1 : nk - 1;
+        const unsigned char* ap = uniform_ptr(a_base + (int64_t)kta * (BK * 2));
+        const unsigned char* bp = uniform_ptr(b_base + ktb * b_ktile);
+        if constexpr (L::NARROW) {
+            wr_a = rd_a == 0 ? (L::A_STAGES - 1) * HALF : rd_a - HALF;
+            wr_b = rd_b == 0 ? (L::B_STAGES - 1) * L::B_STAGE : rd_b - L::B_STAGE;
+            if constexpr (FUSED && STATS) {
+                a_rd_st[0] = a_rd[0] + wn * 8192;
+                a_rd_st[1] = a_rd[1] + wn * 8192;
+            }
+        }
         settle_bases(ap, bp);
         kstep(s_c, I0{}, I0{}, st_c, hj, af1, bf1, af0, bf0, ap, bp);   // step (kt-1, 1)
-        kstep(s_c, I1{}, I64{}, st_c, hj, af0, bf0, af1, bf1, ap, bp);  // step (kt, 0)
-        __builtin_amdgcn_s_waitcnt(0);
-        __syncthreads();
+        kstep(s_c, I1{}, IStep{}, st_c, hj, af0, bf0, af1, bf1, ap, bp);  // step (kt, 0)
+        if constexpr (L::NARROW) {
+            asm volatile("" ::: "memory");
+            // what this body sent out for tile kt+2 may be in flight: the youngest 8 (A) or 8 + NF (A and B) loads
+            __builtin_amdgcn_s_waitcnt(0x70 | (L::B_STAGES == 3 ? 8 + NF : 8));  // vmcnt, lgkmcnt(0)
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+            const uint32_t na = next_stage(rd_a, HALF, L::A_STAGES), nb = next_stage(rd_b, L::B_STAGE, L::B_STAGES);
+            const uint32_t da = na - rd_a, db = nb - rd_b;
+            rd_a = na;
+            rd_b = nb;
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks) a_rd[ks] = a_rd[ks] + (int)da;
+#pragma unroll
+            for (int q = 0; q < (TRANSB ? 2 : NF); ++q) b_rd[q] = b_rd[q] + (int)db;
+        } else {
+            __builtin_amdgcn_s_waitcnt(0);
+            __syncthreads();
+        }
     };
     if (FUSED) {
         // Tiles are walked in units of two (so the stage parity stays a compile-time constant): plain units in
@@ -789,7 +873,7 @@ __global__ __launch_bounds__(256) void gemm16_fast_kernel(const GemmArgs g) {
 #pragma unroll
         for (int mi = 0; mi < 8; ++mi)
 #pragma unroll
-            for (int ni = 0; ni < 8; ++ni) Mfma16x<T>::acc_a(acc[mi][ni], bf1[ni], af1[mi]);
+            for (int ni = 0; ni < NF; ++ni) Mfma16x<T>::acc_a(acc[mi][ni], bf1[ni], af1[mi]);
     } else if constexpr (KSNAP) {
         // One loop nest per K-block: the plain loop over the block's k-tiles, then the fragment pipeline is drained
         // (the pending second step of the block's last tile is multiplied), the prefix is taken with no fragment
@@ -810,7 +894,7 @@ __global__ __launch_bounds__(256) void gemm16_fast_kernel(const GemmArgs g) {
 #pragma unroll
             for (int mi = 0; mi < 8; ++mi)
 #pragma unroll
-                for (int ni = 0; ni < 8; ++ni) Mfma16x<T>::acc_a(acc[mi][ni], bf1[ni], af1[mi]);
+                for (int ni = 0; ni < NF; ++ni) Mfma16x<T>::acc_a(acc[mi][ni], bf1[ni], af1[mi]);
             if (kt >= nk) break;  // the last prefix is taken in the epilogue, behind the injector
             snapshot(ksnap_idx);
             ++ksnap_idx;
@@ -829,30 +913,40 @@ __global__ __launch_bounds__(256) void gemm16_fast_kernel(const GemmArgs g) {
 #pragma unroll
         for (int mi = 0; mi < 8; ++mi)
 #pragma unroll
-            for (int ni = 0; ni < 8; ++ni) Mfma16x<T>::acc_a(acc[mi][ni], bf1[ni], af1[mi]);
+            for (int ni = 0; ni < NF; ++ni) Mfma16x<T>::acc_a(acc[mi][ni], bf1[ni], af1[mi]);
     }
     if constexpr (EDGE) {
         const int kt0 = nk * BK, klen = g.K - kt0;  // the k past the last whole tile: a multiple of 8, below 64
         if (klen > 0) {
             // registers -> stage 0 (its last reads completed before the loop's closing barrier), zero past K
+            if constexpr (L::NARROW) {
+                __builtin_amdgcn_s_waitcnt(0);  // the loop's last loads have landed, here and in the other wavefronts
+                __syncthreads();
+#pragma unroll
+                for (int ks = 0; ks < 2; ++ks) a_rd[ks] = a_rd[ks] - (int)rd_a;
+#pragma unroll
+                for (int q = 0; q < (TRANSB ? 2 : NF); ++q) b_rd[q] = b_rd[q] - (int)rd_b;
+            }
             const raw16 z = {{0u, 0u, 0u, 0u}};
 #pragma unroll
             for (int l = 0; l < 8; ++l) {
                 const int q = wave * 64 + (lane >> 3) + 8 * l;
                 const int c = (lane & 7) ^ (lane >> 4) ^ (4 * (l & 1));  // chunk of 8 k at LDS position lane % 8
                 const unsigned char* pa = A + ((int64_t)min(row0 + q, g.M - 1) * g.lda + kt0 + c * 8) * 2;
-                const raw16 va = c * 8 < klen ? ld16(pa) : z;
+                *reinterpret_cast<raw16*>(smem + wave * 8192 + l * 1024 + lane * 16) = c * 8 < klen ? ld16(pa) : z;
+                if (l >= NF) continue;
                 raw16 vb;
                 if (TRANSB) {
-                    const unsigned char* pb = B + ((int64_t)min(col0 + q, g.N - 1) * g.ldb + kt0 + c * 8) * 2;
+                    const int qb = wave * 8 * NF + (lane >> 3) + 8 * l;
+                    const unsigned char* pb = B + ((int64_t)min(col0 + qb, g.N - 1) * g.ldb + kt0 + c * 8) * 2;
                     vb = c * 8 < klen ? ld16(pb) : z;
                 } else {
-                    const int k = wave * 16 + 2 * l + lh, f = 2 * ((2 * (l & 1) + lh) | (4 * (l >> 2)));
-                    const unsigned char* pb = B + ((int64_t)(kt0 + k) * g.ldb + col0 + min((l32 ^ f) << 3, g.N - 8 - col0)) * 2;
+                    const int kl = (l * 64 + lane) / (4 * NF), n = ((l * 64 + lane) % (4 * NF) ^ kn_swz(kl)) << 3;
+                    const int k = wave * 16 + kl;
+                    const unsigned char* pb = B + ((int64_t)(kt0 + k) * g.ldb + min(col0 + n, g.N - 8)) * 2;
                     vb = k < klen ? ld16(pb) : z;
                 }
-                *reinterpret_cast<raw16*>(smem + wave * 8192 + l * 1024 + lane * 16) = va;
-                *reinterpret_cast<raw16*>(smem + B_BASE + wave * 8192 + l * 1024 + lane * 16) = vb;
+                *reinterpret_cast<raw16*>(smem + B_BASE + wave * NF * 1024 + l * 1024 + lane * 16) = vb;
             }
             __builtin_amdgcn_s_waitcnt(0);
             __syncthreads();
@@ -863,29 +957,38 @@ __global__ __launch_bounds__(256) void gemm16_fast_kernel(const GemmArgs g) {
                 // whatever moved them clear of the MFMAs)
 #pragma unroll
                 for (int i = 0; i < 8; ++i) {
-                    u32x4_t x = __builtin_bit_cast(u32x4_t, af1[i]), y = __builtin_bit_cast(u32x4_t, bf1[i]);
-                    asm volatile("" : "+v"(x), "+v"(y));
+                    u32x4_t x = __builtin_bit_cast(u32x4_t, af1[i]);
+                    asm volatile("" : "+v"(x));
                     af1[i] = __builtin_bit_cast(raw16, x);
-                    bf1[i] = __builtin_bit_cast(raw16, y);
+                }
+#pragma unroll
+                for (int i = 0; i < NF; ++i) {
+                    u32x4_t x = __builtin_bit_cast(u32x4_t, bf1[i]);
+                    asm volatile("" : "+v"(x));
+                    bf1[i] = __builtin_bit_cast(raw16, x);
                 }
                 asm volatile("s_nop 7\n\ts_nop 7" ::: "memory");
 #pragma unroll
                 for (int mi = 0; mi < 8; ++mi)
 #pragma unroll
-                    for (int ni = 0; ni < 8; ++ni) Mfma16x<T>::acc_a(acc[mi][ni], bf1[ni], af1[mi]);
+                    for (int ni = 0; ni < NF; ++ni) Mfma16x<T>::acc_a(acc[mi][ni], bf1[ni], af1[mi]);
                 asm volatile("s_nop 7\n\ts_nop 7" ::: "memory");
             });
             __syncthreads();  // the epilogue reuses the operand stages
         }
     }
+    if constexpr (L::NARROW) {
+        __builtin_amdgcn_s_waitcnt(0);  // the epilogue reuses the stages that the loop's last loads went to
+        __syncthreads();
+    }
     settle_accumulators(acc);
     if constexpr (EDGE && MODE >= 1) {
-        if (col0 + BN > g.N) {  // columns past the end count as zero in the row sums
+        if (col0 + TN > g.N) {  // columns past the end count as zero in the row sums
             static_for<0, 8>([&](auto mi_c) {
-                static_for<0, 8>([&](auto ni_c) {
+                static_for<0, NF>([&](auto ni_c) {
                     static_for<0, 4>([&](auto r_c) {
                         constexpr int mi = decltype(mi_c)::value, ni = decltype(ni_c)::value, r = decltype(r_c)::value;
-                        acc[mi][ni][r] = col0 + wn * 128 + ni * 16 + 4 * lq + r < g.N ? acc[mi][ni][r] : 0.f;
+                        acc[mi][ni][r] = col0 + wn * (16 * NF) + ni * 16 + 4 * lq + r < g.N ? acc[mi][ni][r] : 0.f;
                     });
                 });
             });
@@ -893,20 +996,20 @@ __global__ __launch_bounds__(256) void gemm16_fast_kernel(const GemmArgs g) {
     }
 
     // ---- epilogue -------------------------------------------------------------------------------------------
-    gemm16x_inject<INJECT>(g, acc, row0, col0, wm, wn, l16, lq);
+    if constexpr (INJECT) gemm16x_inject<INJECT>(g, acc, row0, col0, wm, wn, l16, lq);
     if constexpr (KSNAP) snapshot(ksnap_idx);  // the last K-block's prefix is the whole row sum
     if (VERIFY) {
         float* red = reinterpret_cast<float*>(smem);                 // [2 wn][256 rows]
         float* sred = reinterpret_cast<float*>(smem + SRED_OFFSET);  // [4][256 rows]
         float* red2 = reinterpret_cast<float*>(smem + RED2_OFFSET);  // [2 wn][256 rows]
         float* cred = reinterpret_cast<float*>(smem + CRED_OFFSET);  // [2 wm][256 columns]
-        if (WSUM)
+        if constexpr (WSUM)
             gemm16x_rowsums12_to_lds(acc, red, red2, col0, wm, wn, l16, lq);
         else
-            gemm16x_rowsum_to_lds(acc, red, wm, wn, l16, lq);
-        if (CSUM) gemm16x_colsum_to_lds(acc, cred, wm, wn, l16, lq);
+            gemm16x_rowsum_to_lds<NF>(acc, red, wm, wn, l16, lq);
+        if constexpr (CSUM) gemm16x_colsum_to_lds(acc, cred, wm, wn, l16, lq);
         if (FUSED) {
-            const float sigma = reinterpret_cast<const float*>(smem + SCALE_X)[4];
+            const float sigma = reinterpret_cast<const float*>(smem + L::SCALE)[4];
             // the four k-chunk lanes of a row hold partial (max, min); lanes 0..15 hold the panel's result
 #pragma unroll
             for (int j = 0; j < 4; ++j) mm[j].merge_xor(16);
@@ -948,43 +1051,60 @@ __global__ __launch_bounds__(256) void gemm16_fast_kernel(const GemmArgs g) {
         // block-wise check: the partials are all this kernel leaves; a later kernel compares them per block
         const bool partials_only = MODE == 5 || (MODE == 2 && g.block_mode);
         if (!partials_only)
-            gemm_tile_row_check<WSUM, FUSED, EDGE>(g, smem, reinterpret_cast<const double*>(smem + S_RED_X), bm, gi, tid);
+            gemm_tile_row_check<WSUM, FUSED, EDGE>(g, smem, reinterpret_cast<const double*>(smem + L::S_RED), bm, gi, tid);
         __syncthreads();  // the store below reuses the LDS the reductions read
     }
-    gemm16x_store_c<T, EDGE>(g, acc, smem, row0, col0, lane, wm, wn, l16, lq);
+    gemm16x_store_c<T, EDGE, NF>(g, acc, smem, row0, col0, lane, wm, wn, l16, lq);
 }
 
-template <typename T, int TRANSB>
-static int gemm16_fast_launch_tb(const GemmArgs& a, int mode, bool edge, hipStream_t st) {
-    const dim3 grid(a.tiles_m * a.tiles_n), block(256);
-    const int fused = a.fused_stats ? 1 : 0;
-    const size_t lds = fused ? g16x::LDS_BYTES_FUSED_X : g16::LDS_BYTES;
-#define VABFT_G16F_CASE(VF, FU, ED)                                                                        \
-    if (mode == VF && fused == FU && edge == ED) {                                                         \
-        auto kern = gemm16_fast_kernel<T, TRANSB, VF, FU != 0, ED>;                                        \
-        static bool attr_set = false;                                                                      \
-        if (!attr_set) {                                                                                   \
-            if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern),                                   \
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)   \
-                return VABFT_EDEVICE;                                                                      \
-            attr_set = true;                                                                               \
-        }                                                                                                  \
-        kern<<<grid, block, lds, st>>>(a);                                                                 \
-        return hipGetLastError() == hipSuccess ? VABFT_OK : VABFT_EDEVICE;                                 \
+template <typename T, int TRANSB, int MODE, bool FUSED, bool EDGE, int NF>
+__global__ __launch_bounds__(256) void gemm16_fast_kernel(const GemmArgs g) {
+    int bm, bn;
+    tile_of_block(blockIdx.x, g.tiles_m, g.tiles_n, bm, bn);
+    gemm16_fast_tile<T, TRANSB, MODE, FUSED, EDGE, NF>(g, bm, bn, bm * 256, bn * 32 * NF);
+}
+
+template <typename KERN> static int gemm16_start(KERN kern, const GemmArgs& a, size_t lds, bool& attr_set, hipStream_t st) {
+    if (!attr_set) {
+        if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                (int)lds) != hipSuccess)
+            return VABFT_EDEVICE;
+        attr_set = true;
     }
-    VABFT_G16F_CASE(0, 0, false)
-    VABFT_G16F_CASE(1, 0, false)
-    VABFT_G16F_CASE(2, 0, false)
-    VABFT_G16F_CASE(3, 0, false)
-    VABFT_G16F_CASE(4, 0, false)
-    VABFT_G16F_CASE(5, 0, false)
-    VABFT_G16F_CASE(6, 0, false)
-    VABFT_G16F_CASE(7, 0, false)
-    VABFT_G16F_CASE(1, 1, false)
-    VABFT_G16F_CASE(2, 1, false)
-    VABFT_G16F_CASE(0, 0, true)
-    VABFT_G16F_CASE(1, 0, true)
-    VABFT_G16F_CASE(1, 1, true)
+    kern<<<dim3(a.tiles_m * a.tiles_n), dim3(256), lds, st>>>(a);
+    return hipGetLastError() == hipSuccess ? VABFT_OK : VABFT_EDEVICE;
+}
+
+// form: see Form16; the tile's width is 256, 192 or 128
+template <typename T, int TRANSB>
+static int gemm16_fast_launch_tb(const GemmArgs& a, int mode, int form, hipStream_t st) {
+    const int fused = a.fused_stats ? 1 : 0;
+    const auto bytes = [&](auto l) { return (size_t)(fused ? decltype(l)::BYTES_FUSED : decltype(l)::BYTES); };
+    using g16x::Lds16;
+    const size_t lds = form == FORM16_128 ? bytes(Lds16<4>{}) : form == FORM16_192 ? bytes(Lds16<6>{}) : bytes(Lds16<8>{});
+#define VABFT_G16F_CASE(VF, FU, FORM, ...)                \
+    if (mode == VF && fused == FU && form == FORM) {      \
+        static bool attr_set = false;                     \
+        return gemm16_start(__VA_ARGS__, a, lds, attr_set, st); \
+    }
+#define VABFT_G16F_WHOLE(VF, FU) VABFT_G16F_CASE(VF, FU, FORM16_WHOLE, gemm16_fast_kernel<T, TRANSB, VF, FU != 0, false, 8>)
+#define VABFT_G16F_SIZES(VF, FU)                                                                        \
+    VABFT_G16F_WHOLE(VF, FU)                                                                            \
+    VABFT_G16F_CASE(VF, FU, FORM16_EDGE, gemm16_fast_kernel<T, TRANSB, VF, FU != 0, true, 8>)          \
+    VABFT_G16F_CASE(VF, FU, FORM16_192, gemm16_fast_kernel<T, TRANSB, VF, FU != 0, true, 6>)           \
+    VABFT_G16F_CASE(VF, FU, FORM16_128, gemm16_fast_kernel<T, TRANSB, VF, FU != 0, true, 4>)
+    VABFT_G16F_SIZES(0, 0)
+    VABFT_G16F_SIZES(1, 0)
+    VABFT_G16F_SIZES(1, 1)
+    VABFT_G16F_WHOLE(2, 0)
+    VABFT_G16F_WHOLE(3, 0)
+    VABFT_G16F_WHOLE(4, 0)
+    VABFT_G16F_WHOLE(5, 0)
+    VABFT_G16F_WHOLE(6, 0)
+    VABFT_G16F_WHOLE(7, 0)
+    VABFT_G16F_WHOLE(2, 1)
+#undef VABFT_G16F_SIZES
+#undef VABFT_G16F_WHOLE
 #undef VABFT_G16F_CASE
     return VABFT_EINVAL;
 }

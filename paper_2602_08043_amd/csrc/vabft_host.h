@@ -151,13 +151,18 @@ int gemm_direct_launch_f64(const DirectArgs& d, int shape, int transB, hipStream
 // per-dtype launchers (one translation unit each, to compile in parallel)
 // mode: 0 plain, 1 check, 2 check + injector + weighted row sums + column sums, 3 check + weighted row
 // sums, 4 check + column sums, 5 row-sum partials only (block-wise check, whole-tile kernels).
-// edge: sizes that are no multiples of the tile's (modes 0 and 1 only).
+// form (16-bit types): whole 256 x 256 tiles; the same for sizes that are no multiples of them; tiles of 256 rows and
+// 192 or 128 columns (the last three: any size, modes 0 and 1 only).
+// tile-columns 256 wide and the others 192; all 128 wide (the last three: any size, modes 0 and 1 only).
 // The kernels do the compare-and-flag step themselves and, with GemmArgs::fused_stats, the A-side statistics and
 // thresholds.
-int gemm16_launch_bf16_nn(const GemmArgs& a, int mode, bool edge, hipStream_t st);
-int gemm16_launch_bf16_nt(const GemmArgs& a, int mode, bool edge, hipStream_t st);
-int gemm16_launch_f16_nn(const GemmArgs& a, int mode, bool edge, hipStream_t st);
-int gemm16_launch_f16_nt(const GemmArgs& a, int mode, bool edge, hipStream_t st);
+// k-units of 128 that the fused 16-bit kernels fold per tile-column at most (256-wide tiles alone; with narrow ones)
+constexpr int PANEL_UNITS_WIDE = 16, PANEL_UNITS_NARROW = 15;
+enum Form16 { FORM16_WHOLE = 0, FORM16_EDGE = 1, FORM16_192 = 2, FORM16_128 = 3 };
+int gemm16_launch_bf16_nn(const GemmArgs& a, int mode, int form, hipStream_t st);
+int gemm16_launch_bf16_nt(const GemmArgs& a, int mode, int form, hipStream_t st);
+int gemm16_launch_f16_nn(const GemmArgs& a, int mode, int form, hipStream_t st);
+int gemm16_launch_f16_nt(const GemmArgs& a, int mode, int form, hipStream_t st);
 int gemm8_launch_f8_nt(const GemmArgs& a, int mode, hipStream_t st);   // E4M3, whole tiles only
 int gemm8_launch_bf8_nt(const GemmArgs& a, int mode, hipStream_t st);  // E5M2, whole tiles only
 

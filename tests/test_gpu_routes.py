@@ -180,32 +180,48 @@ def test_direct_infinities_stay_in_their_row_and_column(dtype, M, N, K, transB):
         assert int(vg.nflag.item()) == int(flags.sum())
 
 
-WHOLE = [("bf16", 2304, 2304, 256, 0), ("bf16", 2304, 2304, 192, 1), ("f16", 2304, 2304, 384, 1), ("f16", 2304, 2304, 64, 0),
+WHOLE = [("bf16", 3840, 4096, 256, 0), ("f16", 4096, 3840, 192, 1), ("bf16", 2304, 2304, 256, 0), ("bf16", 2304, 2304, 192, 1), ("f16", 2304, 2304, 384, 1), ("f16", 2304, 2304, 64, 0),
          ("f8", 1792, 1792, 512, 1), ("f8e5m2", 1792, 1792, 256, 1)]
 
 
 @pytest.mark.parametrize("dtype,M,N,K,transB", WHOLE)
 def test_whole_tile_kernels(dtype, M, N, K, transB):
-    """81 (FP8: 49) tiles of 256 x 256: just above the line below which the direct kernels take over."""
+    """240 tiles of 256 x 256, which the 16-bit types run as such, and 81 (FP8: 49), just above the line below which the
+    direct kernels take over (in tiles of 128 columns where the product is the plain or the checked one)."""
     A, B = _gen(dtype, M, N, K, transB, 9)
     vg = _session(M, N, K, dtype, transB)
     _check(vg, A, B, _dev(A, dtype), _dev(B, dtype), dtype, M, N, K, transB, ALL)
 
 
 RAGGED = [("bf16", 2049, 2056, 200, 0), ("bf16", 2303, 2296, 72, 1), ("f16", 2100, 2184, 256, 1), ("f16", 2050, 2064, 384, 0),
-          ("bf16", 2175, 2112, 128, 1), ("bf16", 2300, 2200, 64, 0), ("f16", 2111, 2080, 1032, 1), ("f16", 2241, 2312, 120, 0)]
+          ("bf16", 2175, 2112, 128, 1), ("bf16", 2300, 2200, 64, 0), ("f16", 2111, 2080, 1032, 1), ("f16", 2241, 2312, 120, 0),
+          # 192 columns
+          ("bf16", 2817, 2888, 64, 0), ("bf16", 3000, 2984, 136, 1), ("f16", 2900, 3064, 384, 0), ("f16", 3072, 2880, 512, 1),
+          ("bf16", 2827, 2976, 320, 0), ("f16", 2818, 3072, 128, 1),
+          # 256 columns
+          ("bf16", 3841, 3848, 72, 0), ("f16", 3900, 4088, 128, 1), ("bf16", 4095, 3904, 256, 1), ("f16", 3999, 3992, 200, 0)]
 
 
 @pytest.mark.parametrize("dtype,M,N,K,transB", RAGGED)
 def test_tiled_kernels_at_ragged_sizes(dtype, M, N, K, transB):
-    """Enough 256 x 256 tiles for the tiled kernels, none of the sizes a multiple of theirs: remainders of one row, of
-    one group of eight columns, and of K below and above one step; K a multiple of 128 runs the fused statistics."""
+    """Enough tiles for the tiled kernels (of 128 columns in front, then 192 and 256), the sizes no multiples of theirs:
+    remainders of one row, of one group of eight columns, and of K below and above one step; K a multiple of 128 runs the
+    fused statistics."""
     A, B = _gen(dtype, M, N, K, transB, 11)
     vg = _session(M, N, K, dtype, transB)
     dA, dB = _dev(A, dtype), _dev(B, dtype)
     _check(vg, A, B, dA, dB, dtype, M, N, K, transB, ("run", "run_fused", "fused_deferred"))
     vg.gemm(dA, dB, 0)  # plain product
     check_C(vg.results(), orc.verify(A, B, dtype, transB, e_max=_emax(dtype, K, N)), A, B, dtype, transB)
+
+
+@pytest.mark.parametrize("K", [1920, 2048])
+def test_narrow_tiles_at_the_end_of_the_checksum_panel(K):
+    """One tile-column folds all of K: as many units as the panel in LDS holds, and one more (a pass of its own)."""
+    dtype, M, N = "bf16", 33000, 128
+    A, B = _gen(dtype, M, N, K, 1, 13)
+    vg = _session(M, N, K, dtype, 1)
+    _check(vg, A, B, _dev(A, dtype), _dev(B, dtype), dtype, M, N, K, 1, ("run_fused",))
 
 
 def test_tiled_kernels_leave_padding_of_C():
