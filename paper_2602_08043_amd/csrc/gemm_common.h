@@ -31,6 +31,11 @@ __device__ __forceinline__ void tile_of_block(int b, int tiles_m, int tiles_n, i
     bn = in / gsize;
 }
 
+// the 64-bit counter behind the tile-rows' arrival counters
+__device__ __forceinline__ unsigned long long* done_counter(const GemmArgs& g) {
+    return reinterpret_cast<unsigned long long*>(g.tickets + ((g.tiles_m * g.ticket_stride + 1) & ~1));
+}
+
 // --- bit flips on accumulator words ----------------------------------------
 __device__ __forceinline__ float flip_bit(float v, int bit) { return __uint_as_float(__float_as_uint(v) ^ (1u << bit)); }
 __device__ __forceinline__ double flip_bit(double v, int bit) {

@@ -267,41 +267,60 @@ template <typename T, int TRANSB, int MF, int NF, int WVK> struct Shape {
 
 }  // namespace gd
 
-// Folds the partial row sums of `rows` rows from row0 on and compares; TPF neighbouring threads share a row.  Returns
-// the number of flagged rows.
-template <typename T, int TPF> __device__ __forceinline__ int direct_compare(const DirectArgs& d, int row0, int rows) {
+// Folds the partial row sums of `rows` rows from row0 on and compares; SUB groups of R neighbouring threads share the
+// tile-columns of R rows, so that a wavefront reads whole pieces of lines: loads for other workgroups' partials pass the
+// caches by, one request per piece.  Against SUB neighbouring threads per row: 16 x 4096 x 4096 14.4 -> 11.7 us, 1024^3
+// 12.6 -> 12.0, 40 x 11008 x 4096 (three batches of loads) 23.6 -> 24.3.  This code runs once, at the end: a variant with
+// 32 loads in flight, twice the instructions to fetch, loses more than it saves (256^3 FP32 8.7 -> 9.8).  Returns the
+// number of flagged rows.
+template <typename T, int R, int SUB>
+__device__ __forceinline__ int direct_compare(const DirectArgs& d, int row0, int rows, unsigned char* smem) {
     using acc_t = typename Elem<T>::acc_t;
-    static_assert(TPF >= 1 && TPF <= 64, "fold mapping");
     const GemmArgs& g = d.g;
-    const int r = threadIdx.x / TPF, sub = threadIdx.x % TPF;
+    const int r = threadIdx.x % R, sub = threadIdx.x / R;
     const bool act = r < rows, wsum = d.wsum != 0;
     const int gi = row0 + (act ? r : 0);
+    // (with the partials in flight, not a round trip behind their fold)
+    const acc_t* ex = reinterpret_cast<const acc_t*>(g.expected) + gi;
+    const acc_t* th = reinterpret_cast<const acc_t*>(g.T) + gi;
+    const acc_t want = d.stat_blocks ? gd::ld_agent(ex) : *ex, t = d.stat_blocks ? gd::ld_agent(th) : *th;
     acc_t s4[4] = {0, 0, 0, 0}, w4[4] = {0, 0, 0, 0};
-    for (int t0 = sub; t0 < g.tiles_n; t0 += 16 * TPF) {
+    for (int t0 = 0; t0 < g.tiles_n; t0 += 16 * SUB) {
         acc_t v[16], v2[16];
 #pragma unroll
         for (int j = 0; j < 16; ++j) {
-            const int t = t0 + j * TPF < g.tiles_n ? t0 + j * TPF : t0;
-            v[j] = gd::ld_agent(reinterpret_cast<const acc_t*>(g.rowpart) + (int64_t)t * g.M + gi);
-            v2[j] = 0;
-            if (wsum) v2[j] = gd::ld_agent(reinterpret_cast<const acc_t*>(g.rowpart2) + (int64_t)t * g.M + gi);
+            v[j] = v2[j] = 0;
+            if (t0 + j * SUB < g.tiles_n) {  // (the same for every thread)
+                const int64_t at = (int64_t)min(t0 + j * SUB + sub, g.tiles_n - 1) * g.M + gi;
+                v[j] = gd::ld_agent(reinterpret_cast<const acc_t*>(g.rowpart) + at);
+                if (wsum) v2[j] = gd::ld_agent(reinterpret_cast<const acc_t*>(g.rowpart2) + at);
+            }
         }
 #pragma unroll
         for (int j = 0; j < 16; ++j)
-            if (t0 + j * TPF < g.tiles_n) {
+            if (t0 + j * SUB + sub < g.tiles_n) {
                 s4[j & 3] += v[j];
                 w4[j & 3] += v2[j];
             }
     }
-    const acc_t s = group_sum<TPF>((s4[0] + s4[1]) + (s4[2] + s4[3]));
-    acc_t s2 = (w4[0] + w4[1]) + (w4[2] + w4[3]);
-    if (wsum) s2 = group_sum<TPF>(s2);
+    acc_t s = (s4[0] + s4[1]) + (s4[2] + s4[3]), s2 = (w4[0] + w4[1]) + (w4[2] + w4[3]);
+    if constexpr (SUB > 1) {
+        acc_t* const red = reinterpret_cast<acc_t*>(smem);  // [2][SUB][R]
+        red[threadIdx.x] = s;
+        red[SUB * R + threadIdx.x] = s2;
+        __syncthreads();
+#pragma unroll
+        for (int half = SUB / 2; half > 0; half /= 2) {
+            if (sub < half) {
+                red[threadIdx.x] = s += red[threadIdx.x + half * R];
+                red[SUB * R + threadIdx.x] = s2 += red[SUB * R + threadIdx.x + half * R];
+            }
+            __syncthreads();
+        }
+    }
     int f = 0;
     if (act && sub == 0) {
-        const acc_t* ex = reinterpret_cast<const acc_t*>(g.expected) + gi;
-        const acc_t* th = reinterpret_cast<const acc_t*>(g.T) + gi;
-        const acc_t e = (d.stat_blocks ? gd::ld_agent(ex) : *ex) - s;
-        const acc_t t = d.stat_blocks ? gd::ld_agent(th) : *th;
+        const acc_t e = want - s;
         f = !(fabs(e) <= t);
         reinterpret_cast<acc_t*>(g.rowsum)[gi] = s;
         if (wsum) reinterpret_cast<acc_t*>(g.rowsum2)[gi] = s2;
@@ -314,27 +333,33 @@ template <typename T, int TPF> __device__ __forceinline__ int direct_compare(con
 // The last workgroup of tile-row bm to arrive (GEMM tiles and, with the A-side pass fused, its workgroups) compares the
 // tile-row.  Problems of a few tiles and no more rows than a workgroup has threads arrive at one counter for all
 // tile-rows: the last workgroup compares every row and knows nflag, one round trip to memory less.
-// Every thread of every workgroup calls this after its partials are written.
-template <typename T, typename S>
-__device__ __forceinline__ void direct_tile_row_check(const DirectArgs& d, int bm, int* s_last) {
+// Every thread of every workgroup calls this after its partials are written.  store_c
+// comes behind the arrival (in front of it, the wait for the partials would be one for the stores of C as well) and, in the
+// workgroup that compares, behind that. 
+template <typename T, typename S, typename F>
+__device__ __forceinline__ void direct_tile_row_check(const DirectArgs& d, int bm, int* s_last, unsigned char* smem, F store_c) {
     const GemmArgs& g = d.g;
     const bool one = g.tiles_m == 1 || (g.tiles_m * g.tiles_n <= 64 && g.M <= S::NT);
     const int at = one ? 0 : bm, row0 = at * S::BM, rows = one ? g.M : min(S::BM, g.M - row0);
     const int arrivals = (one ? g.tiles_m : 1) * g.tiles_n + (d.stat_blocks ? (rows + S::NW - 1) / S::NW : 0);
     __builtin_amdgcn_s_waitcnt(0);  // this wavefront's partials are performed
     __syncthreads();
-    if (threadIdx.x == 0) *s_last = (atomicAdd(&g.tickets[at], 1) == arrivals - 1);
+    if (threadIdx.x == 0) *s_last = (atomicAdd(&g.tickets[at * g.ticket_stride], 1) == arrivals - 1);
     __syncthreads();
-    if (!*s_last) return;
-    const int cnt = one && g.tiles_m > 1 ? direct_compare<T, 1>(d, 0, rows) : direct_compare<T, S::NT / S::BM>(d, row0, rows);
+    if (!*s_last) {
+        store_c();
+        return;
+    }
+    const int cnt = one && g.tiles_m > 1 ? direct_compare<T, S::NT, 1>(d, 0, rows, smem)
+                                        : direct_compare<T, S::BM, S::NT / S::BM>(d, row0, rows, smem);
     if (threadIdx.x == 0) {
-        __hip_atomic_store(&g.tickets[at], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&g.tickets[at * g.ticket_stride], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (one) {
             *g.d_nflag = cnt;
         } else {
             // one 64-bit atomic counts the finished tile-rows (high word) and the flagged rows (low word); whoever
             // completes the count publishes nflag and leaves the counter zero
-            unsigned long long* done = reinterpret_cast<unsigned long long*>(g.tickets + ((g.tiles_m + 1) & ~1));
+            unsigned long long* done = done_counter(g);
             const unsigned long long old = atomicAdd(done, (1ull << 32) | (unsigned long long)(unsigned)cnt);
             if ((int)(old >> 32) == g.tiles_m - 1) {
                 *g.d_nflag = (int)(unsigned)(old & 0xffffffffull) + cnt;
@@ -342,11 +367,12 @@ __device__ __forceinline__ void direct_tile_row_check(const DirectArgs& d, int b
             }
         }
     }
+    store_c();
 }
 
 // The A-side pass inside the GEMM launch: one wavefront per row
 template <typename T, typename S>
-__device__ __forceinline__ void direct_stats(const DirectArgs& d, double* s_red, int* s_last) {
+__device__ __forceinline__ void direct_stats(const DirectArgs& d, double* s_red, int* s_last, unsigned char* smem) {
     using acc_t = typename Elem<T>::acc_t;
     const GemmArgs& g = d.g;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -372,7 +398,7 @@ __device__ __forceinline__ void direct_stats(const DirectArgs& d, double* s_red,
             gd::st_agent(reinterpret_cast<acc_t*>(const_cast<void*>(g.T)) + m, t);
         }
     }
-    direct_tile_row_check<T, S>(d, blockIdx.x * S::NW / S::BM, s_last);
+    direct_tile_row_check<T, S>(d, blockIdx.x * S::NW / S::BM, s_last, smem, [] {});
 }
 
 // ANY: for rows so far apart that 32 bits do not hold a tile's byte offsets, and for rows of under 16 bytes.
@@ -405,7 +431,7 @@ __global__ __launch_bounds__(64 * WVK, 2) void gemm_direct_kernel(const DirectAr
         if (g.d_ncolflag) *g.d_ncolflag = 0;
     }
     if ((int)blockIdx.x < d.stat_blocks) {
-        direct_stats<T, S>(d, s_red, s_last);
+        direct_stats<T, S>(d, s_red, s_last, smem);
         return;
     }
     const int lane = tid & 63, l16 = lane & 15, lq = lane >> 4;
@@ -676,45 +702,46 @@ __global__ __launch_bounds__(64 * WVK, 2) void gemm_direct_kernel(const DirectAr
     constexpr int EPT = S::EPT;
     static_assert(EPT * sizeof(acc_t) < 16 || EPT * sizeof(acc_t) % 16 == 0, "LDS vectors");
     const int tr = tid / S::TPR, tc = tid % S::TPR * EPT;
-    for (int r0 = 0; r0 < S::BM; r0 += S::RPP) {
-        const int gi = row0 + r0 + tr;
-        acc_t* const src = tile + (r0 + tr) * S::PITCH + tc;
-        alignas(16) acc_t v[EPT];
-        gd::copy_aligned<EPT>(v, src);
-        if (S::SLOTS == 2 && !inject) {
-            alignas(16) acc_t u[EPT];
-            gd::copy_aligned<EPT>(u, src + (S::SLOTS - 1) * S::BM * S::PITCH);
+    static_assert(S::RPP == S::BM, "one pass");
+    const int gi = row0 + tr;
+    acc_t* const src = tile + tr * S::PITCH + tc;
+    alignas(16) acc_t v[EPT];
+    gd::copy_aligned<EPT>(v, src);
+    if (S::SLOTS == 2 && !inject) {
+        alignas(16) acc_t u[EPT];
+        gd::copy_aligned<EPT>(u, src + (S::SLOTS - 1) * S::BM * S::PITCH);
 #pragma unroll
-            for (int e = 0; e < EPT; ++e) v[e] += u[e];
+        for (int e = 0; e < EPT; ++e) v[e] += u[e];
+    }
+    if (verify) {
+        acc_t x[EPT];
+#pragma unroll
+        for (int e = 0; e < EPT; ++e) x[e] = (!nedge || column_of(tc + e) >= 0) && gi < g.M ? v[e] : (acc_t)0;
+        if (csum) {
+#pragma unroll
+            for (int e = 0; e < EPT; ++e) src[e] = x[e];
         }
-        if (verify) {
-            acc_t x[EPT];
+        acc_t s2 = 0;
+        if (wsum) {
+            // weights from the thread's first column on; that column's own weight goes with the plain sum below
 #pragma unroll
-            for (int e = 0; e < EPT; ++e) x[e] = (!nedge || column_of(tc + e) >= 0) && gi < g.M ? v[e] : (acc_t)0;
-            if (csum) {
-#pragma unroll
-                for (int e = 0; e < EPT; ++e) src[e] = x[e];
-            }
-            acc_t s2 = 0;
-            if (wsum) {
-                // weights from the thread's first column on; that column's own weight goes with the plain sum below
-#pragma unroll
-                for (int e = 0; e < EPT; ++e)
-                    s2 = fma((acc_t)(nedge ? max(0, column_of(tc + e)) - (col0 + tc) : e), x[e], s2);
-            }
-#pragma unroll
-            for (int w = 1; w < EPT; w *= 2)
-#pragma unroll
-                for (int e = 0; e + w < EPT; e += 2 * w) x[e] += x[e + w];
-            acc_t s = x[0];
-            if (wsum) s2 = fma((acc_t)(col0 + tc + 1), s, s2);
-            s = group_sum<S::TPR>(s);
-            if (wsum) s2 = group_sum<S::TPR>(s2);
-            if (tid % S::TPR == 0 && gi < g.M) {
-                gd::st_agent(reinterpret_cast<acc_t*>(g.rowpart) + (int64_t)bn * g.M + gi, s);
-                if (wsum) gd::st_agent(reinterpret_cast<acc_t*>(g.rowpart2) + (int64_t)bn * g.M + gi, s2);
-            }
+            for (int e = 0; e < EPT; ++e)
+                s2 = fma((acc_t)(nedge ? max(0, column_of(tc + e)) - (col0 + tc) : e), x[e], s2);
         }
+#pragma unroll
+        for (int w = 1; w < EPT; w *= 2)
+#pragma unroll
+            for (int e = 0; e + w < EPT; e += 2 * w) x[e] += x[e + w];
+        acc_t s = x[0];
+        if (wsum) s2 = fma((acc_t)(col0 + tc + 1), s, s2);
+        s = group_sum<S::TPR>(s);
+        if (wsum) s2 = group_sum<S::TPR>(s2);
+        if (tid % S::TPR == 0 && gi < g.M) {
+            gd::st_agent(reinterpret_cast<acc_t*>(g.rowpart) + (int64_t)bn * g.M + gi, s);
+            if (wsum) gd::st_agent(reinterpret_cast<acc_t*>(g.rowpart2) + (int64_t)bn * g.M + gi, s2);
+        }
+    }
+    const auto store_c = [&]() __attribute__((always_inline)) {
         if (gi < g.M) {
             out_t* c = reinterpret_cast<out_t*>(g.C) + (int64_t)gi * g.ldc;
             if (EPT >= 4 && !nedge) {
@@ -728,7 +755,9 @@ __global__ __launch_bounds__(64 * WVK, 2) void gemm_direct_kernel(const DirectAr
                 }
             }
         }
-    }
+    };
+    const bool check = verify && !g.block_mode;
+    if (!check) store_c();
     if (!verify) return;
     if (csum) {
         __syncthreads();
@@ -742,7 +771,7 @@ __global__ __launch_bounds__(64 * WVK, 2) void gemm_direct_kernel(const DirectAr
                 reinterpret_cast<acc_t*>(g.colpart)[(int64_t)bm * g.N + gj] = (q[0] + q[1]) + (q[2] + q[3]);
         }
     }
-    if (!g.block_mode) direct_tile_row_check<T, S>(d, bm, s_last);
+    if (check) direct_tile_row_check<T, S>(d, bm, s_last, smem, store_c);
 }
 
 template <typename T, int TRANSB, int MF, int NF, int WVK, int D, bool ANY = false>

@@ -114,7 +114,7 @@ __device__ __forceinline__ void gemm_tile_row_check(const GemmArgs& g, unsigned 
     // shadow.
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
-    if (tid == 0) *s_last = (atomicAdd(&g.tickets[bm], 1) == g.tiles_n - 1);
+    if (tid == 0) *s_last = (atomicAdd(&g.tickets[bm * g.ticket_stride], 1) == g.tiles_n - 1);
     __syncthreads();
     if (*s_last) {
         // Combine the tile-column partials in tile order.  The device-scope loads are issued
@@ -124,6 +124,17 @@ __device__ __forceinline__ void gemm_tile_row_check(const GemmArgs& g, unsigned 
         float rs4[4] = {0.f, 0.f, 0.f, 0.f}, rs24[4] = {0.f, 0.f, 0.f, 0.f}, sum4[4] = {0.f, 0.f, 0.f, 0.f},
               dot4[4] = {0.f, 0.f, 0.f, 0.f};
         float mx = -3.402823466e+38f, mn = 3.402823466e+38f;
+        // (with the partials in flight, not a round trip behind their fold)
+        double S1 = 0, S2 = 0, S3 = 0;
+        float expv = 0, thr = 0;
+        if (FUSED) {
+            S1 = g.S ? g.S[0] : folded_s(s_red, 0);
+            S2 = g.S ? g.S[1] : folded_s(s_red, 1);
+            S3 = g.S ? g.S[2] : folded_s(s_red, 2);
+        } else {
+            expv = reinterpret_cast<const float*>(g.expected)[gi];
+            thr = reinterpret_cast<const float*>(g.T)[gi];
+        }
         for (int t0 = 0; t0 < g.tiles_n; t0 += 16) {
             float v[16][5];
             float v2[16];
@@ -180,13 +191,11 @@ __device__ __forceinline__ void gemm_tile_row_check(const GemmArgs& g, unsigned 
         }
         const float rs = (rs4[0] + rs4[1]) + (rs4[2] + rs4[3]), rs2 = (rs24[0] + rs24[1]) + (rs24[2] + rs24[3]);
         const float sum = (sum4[0] + sum4[1]) + (sum4[2] + sum4[3]), dot = (dot4[0] + dot4[1]) + (dot4[2] + dot4[3]);
-        float expv, thr;
         if (FUSED) {
             const double mu = (double)sum / (double)g.K;
             double var = ((double)mx - mu) * (mu - (double)mn);
             var = var > 0 ? var : 0;
-            const double S1 = g.S ? g.S[0] : folded_s(s_red, 0), S2 = g.S ? g.S[1] : folded_s(s_red, 1),
-                         S3 = g.S ? g.S[2] : folded_s(s_red, 2), dN = (double)g.N;
+            const double dN = (double)g.N;
             const double t_det = dN * fabs(mu) * S1;
             const double t_var23 = g.c_sigma * sqrt(dN * mu * mu * S2 + dN * dN * var * S3);
             const double t_var4 = g.c_sigma * sqrt(dN * var * S2);  // = c sqrt(N) sigma_A sqrt(S2), one root
@@ -200,9 +209,6 @@ __device__ __forceinline__ void gemm_tile_row_check(const GemmArgs& g, unsigned 
                 reinterpret_cast<float*>(const_cast<void*>(g.expected))[gi] = expv;
                 reinterpret_cast<float*>(const_cast<void*>(g.T))[gi] = thr;
             }
-        } else {
-            expv = reinterpret_cast<const float*>(g.expected)[gi];
-            thr = reinterpret_cast<const float*>(g.T)[gi];
         }
         const float e = expv - rs;
         const int f = act && !(fabsf(e) <= thr);
@@ -217,8 +223,8 @@ __device__ __forceinline__ void gemm_tile_row_check(const GemmArgs& g, unsigned 
             // this tile-row is done: reset its ticket, then one 64-bit atomic both counts the
             // finished row blocks (high word) and accumulates the flagged rows (low word);
             // whoever completes the count publishes nflag and leaves the counter zero
-            __hip_atomic_store(&g.tickets[bm], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            unsigned long long* done = reinterpret_cast<unsigned long long*>(g.tickets + ((g.tiles_m + 1) & ~1));
+            __hip_atomic_store(&g.tickets[bm * g.ticket_stride], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            unsigned long long* done = done_counter(g);
             const unsigned long long old = atomicAdd(done, (1ull << 32) | (unsigned long long)(unsigned)cnt);
             if ((int)(old >> 32) == g.tiles_m - 1) {
                 *g.d_nflag = (int)(unsigned)(old & 0xffffffffull) + cnt;

@@ -76,6 +76,7 @@ struct GemmArgs {
     int32_t* flags;        // [M]
     int32_t* tickets;      // [tiles_m] arrival counters, then (8-byte aligned) one 64-bit word:
                            // finished row blocks << 32 | flagged rows; all zero between launches
+    int32_t ticket_stride; // int32 from one tile-row's arrival counter to the next
     // fused A-side statistics (Algorithm 1 for the rows of A, inside the GEMM)
     int32_t fused_stats;
     const void* Be;   // [K] acc
