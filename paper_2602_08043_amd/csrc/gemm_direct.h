@@ -272,6 +272,68 @@ template <typename T, int TRANSB, int MF, int NF, int WVK, int WN> struct Shape 
     static_assert(TPR <= 64 && BM % RPP == 0 && BM % NW == 0 && (OWN || PASSES == 1), "epilogue mapping");
 };
 
+// K shared by d.split workgroups: each leaves its tile (the sum of the wavefronts') in the workspace, and the last one to
+// arrive at the tile's counter adds them up in a fixed order, four sums side by side, puts the result back into LDS and goes
+// on with the tile; the others are done (false).
+template <typename S> __device__ bool join_split(const DirectArgs& d, int at, int z, typename S::acc_t* tile, int* s_last) {
+    using acc_t = typename S::acc_t;
+    constexpr int E = S::EPT * (int)sizeof(acc_t) >= 8 ? 8 / (int)sizeof(acc_t) : 1, Q = S::EPT / E;  // of a store; stores
+    using word_t = typename std::conditional<E * sizeof(acc_t) == 8, uint64_t, uint32_t>::type;
+    const int tid = threadIdx.x;
+    acc_t* const mine = tile + tid / S::TPR * S::PITCH + tid % S::TPR * S::EPT;
+    word_t* const first = reinterpret_cast<word_t*>(d.g.apart) + (int64_t)at * d.split * Q * S::NT + tid;
+    alignas(16) acc_t v[S::EPT];
+    copy_aligned<S::EPT>(v, mine);
+    if constexpr (S::SLOTS == 2) {
+        alignas(16) acc_t u[S::EPT];
+        copy_aligned<S::EPT>(u, mine + S::BM * S::PITCH);
+#pragma unroll
+        for (int e = 0; e < S::EPT; ++e) v[e] += u[e];
+    }
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        word_t w;
+        __builtin_memcpy(&w, v + q * E, sizeof(w));
+        __hip_atomic_store(first + (int64_t)(z * Q + q) * S::NT, w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __builtin_amdgcn_s_waitcnt(0);  // this wavefront's part is performed
+    __syncthreads();
+    int32_t* const ticket = d.g.tickets + (d.g.tiles_m + 1 + at) * d.g.ticket_stride;  // behind the tile-rows'
+    if (tid == 0) *s_last = atomicAdd(ticket, 1) == d.split - 1;
+    __syncthreads();
+    if (!*s_last) return false;
+    if (tid == 0) __hip_atomic_store(ticket, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    acc_t sum[4][S::EPT] = {};
+    for (int z0 = 0; z0 < d.split; z0 += 4) {
+        word_t w[4][Q];
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int q = 0; q < Q; ++q)
+                w[j][q] = z0 + j < d.split ? __hip_atomic_load(first + (int64_t)((z0 + j) * Q + q) * S::NT, __ATOMIC_RELAXED,
+                                                              __HIP_MEMORY_SCOPE_AGENT)
+                                           : (word_t)0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int q = 0; q < Q; ++q) {
+                acc_t x[E];
+                __builtin_memcpy(x, &w[j][q], sizeof(x));
+#pragma unroll
+                for (int e = 0; e < E; ++e) sum[j][q * E + e] += x[e];
+            }
+    }
+#pragma unroll
+    for (int e = 0; e < S::EPT; ++e) v[e] = (sum[0][e] + sum[1][e]) + (sum[2][e] + sum[3][e]);
+    copy_aligned<S::EPT>(mine, v);
+    if constexpr (S::SLOTS == 2) {
+        alignas(16) const acc_t zero[S::EPT] = {};
+        copy_aligned<S::EPT>(mine + S::BM * S::PITCH, zero);
+    }
+    __syncthreads();
+    return true;
+}
+
 // Workgroups of a launch, at most: a launch holds fewer than 2^32 threads in one dimension, and tiles of 32 rows of a tall
 // and narrow product may be more.  They go on in a second launch: a second dimension costs every workgroup of every launch
 // (BF16 1 x 4096 x 4096 7.0 us, 7.3; with the row's width out of the launch's record 7.6).
@@ -432,7 +494,8 @@ __device__ __forceinline__ void direct_stats(const DirectArgs& d, int block, dou
 
 // ANY: for rows so far apart that 32 bits do not hold a tile's byte offsets, and for rows of under 16 bytes.
 // D: steps in flight from global memory.
-template <typename T, int TRANSB, int MF, int NF, int WVK, int WN, int D, bool ANY>
+// SPLIT: d.split workgroups share the K of a tile (kernels of their own: the code in the others, skipped, cost short calls 3 %).
+template <typename T, int TRANSB, int MF, int NF, int WVK, int WN, int D, bool ANY, bool SPLIT>
 __global__ __launch_bounds__(64 * WVK * WN, 2) void gemm_direct_kernel(const DirectArgs d) {
     using S = gd::Shape<T, TRANSB, MF, NF, WVK, WN>;
     using OFF = typename std::conditional<ANY, uint64_t, uint32_t>::type;
@@ -460,21 +523,28 @@ __global__ __launch_bounds__(64 * WVK * WN, 2) void gemm_direct_kernel(const Dir
         }
         if (g.d_ncolflag) *g.d_ncolflag = 0;
     }
-    if (block < d.stat_blocks) {
-        direct_stats<T, S>(d, block, s_red, s_last, smem);
+    static_assert(!SPLIT || (!S::OWN && !ANY), "");
+    const int nth = block - d.stats_front;
+    if (__builtin_expect((unsigned)nth >= (unsigned)d.tile_blocks, 0)) {
+        direct_stats<T, S>(d, nth < 0 ? block : nth - d.tile_blocks, s_red, s_last, smem);
         return;
     }
     const int lane = tid & 63, l16 = lane & 15, lq = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wk = S::OWN ? 0 : wave, wn = S::OWN ? wave : 0;
+    // Workgroup z of the d.split that share the K of a tile, and the whole steps [s0, s0 + full) it takes of all of them
+    const int tiles = g.tiles_m * g.tiles_n, split = SPLIT ? d.split : 1, z = SPLIT ? nth / tiles : 0;
     int bm, bn;
-    tile_of_block(block - d.stat_blocks, g.tiles_m, g.tiles_n, bm, bn);
+    tile_of_block(nth - z * tiles, g.tiles_m, g.tiles_n, bm, bn);
+    const int steps = g.K / KSTEP, s0 = SPLIT ? (int)((int64_t)steps * z / split) : 0;
+    const int full = (SPLIT ? (int)((int64_t)steps * (z + 1) / split) : steps) - s0;
+    const int rest = z == split - 1 ? g.K - steps * KSTEP : 0;  // k behind the last whole step
     const int row0 = bm * S::BM, col0 = bn * S::BN + wn * S::BNW;
 
     // ---- global memory -> registers ---------------------------------------------------------------------------
     // Row loads: load t covers LDS rows 8 t .. 8 t + 7, eight lanes each; the lane at position lane % 8 of row r
     // fetches chunk (lane % 8) ^ ((r >> 1) & 7), so that the 16 rows of a fragment read hit 16 distinct slots.
     const int lrow = lane >> 3;
-    const char* const abase = reinterpret_cast<const char*>(g.A) + ((int64_t)row0 * g.lda + wk * KSTEP) * ES;
+    const char* const abase = reinterpret_cast<const char*>(g.A) + ((int64_t)row0 * g.lda + (s0 + wk) * KSTEP) * ES;
     OFF aoff[LA];
 #pragma unroll
     for (int t = 0; t < LA; ++t) {
@@ -484,7 +554,7 @@ __global__ __launch_bounds__(64 * WVK * WN, 2) void gemm_direct_kernel(const Dir
     const char* bbase;
     OFF boff[LB];
     if constexpr (TRANSB != 0) {
-        bbase = reinterpret_cast<const char*>(g.B) + ((int64_t)col0 * g.ldb + wk * KSTEP) * ES;
+        bbase = reinterpret_cast<const char*>(g.B) + ((int64_t)col0 * g.ldb + (s0 + wk) * KSTEP) * ES;
 #pragma unroll
         for (int t = 0; t < LB; ++t) {
             // LDS row ni * 16 + i holds column i * NF + ni of the tile
@@ -495,7 +565,7 @@ __global__ __launch_bounds__(64 * WVK * WN, 2) void gemm_direct_kernel(const Dir
         // LDS row k of RB bytes: the tile's columns of row k of the step, in groups of V; a group that would cross the
         // row's end starts at N - V instead (see column_of)
         const int c = max(0, min(col0 + lane * 16 % RB / ES, g.N - V));
-        bbase = reinterpret_cast<const char*>(g.B) + ((int64_t)(wk * KSTEP) * g.ldb) * ES;
+        bbase = reinterpret_cast<const char*>(g.B) + ((int64_t)((s0 + wk) * KSTEP) * g.ldb) * ES;
 #pragma unroll
         for (int t = 0; t < LB; ++t) boff[t] = (OFF)((t * 1024 + lane * 16) / RB) * (OFF)(g.ldb * ES) + (OFF)c * ES;
     }
@@ -615,16 +685,15 @@ __global__ __launch_bounds__(64 * WVK * WN, 2) void gemm_direct_kernel(const Dir
         __builtin_amdgcn_sched_barrier(0);
     };
     if (!S::OWN || col0 < g.N) {  // (of the last wavefronts of a tile-row some may have no columns)
-        const int full = tiny ? 0 : g.K / KSTEP;                        // whole steps
-        const int cnt = full > wk ? (full - wk + WVK - 1) / WVK : 0;  // ... of this wavefront
+        const int cnt = !tiny && full > wk ? (full - wk + WVK - 1) / WVK : 0;  // whole steps of this wavefront
         Stage sg[D];
-        if (full * KSTEP < g.K && full % WVK == wk && !tiny) {
+        if (rest > 0 && full % WVK == wk && !tiny) {
             // the step that K ends in comes first, with the first whole step in flight behind it
             Stage part;
-            load_part(full / WVK, g.K - full * KSTEP, part);
+            load_part(full / WVK, rest, part);
             if (cnt > 0) load_step(0, sg[0]);
             __builtin_amdgcn_sched_barrier(0);
-            finish_part(g.K - full * KSTEP, part);
+            finish_part(rest, part);
             compute(part, [] {});
         } else if (cnt > 0) {
             load_step(0, sg[0]);
@@ -715,6 +784,9 @@ __global__ __launch_bounds__(64 * WVK * WN, 2) void gemm_direct_kernel(const Dir
     const bool inject = g.inj.mode != 0;
     if (wk < S::SLOTS && (!S::OWN || inject)) to_tile();  // (OWN: row sums first, see the epilogue)
     if constexpr (!S::OWN) __syncthreads();
+    if constexpr (SPLIT) {
+        if (!gd::join_split<S>(d, bm * g.tiles_n + bn, z, tile, s_last)) return;
+    }
 
     // ---- fault injector (section 6.1 "Error injection"): the sum of the partial tiles, edited in place --------------
     if (inject) {
@@ -909,10 +981,12 @@ __global__ __launch_bounds__(64 * WVK * WN, 2) void gemm_direct_kernel(const Dir
     if (check) direct_tile_row_check<T, S>(d, bm, s_last, smem, store_c);
 }
 
-template <typename T, int TRANSB, int MF, int NF, int WVK, int D, bool ANY = false, int WN = 1>
+template <typename T, int TRANSB, int MF, int NF, int WVK, int D, bool ANY = false, int WN = 1, bool SPLIT = false>
 static int gemm_direct_launch_shape(const DirectArgs& d, hipStream_t st) {
     using S = gd::Shape<T, TRANSB, MF, NF, WVK, WN>;
-    auto kern = gemm_direct_kernel<T, TRANSB, MF, NF, WVK, WN, D, ANY>;
+    if constexpr (!SPLIT && WVK > 1 && !ANY)
+        if (d.split > 1) return gemm_direct_launch_shape<T, TRANSB, MF, NF, WVK, D, ANY, WN, true>(d, st);
+    auto kern = gemm_direct_kernel<T, TRANSB, MF, NF, WVK, WN, D, ANY, SPLIT>;
     if constexpr (S::LDS > 65536) {
         static bool attr_set = false;
         if (!attr_set) {
@@ -922,7 +996,7 @@ static int gemm_direct_launch_shape(const DirectArgs& d, hipStream_t st) {
             attr_set = true;
         }
     }
-    const int blocks = d.stat_blocks + d.g.tiles_m * d.g.tiles_n;
+    const int blocks = d.stat_blocks + d.tile_blocks;
     DirectArgs part = d;
     for (int64_t at = 0; at < blocks; at += gd::LAUNCH_MOST) {
         part.first_block = (int32_t)at;

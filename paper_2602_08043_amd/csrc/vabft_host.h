@@ -132,7 +132,8 @@ struct ColArgs {
 int gemm_dispatch(const vabft_problem* p, const void* dA, const void* dB, void* dC, void* d_expected, void* d_T,
                   int verify, const FusedArgs* fused, const vabft_inject* inj, void* d_rowsum, void* d_rowsum2,
                   void* d_E, int32_t* d_flags, int32_t* d_nflag, vabft_inject_rec* d_injlog, int32_t* d_ninj,
-                  void* ws, hipStream_t st, const ColArgs* cols = nullptr, const BlockArgs* blocks = nullptr);
+                  void* ws, size_t ws_bytes, hipStream_t st, const ColArgs* cols = nullptr,
+                  const BlockArgs* blocks = nullptr);
 void workspace_init_launch(void* ws, size_t bytes, hipStream_t st);
 
 // gemm_direct.h: workgroup tiles of 16 x 32 (K x N B: 16 x 64), 32 x 32 (32 x 64), 32 x 64 (ANY: rows of any length and
@@ -142,9 +143,13 @@ enum DirectShape { DIRECT_NONE = -1, DIRECT_16 = 0, DIRECT_32 = 1, DIRECT_32W = 
 struct DirectArgs {
     GemmArgs g;
     int32_t verify, wsum, csum;  // the check; with position-weighted row sums; with column sums
-    int32_t stat_blocks;         // > 0: that many workgroups in front run the A-side pass,
+    int32_t stat_blocks;         // > 0: that many workgroups run the A-side pass,
+    int32_t stats_front;         // in front of the tiles' (as many) or behind them (0),
     int32_t stat_rows;           // of so many rows each: one, two or four per wavefront
     int32_t first_block;         // of this launch (set by the launcher)
+    int32_t tile_blocks;         // workgroups of the tiles, tiles_m * tiles_n * split
+    int32_t split;               // workgroups that share the K of a tile (> 1: g.apart holds [tile][split] tiles of
+                                 // accumulator words, and an arrival counter per tile lies behind the tile-rows')
 };
 int gemm_direct_launch_bf16(const DirectArgs& d, int shape, int transB, hipStream_t st);
 int gemm_direct_launch_f16(const DirectArgs& d, int shape, int transB, hipStream_t st);

@@ -110,6 +110,30 @@ def test_direct_shapes(dtype, M, N, K, transB):
     _check(vg, A, B, _dev(A, dtype), _dev(B, dtype), dtype, M, N, K, transB, ALL)
 
 
+# few tiles and a long K: several workgroups share the K of a tile (every tile shape; K that ends inside a step, and at one)
+SPLIT = [
+    ("f32", 93, 345, 5527, 0), ("f32", 33, 65, 4096, 0), ("f32", 400, 520, 2500, 1), ("f32", 1, 153, 5193, 1),
+    ("bf16", 78, 192, 6871, 0), ("bf16", 161, 128, 5120, 0), ("bf16", 300, 450, 6145, 1), ("f16", 3, 70, 9001, 1),
+    ("f64", 48, 192, 1921, 1), ("f64", 100, 130, 1500, 0), ("f8", 100, 300, 8001, 0), ("f8e5m2", 9, 211, 6032, 0),
+    ("f8", 53, 192, 9000, 1),
+]
+
+
+@pytest.mark.parametrize("dtype,M,N,K,transB", SPLIT)
+def test_workgroups_that_share_the_k_of_a_tile(dtype, M, N, K, transB):
+    A, B = _gen(dtype, M, N, K, transB, 19)
+    vg = _session(M, N, K, dtype, transB)
+    dA, dB = _dev(A, dtype), _dev(B, dtype)
+    _check(vg, A, B, dA, dB, dtype, M, N, K, transB, ALL)
+    vg.gemm(dA, dB)
+    C = vg.C.clone()
+    vg.gemm(dA, dB, 0)  # plain product
+    assert torch.equal(vg.C, C)
+    # a workspace without room for the parts of tiles serves as well
+    vg.ws_bytes -= 5 << 20
+    _check(vg, A, B, dA, dB, dtype, M, N, K, transB, ("run_fused",))
+
+
 @pytest.mark.parametrize("dtype,M,N,K,transB", [("bf16", 70, 131, 200, 1), ("f16", 33, 100, 2065, 0), ("f32", 65, 67, 70, 0),
                                                 ("f64", 40, 70, 33, 1), ("f8", 50, 70, 131, 1), ("f8e5m2", 17, 90, 70, 0)])
 def test_direct_unaligned_base_and_pitch(dtype, M, N, K, transB):

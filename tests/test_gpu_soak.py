@@ -31,6 +31,7 @@ def _differs(a, b):
     ("bf16", 2304, 2304, 256, 1, 600),    # narrow tiles
     ("bf16", 2100, 2184, 256, 0, 600),    # tiled kernels at a ragged size
     ("bf16", 16000, 96, 128, 1, 600),     # 500 tile-rows that share counters, beside 1000 workgroups of the A-side pass
+    ("f32", 93, 345, 5527, 0, 800), ("bf16", 161, 128, 5120, 0, 800),          # several workgroups per tile
     ("f32", 9000, 500, 260, 0, 400),      # 282 tile-rows with a counter each, the same pass in front
 ])
 def test_back_to_back_fused_launches_repeat_bit_for_bit(dtype, M, N, K, transB, launches):
