@@ -14,7 +14,7 @@ LIB = os.path.join(PKG, "libvabft.so")
 
 DIRECT = [f"gemm_direct_{t}.hip" for t in ("bf16", "f16", "f8", "bf8", "f32", "f64")]
 SOURCES = DIRECT + ["gemm16_bf16_nn.hip", "gemm16_bf16_nt.hip", "gemm16_f16_nn.hip", "gemm16_f16_nt.hip",
-                    "gemm8_f8_nt.hip", "gemm8_bf8_nt.hip", "api.hip", "encode.hip", "blocks.hip", "probe.hip"]
+                    "gemm8_f8_nt.hip", "gemm8_bf8_nt.hip", "api.hip", "encode.hip", "blocks.hip", "pack.hip", "probe.hip"]
 
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",

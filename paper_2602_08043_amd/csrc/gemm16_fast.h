@@ -547,7 +547,7 @@ __device__ __forceinline__ void gemm16_fast_tile(const GemmArgs& g, int bm, int 
                 k = lh + 2 * l;
                 n = (l32 ^ 2 * ((2 * (l & 1) + lh) | (4 * (l >> 2)))) << 3;
             }
-            const int bc = EDGE ? min(n, g.N - 8 - col0) : n;
+            const int bc = EDGE ? min(n, g.b_cols - 8 - col0) : n;
             if (l < NF) b_voff[l] = (uint32_t)k * (uint32_t)g.ldb * 2 + bc * 2 - (l & 3) * 1024 + BIAS;
         }
     }
@@ -953,7 +953,7 @@ __device__ __forceinline__ void gemm16_fast_tile(const GemmArgs& g, int bm, int 
                 } else {
                     const int kl = (l * 64 + lane) / (4 * NF), n = ((l * 64 + lane) % (4 * NF) ^ kn_swz(kl)) << 3;
                     const int k = wave * 16 + kl;
-                    const unsigned char* pb = B + ((int64_t)(kt0 + k) * g.ldb + min(col0 + n, g.N - 8)) * 2;
+                    const unsigned char* pb = B + ((int64_t)(kt0 + k) * g.ldb + min(col0 + n, g.b_cols - 8)) * 2;
                     vb = k < klen ? ld16(pb) : z;
                 }
                 *reinterpret_cast<raw16*>(smem + B_BASE + wave * NF * 1024 + l * 1024 + lane * 16) = vb;

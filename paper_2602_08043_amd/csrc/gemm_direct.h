@@ -137,16 +137,6 @@ template <int ES> __device__ __forceinline__ u32x4_t shift_elems(u32x4_t v, int 
     return o;
 }
 
-template <typename T> __device__ __forceinline__ uint32_t widen2(uint32_t w, bool hi);
-template <> __device__ __forceinline__ uint32_t widen2<f8_t>(uint32_t w, bool hi) {
-    const f32x2_t v = hi ? __builtin_amdgcn_cvt_pk_f32_fp8((int)w, true) : __builtin_amdgcn_cvt_pk_f32_fp8((int)w, false);
-    return __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(v[0], v[1]));  // exact
-}
-template <> __device__ __forceinline__ uint32_t widen2<bf8_t>(uint32_t w, bool hi) {
-    const f32x2_t v = hi ? __builtin_amdgcn_cvt_pk_f32_bf8((int)w, true) : __builtin_amdgcn_cvt_pk_f32_bf8((int)w, false);
-    return __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(v[0], v[1]));  // exact
-}
-
 // chunk as loaded (CB bytes) -> MFMA fragment (16 bytes)
 template <typename T> __device__ __forceinline__ raw16 to_frag(const uint32_t* w) {
     if constexpr (Traits<T>::ES == 1)

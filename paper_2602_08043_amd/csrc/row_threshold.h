@@ -14,11 +14,15 @@ template <typename acc_t> struct RowSums {
 
 // W: also the dot product with Be2.  NL: 16-byte pieces of the row in flight per lane.  LW: lanes per row (lane is the
 // number among them), 64 or, for rows of that many pieces at most, fewer: the same bits, as what the other lanes would add
-// is zero.  The pieces need no alignment beyond the element's.
-template <typename T, bool W, int NL, int LW = WAVE>
+// is zero.  The pieces need no alignment beyond the element's.  sink(c, piece) is handed every whole piece.
+struct NoSink {
+    __device__ __forceinline__ void operator()(int, const raw16&) const {}
+};
+template <typename T, bool W, int NL, int LW = WAVE, typename SINK = NoSink>
 __device__ __forceinline__ RowSums<typename Elem<T>::acc_t> row_sums(const char* row, int K, int lane,
                                                                      const typename Elem<T>::acc_t* __restrict__ Be,
-                                                                     const typename Elem<T>::acc_t* __restrict__ Be2) {
+                                                                     const typename Elem<T>::acc_t* __restrict__ Be2,
+                                                                     SINK sink = SINK{}) {
     using acc_t = typename Elem<T>::acc_t;
     constexpr int V = Elem<T>::vec;
     acc_t sum = 0, dot = 0, dot2 = 0, mx = -type_max<acc_t>(), mn = type_max<acc_t>();
@@ -34,6 +38,7 @@ __device__ __forceinline__ RowSums<typename Elem<T>::acc_t> row_sums(const char*
             acc_t v[V], b[V];
 #pragma unroll
             for (int e = 0; e < V; ++e) b[e] = Be[(int64_t)(c + LW * u) * V + e];
+            sink(c + LW * u, r[u]);
             Unpack<T>::run(r[u], v);
 #pragma unroll
             for (int e = 0; e < V; ++e) {
@@ -48,6 +53,7 @@ __device__ __forceinline__ RowSums<typename Elem<T>::acc_t> row_sums(const char*
     for (; c < nchunks; c += LW) {
         raw16 r0 = ld16u<T>(row + (int64_t)c * 16);
         acc_t v0[V];
+        sink(c, r0);
         Unpack<T>::run(r0, v0);
 #pragma unroll
         for (int e = 0; e < V; ++e) {

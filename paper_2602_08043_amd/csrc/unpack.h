@@ -1,5 +1,7 @@
 // 16 raw bytes -> accumulator-typed values, for the streaming kernels.
 #pragma once
+#include <type_traits>
+
 #include "vabft_device.h"
 
 namespace vabft {
@@ -79,6 +81,17 @@ template <> struct Unpack<double> {
     }
 };
 
+
+// two FP8 values of w -> two FP16 values (exact)
+template <typename T> __device__ __forceinline__ uint32_t widen2(uint32_t w, bool hi) {
+    typedef __attribute__((ext_vector_type(2))) float pair_t;
+    pair_t v;
+    if constexpr (std::is_same<T, f8_t>::value)
+        v = hi ? __builtin_amdgcn_cvt_pk_f32_fp8((int)w, true) : __builtin_amdgcn_cvt_pk_f32_fp8((int)w, false);
+    else
+        v = hi ? __builtin_amdgcn_cvt_pk_f32_bf8((int)w, true) : __builtin_amdgcn_cvt_pk_f32_bf8((int)w, false);
+    return __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(v[0], v[1]));
+}
 
 // 16 bytes of a row of T elements, aligned to the element only (the hardware takes unaligned global loads)
 template <typename T> __device__ __forceinline__ raw16 ld16u(const void* p) {

@@ -63,6 +63,7 @@ struct GemmArgs {
     void* C;
     int32_t M, N, K;
     int64_t lda, ldb, ldc;
+    int32_t b_cols;   // elements that a row of B holds (16-bit tiled kernels, B stored K x N): N, in a copy more
     int32_t tiles_m, tiles_n;
     void* rowpart;    // [tiles_n][M] acc: per-tile-column partial row sums
     int32_t* d_nflag; // number of flagged rows
@@ -129,6 +130,18 @@ struct ColArgs {
     int32_t* d_colflags;         // [N]
     int32_t* d_ncolflag;         // [1]
 };
+// pack.hip: copies of operands in the tiled kernels' layout
+struct PackArgs {
+    const void* src;
+    void* dst;               // null: nothing to do
+    int32_t rows, len;       // of the matrix
+    int64_t ld;
+    int32_t rows_out, pitch; // of the copy: rows (zeros behind the matrix's), elements from row to row (a multiple of 64)
+    int32_t block_rows, blocks;  // set by pack_dispatch
+};
+// a, b: the copies of A and B.  fused: with the A-side pass (over all of A, which a copies).
+int pack_dispatch(int dtype, const PackArgs& a, const PackArgs& b, const FusedArgs* fused, const double* s_partial,
+                  int s_nparts, int N, void* d_expected, void* d_T, hipStream_t st);
 int gemm_dispatch(const vabft_problem* p, const void* dA, const void* dB, void* dC, void* d_expected, void* d_T,
                   int verify, const FusedArgs* fused, const vabft_inject* inj, void* d_rowsum, void* d_rowsum2,
                   void* d_E, int32_t* d_flags, int32_t* d_nflag, vabft_inject_rec* d_injlog, int32_t* d_ninj,

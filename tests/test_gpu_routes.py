@@ -442,6 +442,52 @@ def test_tiled_kernels_with_more_sums_at_ragged_sizes(dtype, M, N, K, transB):
     _check(vg, A, B, _dev(A, dtype), _dev(B, dtype), dtype, M, N, K, transB, ("run_weighted", "run_rc", "blocks"))
 
 
+# copies of operands in front of the tiled kernels: of both, of A (rows at odd addresses), of B (an odd number of columns);
+# K one above and below whole steps, rows that share a wavefront, FP8 of every layout
+COPIED = [("bf16", 2049, 2303, 1001, 1), ("f16", 2100, 2183, 1003, 0), ("bf16", 1801, 4097, 513, 0), ("f16", 4000, 3001, 127, 1),
+          ("bf16", 2304, 3073, 1024, 0), ("f16", 7479, 1729, 995, 1), ("f8", 2811, 2754, 2047, 1), ("f8e5m2", 2500, 3000, 1500, 0),
+          ("f8", 2304, 3072, 2048, 0)]
+
+
+@pytest.mark.parametrize("dtype,M,N,K,transB", COPIED)
+def test_copied_operands(dtype, M, N, K, transB):
+    A, B = _gen(dtype, M, N, K, transB, 27)
+    dA, dB = _dev(A, dtype), _dev(B, dtype)
+    vg = _session(M, N, K, dtype, transB)
+    # not zeros where the copies go: what lies behind their rows has to be written
+    vg.ws.view(torch.uint8)[vg.ws_bytes // 2:].fill_(0xff)
+    _check(vg, A, B, dA, dB, dtype, M, N, K, transB, ALL)
+    vg.gemm(dA, dB)
+    C = vg.C.clone()
+    vg.gemm(dA, dB, 0)  # plain product
+    assert torch.equal(vg.C, C)
+
+
+@pytest.mark.parametrize("dtype,M,N,K,transB", [("bf16", 2049, 2303, 1001, 1), ("f8", 2811, 2754, 2047, 1), ("f16", 3000, 2500, 511, 0)])
+def test_copied_rows_give_the_bits_of_the_separate_pass(dtype, M, N, K, transB):
+    """The A-side pass on the rows as they are copied against vabft_threshold, S1..S3 folded before and in the pass; what
+    the caller passes is not written, and infinities stay in their row and column."""
+    A, B = _gen(dtype, M, N, K, transB, 28)
+    dA, dB = _dev(A, dtype), _dev(B, dtype)
+    vg = _session(M, N, K, dtype, transB)
+    vg.encode(dB)
+    vg.threshold(dA)
+    want = [vg.astat.clone(), vg.expected.clone(), vg.T.clone()]
+    for defer in (False, True):
+        vg.astat.fill_(float("nan"))
+        vg.run_fused(dA, dB, defer_S=defer)
+        assert all(torch.equal(x, y) for x, y in zip(want, [vg.astat, vg.expected, vg.T]))
+    assert torch.equal(dA.view(torch.uint8), _dev(A, dtype).view(torch.uint8))
+    if dtype != "f8":
+        dA[M - 1, K - 1] = float("inf")
+        dB.abs_().add_(0.1)
+        dA[: M - 1].abs_()
+        vg.encode(dB)
+        vg.gemm_fused(dA, dB)
+        bad = ~torch.isfinite(vg.C)
+        assert bad[M - 1].all() and not bad[: M - 1].any() and int(vg.nflag.item()) == 1 and int(vg.flags[M - 1].item()) == 1
+
+
 @pytest.mark.parametrize("dtype,M,N,K,ldc,shift", [
     ("bf16", 2300, 2201, 64, 2201, 0), ("f16", 2049, 2303, 200, 2303, 0), ("bf16", 2100, 2056, 136, 2057, 0),
     ("f16", 2048, 2304, 128, 2304, 1), ("bf16", 3000, 2985, 136, 2985, 0), ("f16", 3900, 4089, 128, 4089, 3)])
