@@ -7,7 +7,12 @@ build when
     or a carry-out) wrote within the five preceding instructions,
   * a global_load_lds directly follows the s_mov that sets M0,
   * a v_mfma from inline assembly reads a vector register that a vector ALU instruction wrote within the four
-    preceding instructions.
+    preceding instructions,
+  * a vector instruction reads an accumulation register that a v_mfma from inline assembly wrote within the eight
+    preceding instructions, or a v_mfma from inline assembly accumulates onto one that a vector instruction wrote
+    within the four preceding ones, or
+  * a kernel that names the accumulation registers from a128 on itself (a[128]: the sums of the chains of a narrow
+    tile) has one of them in an instruction of the compiler's.
 """
 from __future__ import annotations
 
@@ -26,6 +31,17 @@ def _regs(tok: str, kind: str) -> set[int]:
             out.add(int(m.group(4)))
         else:
             out.update(range(int(m.group(2)), int(m.group(3)) + 1))
+    return out
+
+
+_ACC_REG = re.compile(r"\ba(?:\[(\d+):(\d+)\]|\[?(\d+)\]?)")
+_ACC = re.compile(r"\ba(?:\[(\d+):(\d+)\]|(\d+))(?!\w)")
+
+
+def _acc_regs(tok: str) -> set[int]:
+    out: set[int] = set()
+    for m in _ACC_REG.finditer(tok):
+        out.update(range(int(m.group(1)), int(m.group(2)) + 1) if m.group(1) else [int(m.group(3))])
     return out
 
 
@@ -68,6 +84,11 @@ def lint(asm_text: str, kernel_pattern: str = r"gemm16_fast_kernel") -> list[str
         if not re.search(kernel_pattern, name):
             continue
         ins = list(_instructions(m.group(0)))
+        if "a[128]" in m.group(0):
+            for i, (mn, ops, _) in enumerate(ins):
+                high = [o for o in ops for r in _ACC.finditer(o) for n in r.groups() if n and int(n) >= 128]
+                if high:
+                    problems.append(f"{name}: {mn} uses {high} of the registers that hold the chains (instruction {i})")
         for i, (mn, ops, in_asm) in enumerate(ins):
             if mn.startswith("global_load") and in_asm:
                 sregs = set()
@@ -83,6 +104,19 @@ def lint(asm_text: str, kernel_pattern: str = r"gemm16_fast_kernel") -> list[str
                         if written & sregs:
                             problems.append(f"{name}: global_load_lds reads s{sorted(written & sregs)} written by {pm} "
                                             f"{d} wait state(s) earlier (instruction {i})")
+            if not mn.startswith("v_mfma"):  # moves, stores of accumulators
+                read = set()
+                for tok in ops[1:] if mn.startswith("v_") or "load" in mn else ops:
+                    read |= _acc_regs(tok)
+                for d, (pm, pops) in _window(ins, i, 8) if read else ():
+                    if pm.startswith("v_mfma") and _acc_regs(pops[0]) & read:
+                        problems.append(f"{name}: {mn} reads a{sorted(_acc_regs(pops[0]) & read)} written by {pm} {d} wait "
+                                        f"state(s) earlier (instruction {i})")
+            if mn.startswith("v_mfma") and in_asm and ops:
+                for d, (pm, pops) in _window(ins, i, 4):
+                    if pm.startswith("v_accvgpr") and pops and _acc_regs(pops[0]) & _acc_regs(ops[0]):
+                        problems.append(f"{name}: v_mfma accumulates on {pops[0]} written by {pm} {d} wait state(s) earlier "
+                                        f"(instruction {i})")
             if mn.startswith("v_mfma") and in_asm and len(ops) >= 3:
                 vregs = _regs(ops[1], "v") | _regs(ops[2], "v")
                 for d, (pm, pops) in _window(ins, i, 4):

@@ -145,6 +145,31 @@ template <int IMM> __device__ __forceinline__ void g2l16_m0(uint32_t voff, const
     static_assert(IMM >= 0 && IMM < 4096, "13-bit signed immediate");
     asm volatile("global_load_lds_dwordx4 %0, %1 offset:%2" ::"v"(voff), "s"(sbase), "n"(IMM));
 }
+// Registers a128 .. a255 for the sums of the chains of a narrow tile (FORM16_128_CHAINS), named here and not by the compiler:
+// as variables beside the 128 accumulators they spilled into scratch memory in any arrangement tried, 60 us a launch.  The
+// compiler needs no accumulation register from a128 on (build.py fails if it uses one: asm_lint.py).
+template <int I> __device__ __forceinline__ void chain_clear() { asm volatile("v_accvgpr_write_b32 a[%0], 0" ::"n"(128 + I)); }
+template <int I> __device__ __forceinline__ void chain_add(float x) {
+    float t;
+    asm volatile("v_accvgpr_read_b32 %0, a[%2]\n\tv_add_f32 %0, %0, %1\n\tv_accvgpr_write_b32 a[%2], %0" : "=&v"(t) : "v"(x), "n"(128 + I));
+}
+template <int I> __device__ __forceinline__ float chain_sum() {
+    float t;
+    asm volatile("v_accvgpr_read_b32 %0, a[%1]" : "=v"(t) : "n"(128 + I));
+    return t;
+}
+__device__ __forceinline__ void chain_reserve() {
+    asm volatile("" ::: "a128", "a129", "a130", "a131", "a132", "a133", "a134", "a135", "a136", "a137", "a138", "a139", "a140", "a141",
+                 "a142", "a143", "a144", "a145", "a146", "a147", "a148", "a149", "a150", "a151", "a152", "a153", "a154", "a155",
+                 "a156", "a157", "a158", "a159", "a160", "a161", "a162", "a163", "a164", "a165", "a166", "a167", "a168", "a169",
+                 "a170", "a171", "a172", "a173", "a174", "a175", "a176", "a177", "a178", "a179", "a180", "a181", "a182", "a183",
+                 "a184", "a185", "a186", "a187", "a188", "a189", "a190", "a191", "a192", "a193", "a194", "a195", "a196", "a197",
+                 "a198", "a199", "a200", "a201", "a202", "a203", "a204", "a205", "a206", "a207", "a208", "a209", "a210", "a211",
+                 "a212", "a213", "a214", "a215", "a216", "a217", "a218", "a219", "a220", "a221", "a222", "a223", "a224", "a225",
+                 "a226", "a227", "a228", "a229", "a230", "a231", "a232", "a233", "a234", "a235", "a236", "a237", "a238", "a239",
+                 "a240", "a241", "a242", "a243", "a244", "a245", "a246", "a247", "a248", "a249", "a250", "a251", "a252", "a253",
+                 "a254", "a255");
+}
 }  // namespace g16x
 
 // ---- epilogue pieces for the 16 x 16 accumulator layout -------------------------------------------------------
@@ -473,10 +498,14 @@ template <int NF> __device__ __forceinline__ void settle_accumulators(f32x4_t (&
 // columns past the end are read from the last valid ones -- the lane offsets are clamped once, the main loop is the
 // same -- and dropped in the epilogue; the k past the last whole tile are multiplied by a step of their own behind the
 // loop, zero-filled on their way to LDS.
-template <typename T, int TRANSB, int MODE, bool FUSED, bool EDGE, int NF>
+// CHAINS: K in four chains behind each other, added up in registers that only the narrowest tile has (3 x 1.3 us a tile):
+// the rounding error of the direct kernels, where copies of their operands come here (row sums of BF16 2049 x 2303 x 1001
+// against 64 bits 1.3e-7, in one chain 2.0e-7; FP16 1001 x 5001 x 9001 3.8e-7, 7.3e-7).
+template <typename T, int TRANSB, int MODE, bool FUSED, bool EDGE, int NF, bool CHAINS>
 __device__ __forceinline__ void gemm16_fast_tile(const GemmArgs& g, int bm, int bn, int row0, int col0) {
     static_assert(!EDGE || MODE <= 1 || (NF == 8 && MODE >= 3 && MODE <= 5), "no injector and no K-blocks at other sizes");
     static_assert(NF == 8 || (EDGE && (NF == 6 || NF == 4)), "narrow tiles");
+    static_assert(!CHAINS || (NF == 4 && MODE <= 1 && !FUSED), "registers for the sum of the chains");
     using namespace g16x;
     // MODE 6 / 7: block-wise check with K split as well (7: with the injector).  The kernel leaves the row sums of
     // the accumulator tile at every K-block boundary and at the end, in double; a kernel of its own forms the
@@ -699,6 +728,10 @@ __device__ __forceinline__ void gemm16_fast_tile(const GemmArgs& g, int bm, int 
     using I1 = std::integral_constant<int, 1>;
     using IStep = std::integral_constant<int, NSLOT>;
 
+    if constexpr (CHAINS) {
+        chain_reserve();
+        static_for<0, 32 * NF>([&](auto i_c) { chain_clear<decltype(i_c)::value>(); });
+    }
     const int nk = g.K / BK;
     raw16 af0[8], bf0[NF], af1[8], bf1[NF];
     // first tile; narrow tiles: and the second one's A (and B) where there is a stage for it
@@ -914,17 +947,49 @@ __device__ __forceinline__ void gemm16_fast_tile(const GemmArgs& g, int bm, int 
         }
     } else {
         int kt = 0;
+        if constexpr (CHAINS) {
+            // the first three chains, of an even number of k-tiles; the last one goes on to the end
+            const int per = (nk + 7) / 8 * 2;
+            for (int stop = per; stop < nk; stop += per) {
+                do {
+                    chain_reserve();
+                    tile_body(I0{}, I0{}, kt, 0);
+                    tile_body(I1{}, I0{}, kt + 1, 0);
+                    kt += 2;
+                    // the last results land before the compiler may move an accumulator (24 of 2048 cycles)
+                    asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7" ::: "memory");
+                    __builtin_amdgcn_sched_barrier(0);
+                } while (kt < stop);
+                // (the fragments on their way land first, as in front of any vector code here)
+                wait_lgkmcnt0();
+                settle_accumulators(acc);
+                static_for<0, 32 * NF>([&](auto i_c) {
+                    constexpr int i = decltype(i_c)::value, mi = i / (4 * NF), ni = i / 4 % NF, r = i % 4;
+                    chain_add<i>(acc[mi][ni][r]);
+                    acc[mi][ni][r] = 0.f;
+                    if constexpr (r == 3) {
+                        asm volatile("" : "+a"(acc[mi][ni]));
+                        chain_reserve();
+                    }
+                });
+                asm volatile("s_nop 7\n\ts_nop 7" ::: "memory");  // vector code wrote the accumulators: see Mfma16x
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
         for (; kt + 1 < nk; kt += 2) {
+            if constexpr (CHAINS) chain_reserve();
             tile_body(I0{}, I0{}, kt, 0);
             tile_body(I1{}, I0{}, kt + 1, 0);
         }
         if (kt < nk) tile_body(I0{}, I0{}, kt, 0);
+        if constexpr (CHAINS) chain_reserve();
         if (!TRANSB) wait_lgkmcnt0();
 #pragma unroll
         for (int mi = 0; mi < 8; ++mi)
 #pragma unroll
             for (int ni = 0; ni < NF; ++ni) Mfma16x<T>::acc_a(acc[mi][ni], bf1[ni], af1[mi]);
     }
+    if constexpr (CHAINS) chain_reserve();
     if constexpr (EDGE) {
         const int kt0 = nk * BK, klen = g.K - kt0;  // the k past the last whole tile: a multiple of 8, below 64
         if (klen > 0) {
@@ -983,6 +1048,7 @@ __device__ __forceinline__ void gemm16_fast_tile(const GemmArgs& g, int bm, int 
 #pragma unroll
                     for (int ni = 0; ni < NF; ++ni) Mfma16x<T>::acc_a(acc[mi][ni], bf1[ni], af1[mi]);
                 asm volatile("s_nop 7\n\ts_nop 7" ::: "memory");
+                if constexpr (CHAINS) chain_reserve();
             });
             __syncthreads();  // the epilogue reuses the operand stages
         }
@@ -992,6 +1058,16 @@ __device__ __forceinline__ void gemm16_fast_tile(const GemmArgs& g, int bm, int 
         __syncthreads();
     }
     settle_accumulators(acc);
+    if constexpr (CHAINS) chain_reserve();
+    if constexpr (CHAINS)
+        static_for<0, 32 * NF>([&](auto i_c) {
+            constexpr int i = decltype(i_c)::value, mi = i / (4 * NF), ni = i / 4 % NF, r = i % 4;
+            acc[mi][ni][r] += chain_sum<i>();
+            if constexpr (r == 3) {
+                asm volatile("" : "+a"(acc[mi][ni]));
+                chain_reserve();
+            }
+        });
     if constexpr (EDGE && MODE >= 1) {
         // columns past the end count as zero in the row sums, rows past it in the column sums
         if (col0 + TN > g.N || (CSUM && row0 + BM > g.M)) {
@@ -1071,11 +1147,11 @@ __device__ __forceinline__ void gemm16_fast_tile(const GemmArgs& g, int bm, int 
     gemm16x_store_c<T, EDGE, NF>(g, acc, smem, row0, col0, lane, wm, wn, l16, lq);
 }
 
-template <typename T, int TRANSB, int MODE, bool FUSED, bool EDGE, int NF>
+template <typename T, int TRANSB, int MODE, bool FUSED, bool EDGE, int NF, bool CHAINS = false>
 __global__ __launch_bounds__(256) void gemm16_fast_kernel(const GemmArgs g) {
     int bm, bn;
     tile_of_block(blockIdx.x, g.tiles_m, g.tiles_n, bm, bn);
-    gemm16_fast_tile<T, TRANSB, MODE, FUSED, EDGE, NF>(g, bm, bn, bm * 256, bn * 32 * NF);
+    gemm16_fast_tile<T, TRANSB, MODE, FUSED, EDGE, NF, CHAINS>(g, bm, bn, bm * 256, bn * 32 * NF);
 }
 
 template <typename KERN> static int gemm16_start(KERN kern, const GemmArgs& a, size_t lds, bool& attr_set, hipStream_t st) {
@@ -1095,7 +1171,7 @@ static int gemm16_fast_launch_tb(const GemmArgs& a, int mode, int form, hipStrea
     const int fused = a.fused_stats ? 1 : 0;
     const auto bytes = [&](auto l) { return (size_t)(fused ? decltype(l)::BYTES_FUSED : decltype(l)::BYTES); };
     using g16x::Lds16;
-    const size_t lds = form == FORM16_128 ? bytes(Lds16<4>{}) : form == FORM16_192 ? bytes(Lds16<6>{}) : bytes(Lds16<8>{});
+    const size_t lds = form >= FORM16_128 ? bytes(Lds16<4>{}) : form == FORM16_192 ? bytes(Lds16<6>{}) : bytes(Lds16<8>{});
 #define VABFT_G16F_CASE(VF, FU, FORM, ...)                \
     if (mode == VF && fused == FU && form == FORM) {      \
         static bool attr_set = false;                     \
@@ -1111,6 +1187,8 @@ static int gemm16_fast_launch_tb(const GemmArgs& a, int mode, int form, hipStrea
     VABFT_G16F_CASE(VF, FU, FORM16_128, gemm16_fast_kernel<T, TRANSB, VF, FU != 0, true, 4>)
     VABFT_G16F_SIZES(0, 0)
     VABFT_G16F_SIZES(1, 0)
+    VABFT_G16F_CASE(0, 0, FORM16_128_CHAINS, gemm16_fast_kernel<T, TRANSB, 0, false, true, 4, true>)
+    VABFT_G16F_CASE(1, 0, FORM16_128_CHAINS, gemm16_fast_kernel<T, TRANSB, 1, false, true, 4, true>)
     VABFT_G16F_SIZES(1, 1)
     VABFT_G16F_WHOLE(2, 0)
     VABFT_G16F_EDGE(3, 0)

@@ -2,9 +2,10 @@
 // any size but whole tiles -- laid out once for the GEMM behind: 16-bit elements (FP8 as FP16: exact), rows of whole 128-byte
 // lines, zeros behind their end.  What is read is a wavefront's pieces of 16 bytes in a row wherever they start; what is
 // written is aligned.  Bound by memory, and at a few MB by the launch: 1021 x 2047 and 2047 x 1531 BF16 4.4 us.  The direct
-// kernels read each such piece as two lines, once per tile: 5001^3 BF16 700 us, with this pass and the tiled kernel 260.
+// kernels read each such piece as two lines, once per tile: BF16 3708 x 1873 x 10496 354 us, with this pass and the tiled
+// kernel 165.
 //
-// With the A-side pass fused the rows of A give their statistics, expected checksum and threshold on the way
+// With the A-side pass fused the rows of A, copied or not, give their statistics, expected checksum and threshold on the way
 // (row_threshold.h, the same bits as the pass by itself).
 #include "row_threshold.h"
 #include "vabft_host.h"
@@ -48,9 +49,12 @@ __device__ __forceinline__ void pack_row(const PackArgs& p, int row, const PackS
     const char* src = reinterpret_cast<const char*>(p.src) + (int64_t)(row < p.rows ? row : 0) * p.ld * Elem<T>::bytes;
     uint16_t* const dst = reinterpret_cast<uint16_t*>(p.dst) + (int64_t)row * p.pitch;
     raw16* const out = reinterpret_cast<raw16*>(dst);
+    const bool copy = p.dst != nullptr;
     if constexpr (STATS) {
         const RowSums<float> r = row_sums<T, false, NL, LW>(src, len, lane, q.Be, nullptr,
-                                                            [&](int c, const raw16& x) { store_piece<T>(out, c, x); });
+                                                            [&](int c, const raw16& x) {
+                                                                if (copy) store_piece<T>(out, c, x);
+                                                            });
         if (lane == 0) {
             double mu;
             const double t = row_threshold(r, len, q.N, S1, S2, S3, q.e_max, q.c_sigma, mu);
@@ -71,6 +75,7 @@ __device__ __forceinline__ void pack_row(const PackArgs& p, int row, const PackS
         }
         for (; c < nchunks; c += LW) store_piece<T>(out, c, ld16u<T>(src + (int64_t)c * 16));
     }
+    if (!copy) return;
     // the elements behind the last whole piece, zeros up to the next 16 bytes, and zeros to the end
     const int whole = nchunks * V, stop = (len + 7) / 8 * 8;
     for (int k = whole + lane; k < stop; k += LW) dst[k] = k < len ? element16<T>(src, k) : (uint16_t)0;
@@ -106,17 +111,17 @@ template <typename T> __global__ __launch_bounds__(256) void pack_kernel(const P
 }
 
 // (rows of up to 16 or 32 pieces share a wavefront)
-static PackArgs with_blocks(PackArgs p, int eb) {
+static PackArgs with_blocks(PackArgs p, int eb, bool read) {
     const int pieces = p.len * eb / 16;
     p.block_rows = pieces <= 16 ? 16 : pieces <= 32 ? 8 : 4;
-    p.blocks = p.dst ? (p.rows_out + p.block_rows - 1) / p.block_rows : 0;
+    p.blocks = p.dst || read ? (p.rows_out + p.block_rows - 1) / p.block_rows : 0;
     return p;
 }
 
 int pack_dispatch(int dtype, const PackArgs& a0, const PackArgs& b0, const FusedArgs* fused, const double* s_partial,
                   int s_nparts, int N, void* d_expected, void* d_T, hipStream_t st) {
     const int eb = dtype == VABFT_F8E4M3 || dtype == VABFT_F8E5M2 ? 1 : 2;
-    const PackArgs a = with_blocks(a0, eb), b = with_blocks(b0, eb);
+    const PackArgs a = with_blocks(a0, eb, fused != nullptr), b = with_blocks(b0, eb, false);
     PackStats q = {};
     if (fused) {
         q.Be = (const float*)fused->d_Be;

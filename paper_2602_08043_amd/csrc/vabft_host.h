@@ -139,7 +139,7 @@ struct PackArgs {
     int32_t rows_out, pitch; // of the copy: rows (zeros behind the matrix's), elements from row to row (a multiple of 64)
     int32_t block_rows, blocks;  // set by pack_dispatch
 };
-// a, b: the copies of A and B.  fused: with the A-side pass (over all of A, which a copies).
+// a, b: the copies of A and B.  fused: with the A-side pass (over all of A, whether a copies it or not).
 int pack_dispatch(int dtype, const PackArgs& a, const PackArgs& b, const FusedArgs* fused, const double* s_partial,
                   int s_nparts, int N, void* d_expected, void* d_T, hipStream_t st);
 int gemm_dispatch(const vabft_problem* p, const void* dA, const void* dB, void* dC, void* d_expected, void* d_T,
@@ -176,12 +176,12 @@ int gemm_direct_launch_f64(const DirectArgs& d, int shape, int transB, hipStream
 // sums, 4 check + column sums, 5 row-sum partials only (block-wise check), 6 prefix row sums per K-block, 7 the same with
 // the injector.
 // form (16-bit types): whole 256 x 256 tiles; the same for sizes that are no multiples of them (modes 0, 1 and 3 to 5);
-// tiles of 256 rows and 192 or 128 columns (any size, modes 0 and 1).
+// tiles of 256 rows and 192 or 128 columns (any size, modes 0 and 1), the last also with K in four chains (copied operands).
 // The kernels do the compare-and-flag step themselves and, with GemmArgs::fused_stats, the A-side statistics and
 // thresholds.
 // k-units of 128 that the fused 16-bit kernels fold per tile-column at most (256-wide tiles alone; with narrow ones)
 constexpr int PANEL_UNITS_WIDE = 16, PANEL_UNITS_NARROW = 15;
-enum Form16 { FORM16_WHOLE = 0, FORM16_EDGE = 1, FORM16_192 = 2, FORM16_128 = 3 };
+enum Form16 { FORM16_WHOLE = 0, FORM16_EDGE = 1, FORM16_192 = 2, FORM16_128 = 3, FORM16_128_CHAINS = 4 };
 int gemm16_launch_bf16_nn(const GemmArgs& a, int mode, int form, hipStream_t st);
 int gemm16_launch_bf16_nt(const GemmArgs& a, int mode, int form, hipStream_t st);
 int gemm16_launch_f16_nn(const GemmArgs& a, int mode, int form, hipStream_t st);
