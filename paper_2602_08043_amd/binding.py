@@ -1,6 +1,7 @@
-"""ctypes binding of libvabft.so: the same entry points as include/vabft.h.
+"""Binding of libvabft.so: the same entry points as include/vabft.h.
 
-Argument marshalling only.  Every step of the path runs in the HIP kernels of the
+Argument marshalling only, by the native module _calls (csrc/calls.cpp) for the entry points that a pass makes and by
+ctypes for the rest.  Pointer arguments may be tensors, integers or None.  Every step of the path runs in the HIP kernels of the
 library; there is no CPU or PyTorch fallback: if the library is missing, loading
 fails with an error that says how to build it.
 """
@@ -64,7 +65,14 @@ def load(path: str | None = None):
         raise ImportError(
             f"{p} not found: the HIP library has not been built. Run "
             "`python -c 'import __graft_entry__ as g; g.build()'` (needs hipcc); there is no fallback path.")
+    try:
+        from . import _calls
+    except ImportError as e:
+        raise ImportError(f"{_PKG}/_calls.so is missing or was built for another interpreter ({e}). Run "
+                          "`python -c 'import __graft_entry__ as g; g.build()'`.") from e
     lib = ctypes.CDLL(p)
+    for name in _calls.ENTRIES:
+        setattr(lib, "call_" + name[len("vabft_"):], _calls.bind(name, ctypes.cast(getattr(lib, name), c_void_p).value))
     lib.vabft_status_string.restype = c_char_p
     lib.vabft_status_string.argtypes = [ctypes.c_int]
     lib.vabft_workspace_bytes.restype = c_size_t
@@ -185,35 +193,35 @@ def _check(rc: int, where: str, check: bool):
 
 
 def vabft_encode(p: Problem, dB, d_Be, d_bstat, d_S, d_workspace, workspace_bytes, stream=None, check=True) -> int:
-    rc = load().vabft_encode(byref(p), dB, d_Be, d_bstat, d_S, d_workspace, workspace_bytes, stream)
+    rc = load().call_encode(p, dB, d_Be, d_bstat, d_S, d_workspace, workspace_bytes, stream)
     return _check(rc, "vabft_encode", check)
 
 
 def vabft_threshold(p: Problem, dA, d_Be, d_S, e_max, c_sigma, d_astat, d_expected, d_T, stream=None,
                     check=True) -> int:
-    rc = load().vabft_threshold(byref(p), dA, d_Be, d_S, float(e_max), float(c_sigma), d_astat, d_expected, d_T,
+    rc = load().call_threshold(p, dA, d_Be, d_S, e_max, c_sigma, d_astat, d_expected, d_T,
                                 stream)
     return _check(rc, "vabft_threshold", check)
 
 
 def vabft_gemm_verified(p: Problem, dA, dB, dC, d_expected, d_T, verify, inj, d_rowsum, d_E, d_flags, d_nflag,
                         d_injlog, d_ninj, d_workspace, workspace_bytes, stream=None, check=True) -> int:
-    rc = load().vabft_gemm_verified(byref(p), dA, dB, dC, d_expected, d_T, int(verify),
-                                    byref(inj) if inj is not None else None, d_rowsum, d_E, d_flags, d_nflag,
+    rc = load().call_gemm_verified(p, dA, dB, dC, d_expected, d_T, int(verify),
+                                    inj, d_rowsum, d_E, d_flags, d_nflag,
                                     d_injlog, d_ninj, d_workspace, workspace_bytes, stream)
     return _check(rc, "vabft_gemm_verified", check)
 
 
 def vabft_workspace_init(d_workspace, workspace_bytes, stream=None, check=True) -> int:
-    rc = load().vabft_workspace_init(d_workspace, workspace_bytes, stream)
+    rc = load().call_workspace_init(d_workspace, workspace_bytes, stream)
     return _check(rc, "vabft_workspace_init", check)
 
 
 def vabft_gemm_verified_fused(p: Problem, dA, dB, dC, d_Be, d_S, e_max, c_sigma, d_astat, d_expected, d_T, inj,
                               d_rowsum, d_E, d_flags, d_nflag, d_injlog, d_ninj, d_workspace, workspace_bytes,
                               stream=None, check=True) -> int:
-    rc = load().vabft_gemm_verified_fused(byref(p), dA, dB, dC, d_Be, d_S, float(e_max), float(c_sigma), d_astat,
-                                          d_expected, d_T, byref(inj) if inj is not None else None, d_rowsum, d_E,
+    rc = load().call_gemm_verified_fused(p, dA, dB, dC, d_Be, d_S, e_max, c_sigma, d_astat,
+                                          d_expected, d_T, inj, d_rowsum, d_E,
                                           d_flags, d_nflag, d_injlog, d_ninj, d_workspace, workspace_bytes, stream)
     return _check(rc, "vabft_gemm_verified_fused", check)
 
@@ -238,21 +246,21 @@ def vabft_static_scratch_bytes() -> int:
 def vabft_gemm_verified_fused_static(p: Problem, dA, dB, dC, d_Be, d_S, e_max, c_sigma, d_astat, d_expected, d_T,
                                      inj, d_rowsum, d_E, d_flags, d_nflag, d_injlog, d_ninj, stream=None,
                                      check=True) -> int:
-    rc = load().vabft_gemm_verified_fused_static(byref(p), dA, dB, dC, d_Be, d_S, float(e_max), float(c_sigma),
-                                                 d_astat, d_expected, d_T, byref(inj) if inj is not None else None,
+    rc = load().call_gemm_verified_fused_static(p, dA, dB, dC, d_Be, d_S, e_max, c_sigma,
+                                                 d_astat, d_expected, d_T, inj,
                                                  d_rowsum, d_E, d_flags, d_nflag, d_injlog, d_ninj, stream)
     return _check(rc, "vabft_gemm_verified_fused_static", check)
 
 
 def vabft_encode_weighted(p: Problem, dB, d_Be, d_Be2, d_bstat, d_S, d_workspace, workspace_bytes, stream=None,
                           check=True) -> int:
-    rc = load().vabft_encode_weighted(byref(p), dB, d_Be, d_Be2, d_bstat, d_S, d_workspace, workspace_bytes, stream)
+    rc = load().call_encode_weighted(p, dB, d_Be, d_Be2, d_bstat, d_S, d_workspace, workspace_bytes, stream)
     return _check(rc, "vabft_encode_weighted", check)
 
 
 def vabft_threshold_weighted(p: Problem, dA, d_Be, d_Be2, d_S, e_max, c_sigma, d_astat, d_expected, d_expected2, d_T,
                              stream=None, check=True) -> int:
-    rc = load().vabft_threshold_weighted(byref(p), dA, d_Be, d_Be2, d_S, float(e_max), float(c_sigma), d_astat,
+    rc = load().call_threshold_weighted(p, dA, d_Be, d_Be2, d_S, e_max, c_sigma, d_astat,
                                          d_expected, d_expected2, d_T, stream)
     return _check(rc, "vabft_threshold_weighted", check)
 
@@ -260,15 +268,15 @@ def vabft_threshold_weighted(p: Problem, dA, d_Be, d_Be2, d_S, e_max, c_sigma, d
 def vabft_gemm_verified_weighted(p: Problem, dA, dB, dC, d_expected, d_T, inj, d_rowsum, d_rowsum2, d_E, d_flags,
                                  d_nflag, d_injlog, d_ninj, d_workspace, workspace_bytes, stream=None,
                                  check=True) -> int:
-    rc = load().vabft_gemm_verified_weighted(byref(p), dA, dB, dC, d_expected, d_T,
-                                             byref(inj) if inj is not None else None, d_rowsum, d_rowsum2, d_E,
+    rc = load().call_gemm_verified_weighted(p, dA, dB, dC, d_expected, d_T,
+                                             inj, d_rowsum, d_rowsum2, d_E,
                                              d_flags, d_nflag, d_injlog, d_ninj, d_workspace, workspace_bytes, stream)
     return _check(rc, "vabft_gemm_verified_weighted", check)
 
 
 def vabft_locate_correct(p: Problem, dC, d_expected, d_expected2, d_rowsum, d_rowsum2, d_flags, correct, d_loc,
                          d_delta, d_ncorrected, stream=None, check=True) -> int:
-    rc = load().vabft_locate_correct(byref(p), dC, d_expected, d_expected2, d_rowsum, d_rowsum2, d_flags,
+    rc = load().call_locate_correct(p, dC, d_expected, d_expected2, d_rowsum, d_rowsum2, d_flags,
                                      int(correct), d_loc, d_delta, d_ncorrected, stream)
     return _check(rc, "vabft_locate_correct", check)
 
@@ -280,19 +288,19 @@ def vabft_default_emax_offline(dtype, K: int, N: int) -> float:
 
 def vabft_check_offline(p: Problem, dC, d_expected, d_T, d_rowsum, d_E, d_flags, d_nflag, stream=None,
                         check=True) -> int:
-    rc = load().vabft_check_offline(byref(p), dC, d_expected, d_T, d_rowsum, d_E, d_flags, d_nflag, stream)
+    rc = load().call_check_offline(p, dC, d_expected, d_T, d_rowsum, d_E, d_flags, d_nflag, stream)
     return _check(rc, "vabft_check_offline", check)
 
 
 def vabft_encode_a(p: Problem, dA, d_eA, d_acolstat, d_SA, d_workspace, workspace_bytes, stream=None,
                    check=True) -> int:
-    rc = load().vabft_encode_a(byref(p), dA, d_eA, d_acolstat, d_SA, d_workspace, workspace_bytes, stream)
+    rc = load().call_encode_a(p, dA, d_eA, d_acolstat, d_SA, d_workspace, workspace_bytes, stream)
     return _check(rc, "vabft_encode_a", check)
 
 
 def vabft_threshold_cols(p: Problem, dB, d_eA, d_SA, e_max, c_sigma, d_bcolstat, d_expected_col, d_Tcol, d_workspace,
                          workspace_bytes, stream=None, check=True) -> int:
-    rc = load().vabft_threshold_cols(byref(p), dB, d_eA, d_SA, float(e_max), float(c_sigma), d_bcolstat,
+    rc = load().call_threshold_cols(p, dB, d_eA, d_SA, e_max, c_sigma, d_bcolstat,
                                      d_expected_col, d_Tcol, d_workspace, workspace_bytes, stream)
     return _check(rc, "vabft_threshold_cols", check)
 
@@ -300,8 +308,8 @@ def vabft_threshold_cols(p: Problem, dB, d_eA, d_SA, e_max, c_sigma, d_bcolstat,
 def vabft_gemm_verified_rc(p: Problem, dA, dB, dC, d_expected, d_T, d_expected_col, d_Tcol, inj, d_rowsum, d_E,
                            d_flags, d_nflag, d_colsum, d_Ecol, d_colflags, d_ncolflag, d_injlog, d_ninj, d_workspace,
                            workspace_bytes, stream=None, check=True) -> int:
-    rc = load().vabft_gemm_verified_rc(byref(p), dA, dB, dC, d_expected, d_T, d_expected_col, d_Tcol,
-                                       byref(inj) if inj is not None else None, d_rowsum, d_E, d_flags, d_nflag,
+    rc = load().call_gemm_verified_rc(p, dA, dB, dC, d_expected, d_T, d_expected_col, d_Tcol,
+                                       inj, d_rowsum, d_E, d_flags, d_nflag,
                                        d_colsum, d_Ecol, d_colflags, d_ncolflag, d_injlog, d_ninj, d_workspace,
                                        workspace_bytes, stream)
     return _check(rc, "vabft_gemm_verified_rc", check)
@@ -314,13 +322,13 @@ def vabft_block_width(dtype) -> int:
 
 def vabft_encode_blocks(p: Problem, dB, d_Be_blk, d_S_blk, d_workspace, workspace_bytes, stream=None,
                         check=True) -> int:
-    rc = load().vabft_encode_blocks(byref(p), dB, d_Be_blk, d_S_blk, d_workspace, workspace_bytes, stream)
+    rc = load().call_encode_blocks(p, dB, d_Be_blk, d_S_blk, d_workspace, workspace_bytes, stream)
     return _check(rc, "vabft_encode_blocks", check)
 
 
 def vabft_threshold_blocks(p: Problem, dA, d_Be_blk, d_S_blk, e_max, c_sigma, d_astat, d_expected_blk, d_T_blk,
                            stream=None, check=True) -> int:
-    rc = load().vabft_threshold_blocks(byref(p), dA, d_Be_blk, d_S_blk, float(e_max), float(c_sigma), d_astat,
+    rc = load().call_threshold_blocks(p, dA, d_Be_blk, d_S_blk, e_max, c_sigma, d_astat,
                                        d_expected_blk, d_T_blk, stream)
     return _check(rc, "vabft_threshold_blocks", check)
 
@@ -335,23 +343,23 @@ def vabft_workspace_bytes_blocks_k(p: Problem, kblock: int) -> int:
 
 def vabft_encode_blocks_k(p: Problem, kblock, dB, d_Be_blk_k, d_S_blk_k, d_workspace, workspace_bytes, stream=None,
                           check=True) -> int:
-    rc = load().vabft_encode_blocks_k(byref(p), int(kblock), dB, d_Be_blk_k, d_S_blk_k, d_workspace, workspace_bytes,
+    rc = load().call_encode_blocks_k(p, int(kblock), dB, d_Be_blk_k, d_S_blk_k, d_workspace, workspace_bytes,
                                       stream)
     return _check(rc, "vabft_encode_blocks_k", check)
 
 
 def vabft_threshold_blocks_k(p: Problem, kblock, dA, d_Be_blk_k, d_S_blk_k, e_max, c_sigma, d_astat_k,
                              d_expected_blk_k, d_T_blk_k, stream=None, check=True) -> int:
-    rc = load().vabft_threshold_blocks_k(byref(p), int(kblock), dA, d_Be_blk_k, d_S_blk_k, float(e_max),
-                                         float(c_sigma), d_astat_k, d_expected_blk_k, d_T_blk_k, stream)
+    rc = load().call_threshold_blocks_k(p, int(kblock), dA, d_Be_blk_k, d_S_blk_k, e_max,
+                                         c_sigma, d_astat_k, d_expected_blk_k, d_T_blk_k, stream)
     return _check(rc, "vabft_threshold_blocks_k", check)
 
 
 def vabft_gemm_verified_blocks_k(p: Problem, kblock, dA, dB, dC, d_expected_blk_k, d_T_blk_k, inj, d_rowsum_blk_k,
                                  d_E_blk_k, d_blockflags_k, d_nblockflag, d_E, d_flags, d_nflag, d_injlog, d_ninj,
                                  d_workspace, workspace_bytes, stream=None, check=True) -> int:
-    rc = load().vabft_gemm_verified_blocks_k(byref(p), int(kblock), dA, dB, dC, d_expected_blk_k, d_T_blk_k,
-                                             byref(inj) if inj is not None else None, d_rowsum_blk_k, d_E_blk_k,
+    rc = load().call_gemm_verified_blocks_k(p, int(kblock), dA, dB, dC, d_expected_blk_k, d_T_blk_k,
+                                             inj, d_rowsum_blk_k, d_E_blk_k,
                                              d_blockflags_k, d_nblockflag, d_E, d_flags, d_nflag, d_injlog, d_ninj,
                                              d_workspace, workspace_bytes, stream)
     return _check(rc, "vabft_gemm_verified_blocks_k", check)
@@ -360,8 +368,8 @@ def vabft_gemm_verified_blocks_k(p: Problem, kblock, dA, dB, dC, d_expected_blk_
 def vabft_gemm_verified_blocks(p: Problem, dA, dB, dC, d_expected_blk, d_T_blk, inj, d_rowsum_blk, d_E_blk,
                                d_blockflags, d_nblockflag, d_E, d_flags, d_nflag, d_injlog, d_ninj, d_workspace,
                                workspace_bytes, stream=None, check=True) -> int:
-    rc = load().vabft_gemm_verified_blocks(byref(p), dA, dB, dC, d_expected_blk, d_T_blk,
-                                           byref(inj) if inj is not None else None, d_rowsum_blk, d_E_blk,
+    rc = load().call_gemm_verified_blocks(p, dA, dB, dC, d_expected_blk, d_T_blk,
+                                           inj, d_rowsum_blk, d_E_blk,
                                            d_blockflags, d_nblockflag, d_E, d_flags, d_nflag, d_injlog, d_ninj,
                                            d_workspace, workspace_bytes, stream)
     return _check(rc, "vabft_gemm_verified_blocks", check)

@@ -1,9 +1,10 @@
-"""Build libvabft.so (hand-written HIP for gfx950) in-tree with hipcc."""
+"""Build libvabft.so (hand-written HIP for gfx950) in-tree with hipcc, and _calls.so, which the binding calls it through."""
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
@@ -11,6 +12,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 OBJ = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libvabft.so")
+CALLS = os.path.join(PKG, "_calls.so")
 
 DIRECT = [f"gemm_direct_{t}.hip" for t in ("bf16", "f16", "f8", "bf8", "f32", "f64")]
 SOURCES = DIRECT + ["gemm16_bf16_nn.hip", "gemm16_bf16_nt.hip", "gemm16_f16_nn.hip", "gemm16_f16_nt.hip",
@@ -42,8 +44,16 @@ def _run(cmd):
 LINTED = ["gemm16_bf16_nn.hip", "gemm16_bf16_nt.hip", "gemm16_f16_nn.hip", "gemm16_f16_nt.hip"]
 
 
+def build_calls() -> str:
+    """The native marshalling module of the binding (host code only)."""
+    _run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-Wall", "-shared", "-fPIC", "-I", os.path.join(ROOT, "include"),
+          "-I", sysconfig.get_paths()["include"], os.path.join(CSRC, "calls.cpp"), "-o", CALLS])
+    return CALLS
+
+
 def build_library(verbose: bool = True, jobs: int = 8) -> str:
     os.makedirs(OBJ, exist_ok=True)
+    build_calls()
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     objs = [os.path.join(OBJ, s.replace(".hip", ".o")) for s in SOURCES]
 

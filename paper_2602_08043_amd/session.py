@@ -2,8 +2,6 @@
 stream handle, nothing else.  All arithmetic happens inside libvabft.so."""
 from __future__ import annotations
 
-import ctypes
-
 import numpy as np
 import torch
 
@@ -94,20 +92,21 @@ class VerifiedGemm:
 
     @staticmethod
     def _stream():
-        return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+        # torch.cuda.current_stream().cuda_stream without the Stream object
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
     def encode(self, B: torch.Tensor, defer_S: bool = False):
         """defer_S: leave S1..S3 as partials in the workspace for gemm_fused(..., deferred_S=True)."""
-        return vb.vabft_encode(self.problem, B.data_ptr(), self.Be.data_ptr(), self.bstat.data_ptr(),
-                               None if defer_S else self.S.data_ptr(), self.ws.data_ptr(), self.ws_bytes,
+        return vb.vabft_encode(self.problem, B, self.Be, self.bstat,
+                               None if defer_S else self.S, self.ws, self.ws_bytes,
                                self._stream())
 
     def threshold(self, A: torch.Tensor, e_max=None, c_sigma=2.5):
         if e_max is None:
             e_max = vb.vabft_default_emax(self.dtype, self.K, self.N)
         self.e_max = e_max
-        return vb.vabft_threshold(self.problem, A.data_ptr(), self.Be.data_ptr(), self.S.data_ptr(), e_max, c_sigma,
-                                  self.astat.data_ptr(), self.expected.data_ptr(), self.T.data_ptr(), self._stream())
+        return vb.vabft_threshold(self.problem, A, self.Be, self.S, e_max, c_sigma,
+                                  self.astat, self.expected, self.T, self._stream())
 
     def make_inject(self, mode=0, faults=None, seed=0, rate=0.0, bit_lo=0, bit_hi=0) -> vb.Inject:
         """mode 1: faults = [(row, col, bit), ...]; mode 2: Bernoulli(seed, rate, bit_lo..bit_hi)."""
@@ -124,11 +123,11 @@ class VerifiedGemm:
         return inj
 
     def gemm(self, A: torch.Tensor, B: torch.Tensor, verify=1, inj: vb.Inject | None = None):
-        return vb.vabft_gemm_verified(self.problem, A.data_ptr(), B.data_ptr(), self.C.data_ptr(),
-                                      self.expected.data_ptr(), self.T.data_ptr(), verify, inj,
-                                      self.rowsum.data_ptr(), self.E.data_ptr(), self.flags.data_ptr(),
-                                      self.nflag.data_ptr(), self.injlog.data_ptr(), self.ninj.data_ptr(),
-                                      self.ws.data_ptr(), self.ws_bytes, self._stream())
+        return vb.vabft_gemm_verified(self.problem, A, B, self.C,
+                                      self.expected, self.T, verify, inj,
+                                      self.rowsum, self.E, self.flags,
+                                      self.nflag, self.injlog, self.ninj,
+                                      self.ws, self.ws_bytes, self._stream())
 
     def gemm_fused(self, A: torch.Tensor, B: torch.Tensor, e_max=None, c_sigma=2.5, inj: vb.Inject | None = None,
                    deferred_S: bool = False):
@@ -136,13 +135,13 @@ class VerifiedGemm:
         if e_max is None:
             e_max = vb.vabft_default_emax(self.dtype, self.K, self.N)
         self.e_max = e_max
-        return vb.vabft_gemm_verified_fused(self.problem, A.data_ptr(), B.data_ptr(), self.C.data_ptr(),
-                                            self.Be.data_ptr(), None if deferred_S else self.S.data_ptr(), e_max,
-                                            c_sigma, self.astat.data_ptr(), self.expected.data_ptr(),
-                                            self.T.data_ptr(), inj,
-                                            self.rowsum.data_ptr(), self.E.data_ptr(), self.flags.data_ptr(),
-                                            self.nflag.data_ptr(), self.injlog.data_ptr(), self.ninj.data_ptr(),
-                                            self.ws.data_ptr(), self.ws_bytes, self._stream())
+        return vb.vabft_gemm_verified_fused(self.problem, A, B, self.C,
+                                            self.Be, None if deferred_S else self.S, e_max,
+                                            c_sigma, self.astat, self.expected,
+                                            self.T, inj,
+                                            self.rowsum, self.E, self.flags,
+                                            self.nflag, self.injlog, self.ninj,
+                                            self.ws, self.ws_bytes, self._stream())
 
     def run(self, A, B, e_max=None, c_sigma=2.5, inj=None):
         """One pass of the whole path: encode, threshold, verified GEMM (three calls)."""
@@ -158,32 +157,32 @@ class VerifiedGemm:
 
     # ---- weighted checksum, localisation, correction ---------------------------------
     def encode_weighted(self, B: torch.Tensor):
-        return vb.vabft_encode_weighted(self.problem, B.data_ptr(), self.Be.data_ptr(), self.Be2.data_ptr(),
-                                        self.bstat.data_ptr(), self.S.data_ptr(), self.ws.data_ptr(), self.ws_bytes,
+        return vb.vabft_encode_weighted(self.problem, B, self.Be, self.Be2,
+                                        self.bstat, self.S, self.ws, self.ws_bytes,
                                         self._stream())
 
     def threshold_weighted(self, A: torch.Tensor, e_max=None, c_sigma=2.5):
         if e_max is None:
             e_max = vb.vabft_default_emax(self.dtype, self.K, self.N)
         self.e_max = e_max
-        return vb.vabft_threshold_weighted(self.problem, A.data_ptr(), self.Be.data_ptr(), self.Be2.data_ptr(),
-                                           self.S.data_ptr(), e_max, c_sigma, self.astat.data_ptr(),
-                                           self.expected.data_ptr(), self.expected2.data_ptr(), self.T.data_ptr(),
+        return vb.vabft_threshold_weighted(self.problem, A, self.Be, self.Be2,
+                                           self.S, e_max, c_sigma, self.astat,
+                                           self.expected, self.expected2, self.T,
                                            self._stream())
 
     def gemm_weighted(self, A: torch.Tensor, B: torch.Tensor, inj: vb.Inject | None = None):
-        return vb.vabft_gemm_verified_weighted(self.problem, A.data_ptr(), B.data_ptr(), self.C.data_ptr(),
-                                               self.expected.data_ptr(), self.T.data_ptr(), inj,
-                                               self.rowsum.data_ptr(), self.rowsum2.data_ptr(), self.E.data_ptr(),
-                                               self.flags.data_ptr(), self.nflag.data_ptr(), self.injlog.data_ptr(),
-                                               self.ninj.data_ptr(), self.ws.data_ptr(), self.ws_bytes,
+        return vb.vabft_gemm_verified_weighted(self.problem, A, B, self.C,
+                                               self.expected, self.T, inj,
+                                               self.rowsum, self.rowsum2, self.E,
+                                               self.flags, self.nflag, self.injlog,
+                                               self.ninj, self.ws, self.ws_bytes,
                                                self._stream())
 
     def locate_correct(self, correct=1):
-        return vb.vabft_locate_correct(self.problem, self.C.data_ptr(), self.expected.data_ptr(),
-                                       self.expected2.data_ptr(), self.rowsum.data_ptr(), self.rowsum2.data_ptr(),
-                                       self.flags.data_ptr(), correct, self.loc.data_ptr(), self.delta.data_ptr(),
-                                       self.ncorrected.data_ptr(), self._stream())
+        return vb.vabft_locate_correct(self.problem, self.C, self.expected,
+                                       self.expected2, self.rowsum, self.rowsum2,
+                                       self.flags, correct, self.loc, self.delta,
+                                       self.ncorrected, self._stream())
 
     def run_weighted(self, A, B, e_max=None, c_sigma=2.5, inj=None, correct=1):
         """Detect, locate, correct: weighted encode, weighted threshold, weighted verified GEMM,
@@ -195,23 +194,23 @@ class VerifiedGemm:
 
     # ---- column checksums --------------------------------------------------------------
     def encode_a(self, A: torch.Tensor):
-        return vb.vabft_encode_a(self.problem, A.data_ptr(), self.eA.data_ptr(), self.acolstat.data_ptr(),
-                                 self.SA.data_ptr(), self.ws.data_ptr(), self.ws_bytes, self._stream())
+        return vb.vabft_encode_a(self.problem, A, self.eA, self.acolstat,
+                                 self.SA, self.ws, self.ws_bytes, self._stream())
 
     def threshold_cols(self, B: torch.Tensor, e_max=None, c_sigma=2.5):
         if e_max is None:
             e_max = vb.vabft_default_emax(self.dtype, self.K, max(self.N, self.M))
-        return vb.vabft_threshold_cols(self.problem, B.data_ptr(), self.eA.data_ptr(), self.SA.data_ptr(), e_max,
-                                       c_sigma, self.bcolstat.data_ptr(), self.expected_col.data_ptr(),
-                                       self.T_col.data_ptr(), self.ws.data_ptr(), self.ws_bytes, self._stream())
+        return vb.vabft_threshold_cols(self.problem, B, self.eA, self.SA, e_max,
+                                       c_sigma, self.bcolstat, self.expected_col,
+                                       self.T_col, self.ws, self.ws_bytes, self._stream())
 
     def gemm_rc(self, A: torch.Tensor, B: torch.Tensor, inj: vb.Inject | None = None):
-        return vb.vabft_gemm_verified_rc(self.problem, A.data_ptr(), B.data_ptr(), self.C.data_ptr(),
-                                         self.expected.data_ptr(), self.T.data_ptr(), self.expected_col.data_ptr(),
-                                         self.T_col.data_ptr(), inj, self.rowsum.data_ptr(), self.E.data_ptr(),
-                                         self.flags.data_ptr(), self.nflag.data_ptr(), self.colsum.data_ptr(),
-                                         self.E_col.data_ptr(), self.colflags.data_ptr(), self.ncolflag.data_ptr(),
-                                         self.injlog.data_ptr(), self.ninj.data_ptr(), self.ws.data_ptr(),
+        return vb.vabft_gemm_verified_rc(self.problem, A, B, self.C,
+                                         self.expected, self.T, self.expected_col,
+                                         self.T_col, inj, self.rowsum, self.E,
+                                         self.flags, self.nflag, self.colsum,
+                                         self.E_col, self.colflags, self.ncolflag,
+                                         self.injlog, self.ninj, self.ws,
                                          self.ws_bytes, self._stream())
 
     def run_rc(self, A, B, e_max=None, e_max_col=None, c_sigma=2.5, inj=None):
@@ -224,23 +223,23 @@ class VerifiedGemm:
 
     # ---- block-wise verification --------------------------------------------------------
     def encode_blocks(self, B: torch.Tensor):
-        return vb.vabft_encode_blocks(self.problem, B.data_ptr(), self.Be_blk.data_ptr(), self.S_blk.data_ptr(),
-                                      self.ws.data_ptr(), self.ws_bytes, self._stream())
+        return vb.vabft_encode_blocks(self.problem, B, self.Be_blk, self.S_blk,
+                                      self.ws, self.ws_bytes, self._stream())
 
     def threshold_blocks(self, A: torch.Tensor, e_max=None, c_sigma=2.5):
         if e_max is None:
             e_max = vb.vabft_default_emax(self.dtype, self.K, min(self.N, self.W))
-        return vb.vabft_threshold_blocks(self.problem, A.data_ptr(), self.Be_blk.data_ptr(), self.S_blk.data_ptr(),
-                                         e_max, c_sigma, self.astat.data_ptr(), self.expected_blk.data_ptr(),
-                                         self.T_blk.data_ptr(), self._stream())
+        return vb.vabft_threshold_blocks(self.problem, A, self.Be_blk, self.S_blk,
+                                         e_max, c_sigma, self.astat, self.expected_blk,
+                                         self.T_blk, self._stream())
 
     def gemm_blocks(self, A: torch.Tensor, B: torch.Tensor, inj: vb.Inject | None = None):
-        return vb.vabft_gemm_verified_blocks(self.problem, A.data_ptr(), B.data_ptr(), self.C.data_ptr(),
-                                             self.expected_blk.data_ptr(), self.T_blk.data_ptr(), inj,
-                                             self.rowsum_blk.data_ptr(), self.E_blk.data_ptr(),
-                                             self.blockflags.data_ptr(), self.nblockflag.data_ptr(),
-                                             self.E.data_ptr(), self.flags.data_ptr(), self.nflag.data_ptr(),
-                                             self.injlog.data_ptr(), self.ninj.data_ptr(), self.ws.data_ptr(),
+        return vb.vabft_gemm_verified_blocks(self.problem, A, B, self.C,
+                                             self.expected_blk, self.T_blk, inj,
+                                             self.rowsum_blk, self.E_blk,
+                                             self.blockflags, self.nblockflag,
+                                             self.E, self.flags, self.nflag,
+                                             self.injlog, self.ninj, self.ws,
                                              self.ws_bytes, self._stream())
 
     def run_blocks(self, A, B, e_max=None, c_sigma=2.5, inj=None):
@@ -252,9 +251,9 @@ class VerifiedGemm:
     def check_offline(self, C: torch.Tensor | None = None):
         """Row sums of a stored product (default: this session's C) against expected / T."""
         C = self.C if C is None else C
-        return vb.vabft_check_offline(self.problem, C.data_ptr(), self.expected.data_ptr(), self.T.data_ptr(),
-                                      self.rowsum.data_ptr(), self.E.data_ptr(), self.flags.data_ptr(),
-                                      self.nflag.data_ptr(), self._stream())
+        return vb.vabft_check_offline(self.problem, C, self.expected, self.T,
+                                      self.rowsum, self.E, self.flags,
+                                      self.nflag, self._stream())
 
     def run_offline(self, A, B, e_max=None, c_sigma=2.5, inj=None):
         """Plain (or fault-injected) GEMM, then the post-hoc check on the stored C with an e_max for
@@ -324,7 +323,7 @@ class KBlockedGemm:
         self.injlog = torch.zeros(max(1, self.log_capacity) * _REC_DTYPE.itemsize, dtype=torch.uint8, device=dev)
         self.ws_bytes = vb.vabft_workspace_bytes_blocks_k(self.problem, kblock)
         self.ws = torch.empty(self.ws_bytes, dtype=torch.uint8, device=dev)
-        vb.vabft_workspace_init(self.ws.data_ptr(), self.ws_bytes, self._stream())
+        vb.vabft_workspace_init(self.ws, self.ws_bytes, self._stream())
         self._list = None
 
     _stream = staticmethod(VerifiedGemm._stream)
@@ -332,23 +331,23 @@ class KBlockedGemm:
     inject_records = VerifiedGemm.inject_records
 
     def encode(self, B: torch.Tensor):
-        return vb.vabft_encode_blocks_k(self.problem, self.kblock, B.data_ptr(), self.Be_blk_k.data_ptr(),
-                                        self.S_blk_k.data_ptr(), self.ws.data_ptr(), self.ws_bytes, self._stream())
+        return vb.vabft_encode_blocks_k(self.problem, self.kblock, B, self.Be_blk_k,
+                                        self.S_blk_k, self.ws, self.ws_bytes, self._stream())
 
     def threshold(self, A: torch.Tensor, e_max=None, c_sigma=2.5):
         if e_max is None:
             e_max = vb.vabft_default_emax(self.dtype, min(self.K, self.kblock), min(self.N, self.W))
-        return vb.vabft_threshold_blocks_k(self.problem, self.kblock, A.data_ptr(), self.Be_blk_k.data_ptr(),
-                                           self.S_blk_k.data_ptr(), e_max, c_sigma, self.astat_k.data_ptr(),
-                                           self.expected_blk_k.data_ptr(), self.T_blk_k.data_ptr(), self._stream())
+        return vb.vabft_threshold_blocks_k(self.problem, self.kblock, A, self.Be_blk_k,
+                                           self.S_blk_k, e_max, c_sigma, self.astat_k,
+                                           self.expected_blk_k, self.T_blk_k, self._stream())
 
     def gemm(self, A: torch.Tensor, B: torch.Tensor, inj: vb.Inject | None = None):
-        return vb.vabft_gemm_verified_blocks_k(self.problem, self.kblock, A.data_ptr(), B.data_ptr(), self.C.data_ptr(),
-                                               self.expected_blk_k.data_ptr(), self.T_blk_k.data_ptr(), inj,
-                                               self.rowsum_blk_k.data_ptr(), self.E_blk_k.data_ptr(),
-                                               self.blockflags_k.data_ptr(), self.nblockflag.data_ptr(),
-                                               self.E.data_ptr(), self.flags.data_ptr(), self.nflag.data_ptr(),
-                                               self.injlog.data_ptr(), self.ninj.data_ptr(), self.ws.data_ptr(),
+        return vb.vabft_gemm_verified_blocks_k(self.problem, self.kblock, A, B, self.C,
+                                               self.expected_blk_k, self.T_blk_k, inj,
+                                               self.rowsum_blk_k, self.E_blk_k,
+                                               self.blockflags_k, self.nblockflag,
+                                               self.E, self.flags, self.nflag,
+                                               self.injlog, self.ninj, self.ws,
                                                self.ws_bytes, self._stream())
 
     def run(self, A, B, e_max=None, c_sigma=2.5, inj=None):

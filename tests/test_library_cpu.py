@@ -209,3 +209,23 @@ def test_asm_lint_flags_the_hazards_it_is_built_for():
     good = kernel("\tv_cndmask_b32_e32 v4, v20, v21, vcc\n\ts_nop 4\n" +
                   asm("v_mfma_f32_16x16x32_bf16 a[0:3], v[4:7], v[8:11], a[0:3]"))
     assert asm_lint.lint(bad) and not asm_lint.lint(good)
+
+
+def test_native_calls_take_every_kind_of_pointer(lib):
+    """Tensors, integers, None and ctypes pointers; what is none of them, a wrong count and a number that does not fit are
+    Python errors, and nothing is called."""
+    import ctypes
+    torch = pytest.importorskip("torch")
+    p = vb.make_problem(8, 8, 8, "f32")
+    t = torch.zeros(64)
+    call = lib.call_encode
+    for ptr in (t, t.data_ptr(), ctypes.c_void_p(t.data_ptr())):  # as far as the check of the workspace, which is missing
+        assert call(p, ptr, ptr, ptr, None, None, 0, None) == vb.VABFT_EWORKSPACE
+        assert call(p, ptr, ctypes.c_void_p(None), ptr, None, None, 0, None) == vb.VABFT_EINVAL
+    assert call(None, t, t, t, None, None, 0, None) == vb.VABFT_EINVAL
+    for bad, error in (((p, "x", t, t, None, None, 0, None), AttributeError), ((p, t), TypeError),
+                       ((p, t, t, t, None, None, -1, None), OverflowError), ((b"short", t, t, t, None, None, 0, None), TypeError)):
+        with pytest.raises(error):
+            call(*bad)
+    with pytest.raises(OverflowError):
+        lib.call_locate_correct(p, t, t, t, t, t, t, 1 << 40, t, t, t, None)
