@@ -505,7 +505,7 @@ __global__ __launch_bounds__(64 * WVK * WN, 2) void gemm_direct_kernel(const Dir
     const GemmArgs& g = d.g;
     const bool verify = d.verify != 0;
     const int tid = threadIdx.x;
-    const int block = d.first_block + blockIdx.x;
+    const int block = d.first_block + ((int)blockIdx.x ^ d.mirror);  // the A-side pass's, then the tiles'
     if (verify && block == 0 && tid == 0) {
         if (g.block_mode) {  // a compare kernel that follows counts into these
             *g.d_nflag = 0;
@@ -514,11 +514,11 @@ __global__ __launch_bounds__(64 * WVK * WN, 2) void gemm_direct_kernel(const Dir
         if (g.d_ncolflag) *g.d_ncolflag = 0;
     }
     static_assert(!SPLIT || (!S::OWN && !ANY), "");
-    const int nth = block - d.stats_front;
-    if (__builtin_expect((unsigned)nth >= (unsigned)d.tile_blocks, 0)) {
-        direct_stats<T, S>(d, nth < 0 ? block : nth - d.tile_blocks, s_red, s_last, smem);
+    if (block < d.stat_blocks) {
+        direct_stats<T, S>(d, block, s_red, s_last, smem);
         return;
     }
+    const int nth = block - d.stat_blocks;
     const int lane = tid & 63, l16 = lane & 15, lq = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wk = S::OWN ? 0 : wave, wn = S::OWN ? wave : 0;
     // Workgroup z of the d.split that share the K of a tile, and the whole steps [s0, s0 + full) it takes of all of them
@@ -989,8 +989,8 @@ static int gemm_direct_launch_shape(const DirectArgs& d, hipStream_t st) {
     const int blocks = d.stat_blocks + d.tile_blocks;
     DirectArgs part = d;
     for (int64_t at = 0; at < blocks; at += gd::LAUNCH_MOST) {
-        part.first_block = (int32_t)at;
-        kern<<<dim3(min(blocks - part.first_block, gd::LAUNCH_MOST)), dim3(S::NT), S::LDS, st>>>(part);
+        part.first_block = (int32_t)(d.mirror ? blocks - at : at);
+        kern<<<dim3((unsigned)std::min<int64_t>(blocks - at, gd::LAUNCH_MOST)), dim3(S::NT), S::LDS, st>>>(part);
     }
     return hipGetLastError() == hipSuccess ? VABFT_OK : VABFT_EDEVICE;
 }

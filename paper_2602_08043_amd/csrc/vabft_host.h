@@ -63,7 +63,6 @@ struct GemmArgs {
     void* C;
     int32_t M, N, K;
     int64_t lda, ldb, ldc;
-    int32_t b_cols;   // elements that a row of B holds (16-bit tiled kernels, B stored K x N): N, in a copy more
     int32_t tiles_m, tiles_n;
     void* rowpart;    // [tiles_n][M] acc: per-tile-column partial row sums
     int32_t* d_nflag; // number of flagged rows
@@ -100,6 +99,7 @@ struct GemmArgs {
     // the accumulator tile taken every kblock_tiles k-tiles, in double
     double* kprefix;        // [K-blocks][2 * tiles_n][M]: prefix row sums (one per wavefront column of a tile-column)
     int32_t kblock_tiles;   // k-tiles (of 64) per K-block; even
+    int32_t b_cols;  // elements that a row of B holds (16-bit tiled kernels, B stored K x N): N, in a copy more
 };
 
 size_t gemm_workspace_bytes(const vabft_problem* p);
@@ -157,8 +157,8 @@ struct DirectArgs {
     GemmArgs g;
     int32_t verify, wsum, csum;  // the check; with position-weighted row sums; with column sums
     int32_t stat_blocks;         // > 0: that many workgroups run the A-side pass,
-    int32_t stats_front;         // in front of the tiles' (as many) or behind them (0),
     int32_t stat_rows;           // of so many rows each: one, two or four per wavefront
+    int32_t mirror;              // 0: they are the launch's first workgroups; -1: its last, the order being reversed
     int32_t first_block;         // of this launch (set by the launcher)
     int32_t tile_blocks;         // workgroups of the tiles, tiles_m * tiles_n * split
     int32_t split;               // workgroups that share the K of a tile (> 1: g.apart holds [tile][split] tiles of
