@@ -3,6 +3,7 @@
 // and the A-side pass: row statistics, expected checksum A*(B r1) and the threshold T_m
 // (section 3.4 boxed formula).  Both are single streaming passes bound by HBM bandwidth.
 #include <algorithm>
+#include <type_traits>
 
 #include "row_threshold.h"
 #include "unpack.h"
@@ -18,37 +19,38 @@ namespace vabft {
 // relaxed atomics (the blocks sit on XCDs with private L2s); the ticket is left at zero.
 // s1..s3 need to be valid in thread 0 only.  Every thread of the block must call this.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ void publish_and_fold_S(double s1, double s2, double s3, double* __restrict__ partial,
-                                                   int32_t* __restrict__ ticket, double* __restrict__ S) {
+// (leaves, entry: which threads of the first wavefront leave an entry, and which; of count)
+__device__ __forceinline__ void publish_entry_and_fold_S(bool leaves, int entry, int count, double s1, double s2, double s3,
+                                                         double* __restrict__ partial, int32_t* __restrict__ ticket,
+                                                         double* __restrict__ S) {
     __shared__ int s_last;
     __shared__ double s_red[3][4];
-    const int t = threadIdx.x, nblocks = gridDim.x;
+    const int t = threadIdx.x;
+    double* const mine = partial + 3 * (int64_t)entry;
     if (S == nullptr) {
         // deferred fold: the partials stay where they are (plain stores: the consumer is a later kernel
         // on the stream, which folds them in this same order)
-        if (t == 0) {
-            double* mine = partial + 3 * (int64_t)blockIdx.x;
+        if (leaves) {
             mine[0] = s1;
             mine[1] = s2;
             mine[2] = s3;
         }
         return;
     }
-    if (t == 0) {
-        double* mine = partial + 3 * (int64_t)blockIdx.x;
+    if (leaves) {
         st_agent(mine, s1);
         st_agent(mine + 1, s2);
         st_agent(mine + 2, s3);
-        __builtin_amdgcn_s_waitcnt(0);  // the partials are performed before the ticket is taken
-        s_last = atomicAdd(ticket, 1) == nblocks - 1;
     }
+    if (t < 64) __builtin_amdgcn_s_waitcnt(0);  // the partials are performed before the ticket is taken
+    if (t == 0) s_last = atomicAdd(ticket, 1) == (int)gridDim.x - 1;
     __syncthreads();
     if (!s_last) return;
     if (t < 256) {
-        // thread t folds blocks t, t + 256, ... in increasing order; butterfly inside each of the
+        // thread t folds entries t, t + 256, ... in increasing order; butterfly inside each of the
         // four wavefronts; the four results in order
         double a1 = 0, a2 = 0, a3 = 0;
-        for (int b = t; b < nblocks; b += 256) {
+        for (int b = t; b < count; b += 256) {
             const double* q = partial + 3 * (int64_t)b;
             a1 += ld_agent(q);
             a2 += ld_agent(q + 1);
@@ -71,6 +73,10 @@ __device__ __forceinline__ void publish_and_fold_S(double s1, double s2, double 
         S[t] = v;
     }
     if (t == 0) __hip_atomic_store(ticket, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void publish_and_fold_S(double s1, double s2, double s3, double* __restrict__ partial,
+                                                   int32_t* __restrict__ ticket, double* __restrict__ S) {
+    publish_entry_and_fold_S(threadIdx.x == 0, blockIdx.x, gridDim.x, s1, s2, s3, partial, ticket, S);
 }
 
 // the three per-row terms of S1, S2, S3 from (row sum, max, min) of a row of N elements
@@ -420,6 +426,197 @@ __global__ __launch_bounds__(256) void encode_cols_combine_kernel(const acc_t* _
 }
 
 // ---------------------------------------------------------------------------
+// The same column reduction in one launch, for matrices of few enough rows: a workgroup of 16 wavefronts takes all rows of
+// LPR * V columns, LPR lanes to a row, and finishes them (panel_pays: where that is the faster form).  The two steps above
+// cost a second launch and the partials' way through memory; here the rows' loads are what it takes, 8 KiB in flight per
+// wavefront, and FP8's and 16-bit types' arithmetic.  Over the rows of a wavefront two values share a lane swap (one value to
+// a swap, BF16 96 x 64 7.4 us against 5.4, FP8 10.1 / 5.9).
+// The panels whose columns share a cache line run on one XCD, one after the other.
+// ---------------------------------------------------------------------------
+constexpr int PANEL_WAVES = 16;
+
+template <typename T, int LPR_> struct Panel {
+    static constexpr int V = Elem<T>::vec;
+    static constexpr int LPR = LPR_, COLS = LPR * V, GROUPS = 64 / LPR;  // (a multiple of 16 columns: of a term of S1..S3)
+    static constexpr int NL = V == 16 || V == 2 ? 4 : 8;                 // rows in flight per lane
+    static_assert(COLS % 16 == 0 && (LPR == 2 || LPR == 4 || LPR == 8), "");
+};
+
+// Lanes of the lower half (of even rows of 16): x of this lane combined with x of its partner OFF lanes on; the others: y.
+template <int OFF> __device__ __forceinline__ void swap_lanes(uint32_t& x, uint32_t& y) {
+    const auto r = OFF == 32 ? __builtin_amdgcn_permlane32_swap(x, y, false, false)
+                             : __builtin_amdgcn_permlane16_swap(x, y, false, false);
+    x = r[0];
+    y = r[1];
+}
+template <int OFF, typename F> __device__ __forceinline__ float pair_over_rows(float x, float y, F f) {
+    uint32_t a = __float_as_uint(x), b = __float_as_uint(y);
+    swap_lanes<OFF>(a, b);
+    return f(__uint_as_float(a), __uint_as_float(b));
+}
+template <int OFF, typename F> __device__ __forceinline__ double pair_over_rows(double x, double y, F f) {
+    uint32_t al = (uint32_t)__double2loint(x), bl = (uint32_t)__double2loint(y);
+    uint32_t ah = (uint32_t)__double2hiint(x), bh = (uint32_t)__double2hiint(y);
+    swap_lanes<OFF>(al, bl);
+    swap_lanes<OFF>(ah, bh);
+    return f(__hiloint2double((int)ah, (int)al), __hiloint2double((int)bh, (int)bl));
+}
+// Over the rows of a wavefront: v[e] of all lanes with the same lane % LPR, two values to a lane swap while there are two.
+// Leaves v[0 .. V / 4) (V = 2: v[0]): element first + i, with first of the lane (panel_first), in the first LPR lanes
+// of every 16.
+template <int V, int LPR, typename A, typename F> __device__ __forceinline__ void over_rows(A* v, F f) {
+#pragma unroll
+    for (int e = 0; e < V / 2; ++e) v[e] = pair_over_rows<32>(v[e], v[e + V / 2], f);
+    constexpr int H = V / 4;
+    if constexpr (H > 0) {
+#pragma unroll
+        for (int e = 0; e < H; ++e) v[e] = pair_over_rows<16>(v[e], v[e + H], f);
+    } else {
+        v[0] = pair_over_rows<16>(v[0], v[0], f);
+    }
+#pragma unroll
+    for (int e = 0; e < (H > 0 ? H : 1); ++e) {
+        A a, b;
+        lane_exchange<8, 64>(v[e], a, b);
+        v[e] = f(a, b);
+        if constexpr (LPR <= 4) {
+            lane_exchange<4, 64>(v[e], a, b);
+            v[e] = f(a, b);
+        }
+        if constexpr (LPR <= 2) {
+            lane_exchange<2, 64>(v[e], a, b);
+            v[e] = f(a, b);
+        }
+    }
+}
+template <int V> __device__ __forceinline__ int panel_first(int lane) {
+    return (lane >> 5) * (V / 2) + (V >= 4 ? (lane >> 4 & 1) * (V / 4) : 0);
+}
+
+// What becomes of a column's (sum, max, min, weighted sum).  Encode: B r1 and statistics, terms of S1..S3 (Be2: weighted).
+template <typename acc_t> struct PanelEncode {
+    acc_t* Be;
+    acc_t* Be2;
+    acc_t* bstat;
+    double* s_partial;
+    int32_t* ticket;
+    double* S;
+    static constexpr bool AGGREGATES = true;
+    __device__ const acc_t* weights() const { return nullptr; }
+    __device__ void column(int k, int rows, acc_t sum, acc_t mx, acc_t mn, acc_t sum2) const {
+        if (Be2) Be2[k] = sum2;
+        Be[k] = sum;
+        bstat[3 * (int64_t)k + 0] = mx;
+        bstat[3 * (int64_t)k + 1] = mn;
+        bstat[3 * (int64_t)k + 2] = (acc_t)((double)sum / (double)rows);
+    }
+};
+
+template <typename T, bool W, int LPR, typename Out>
+__global__ __launch_bounds__(64 * PANEL_WAVES) void panel_kernel(const void* __restrict__ Bt, int K, int N, int64_t ldb,
+                                                                 const Out out) {
+    using acc_t = typename Elem<T>::acc_t;
+    using P = Panel<T, LPR>;
+    constexpr int V = P::V, COLS = P::COLS, Q = W ? 4 : 3, STEP = PANEL_WAVES * P::GROUPS;
+    __shared__ acc_t red[PANEL_WAVES][Q][COLS];
+    __shared__ double terms[COLS][3];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, cl = lane % P::LPR;
+    // G panels to a line of 128 bytes: of every 8 G consecutive workgroups those G that run on one XCD take a line's
+    constexpr int G = 128 / (16 * P::LPR);
+    const int chunk = blockIdx.x / (8 * G), r = blockIdx.x % (8 * G);
+    const int panel = (chunk + 1) * 8 * G <= (int)gridDim.x ? chunk * 8 * G + r % 8 * G + r / 8 : (int)blockIdx.x;
+    // (a lane whose columns would cross the end of the row takes the last V instead, lanes behind it the same)
+    const int nominal = panel * COLS + cl * V, k0 = min(nominal, K - V);
+    acc_t sum[V], sum2[W ? V : 1], mx[V], mn[V];
+#pragma unroll
+    for (int e = 0; e < V; ++e) {
+        sum[e] = 0;
+        if constexpr (W) sum2[e] = 0;
+        mx[e] = -type_max<acc_t>();
+        mn[e] = type_max<acc_t>();
+    }
+    const acc_t* const wvec = out.weights();
+    const char* const base = reinterpret_cast<const char*>(Bt) + (int64_t)k0 * Elem<T>::bytes;
+    for (int n = wave * P::GROUPS + lane / P::LPR; n < N; n += STEP * P::NL) {
+        raw16 x[P::NL];
+        acc_t w[P::NL];
+#pragma unroll
+        for (int u = 0; u < P::NL; ++u) {  // (rows behind the last one: loaded again, not counted)
+            const int row = min(n + u * STEP, N - 1);
+            x[u] = ld16u<T>(base + (int64_t)row * ldb * Elem<T>::bytes);
+            if constexpr (W) w[u] = wvec ? wvec[row] : (acc_t)(row + 1);
+        }
+#pragma unroll
+        for (int u = 0; u < P::NL; ++u) {
+            if (n + u * STEP >= N) break;
+            acc_t v[V];
+            Unpack<T>::run(x[u], v);
+#pragma unroll
+            for (int e = 0; e < V; ++e) {
+                sum[e] += v[e];
+                if constexpr (W) sum2[e] = fma(w[u], v[e], sum2[e]);
+                mx[e] = fmax(mx[e], v[e]);
+                mn[e] = fmin(mn[e], v[e]);
+            }
+        }
+    }
+    const auto add = [](acc_t a, acc_t b) { return a + b; };
+    over_rows<V, P::LPR>(sum, add);
+    over_rows<V, P::LPR>(mx, [](acc_t a, acc_t b) { return fmax(a, b); });
+    over_rows<V, P::LPR>(mn, [](acc_t a, acc_t b) { return fmin(a, b); });
+    if constexpr (W) over_rows<V, P::LPR>(sum2, add);
+    if (lane % 16 < P::LPR) {
+        const int at = cl * V + panel_first<V>(lane);
+#pragma unroll
+        for (int e = 0; e < (V + 3) / 4; ++e) {
+            red[wave][0][at + e] = sum[e];
+            red[wave][1][at + e] = mx[e];
+            red[wave][2][at + e] = mn[e];
+            if constexpr (W) red[wave][3][at + e] = sum2[e];
+        }
+    }
+    __syncthreads();
+    if (tid < COLS) {  // (within the first wavefront) the wavefronts' in order
+        const int at = tid / V * V, first = panel * COLS + at, k = min(first, K - V) + tid % V;
+        acc_t v[4] = {red[0][0][tid], red[0][1][tid], red[0][2][tid], 0};
+        if constexpr (W) v[3] = red[0][3][tid];
+#pragma unroll
+        for (int q = 1; q < PANEL_WAVES; ++q) {
+            v[0] += red[q][0][tid];
+            v[1] = fmax(v[1], red[q][1][tid]);
+            v[2] = fmin(v[2], red[q][2][tid]);
+            if constexpr (W) v[3] += red[q][3][tid];
+        }
+        const bool own = k >= first && k < K;  // (not the columns that a lane moved back shares with the one before it)
+        if (own) out.column(k, N, v[0], v[1], v[2], v[3]);
+        if constexpr (Out::AGGREGATES) {
+            terms[tid][0] = terms[tid][1] = terms[tid][2] = 0;
+            // (the first wavefront's LDS operations complete in order: the column's own terms replace the zeros)
+            double t1, t2, t3;
+            row_terms(v[0], v[1], v[2], N, t1, t2, t3);
+            if (own) {
+                terms[k - panel * COLS][0] = t1;
+                terms[k - panel * COLS][1] = t2;
+                terms[k - panel * COLS][2] = t3;
+            }
+        }
+    }
+    if constexpr (Out::AGGREGATES) {
+        __syncthreads();
+        // S1..S3: 16 columns in order, as the combining step above leaves them
+        double s[3] = {0, 0, 0};
+        const int entry = panel * (COLS / 16) + tid;
+        const bool leaves = tid < COLS / 16 && entry * 16 < K;
+        if (leaves)
+#pragma unroll
+            for (int c = 0; c < 16; ++c)
+#pragma unroll
+                for (int q = 0; q < 3; ++q) s[q] += terms[tid * 16 + c][q];
+        publish_entry_and_fold_S(leaves, entry, (K + 15) / 16, s[0], s[1], s[2], out.s_partial, out.ticket, out.S);
+    }
+}
+
+// ---------------------------------------------------------------------------
 // A side: one wavefront per row m: (max, min, mean), dot with Be, threshold
 // ---------------------------------------------------------------------------
 // W: also the expected weighted checksum C^{r2} = A (B r2) (section 2.2).
@@ -567,6 +764,39 @@ size_t encode_workspace_bytes(const vabft_problem* p) {
     return bytes;
 }
 
+// Column reductions of rows x cols: in one launch (panel_kernel) or two.  A workgroup's time grows with the rows, the launch's
+// with both; workgroups behind the first 256, on few of the compute units, take a second one's time.  Two launches / one (us,
+// columns x rows): BF16 96 x 64 8.1 / 5.4, 1536 x 1024 9.2 / 6.9, 4096 x 4096 16.4 / 12.0, but 96 x 11008 11.2 / 14.7, 9342 x
+// 6400 38.6 / 48.4; FP8 4096 x 512 12.4 / 8.0, 4096 x 4096 15.2 / 14.1, 1536 x 4096 12.0 / 12.9; FP32 1536 x 1024 8.5 / 6.7,
+// 4096 x 4096 19.7 / 15.3, 96 x 4096 8.3 / 8.7, 8301 x 7262 56 / 78, 4890 x 2902 (306 panels) 20 / 23; FP64 96 x 1024
+// 8.1 / 6.7, 4126 x 1024 (258 panels) 15.2 / 17.8.  700 problems of up to 12000 x 11264 take 0.80 (BF16), 0.82, 0.85 and
+// 0.91 (FP64) of the time of two launches, ten of them longer (with the better of the two each 0.76, 0.80, 0.82, 0.89).
+template <typename T> static bool panel_pays(int64_t cols, int64_t rows) {
+    constexpr int V = Elem<T>::vec;
+    const int64_t most = V == 16 ? 2048 + cols * 3 / 5 : V == 8 ? 3072 + cols * 4 / 5 : V == 4 ? 2560 + cols * 4 / 5 : 1280 + cols * 3 / 4;
+    const int64_t panels = (cols - 1) / Panel<T, V == 2 ? 8 : 4>::COLS + 1, rounds = (panels + 255) / 256;
+    const bool tail = rounds > 1 && 5 * 256 * rounds > 7 * panels && rows > 512;
+    const bool large = rounds > 1 && (double)cols * (double)rows * Elem<T>::bytes > (V >= 8 ? 72e6 : 60e6);
+    return cols >= V && !tail && !large && rows <= most;
+}
+template <typename T, bool W, typename Out>
+static void panel_launch(const void* src, int cols, int rows, int64_t ld, const Out& out, hipStream_t st) {
+    const auto launch = [&](auto lpr) {
+        constexpr int LPR = decltype(lpr)::value;
+        const unsigned panels = (unsigned)((cols - 1) / Panel<T, LPR>::COLS + 1);
+        panel_kernel<T, W, LPR, Out><<<dim3(panels), dim3(64 * PANEL_WAVES), 0, st>>>(src, cols, rows, ld, out);
+    };
+    // 16-bit and FP8: half as wide for long columns, where the chip holds all panels at once (32 bytes of a row against 64:
+    // BF16 1536 x 4096 9.7 against 12.5, 4096 x 512 8.4 / 7.2, 8192 x 4096 20.6 / 16.2; FP8 4096 x 2048 10.8 / 13.0, x 64
+    // 8.0 / 7.0)
+    if constexpr (Elem<T>::vec >= 8) {
+        constexpr bool fp8 = Elem<T>::vec == 16;
+        if (cols <= 256 * Panel<T, 2>::COLS && rows >= (fp8 ? std::max(256, cols / 6) : std::max(384, cols / 2)))
+            return launch(std::integral_constant<int, 2>());
+    }
+    launch(std::integral_constant<int, Elem<T>::vec == 2 ? 8 : 4>());
+}
+
 template <typename T, bool W>
 static int encode_launch(const vabft_problem* p, const void* dB, void* d_Be, void* d_Be2, void* d_bstat, double* d_S,
                          double* s_partial, void* ws, int32_t* ticket, hipStream_t st) {
@@ -594,6 +824,9 @@ static int encode_launch(const vabft_problem* p, const void* dB, void* d_Be, voi
         }
 #undef VABFT_ENC_ROWS_SWITCH
 #undef VABFT_ENC_ROWS
+    } else if (panel_pays<T>(p->K, p->N)) {
+        const PanelEncode<acc_t> out = {(acc_t*)d_Be, (acc_t*)d_Be2, (acc_t*)d_bstat, s_partial, ticket, d_S};
+        panel_launch<T, W>(dB, p->K, p->N, p->ldb, out, st);
     } else {
         constexpr int V = Elem<T>::vec;
         const int rpb = col_rows_per_block(p->dtype, p->N, p->K);
@@ -681,6 +914,33 @@ int threshold_dispatch(const vabft_problem* p, const void* dA, const void* d_Be,
 
 // Per column n of a K x N row-major B: fold the row-slab partials (sum, max, min, dot with c1 A) in slab
 // order and evaluate the column threshold.
+// Column threshold and expected column checksum from (sum, max, min, dot with c1 A) of a column of B
+template <typename acc_t> struct PanelThreshold {
+    const acc_t* eA;
+    const double* SA;
+    int M;
+    double e_max, c_sigma;
+    acc_t* colstat;
+    acc_t* expected_col;
+    acc_t* Tcol;
+    static constexpr bool AGGREGATES = false;
+    __device__ const acc_t* weights() const { return eA; }
+    __device__ void column(int n, int K, acc_t sum, acc_t mx, acc_t mn, acc_t dot) const {
+        const double mu = (double)sum / (double)K;
+        double var = ((double)mx - mu) * (mu - (double)mn);
+        var = var > 0 ? var : 0;
+        const double S1 = SA[0], S2 = SA[1], S3 = SA[2], dM = (double)M;
+        const double t_det = dM * fabs(mu) * S1;
+        const double t_var23 = c_sigma * sqrt(dM * mu * mu * S2 + dM * dM * var * S3);
+        const double t_var4 = c_sigma * sqrt(dM) * sqrt(var) * sqrt(S2);
+        colstat[3 * (int64_t)n + 0] = mx;
+        colstat[3 * (int64_t)n + 1] = mn;
+        colstat[3 * (int64_t)n + 2] = (acc_t)mu;
+        expected_col[n] = dot;
+        Tcol[n] = (acc_t)(e_max * (t_det + t_var23 + t_var4));
+    }
+};
+
 template <typename acc_t>
 __global__ __launch_bounds__(256) void threshold_cols_finish_kernel(const acc_t* __restrict__ part, int nsplit,
                                                                     int N, int K, int M, const double* __restrict__ SA,
@@ -710,18 +970,8 @@ __global__ __launch_bounds__(256) void threshold_cols_finish_kernel(const acc_t*
                 dot += v[u][3];
             }
     }
-    const double mu = (double)sum / (double)K;
-    double var = ((double)mx - mu) * (mu - (double)mn);
-    var = var > 0 ? var : 0;
-    const double S1 = SA[0], S2 = SA[1], S3 = SA[2], dM = (double)M;
-    const double t_det = dM * fabs(mu) * S1;
-    const double t_var23 = c_sigma * sqrt(dM * mu * mu * S2 + dM * dM * var * S3);
-    const double t_var4 = c_sigma * sqrt(dM) * sqrt(var) * sqrt(S2);
-    colstat[3 * (int64_t)n + 0] = mx;
-    colstat[3 * (int64_t)n + 1] = mn;
-    colstat[3 * (int64_t)n + 2] = (acc_t)mu;
-    expected_col[n] = dot;
-    Tcol[n] = (acc_t)(e_max * (t_det + t_var23 + t_var4));
+    const PanelThreshold<acc_t> out = {nullptr, SA, M, e_max, c_sigma, colstat, expected_col, Tcol};
+    out.column(n, K, sum, mx, mn, dot);
 }
 
 static vabft_problem swapped_problem(const vabft_problem* p, int32_t M, int32_t N, int32_t transB, int64_t lda,
@@ -760,6 +1010,12 @@ static int threshold_cols_launch(const vabft_problem* p, const void* dB, const v
                                  void* ws, hipStream_t st) {
     using acc_t = typename Elem<T>::acc_t;
     constexpr int V = Elem<T>::vec;
+    if (panel_pays<T>(p->N, p->K)) {
+        const PanelThreshold<acc_t> out = {(const acc_t*)d_eA, d_SA, p->M, e_max, c_sigma, (acc_t*)d_bcolstat,
+                                           (acc_t*)d_expected_col, (acc_t*)d_Tcol};
+        panel_launch<T, true>(dB, p->N, p->K, p->ldb, out, st);
+        return hipGetLastError() == hipSuccess ? VABFT_OK : VABFT_EDEVICE;
+    }
     const int rpb = col_rows_per_block(p->dtype, p->K, p->N);
     const int nsplit = (p->K + rpb - 1) / rpb;
     acc_t* part = reinterpret_cast<acc_t*>(ws);

@@ -222,3 +222,56 @@ def test_encode_of_B_serves_any_row_count(dtype, Ms, Ml, N, K, transB):
     # ... and an encode of the columns of A takes that place: documented to invalidate the deferred fold
     o = orc.verify(A, B, dtype, transB, e_max=_emax(dtype, K, N))
     assert np.all(np.abs(r["T"] - o["T"]) <= 1e-5 * o["T"] + 1e-300)
+
+
+# columns and rows of the reduction: one column group, remainders of it (lanes moved back, whole lanes without a column), several
+# groups to a cache line, panels half as wide, first and last size of either form
+COLUMN_PASSES = [("bf16", 8, 1), ("bf16", 9, 3), ("f16", 31, 257), ("bf16", 33, 383), ("f16", 40, 384), ("bf16", 1000, 600),
+                 ("f16", 2055, 1100), ("bf16", 300, 3312), ("bf16", 300, 3313), ("bf16", 7, 40), ("f32", 4, 1), ("f32", 17, 255),
+                 ("f32", 515, 1025), ("f32", 100, 2640), ("f32", 100, 2641), ("f64", 2, 2), ("f64", 15, 130), ("f64", 259, 513),
+                 ("f64", 70, 1332), ("f64", 70, 1333), ("f64", 4113, 600), ("f8", 16, 5), ("f8", 65, 255), ("f8", 77, 256),
+                 ("f8e5m2", 1300, 300), ("f8", 1001, 2047), ("f8e5m2", 500, 2348), ("f8", 500, 2349), ("f32", 4113, 700)]
+
+
+@pytest.mark.parametrize("dtype,cols,rows", COLUMN_PASSES)
+def test_column_passes_are_exact_on_small_integers(dtype, cols, rows):
+    """The passes over the columns of a row-major matrix (encode of an N x K B, plain and weighted, of A, and the column
+    thresholds), in one launch or two: sums of integers of at most 2 are exact in every order, weighted ones below 2^24."""
+    g = wl.rng(cols * 31 + rows, 41)
+    X = g.integers(-2, 3, size=(rows, cols)).astype(np.float64)
+    dX = _dev(wl.to_storage(X, dtype), dtype)
+    print(f"column passes {dtype} {cols} columns {rows} rows", flush=True)
+    acc = np.float64 if dtype == "f64" else np.float32
+    mean = X.sum(0) / rows
+    var = np.maximum((X.max(0) - mean) * (mean - X.min(0)), 0)
+    S = np.array([np.abs(mean).sum(), var.sum(), (mean * mean).sum()])
+
+    def stats(t):
+        t = t.cpu().numpy()
+        assert np.array_equal(t[:, 0], X.max(0)) and np.array_equal(t[:, 1], X.min(0))
+        assert np.array_equal(t[:, 2], mean.astype(acc))
+
+    vg = _session(3, rows, cols, dtype, 1)
+    for rep in range(2):  # (a second call finds the arrival counter at zero)
+        for weighted in (False, True):
+            vg.Be.fill_(float("nan"))
+            vg.bstat.fill_(float("nan"))
+            vg.S.fill_(float("nan"))
+            vg.encode_weighted(dX) if weighted else vg.encode(dX)
+            assert np.array_equal(vg.Be.cpu().numpy(), X.sum(0))
+            stats(vg.bstat)
+            # (up to `cols` additions of doubles each way)
+            assert np.all(np.abs(vg.S.cpu().numpy() - S) <= cols * 2.0 ** -52 * S)
+            if weighted:
+                assert np.array_equal(vg.Be2.cpu().numpy(), np.arange(1, rows + 1) @ X)
+    # as B (K x N): thresholds of its columns, behind the column pass over an A of three rows
+    vg = _session(3, cols, rows, dtype, 0)
+    A = g.integers(-2, 3, size=(3, rows)).astype(np.float64)
+    vg.encode_a(_dev(wl.to_storage(A, dtype), dtype))
+    vg.threshold_cols(dX, e_max=2.0 ** -10)
+    assert np.array_equal(vg.eA.cpu().numpy(), A.sum(0))
+    stats(vg.bcolstat)
+    assert np.array_equal(vg.expected_col.cpu().numpy(), A.sum(0) @ X)
+    S1, S2, S3 = vg.SA.cpu().numpy()
+    T = 3 * np.abs(mean) * S1 + 2.5 * np.sqrt(3 * mean * mean * S2 + 9 * var * S3) + 2.5 * np.sqrt(3 * var * S2)
+    assert np.all(np.abs(vg.T_col.cpu().numpy() * 2.0 ** 10 - T) <= 1e-6 * T)
