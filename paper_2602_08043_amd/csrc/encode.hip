@@ -439,7 +439,7 @@ template <typename T, int LPR_> struct Panel {
     static constexpr int V = Elem<T>::vec;
     static constexpr int LPR = LPR_, COLS = LPR * V, GROUPS = 64 / LPR;  // (a multiple of 16 columns: of a term of S1..S3)
     static constexpr int NL = V == 16 || V == 2 ? 4 : 8;                 // rows in flight per lane
-    static_assert(COLS % 16 == 0 && (LPR == 2 || LPR == 4 || LPR == 8), "");
+    static_assert(COLS % 16 == 0 && (LPR == 1 || LPR == 2 || LPR == 4 || LPR == 8), "");
 };
 
 // Lanes of the lower half (of even rows of 16): x of this lane combined with x of its partner OFF lanes on; the others: y.
@@ -485,6 +485,10 @@ template <int V, int LPR, typename A, typename F> __device__ __forceinline__ voi
         }
         if constexpr (LPR <= 2) {
             lane_exchange<2, 64>(v[e], a, b);
+            v[e] = f(a, b);
+        }
+        if constexpr (LPR == 1) {
+            lane_exchange<1, 64>(v[e], a, b);
             v[e] = f(a, b);
         }
     }
@@ -535,9 +539,12 @@ __global__ __launch_bounds__(64 * PANEL_WAVES) void panel_kernel(const void* __r
         mx[e] = -type_max<acc_t>();
         mn[e] = type_max<acc_t>();
     }
+    // (a panel's columns from its first on: a lane moved back leaves them at other threads' places)
+    if (Out::AGGREGATES && tid < COLS) terms[tid][0] = terms[tid][1] = terms[tid][2] = 0;
     const acc_t* const wvec = out.weights();
     const char* const base = reinterpret_cast<const char*>(Bt) + (int64_t)k0 * Elem<T>::bytes;
-    for (int n = wave * P::GROUPS + lane / P::LPR; n < N; n += STEP * P::NL) {
+    const int rows = panel * COLS < K ? N : 0;  // (a launch of whole chunks ends with workgroups that have no columns)
+    for (int n = wave * P::GROUPS + lane / P::LPR; n < rows; n += STEP * P::NL) {
         raw16 x[P::NL];
         acc_t w[P::NL];
 #pragma unroll
@@ -590,8 +597,6 @@ __global__ __launch_bounds__(64 * PANEL_WAVES) void panel_kernel(const void* __r
         const bool own = k >= first && k < K;  // (not the columns that a lane moved back shares with the one before it)
         if (own) out.column(k, N, v[0], v[1], v[2], v[3]);
         if constexpr (Out::AGGREGATES) {
-            terms[tid][0] = terms[tid][1] = terms[tid][2] = 0;
-            // (the first wavefront's LDS operations complete in order: the column's own terms replace the zeros)
             double t1, t2, t3;
             row_terms(v[0], v[1], v[2], N, t1, t2, t3);
             if (own) {
@@ -766,16 +771,19 @@ size_t encode_workspace_bytes(const vabft_problem* p) {
 
 // Column reductions of rows x cols: in one launch (panel_kernel) or two.  A workgroup's time grows with the rows, the launch's
 // with both; workgroups behind the first 256, on few of the compute units, take a second one's time.  Two launches / one (us,
-// columns x rows): BF16 96 x 64 8.1 / 5.4, 1536 x 1024 9.2 / 6.9, 4096 x 4096 16.4 / 12.0, but 96 x 11008 11.2 / 14.7, 9342 x
-// 6400 38.6 / 48.4; FP8 4096 x 512 12.4 / 8.0, 4096 x 4096 15.2 / 14.1, 1536 x 4096 12.0 / 12.9; FP32 1536 x 1024 8.5 / 6.7,
-// 4096 x 4096 19.7 / 15.3, 96 x 4096 8.3 / 8.7, 8301 x 7262 56 / 78, 4890 x 2902 (306 panels) 20 / 23; FP64 96 x 1024
-// 8.1 / 6.7, 4126 x 1024 (258 panels) 15.2 / 17.8.  700 problems of up to 12000 x 11264 take 0.80 (BF16), 0.82, 0.85 and
-// 0.91 (FP64) of the time of two launches, ten of them longer (with the better of the two each 0.76, 0.80, 0.82, 0.89).
+// columns x rows): BF16 96 x 64 8.1 / 5.4, 1536 x 1024 9.2 / 6.9, 4096 x 4096 16.4 / 12.1, but 96 x 11008 11.2 / 14.7, 5000 x
+// 5000 16.0 / 17.0 (fold deferred), 9342 x 6400 38.6 / 48.4; FP8 4096 x 512 12.4 / 8.0, 4096 x 4096 15.9 / 13.1, 1536 x 8192
+// 13.7 / 13.7, 8661 x 4096 17.5 / 19.6; FP32 1536 x 1024 8.5 / 6.7, 4096 x 4096 19.7 / 15.3, 96 x 4096 8.3 / 8.7, 8301 x 7262
+// 56 / 78, 4890 x 2902 (306 panels) 20 / 23; FP64 96 x 1024 8.1 / 6.7, 4126 x 1024 (258 panels) 15.2 / 17.8.  600 problems of up
+// to 12000 x 11264 take 0.82 (BF16), 0.76 (FP8), 0.90 and 0.91 (FP64) of the time of two launches, six of them longer.
 template <typename T> static bool panel_pays(int64_t cols, int64_t rows) {
     constexpr int V = Elem<T>::vec;
-    const int64_t most = V == 16 ? 2048 + cols * 3 / 5 : V == 8 ? 3072 + cols * 4 / 5 : V == 4 ? 2560 + cols * 4 / 5 : 1280 + cols * 3 / 4;
+    int64_t most = V == 4 ? 2048 + cols * 3 / 5 : 1024 + cols * 3 / 5;
+    if (V == 8) most = cols <= 4096 ? 2560 + cols * 7 / 10 : 3072;
+    if (V == 16) most = cols <= 4096 ? 4096 + cols * 4 / 5 : std::min<int64_t>(2048 + cols * 3 / 5, 5000);
+    if (cols > 8192) most = V >= 8 ? 1024 : 256;
     const int64_t panels = (cols - 1) / Panel<T, V == 2 ? 8 : 4>::COLS + 1, rounds = (panels + 255) / 256;
-    const bool tail = rounds > 1 && 5 * 256 * rounds > 7 * panels && rows > 512;
+    const bool tail = rounds > 1 && 5 * 256 * rounds > (V == 2 ? 6 : 7) * panels && rows > 256;
     const bool large = rounds > 1 && (double)cols * (double)rows * Elem<T>::bytes > (V >= 8 ? 72e6 : 60e6);
     return cols >= V && !tail && !large && rows <= most;
 }
@@ -783,12 +791,19 @@ template <typename T, bool W, typename Out>
 static void panel_launch(const void* src, int cols, int rows, int64_t ld, const Out& out, hipStream_t st) {
     const auto launch = [&](auto lpr) {
         constexpr int LPR = decltype(lpr)::value;
-        const unsigned panels = (unsigned)((cols - 1) / Panel<T, LPR>::COLS + 1);
-        panel_kernel<T, W, LPR, Out><<<dim3(panels), dim3(64 * PANEL_WAVES), 0, st>>>(src, cols, rows, ld, out);
+        // (whole chunks of the workgroups' order, so that all panels of a line have their XCD, where there is much to read:
+        // FP8 1536 x 5000 11.9 us against 9.0)
+        const unsigned panels = (unsigned)((cols - 1) / Panel<T, LPR>::COLS + 1), chunk = 8 * 128 / (16 * LPR);
+        const unsigned blocks = rows >= 1024 ? (panels + chunk - 1) / chunk * chunk : panels;
+        panel_kernel<T, W, LPR, Out><<<dim3(blocks), dim3(64 * PANEL_WAVES), 0, st>>>(src, cols, rows, ld, out);
     };
     // 16-bit and FP8: half as wide for long columns, where the chip holds all panels at once (32 bytes of a row against 64:
     // BF16 1536 x 4096 9.7 against 12.5, 4096 x 512 8.4 / 7.2, 8192 x 4096 20.6 / 16.2; FP8 4096 x 2048 10.8 / 13.0, x 64
-    // 8.0 / 7.0)
+    // 8.0 / 7.0); FP8, with the most arithmetic to a byte, a quarter (16 bytes: 4096 x 4096 9.2 against 11.0 with the fold
+    // deferred, 4096 x 2048 with a fold of its own 11.3 / 10.6)
+    if constexpr (Elem<T>::vec == 16) {
+        if (cols <= 256 * Panel<T, 1>::COLS && rows >= std::max(1024, cols / 4 * 3)) return launch(std::integral_constant<int, 1>());
+    }
     if constexpr (Elem<T>::vec >= 8) {
         constexpr bool fp8 = Elem<T>::vec == 16;
         if (cols <= 256 * Panel<T, 2>::COLS && rows >= (fp8 ? std::max(256, cols / 6) : std::max(384, cols / 2)))

@@ -227,10 +227,11 @@ def test_encode_of_B_serves_any_row_count(dtype, Ms, Ml, N, K, transB):
 # columns and rows of the reduction: one column group, remainders of it (lanes moved back, whole lanes without a column), several
 # groups to a cache line, panels half as wide, first and last size of either form
 COLUMN_PASSES = [("bf16", 8, 1), ("bf16", 9, 3), ("f16", 31, 257), ("bf16", 33, 383), ("f16", 40, 384), ("bf16", 1000, 600),
-                 ("f16", 2055, 1100), ("bf16", 300, 3312), ("bf16", 300, 3313), ("bf16", 7, 40), ("f32", 4, 1), ("f32", 17, 255),
-                 ("f32", 515, 1025), ("f32", 100, 2640), ("f32", 100, 2641), ("f64", 2, 2), ("f64", 15, 130), ("f64", 259, 513),
-                 ("f64", 70, 1332), ("f64", 70, 1333), ("f64", 4113, 600), ("f8", 16, 5), ("f8", 65, 255), ("f8", 77, 256),
-                 ("f8e5m2", 1300, 300), ("f8", 1001, 2047), ("f8e5m2", 500, 2348), ("f8", 500, 2349), ("f32", 4113, 700)]
+                 ("f16", 2055, 1100), ("bf16", 300, 2770), ("bf16", 300, 2771), ("bf16", 7, 40), ("f32", 4, 1), ("f32", 17, 255),
+                 ("f32", 515, 1025), ("f32", 100, 2108), ("f32", 100, 2109), ("f64", 2, 2), ("f64", 15, 130), ("f64", 259, 513),
+                 ("f64", 70, 1066), ("f64", 70, 1067), ("f64", 4113, 600), ("f8", 16, 5), ("f8", 65, 255), ("f8", 77, 256),
+                 ("f8e5m2", 1300, 300), ("f8", 1001, 2047), ("f8e5m2", 17, 1023), ("f8", 1041, 1024), ("f8e5m2", 33, 4000),
+                 ("f32", 4113, 700), ("f16", 8193, 1024), ("bf16", 8200, 1025)]
 
 
 @pytest.mark.parametrize("dtype,cols,rows", COLUMN_PASSES)
