@@ -47,7 +47,7 @@ typedef enum {
     VABFT_OK = 0,
     VABFT_EINVAL = 1,       /* bad argument */
     VABFT_EUNSUPPORTED = 2, /* valid but not implemented for this dtype/layout */
-    VABFT_EWORKSPACE = 3,   /* workspace missing or smaller than vabft_workspace_bytes */
+    VABFT_EWORKSPACE = 3,   /* workspace missing or smaller than the call needs (vabft_workspace_bytes is enough) */
     VABFT_EDEVICE = 4       /* the HIP runtime reported an error at launch */
 } vabft_status;
 
@@ -96,8 +96,10 @@ typedef struct {
 
 const char* vabft_status_string(int status);
 
-/* Bytes of device scratch that vabft_encode and vabft_gemm_verified need for this
- * problem (0 is never returned for a valid problem; returns 0 for an invalid one). */
+/* Bytes of device scratch that vabft_encode and vabft_gemm_verified use for this
+ * problem (0 is never returned for a valid problem; returns 0 for an invalid one).  It includes room for faster
+ * forms (workgroups that share the K of a tile, copies of unaligned operands); a workspace without that room is
+ * accepted and takes the forms that do without. */
 size_t vabft_workspace_bytes(const vabft_problem* p);
 
 /* Zero-fill a freshly allocated workspace (a small fill kernel on `stream`; safe to capture
@@ -147,7 +149,8 @@ int vabft_threshold(const vabft_problem* p, const void* dA, const void* d_Be, co
 /* GEMM on the matrix cores with the fused check (section 2.2 Eq. abft-check and the
  * verification difference E_i; section 3.6 "Online (Fused Kernel) ABFT").
  *   verify == 0: plain C = A x B from the same kernel with the check compiled out;
- *                d_expected, d_T, d_rowsum, d_E, d_flags, d_nflag and inj may be NULL.
+ *                d_expected, d_T, d_rowsum, d_E, d_flags, d_nflag, inj and d_workspace may be NULL.  With a
+ *                workspace (16-byte aligned) C has the bits of the checked product.
  *   verify == 1: additionally
  *     d_rowsum [M] acc : sum_j acc[i][j] taken on the accumulator tile before quantisation,
  *                        partial sums combined in a fixed order
@@ -176,7 +179,7 @@ int vabft_gemm_verified(const vabft_problem* p, const void* dA, const void* dB, 
  * enough for the kernels of wide tiles, its operands' rows are 16-byte aligned and K is a multiple of 128 (FP8: of
  * 256, M and N too), the statistics ride on the operand tiles inside the GEMM kernel.  Elsewhere the A-side pass
  * has workgroups of its own: in the same launch, or, with very many rows or beside the kernels of wide tiles, in
- * a launch in front of it.  The route depends on shape, type, layout and alignment alone, never on the data.  The
+ * a launch in front of it, which also copies operands whose rows are not aligned for those kernels.  The route depends on shape, type, layout and alignment alone, never on the data.  The
  * compare-and-flag step runs in the last workgroup of each row block.  The summation order of the A-side sums
  * differs between statistics on the operand tiles and in workgroups of their own (both are fixed and
  * bit-reproducible; the second has the bits of vabft_threshold). */
@@ -193,7 +196,8 @@ int vabft_gemm_verified_fused(const vabft_problem* p, const void* dA, const void
  * VABFT_STATIC_SCRATCH_BYTES (16 MiB) of device memory inside the library, one copy per GPU, held until the
  * process ends.  The call allocates nothing and frees nothing.
  *   - d_S must not be NULL (no encode runs on this array, so there are no deferred partials to fold).
- *   - A problem whose workspace need (vabft_workspace_bytes) exceeds the array returns VABFT_EWORKSPACE;
+ *   - A problem whose partials and counters exceed the array returns VABFT_EWORKSPACE (the room for faster forms
+ *     that vabft_workspace_bytes adds is not counted: they are taken where the array has it);
  *     every benchmark configuration fits (the largest, FP16 8192^3, needs 8.4 MB).
  *   - Every call on a GPU shares that GPU's array, which keeps the previous call's contents; the call clears
  *     the arrival counters itself.  Calls that overlap on one GPU (two streams, two threads) race: order them.

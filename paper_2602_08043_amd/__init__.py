@@ -1,7 +1,7 @@
 """V-ABFT verified GEMM for AMD MI355X (gfx950): hand-written HIP kernels behind a C ABI.
 
-  binding  - ctypes mirror of include/vabft.h (vabft_encode, vabft_threshold,
-             vabft_gemm_verified, ...)
+  binding  - mirror of include/vabft.h (vabft_encode, vabft_threshold,
+             vabft_gemm_verified, ...): ctypes, the session's calls through a native module
   session  - PyTorch-backed device buffers around those calls
   build    - in-tree hipcc build of libvabft.so
 

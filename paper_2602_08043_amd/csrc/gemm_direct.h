@@ -18,6 +18,9 @@
 // chains, as four wavefronts do: with one chain (1 - 4 % faster) the error of C against more precision doubled (FP32
 // 8192 x 1024 x 1024 5.7e-7, now 2.9e-7).
 //
+// Where there are few tiles and a long K, several workgroups share the K of a tile (SPLIT): the last to arrive adds their tiles
+// up and goes on as if it had computed the sum alone.  FP32 93 x 345 x 5527 52 us, now 15.5.
+//
 // Operands pass from global memory through registers into LDS rows of the wavefront's own and back as MFMA fragments.
 // Loading fragments straight into registers needs no LDS, but puts 16 rows side by side in a quarter of a wavefront,
 // one tag look-up per lane: measured 14 B / clk of L1, 2048^3 BF16 (N x K) 75 us against 42.  With eight lanes per row of
@@ -39,7 +42,7 @@
 // Check: the wavefronts' partial tiles are added in LDS as a fixed tree, the injector edits the sum, row sums (and
 // weighted and column sums) are taken from it before it is rounded to the output type, and the last workgroup of a
 // tile-row to arrive folds the tile-columns' partials and compares (section 2.2, Eq. abft-check).  With the A-side
-// pass fused, the first workgroups of the launch run it (row_threshold.h), a wavefront or a part of one per row, and count as
+// pass fused, the first (or last) workgroups of the launch run it (row_threshold.h), a wavefront or a part of one per row, and count as
 // arrivals of their tile-row: one launch instead of three (pass over A, GEMM, compare).
 #pragma once
 #include "gemm_common.h"
