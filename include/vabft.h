@@ -150,7 +150,10 @@ int vabft_threshold(const vabft_problem* p, const void* dA, const void* d_Be, co
  * verification difference E_i; section 3.6 "Online (Fused Kernel) ABFT").
  *   verify == 0: plain C = A x B from the same kernel with the check compiled out;
  *                d_expected, d_T, d_rowsum, d_E, d_flags, d_nflag, inj and d_workspace may be NULL.  With a
- *                workspace (16-byte aligned) C has the bits of the checked product.
+ *                workspace (16-byte aligned) C has the bits of the checked product; the call then writes to it, so
+ *                the order of calls that share one goes for this call too, but it need not have been zero-filled.
+ *                Without one, C is the same product from kernels that need none: another order of summation, other
+ *                bits, for few tiles with a long K and for large products of unaligned 16-bit or FP8 rows.
  *   verify == 1: additionally
  *     d_rowsum [M] acc : sum_j acc[i][j] taken on the accumulator tile before quantisation,
  *                        partial sums combined in a fixed order

@@ -134,6 +134,21 @@ def test_workgroups_that_share_the_k_of_a_tile(dtype, M, N, K, transB):
     _check(vg, A, B, dA, dB, dtype, M, N, K, transB, ("run_fused",))
 
 
+@pytest.mark.parametrize("dtype,M,N,K,transB", [("f32", 93, 345, 5527, 0), ("bf16", 300, 450, 6145, 1), ("f64", 100, 130, 1500, 0)])
+def test_plain_product_with_a_workspace_that_was_never_zeroed(dtype, M, N, K, transB):
+    """The counters of shared tiles start at anything (here -1): the product is whole all the same, twice in a row."""
+    A, B = _gen(dtype, M, N, K, transB, 23)
+    vg = _session(M, N, K, dtype, transB)
+    dA, dB = _dev(A, dtype), _dev(B, dtype)
+    vg.gemm(dA, dB, 0)
+    C = vg.C.clone()
+    vg.ws.view(torch.uint8).fill_(0xff)
+    for _ in range(2):
+        vg.C.fill_(float("nan"))
+        vg.gemm(dA, dB, 0)
+        assert torch.equal(vg.C, C)
+
+
 @pytest.mark.parametrize("dtype,M,N,K,transB", [("bf16", 70, 131, 200, 1), ("f16", 33, 100, 2065, 0), ("f32", 65, 67, 70, 0),
                                                 ("f64", 40, 70, 33, 1), ("f8", 50, 70, 131, 1), ("f8e5m2", 17, 90, 70, 0)])
 def test_direct_unaligned_base_and_pitch(dtype, M, N, K, transB):
