@@ -1,9 +1,9 @@
 """Binding of libvabft.so: the same entry points as include/vabft.h.
 
 Argument marshalling only, by the native module _calls (csrc/calls.cpp) for the entry points that a pass makes and by
-ctypes for the rest.  Pointer arguments may be tensors, integers or None.  Every step of the path runs in the HIP kernels of the
-library; there is no CPU or PyTorch fallback: if the library is missing, loading
-fails with an error that says how to build it.
+ctypes for the rest.  Pointer arguments may be tensors, integers, None or what ctypes takes for a c_void_p.  Every step of the
+path runs in the HIP kernels of the library; there is no CPU or PyTorch fallback: if the library is missing, loading fails with an
+error that says how to build it.
 """
 from __future__ import annotations
 
@@ -71,8 +71,10 @@ def load(path: str | None = None):
         raise ImportError(f"{_PKG}/_calls.so is missing or was built for another interpreter ({e}). Run "
                           "`python -c 'import __graft_entry__ as g; g.build()'`.") from e
     lib = ctypes.CDLL(p)
+    _calls.structures(Problem, Inject)
     for name in _calls.ENTRIES:
         setattr(lib, "call_" + name[len("vabft_"):], _calls.bind(name, ctypes.cast(getattr(lib, name), c_void_p).value))
+    # (prototypes of all entry points: load().vabft_...() can be called as it is, too)
     lib.vabft_status_string.restype = c_char_p
     lib.vabft_status_string.argtypes = [ctypes.c_int]
     lib.vabft_workspace_bytes.restype = c_size_t

@@ -1,10 +1,12 @@
 // Python arguments -> calls of the C ABI (include/vabft.h).  A call of the session has 9 to 24 arguments; marshalled by
 // ctypes, with data_ptr() of every tensor called from Python, it took 8 to 9 us of host time, more than the GPU needs for a
 // small product (f32 256^3, two calls: 16.5 us a pass on the host, 12.8 on the GPU).  Converted here it takes 4 to 5, most of
-// it the launch.  Pointers may be tensors (anything with data_ptr()), integers, None or ctypes pointers; structures are ctypes structures.
+// it the launch.  Pointers may be tensors (anything with data_ptr()), integers, None or what ctypes takes for a c_void_p;
+// structures are the binding's own.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
+#include <cstring>
 #include <tuple>
 #include <type_traits>
 #include <utility>
@@ -13,8 +15,13 @@
 
 namespace {
 
-PyObject* g_data_ptr;
-PyObject* g_value;
+PyObject* g_data_ptr;  // "data_ptr"
+PyObject* g_value;     // "value"
+PyObject* g_cast;      // ctypes.cast, ctypes.c_void_p, ctypes.c_size_t
+PyObject* g_void_p;
+PyObject* g_size_t;
+PyObject* g_problem;   // the binding's structures
+PyObject* g_inject;
 
 bool to_address(PyObject* o, void** out) {
     if (o == Py_None) {
@@ -26,46 +33,73 @@ bool to_address(PyObject* o, void** out) {
         return !PyErr_Occurred();
     }
     PyObject* r = PyObject_CallMethodNoArgs(o, g_data_ptr);
-    if (!r && PyErr_ExceptionMatches(PyExc_AttributeError)) {
+    if (!r && PyErr_ExceptionMatches(PyExc_AttributeError) && !PyUnicode_Check(o) && !PyBytes_Check(o)) {
+        // what ctypes takes for a c_void_p: pointers, arrays, byref(); of anything else it makes an ArgumentError
         PyErr_Clear();
-        r = PyObject_GetAttr(o, g_value);  // ctypes.c_void_p
+        PyObject* const p = PyObject_CallFunctionObjArgs(g_cast, o, g_void_p, nullptr);
+        r = p ? PyObject_GetAttr(p, g_value) : nullptr;
+        Py_XDECREF(p);
     }
     if (!r) return false;
     const bool ok = r == Py_None || PyLong_Check(r);
     *out = ok && r != Py_None ? PyLong_AsVoidPtr(r) : nullptr;
     Py_DECREF(r);
-    if (!ok) PyErr_SetString(PyExc_TypeError, "a pointer must be a tensor, an integer, None or a ctypes pointer");
+    if (!ok) PyErr_SetString(PyExc_TypeError, "data_ptr() must give an integer");
     return ok && !PyErr_Occurred();
 }
 
-// the memory of a ctypes structure, which its owner keeps for the length of the call
-bool to_struct(PyObject* o, size_t bytes, const void** out) {
+// the memory of one of the binding's structures, which its owner keeps for the length of the call
+bool to_struct(PyObject* o, PyObject* type, size_t bytes, const void** out) {
     *out = nullptr;
     if (o == Py_None) return true;
+    const int is = type ? PyObject_IsInstance(o, type) : 0;
+    if (is < 0) return false;
     Py_buffer view;
-    if (PyObject_GetBuffer(o, &view, PyBUF_SIMPLE) != 0) return false;
-    const bool ok = (size_t)view.len == bytes;
+    if (!is || PyObject_GetBuffer(o, &view, PyBUF_SIMPLE) != 0) {
+        if (!PyErr_Occurred()) PyErr_SetString(PyExc_TypeError, "a structure of another type");
+        return false;
+    }
+    const bool ok = (size_t)view.len >= bytes;
     *out = view.buf;
     PyBuffer_Release(&view);
     if (!ok) PyErr_SetString(PyExc_TypeError, "structure of another size");
     return ok;
 }
 
+// float(o)
+bool to_double(PyObject* o, double* out) {
+    PyObject* const f = PyFloat_CheckExact(o) ? nullptr : PyNumber_Float(o);
+    if (!f && PyErr_Occurred()) return false;
+    *out = PyFloat_AS_DOUBLE(f ? f : o);
+    Py_XDECREF(f);
+    return true;
+}
+
+// an integer, or a ctypes.c_size_t
+bool to_size(PyObject* o, size_t* out) {
+    PyObject* r = nullptr;
+    if (!PyLong_Check(o)) {
+        const int is = PyObject_IsInstance(o, g_size_t);
+        if (is < 0 || (is && !(r = PyObject_GetAttr(o, g_value)))) return false;
+    }
+    *out = PyLong_AsSize_t(r ? r : o);
+    Py_XDECREF(r);
+    return !(*out == (size_t)-1 && PyErr_Occurred());
+}
+
 template <typename T> bool convert(PyObject* o, T* out) {
     if constexpr (std::is_same<T, const vabft_problem*>::value || std::is_same<T, const vabft_inject*>::value) {
         const void* p;
-        if (!to_struct(o, sizeof(**out), &p)) return false;
+        if (!to_struct(o, std::is_same<T, const vabft_problem*>::value ? g_problem : g_inject, sizeof(**out), &p)) return false;
         *out = static_cast<T>(p);
     } else if constexpr (std::is_pointer<T>::value) {
         void* p;
         if (!to_address(o, &p)) return false;
         *out = static_cast<T>(p);
     } else if constexpr (std::is_floating_point<T>::value) {
-        *out = PyFloat_AsDouble(o);
-        return !(*out == -1.0 && PyErr_Occurred());
+        return to_double(o, out);
     } else if constexpr (std::is_same<T, size_t>::value) {
-        *out = PyLong_AsSize_t(o);
-        return !(*out == (size_t)-1 && PyErr_Occurred());
+        return to_size(o, out);
     } else {
         static_assert(std::is_same<T, int32_t>::value, "a type of the ABI");
         const long v = PyLong_AsLong(o);
@@ -122,7 +156,18 @@ PyObject* bind(PyObject*, PyObject* args) {
     return PyErr_Format(PyExc_KeyError, "no entry point %s", name);
 }
 
+PyObject* structures(PyObject*, PyObject* args) {
+    PyObject *problem, *inject;
+    if (!PyArg_ParseTuple(args, "O!O!", &PyType_Type, &problem, &PyType_Type, &inject)) return nullptr;
+    Py_INCREF(problem);
+    Py_INCREF(inject);
+    Py_XSETREF(g_problem, problem);
+    Py_XSETREF(g_inject, inject);
+    Py_RETURN_NONE;
+}
+
 PyMethodDef g_methods[] = {
+    {"structures", structures, METH_VARARGS, "structures(Problem, Inject): the ctypes classes of vabft_problem and vabft_inject"},
     {"bind", bind, METH_VARARGS, "bind(name, address): the entry point at an address as a Python callable"},
     {nullptr, nullptr, 0, nullptr}};
 PyModuleDef g_module = {PyModuleDef_HEAD_INIT, "_calls", "Native calls of libvabft's entry points.", -1, g_methods,
@@ -133,7 +178,12 @@ PyModuleDef g_module = {PyModuleDef_HEAD_INIT, "_calls", "Native calls of libvab
 PyMODINIT_FUNC PyInit__calls(void) {
     g_data_ptr = PyUnicode_InternFromString("data_ptr");
     g_value = PyUnicode_InternFromString("value");
-    PyObject* m = g_data_ptr && g_value ? PyModule_Create(&g_module) : nullptr;
+    PyObject* const ctypes = PyImport_ImportModule("ctypes");
+    g_cast = ctypes ? PyObject_GetAttrString(ctypes, "cast") : nullptr;
+    g_void_p = ctypes ? PyObject_GetAttrString(ctypes, "c_void_p") : nullptr;
+    g_size_t = ctypes ? PyObject_GetAttrString(ctypes, "c_size_t") : nullptr;
+    Py_XDECREF(ctypes);
+    PyObject* m = g_data_ptr && g_value && g_cast && g_void_p && g_size_t ? PyModule_Create(&g_module) : nullptr;
     PyObject* names = m ? PyList_New(0) : nullptr;
     for (PyMethodDef* e = g_entries; names && e->ml_name; ++e) {
         PyObject* s = PyUnicode_FromString(e->ml_name);

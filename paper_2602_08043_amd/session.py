@@ -97,7 +97,7 @@ class VerifiedGemm:
 
     def encode(self, B: torch.Tensor, defer_S: bool = False):
         """defer_S: leave S1..S3 as partials in the workspace for gemm_fused(..., deferred_S=True)."""
-        return vb.vabft_encode(self.problem, B, self.Be, self.bstat,
+        return vb.vabft_encode(self.problem, B.data_ptr(), self.Be, self.bstat,
                                None if defer_S else self.S, self.ws, self.ws_bytes,
                                self._stream())
 
@@ -105,7 +105,7 @@ class VerifiedGemm:
         if e_max is None:
             e_max = vb.vabft_default_emax(self.dtype, self.K, self.N)
         self.e_max = e_max
-        return vb.vabft_threshold(self.problem, A, self.Be, self.S, e_max, c_sigma,
+        return vb.vabft_threshold(self.problem, A.data_ptr(), self.Be, self.S, e_max, c_sigma,
                                   self.astat, self.expected, self.T, self._stream())
 
     def make_inject(self, mode=0, faults=None, seed=0, rate=0.0, bit_lo=0, bit_hi=0) -> vb.Inject:
@@ -123,7 +123,7 @@ class VerifiedGemm:
         return inj
 
     def gemm(self, A: torch.Tensor, B: torch.Tensor, verify=1, inj: vb.Inject | None = None):
-        return vb.vabft_gemm_verified(self.problem, A, B, self.C,
+        return vb.vabft_gemm_verified(self.problem, A.data_ptr(), B.data_ptr(), self.C,
                                       self.expected, self.T, verify, inj,
                                       self.rowsum, self.E, self.flags,
                                       self.nflag, self.injlog, self.ninj,
@@ -135,7 +135,7 @@ class VerifiedGemm:
         if e_max is None:
             e_max = vb.vabft_default_emax(self.dtype, self.K, self.N)
         self.e_max = e_max
-        return vb.vabft_gemm_verified_fused(self.problem, A, B, self.C,
+        return vb.vabft_gemm_verified_fused(self.problem, A.data_ptr(), B.data_ptr(), self.C,
                                             self.Be, None if deferred_S else self.S, e_max,
                                             c_sigma, self.astat, self.expected,
                                             self.T, inj,
@@ -157,7 +157,7 @@ class VerifiedGemm:
 
     # ---- weighted checksum, localisation, correction ---------------------------------
     def encode_weighted(self, B: torch.Tensor):
-        return vb.vabft_encode_weighted(self.problem, B, self.Be, self.Be2,
+        return vb.vabft_encode_weighted(self.problem, B.data_ptr(), self.Be, self.Be2,
                                         self.bstat, self.S, self.ws, self.ws_bytes,
                                         self._stream())
 
@@ -165,13 +165,13 @@ class VerifiedGemm:
         if e_max is None:
             e_max = vb.vabft_default_emax(self.dtype, self.K, self.N)
         self.e_max = e_max
-        return vb.vabft_threshold_weighted(self.problem, A, self.Be, self.Be2,
+        return vb.vabft_threshold_weighted(self.problem, A.data_ptr(), self.Be, self.Be2,
                                            self.S, e_max, c_sigma, self.astat,
                                            self.expected, self.expected2, self.T,
                                            self._stream())
 
     def gemm_weighted(self, A: torch.Tensor, B: torch.Tensor, inj: vb.Inject | None = None):
-        return vb.vabft_gemm_verified_weighted(self.problem, A, B, self.C,
+        return vb.vabft_gemm_verified_weighted(self.problem, A.data_ptr(), B.data_ptr(), self.C,
                                                self.expected, self.T, inj,
                                                self.rowsum, self.rowsum2, self.E,
                                                self.flags, self.nflag, self.injlog,
@@ -194,18 +194,18 @@ class VerifiedGemm:
 
     # ---- column checksums --------------------------------------------------------------
     def encode_a(self, A: torch.Tensor):
-        return vb.vabft_encode_a(self.problem, A, self.eA, self.acolstat,
+        return vb.vabft_encode_a(self.problem, A.data_ptr(), self.eA, self.acolstat,
                                  self.SA, self.ws, self.ws_bytes, self._stream())
 
     def threshold_cols(self, B: torch.Tensor, e_max=None, c_sigma=2.5):
         if e_max is None:
             e_max = vb.vabft_default_emax(self.dtype, self.K, max(self.N, self.M))
-        return vb.vabft_threshold_cols(self.problem, B, self.eA, self.SA, e_max,
+        return vb.vabft_threshold_cols(self.problem, B.data_ptr(), self.eA, self.SA, e_max,
                                        c_sigma, self.bcolstat, self.expected_col,
                                        self.T_col, self.ws, self.ws_bytes, self._stream())
 
     def gemm_rc(self, A: torch.Tensor, B: torch.Tensor, inj: vb.Inject | None = None):
-        return vb.vabft_gemm_verified_rc(self.problem, A, B, self.C,
+        return vb.vabft_gemm_verified_rc(self.problem, A.data_ptr(), B.data_ptr(), self.C,
                                          self.expected, self.T, self.expected_col,
                                          self.T_col, inj, self.rowsum, self.E,
                                          self.flags, self.nflag, self.colsum,
@@ -223,18 +223,18 @@ class VerifiedGemm:
 
     # ---- block-wise verification --------------------------------------------------------
     def encode_blocks(self, B: torch.Tensor):
-        return vb.vabft_encode_blocks(self.problem, B, self.Be_blk, self.S_blk,
+        return vb.vabft_encode_blocks(self.problem, B.data_ptr(), self.Be_blk, self.S_blk,
                                       self.ws, self.ws_bytes, self._stream())
 
     def threshold_blocks(self, A: torch.Tensor, e_max=None, c_sigma=2.5):
         if e_max is None:
             e_max = vb.vabft_default_emax(self.dtype, self.K, min(self.N, self.W))
-        return vb.vabft_threshold_blocks(self.problem, A, self.Be_blk, self.S_blk,
+        return vb.vabft_threshold_blocks(self.problem, A.data_ptr(), self.Be_blk, self.S_blk,
                                          e_max, c_sigma, self.astat, self.expected_blk,
                                          self.T_blk, self._stream())
 
     def gemm_blocks(self, A: torch.Tensor, B: torch.Tensor, inj: vb.Inject | None = None):
-        return vb.vabft_gemm_verified_blocks(self.problem, A, B, self.C,
+        return vb.vabft_gemm_verified_blocks(self.problem, A.data_ptr(), B.data_ptr(), self.C,
                                              self.expected_blk, self.T_blk, inj,
                                              self.rowsum_blk, self.E_blk,
                                              self.blockflags, self.nblockflag,
@@ -251,7 +251,7 @@ class VerifiedGemm:
     def check_offline(self, C: torch.Tensor | None = None):
         """Row sums of a stored product (default: this session's C) against expected / T."""
         C = self.C if C is None else C
-        return vb.vabft_check_offline(self.problem, C, self.expected, self.T,
+        return vb.vabft_check_offline(self.problem, C.data_ptr(), self.expected, self.T,
                                       self.rowsum, self.E, self.flags,
                                       self.nflag, self._stream())
 
@@ -331,18 +331,18 @@ class KBlockedGemm:
     inject_records = VerifiedGemm.inject_records
 
     def encode(self, B: torch.Tensor):
-        return vb.vabft_encode_blocks_k(self.problem, self.kblock, B, self.Be_blk_k,
+        return vb.vabft_encode_blocks_k(self.problem, self.kblock, B.data_ptr(), self.Be_blk_k,
                                         self.S_blk_k, self.ws, self.ws_bytes, self._stream())
 
     def threshold(self, A: torch.Tensor, e_max=None, c_sigma=2.5):
         if e_max is None:
             e_max = vb.vabft_default_emax(self.dtype, min(self.K, self.kblock), min(self.N, self.W))
-        return vb.vabft_threshold_blocks_k(self.problem, self.kblock, A, self.Be_blk_k,
+        return vb.vabft_threshold_blocks_k(self.problem, self.kblock, A.data_ptr(), self.Be_blk_k,
                                            self.S_blk_k, e_max, c_sigma, self.astat_k,
                                            self.expected_blk_k, self.T_blk_k, self._stream())
 
     def gemm(self, A: torch.Tensor, B: torch.Tensor, inj: vb.Inject | None = None):
-        return vb.vabft_gemm_verified_blocks_k(self.problem, self.kblock, A, B, self.C,
+        return vb.vabft_gemm_verified_blocks_k(self.problem, self.kblock, A.data_ptr(), B.data_ptr(), self.C,
                                                self.expected_blk_k, self.T_blk_k, inj,
                                                self.rowsum_blk_k, self.E_blk_k,
                                                self.blockflags_k, self.nblockflag,

@@ -229,3 +229,66 @@ def test_native_calls_take_every_kind_of_pointer(lib):
             call(*bad)
     with pytest.raises(OverflowError):
         lib.call_locate_correct(p, t, t, t, t, t, t, 1 << 40, t, t, t, None)
+
+
+def test_native_calls_take_what_ctypes_takes_for_a_pointer(lib):
+    """byref() with an offset, POINTER instances, arrays, c_size_t and numbers as text as a ctypes call takes them; what that
+    refuses (another ctypes type, an array of numpy, another structure of the same size) is refused.  An address off by one byte
+    is EINVAL here, an aligned one gets as far as the missing workspace."""
+    import ctypes
+    import numpy as np
+    p = vb.make_problem(8, 8, 8, "f32")
+    buf = (ctypes.c_float * 64)()
+    at = ctypes.addressof(buf)
+
+    class Subclass(vb.Problem):
+        _fields_ = [("more", ctypes.c_int64)]
+
+    def call(ptr, problem=p, size=0):
+        return lib.call_encode(problem, ptr, buf, buf, None, None, size, None)
+
+    off = (ctypes.c_float * 8).from_address(at + 1)
+    for good, bad in ((ctypes.byref(buf), ctypes.byref(buf, 1)), (buf, off),
+                      (ctypes.cast(at, ctypes.POINTER(ctypes.c_float)), ctypes.cast(at + 1, ctypes.POINTER(ctypes.c_float))),
+                      (ctypes.c_void_p(at), ctypes.c_void_p(at + 1))):
+        assert call(good) == vb.VABFT_EWORKSPACE and call(bad) == vb.VABFT_EINVAL
+    assert call(buf, size=ctypes.c_size_t(1 << 20)) == vb.VABFT_EWORKSPACE
+    assert call(buf, Subclass(8, 8, 8, vb.VABFT_F32, 0, 0, 8, 8, 8)) == vb.VABFT_EWORKSPACE
+    assert lib.call_threshold(p, buf, buf, buf, "1e-6", 2, buf, None, buf, None) == vb.VABFT_EINVAL  # as float() reads it
+    for refused in (ctypes.c_int(5), ctypes.c_size_t(at), np.zeros(64, np.float32), np.int64(at), 1.5, [at]):
+        with pytest.raises(ctypes.ArgumentError):
+            call(refused)
+    assert ctypes.sizeof(vb.Inject) == ctypes.sizeof(vb.Problem)
+    for other in (vb.Inject(), np.zeros(48, np.uint8), bytearray(48)):
+        with pytest.raises(TypeError):
+            call(buf, other)
+    with pytest.raises(TypeError):
+        lib.call_gemm_verified(p, buf, buf, buf, None, None, 0, p, None, None, None, None, None, None, None, 0, None)
+    with pytest.raises(TypeError):
+        call(buf, size=ctypes.c_int(5))
+
+
+@pytest.mark.parametrize("method", ["encode", "threshold", "gemm", "gemm_fused", "encode_weighted", "threshold_weighted",
+                                    "gemm_weighted", "encode_a", "threshold_cols", "gemm_rc", "encode_blocks",
+                                    "threshold_blocks", "gemm_blocks", "check_offline"])
+def test_session_operands_are_tensors(lib, method):
+    """An address or nothing in the place of a tensor is an error of Python's, not a call with that address."""
+    pytest.importorskip("torch")
+    from paper_2602_08043_amd.session import VerifiedGemm
+
+    class Any_(VerifiedGemm):
+        def __init__(self):
+            self.problem = vb.make_problem(8, 8, 8, "f32")
+            self.dtype, self.M, self.N, self.K, self.W = "f32", 8, 8, 8, 64
+
+        def __getattr__(self, name):  # any buffer of the session
+            return None
+
+        @staticmethod
+        def _stream():
+            return None
+
+    for wrong in (4096, "x") + ((None,) if method != "check_offline" else ()):
+        operands = (wrong, wrong) if method.startswith("gemm") else (wrong,)
+        with pytest.raises(AttributeError, match="data_ptr"):
+            getattr(Any_(), method)(*operands)
