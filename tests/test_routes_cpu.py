@@ -1,0 +1,44 @@
+"""What a GEMM call runs on, asked on the host (no GPU): the library's own decision for a problem, its operands' addresses and
+the room of its workspace."""
+import ctypes
+import random
+
+import pytest
+
+vb = pytest.importorskip("paper_2602_08043_amd.binding")
+
+DIRECT_16, DIRECT_32, DIRECT_32W, DIRECT_ANY, DIRECT_64, OWN32, OWN64 = range(7)
+TILED, CHAINS = -1, 4
+
+
+def route(dtype, M, N, K, transB=0, *, lda=None, ldb=None, ldc=None, A=4096, B=4096, C=4096, more_sums=0, injects=0, room=None):
+    """(A copied, B copied, kernel, workgroups per tile, tiled kernel's form, A-side pass): see vabft_internal_route."""
+    lib = vb.load()
+    p = vb.make_problem(M, N, K, dtype, transB, lda, ldb, ldc)
+    out = (ctypes.c_int32 * 6)()
+    ptr = ctypes.c_void_p
+    f = lib.vabft_internal_route
+    f.restype = None
+    f.argtypes = [ctypes.POINTER(vb.Problem), ptr, ptr, ptr, ctypes.c_int32, ctypes.c_int32, ctypes.c_size_t,
+                  ctypes.POINTER(ctypes.c_int32)]
+    f(p, A, B, C, more_sums, injects, vb.vabft_workspace_bytes(p) if room is None else room, out)
+    return tuple(out)
+
+
+def test_copied_operands_run_on_the_kernel_they_are_priced_for():
+    """Copies are made for the 128-wide tiled kernel with K in four chains; no size makes them for another one."""
+    copied = 0
+    r = random.Random(5)
+    problems = [("bf16", 1717, 1961, 5119, 1), ("bf16", 1308, 1402, 10752, 0), ("f16", 1661, 1687, 4441, 1)]
+    problems += [(r.choice(["bf16", "f16", "f8", "f8e5m2"]), r.randint(300, 8192), r.randint(300, 11008), r.randint(64, 11008),
+                  r.randint(0, 1)) for _ in range(3000)]
+    for p in problems:
+        a, b, kernel, split, form, _ = route(*p)
+        if a or b:
+            copied += 1
+            assert (kernel, split, form) == (TILED, 1, CHAINS), p
+    assert copied > 500
+    # rows further apart than the tiled kernels take are not copied for them, but read as they lie
+    far = dict(lda=(1 << 22) + 8)
+    assert route("bf16", 3000, 3001, 2048, 0)[:3] == (0, 1, TILED)
+    assert route("bf16", 3000, 3001, 2048, 0, **far)[:2] == (0, 0)
