@@ -42,3 +42,18 @@ def test_copied_operands_run_on_the_kernel_they_are_priced_for():
     far = dict(lda=(1 << 22) + 8)
     assert route("bf16", 3000, 3001, 2048, 0)[:3] == (0, 1, TILED)
     assert route("bf16", 3000, 3001, 2048, 0, **far)[:2] == (0, 0)
+
+
+# measured: as the rows lie / copied (us)
+COPIES_PAY = [("bf16", 3708, 1873, 10496, 0), ("f16", 1694, 8971, 5807, 1), ("f16", 5598, 2257, 2431, 0),  # 354 / 165, 479 / 213, 195 / 97
+              ("bf16", 2048, 1659, 10987, 1), ("f8", 1792, 5243, 9984, 0), ("f8e5m2", 3584, 2465, 3764, 0)]  # 226 / 134, 268 / 248, 125 / 114
+COPIES_LOSE = [("bf16", 1024, 2497, 3584, 0), ("f16", 512, 5219, 9216, 0), ("bf16", 1308, 1402, 10752, 0),  # 49 / 55, 112 / 127, 92 / 121
+               ("bf16", 2568, 9722, 448, 0), ("f16", 2560, 7283, 464, 0),  # 67 / 80, 63 / 76
+               ("f8", 2048, 2048, 4352, 0), ("f8", 3840, 2304, 2048, 0), ("f8", 2560, 1561, 4096, 1)]  # 57 / 65, 66 / 75, 51 / 61
+
+
+def test_operands_are_copied_where_that_is_faster():
+    for p in COPIES_PAY:
+        assert route(*p)[2] == TILED and sum(route(*p)[:2]) > 0, p
+    for p in COPIES_LOSE:
+        assert route(*p)[:2] == (0, 0), p
