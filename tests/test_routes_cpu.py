@@ -57,3 +57,17 @@ def test_operands_are_copied_where_that_is_faster():
         assert route(*p)[2] == TILED and sum(route(*p)[:2]) > 0, p
     for p in COPIES_LOSE:
         assert route(*p)[:2] == (0, 0), p
+
+
+FIRST, LAST = 0, 1
+# measured fused calls, the pass in front of the tiles / behind them (us)
+PASS_ORDER = [("f16", 179, 256, 2560, 0, LAST), ("f32", 7168, 256, 128, 1, LAST), ("bf16", 507, 256, 1729, 0, LAST),  # 11.9 / 9.6, 19.0 / 14.2, 14.3 / 11.4
+              ("f8e5m2", 8192, 375, 293, 0, LAST), ("f32", 3072, 128, 10467, 0, LAST),  # 24.9 / 18.6, 190 / 113
+              ("bf16", 192, 4995, 2145, 0, FIRST), ("f16", 906, 2467, 1092, 1, FIRST), ("f64", 1536, 3072, 80, 1, FIRST),  # 21.0 / 22.7, 26.5 / 29.2, 36.4 / 37.9
+              ("f64", 2147, 768, 125, 1, LAST), ("f64", 683, 80, 231, 1, LAST),  # 28.0 / 20.8, 13.6 / 13.2
+              ("bf16", 261, 9647, 128, 0, FIRST), ("f32", 3259, 7979, 128, 0, FIRST), ("f64", 552, 3165, 392, 1, FIRST)]  # 12.3 / 14.3, 87 / 94, 41.4 / 43.8
+
+
+def test_place_of_the_a_side_pass():
+    for *p, place in PASS_ORDER:
+        assert route(*p)[5] == place, p
