@@ -61,13 +61,26 @@ def test_operands_are_copied_where_that_is_faster():
 
 FIRST, LAST = 0, 1
 # measured fused calls, the pass in front of the tiles / behind them (us)
-PASS_ORDER = [("f16", 179, 256, 2560, 0, LAST), ("f32", 7168, 256, 128, 1, LAST), ("bf16", 507, 256, 1729, 0, LAST),  # 11.9 / 9.6, 19.0 / 14.2, 14.3 / 11.4
+PASS_ORDER = [("f16", 179, 256, 2560, 0, LAST), ("f32", 7168, 256, 128, 1, LAST),  # 11.9 / 9.6, 19.0 / 14.2
               ("f8e5m2", 8192, 375, 293, 0, LAST), ("f32", 3072, 128, 10467, 0, LAST),  # 24.9 / 18.6, 190 / 113
               ("bf16", 192, 4995, 2145, 0, FIRST), ("f16", 906, 2467, 1092, 1, FIRST), ("f64", 1536, 3072, 80, 1, FIRST),  # 21.0 / 22.7, 26.5 / 29.2, 36.4 / 37.9
-              ("f64", 2147, 768, 125, 1, LAST), ("f64", 683, 80, 231, 1, LAST),  # 28.0 / 20.8, 13.6 / 13.2
+              ("f64", 2147, 768, 125, 1, LAST),  # 28.0 / 20.8
               ("bf16", 261, 9647, 128, 0, FIRST), ("f32", 3259, 7979, 128, 0, FIRST), ("f64", 552, 3165, 392, 1, FIRST)]  # 12.3 / 14.3, 87 / 94, 41.4 / 43.8
 
 
 def test_place_of_the_a_side_pass():
     for *p, place in PASS_ORDER:
         assert route(*p)[5] == place, p
+
+
+# measured fused calls, not shared / shared (us)
+SHARED = [("f32", 93, 345, 5527, 0), ("f64", 48, 192, 3840, 1), ("bf16", 78, 192, 6871, 0), ("bf16", 1280, 99, 6882, 1)]  # 52 / 20, 40 / 11, 23 / 10, 29 / 21
+NOT_SHARED = [("bf16", 40, 512, 1280, 1), ("f64", 683, 80, 231, 1), ("f8", 48, 6400, 9065, 1),  # 7.9 / 8.5, 12.0 / 12.8, 30 / 36
+              ("f16", 30, 3584, 1974, 1), ("bf16", 507, 256, 1729, 0)]  # 10.2 / 11.0, 10.7 / 11.4
+
+
+def test_workgroups_share_the_k_of_a_tile_where_that_is_faster():
+    for p in SHARED:
+        assert route(*p)[3] > 1, p
+    for p in NOT_SHARED:
+        assert route(*p)[3] == 1, p
