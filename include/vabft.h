@@ -182,7 +182,11 @@ int vabft_gemm_verified(const vabft_problem* p, const void* dA, const void* dB, 
  * enough for the kernels of wide tiles, its operands' rows are 16-byte aligned and K is a multiple of 128 (FP8: of
  * 256, M and N too), the statistics ride on the operand tiles inside the GEMM kernel.  Elsewhere the A-side pass
  * has workgroups of its own: in the same launch, or, with very many rows or beside the kernels of wide tiles, in
- * a launch in front of it, which also copies operands whose rows are not aligned for those kernels.  The route depends on shape, type, layout and alignment alone, never on the data.  The
+ * a launch in front of it, which also copies operands whose rows are not aligned for those kernels.  The route depends
+ * on shape, type, layout and alignment, on whether the injector is on and on the room of the workspace (with that of
+ * vabft_workspace_bytes or more it is the same), never on the data.  Another route sums K in another order: with the
+ * injector on, large products of 16-bit and FP8 rows that the kernels of wide tiles take without it run on others, and
+ * elements of C that no fault touched may differ in their last bits from a call's without it.  The
  * compare-and-flag step runs in the last workgroup of each row block.  The summation order of the A-side sums
  * differs between statistics on the operand tiles and in workgroups of their own (both are fixed and
  * bit-reproducible; the second has the bits of vabft_threshold). */
@@ -194,8 +198,10 @@ int vabft_gemm_verified_fused(const vabft_problem* p, const void* dA, const void
                               size_t workspace_bytes, void* stream);
 
 /* The fused call for callers that cannot allocate device memory: code under HIP graph capture, tight serving
- * loops, harnesses that forbid hipMalloc.  Same inputs, outputs and results as vabft_gemm_verified_fused, but
- * without a workspace argument: the partials and arrival counters live in a fixed array of
+ * loops, harnesses that forbid hipMalloc.  Same inputs and outputs as vabft_gemm_verified_fused, and the same results
+ * bit for bit but for large products of 16-bit or FP8 rows that are not aligned to 16 bytes (FP8: of other sizes than
+ * whole tiles, or B stored K x N), where a workspace has room for copies of them and this array has not: they take the
+ * kernels that read rows as they lie, which sum K in another order.  There is no workspace argument: the partials and arrival counters live in a fixed array of
  * VABFT_STATIC_SCRATCH_BYTES (16 MiB) of device memory inside the library, one copy per GPU, held until the
  * process ends.  The call allocates nothing and frees nothing.
  *   - d_S must not be NULL (no encode runs on this array, so there are no deferred partials to fold).

@@ -85,3 +85,15 @@ def test_workgroups_share_the_k_of_a_tile_where_that_is_faster():
         assert route(*p)[3] > 1, p
     for p in NOT_SHARED:
         assert route(*p)[3] == 1, p
+
+
+def test_static_scratch_decides_like_a_workspace_but_for_copies():
+    """The call without a workspace (16 MiB and 128 KiB of its own) takes the same kernel, tile and split."""
+    r = random.Random(11)
+    problems = [("f32", 3, 200, 7_000_000, 1), ("f64", 2, 128, 9_000_000, 1)]  # S1..S3's partials take most of the array
+    problems += [(r.choice(list(vb.DTYPE_CODE)), r.randint(1, 3000), r.randint(1, 9000), r.randint(1, 20000), r.randint(0, 1))
+                 for _ in range(3000)]
+    for p in problems:
+        here = route(*p)
+        if here[:2] == (0, 0):
+            assert route(*p, room=(16 << 20) + (128 << 10)) == here, p

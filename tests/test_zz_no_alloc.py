@@ -1,5 +1,6 @@
 """The entry point that allocates nothing (vabft_gemm_verified_fused_static) against the entry point it is a
-variant of (vabft_gemm_verified_fused): same kernels, so every output must be the same bit for bit -- on two calls
+variant of (vabft_gemm_verified_fused): same kernels but where operands are copied into a workspace and the array has no room
+for that, so every output must be the same bit for bit elsewhere -- on two calls
 in a row on the library's fixed scratch array, the second with a smaller input (the array keeps the first call's
 partials and counters)."""
 import numpy as np
@@ -11,6 +12,9 @@ torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
 from test_gpu_parity import _dev, _emax, _gen, _session  # noqa: E402
+from test_routes_cpu import route  # noqa: E402
+
+STATIC = (16 << 20) + (128 << 10)  # bytes of the array
 
 
 def _static_call(vg, dA, dB, e_max, inj=None):
@@ -53,6 +57,49 @@ def test_static_scratch_call_matches_the_workspace_call(dtype, transB, shapes):
         assert got["nflag"] == want["nflag"] == (1 if call == 1 else 0)
         o = orc.verify(A, B, dtype, transB, e_max=e_max)
         assert np.all(np.abs(got["T"] - o["T"]) <= 1e-5 * o["T"] + 1e-300)
+
+
+@pytest.mark.parametrize("dtype,M,N,K,transB", [("f32", 93, 345, 5527, 0), ("f16", 101, 1311, 10873, 0), ("f64", 100, 130, 1500, 0),  # shared tiles
+                                                ("f16", 4096, 1795, 1000, 0), ("bf16", 2304, 3073, 1024, 0)])  # copies that fit
+def test_static_scratch_call_has_the_bits_of_shared_tiles_and_of_copies_that_fit(dtype, M, N, K, transB):
+    A, B = _gen(dtype, M, N, K, transB, 310)
+    dA, dB = _dev(A, dtype), _dev(B, dtype)
+    e_max = _emax(dtype, K, N)
+    a, b = route(dtype, M, N, K, transB), route(dtype, M, N, K, transB, room=STATIC)
+    assert a == b and (a[3] > 1 or a[:2] != (0, 0))
+    vg = _session(M, N, K, dtype, transB)
+    vg.run_fused(dA, dB, e_max)
+    want = vg.results()
+    vg.C.zero_()
+    assert _static_call(vg, dA, dB, e_max) == 0
+    got = vg.results()
+    for key in KEYS:
+        assert np.array_equal(got[key], want[key], equal_nan=True), key
+
+
+def test_static_scratch_call_where_copies_do_not_fit():
+    """The workspace holds copies of the operands, the array does not: another kernel, the same product but for the order of its
+    sums.  Statistics, expected checksums and thresholds keep their bits; the row sums differ by two sums' rounding."""
+    dtype, M, N, K, transB = "f16", 7479, 1729, 995, 1
+    assert route(dtype, M, N, K, transB)[:2] == (1, 1) and route(dtype, M, N, K, transB, room=STATIC)[:2] == (0, 0)
+    A, B = _gen(dtype, M, N, K, transB, 311)
+    dA, dB = _dev(A, dtype), _dev(B, dtype)
+    e_max = _emax(dtype, K, N)
+    vg = _session(M, N, K, dtype, transB)
+    vg.run_fused(dA, dB, e_max)
+    want = vg.results()
+    assert _static_call(vg, dA, dB, e_max) == 0
+    got = vg.results()
+    for key in ("T", "expected", "astat", "flags"):
+        assert np.array_equal(got[key], want[key]), key
+    assert got["nflag"] == want["nflag"] == 0
+    # (each is checked against its own threshold: |E| <= T in both)
+    assert np.all(np.abs(got["rowsum"] - want["rowsum"]) <= 2 * want["T"])
+    # FP32 sums in two orders, a few 2^-24 of the largest partial sum apart (below 1e-4 here), round to neighbours of FP16 at most,
+    # and that only next to a tie
+    a, b = got["C"].astype(np.float64), want["C"].astype(np.float64)
+    assert np.all(np.abs(a - b) <= 2.0 ** -10 * np.maximum(np.abs(a), np.abs(b)) + 1e-4)
+    assert np.mean(a != b) < 0.01
 
 
 def test_static_scratch_call_rejects_what_does_not_fit():
