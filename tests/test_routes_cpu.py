@@ -90,7 +90,7 @@ def test_workgroups_share_the_k_of_a_tile_where_that_is_faster():
 def test_static_scratch_decides_like_a_workspace_but_for_copies():
     """The call without a workspace (16 MiB and 128 KiB of its own) takes the same kernel, tile and split."""
     r = random.Random(11)
-    problems = [("f32", 3, 200, 7_000_000, 1), ("f64", 2, 128, 9_000_000, 1)]  # S1..S3's partials take most of the array
+    problems = [("f32", 200, 300, k, 1) for k in range(9_700_000, 10_500_000, 100_000)]  # S1..S3's partials take most of the array
     problems += [(r.choice(list(vb.DTYPE_CODE)), r.randint(1, 3000), r.randint(1, 9000), r.randint(1, 20000), r.randint(0, 1))
                  for _ in range(3000)]
     for p in problems:
