@@ -110,7 +110,8 @@ def test_direct_shapes(dtype, M, N, K, transB):
     _check(vg, A, B, _dev(A, dtype), _dev(B, dtype), dtype, M, N, K, transB, ALL)
 
 
-# few tiles and a long K: several workgroups share the K of a tile (every tile shape; K that ends inside a step, and at one)
+# few tiles and a long K: several workgroups share the K of a tile (K that ends inside a step, and at one; mostly tiles of 16 x 32
+# and 16 x 64: test_gpu_shared_and_copied has every shape)
 SPLIT = [
     ("f32", 93, 345, 5527, 0), ("f32", 33, 65, 4096, 0), ("f32", 400, 520, 2500, 1), ("f32", 1, 153, 5193, 1),
     ("bf16", 78, 192, 6871, 0), ("bf16", 161, 128, 5120, 0), ("bf16", 300, 450, 6145, 1), ("f16", 3, 70, 9001, 1),
@@ -352,6 +353,7 @@ OWN = [
     # 64 rows
     ("f32", 2100, 3100, 33, 0), ("f32", 2049, 3329, 70, 1), ("bf16", 2100, 3101, 33, 1), ("f16", 2111, 3073, 131, 0),
     ("f8", 2100, 3100, 190, 0), ("f8e5m2", 2177, 3120, 65, 1), ("bf16", 2041, 3500, 801, 1),
+    ("bf16", 3607, 1665, 407, 1),  # (the size before is one that is copied for the tiled kernels)
 ]
 
 
@@ -457,8 +459,8 @@ def test_tiled_kernels_with_more_sums_at_ragged_sizes(dtype, M, N, K, transB):
     _check(vg, A, B, _dev(A, dtype), _dev(B, dtype), dtype, M, N, K, transB, ("run_weighted", "run_rc", "blocks"))
 
 
-# copies of operands in front of the tiled kernels: of both, of A (rows at odd addresses), of B (an odd number of columns);
-# K one above and below whole steps, rows that share a wavefront, FP8 of every layout
+# around the line from which operands are copied in front of the tiled kernels, on both sides of it (of both, of B alone; K one
+# above and below whole steps, FP8 of every layout); test_gpu_shared_and_copied asks which side a size is on
 COPIED = [("bf16", 2049, 2303, 1001, 1), ("f16", 2100, 2183, 1003, 0), ("bf16", 1801, 4097, 513, 0), ("f16", 4000, 3001, 127, 1),
           ("bf16", 2304, 3073, 1024, 0), ("f16", 7479, 1729, 995, 1), ("f8", 2811, 2754, 2047, 1), ("f8e5m2", 2500, 3000, 1500, 0),
           ("f8", 2304, 3072, 2048, 0)]

@@ -32,6 +32,8 @@ def _differs(a, b):
     ("bf16", 2100, 2184, 256, 0, 600),    # tiled kernels at a ragged size
     ("bf16", 16000, 96, 128, 1, 600),     # 500 tile-rows that share counters, beside 1000 workgroups of the A-side pass
     ("f32", 93, 345, 5527, 0, 800), ("bf16", 161, 128, 5120, 0, 800),          # several workgroups per tile
+    ("f16", 101, 1311, 10873, 0, 400), ("f32", 1093, 100, 799, 0, 600),        # ... of 64 x 64 and of 32 x 64 in eight wavefronts
+    ("bf16", 1738, 2885, 577, 1, 300),    # copied operands
     ("f32", 9000, 500, 260, 0, 400),      # 282 tile-rows with a counter each, the same pass in front
 ])
 def test_back_to_back_fused_launches_repeat_bit_for_bit(dtype, M, N, K, transB, launches):
