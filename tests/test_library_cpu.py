@@ -183,7 +183,7 @@ def test_missing_library_fails_loudly(tmp_path):
 
 
 def test_asm_lint_flags_the_hazards_it_is_built_for():
-    """The build-time hazard pass on the generated assembly of the inline-assembly kernels: each of its three
+    """The build-time hazard pass on the generated assembly of the inline-assembly kernels: each of its
     rules fires on a planted case and stays quiet on the padded form of the same sequence."""
     from paper_2602_08043_amd import asm_lint
 
@@ -209,6 +209,26 @@ def test_asm_lint_flags_the_hazards_it_is_built_for():
     good = kernel("\tv_cndmask_b32_e32 v4, v20, v21, vcc\n\ts_nop 4\n" +
                   asm("v_mfma_f32_16x16x32_bf16 a[0:3], v[4:7], v[8:11], a[0:3]"))
     assert asm_lint.lint(bad) and not asm_lint.lint(good)
+    mfma = asm("v_mfma_f32_16x16x32_bf16 a[4:7], v[4:7], v[8:11], a[4:7]")
+    # a vector instruction, or a store, reads an accumulator that an MFMA from assembly wrote within eight wait states
+    for read in ("\tv_accvgpr_read_b32 v4, a6\n", asm("v_accvgpr_read_b32 v4, a[6]"), "\tds_write_b128 v3, a[4:7]\n",
+                 "\tv_mov_b64_e32 v[2:3], a[6:7]\n"):
+        assert asm_lint.lint(kernel(mfma + read)), read
+        assert asm_lint.lint(kernel(mfma + "\ts_nop 6\n" + read)), read
+        assert not asm_lint.lint(kernel(mfma + "\ts_nop 7\n\ts_nop 1\n" + read)), read
+    assert not asm_lint.lint(kernel(mfma + "\tv_accvgpr_read_b32 v4, a8\n"))  # another accumulator
+    # an MFMA from assembly accumulates onto a register that a vector instruction wrote within four wait states
+    for write in ("\tv_accvgpr_write_b32 a5, v30\n", asm("v_accvgpr_write_b32 a[7], 0")):
+        assert asm_lint.lint(kernel(write + mfma)) and asm_lint.lint(kernel(write + "\ts_nop 2\n" + mfma)), write
+        assert not asm_lint.lint(kernel(write + "\ts_nop 4\n" + mfma)), write
+    assert not asm_lint.lint(kernel("\tv_accvgpr_write_b32 a9, v30\n" + mfma))
+    # a kernel that names the registers of the chains (a[128] to a[255]) has one of them in an instruction of the compiler's
+    chains = asm("v_accvgpr_write_b32 a[128], 0") + asm("v_accvgpr_read_b32 v4, a[255]")
+    assert not asm_lint.lint(kernel(chains + "\tv_accvgpr_write_b32 a127, v1\n\tv_accvgpr_read_b32 v1, a64\n"))
+    for use in ("v_accvgpr_write_b32 a130, v1", "v_accvgpr_read_b32 v1, a255", "v_mfma_f32_16x16x32_bf16 a[126:129], v[4:7], v[8:11], a[126:129]",
+                "ds_write_b128 v3, a[200:203]", "v_accvgpr_mov_b32 a3, a128", "scratch_load_dword a130, off, s32"):
+        assert asm_lint.lint(kernel(chains + "\t" + use + "\n")), use
+        assert not asm_lint.lint(kernel("\t" + use + "\n")), use  # (of a kernel that has no such sums)
 
 
 def test_native_calls_take_every_kind_of_pointer(lib):
