@@ -65,6 +65,7 @@ PASS_ORDER = [("f16", 179, 256, 2560, 0, LAST), ("f32", 7168, 256, 128, 1, LAST)
               ("f8e5m2", 8192, 375, 293, 0, LAST), ("f32", 3072, 128, 10467, 0, LAST),  # 24.9 / 18.6, 190 / 113
               ("bf16", 192, 4995, 2145, 0, FIRST), ("f16", 906, 2467, 1092, 1, FIRST), ("f64", 1536, 3072, 80, 1, FIRST),  # 21.0 / 22.7, 26.5 / 29.2, 36.4 / 37.9
               ("f64", 2147, 768, 125, 1, LAST),  # 28.0 / 20.8
+              ("f16", 1280, 1792, 1134, 0, FIRST), ("f16", 783, 1589, 7788, 0, FIRST),  # 22.4 / 24.3, 84.6 / 89.8
               ("bf16", 261, 9647, 128, 0, FIRST), ("f32", 3259, 7979, 128, 0, FIRST), ("f64", 552, 3165, 392, 1, FIRST)]  # 12.3 / 14.3, 87 / 94, 41.4 / 43.8
 
 
