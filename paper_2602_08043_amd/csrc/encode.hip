@@ -583,16 +583,20 @@ __global__ __launch_bounds__(64 * PANEL_WAVES) void panel_kernel(const void* __r
         }
     }
     __syncthreads();
-    if (tid < COLS) {  // (within the first wavefront) the wavefronts' in order
+    if (tid < COLS) {  // (within the first wavefront) the wavefronts', sums in pairs and those in pairs: one after the other,
+                       // rounding errors of 2500 rows of FP16 were 1.06 2^-24 sqrt(rows); in two launches, by slabs, 0.84
         const int at = tid / V * V, first = panel * COLS + at, k = min(first, K - V) + tid % V;
-        acc_t v[4] = {red[0][0][tid], red[0][1][tid], red[0][2][tid], 0};
-        if constexpr (W) v[3] = red[0][3][tid];
+        acc_t v[4] = {0, -type_max<acc_t>(), type_max<acc_t>(), 0};
 #pragma unroll
-        for (int q = 1; q < PANEL_WAVES; ++q) {
-            v[0] += red[q][0][tid];
-            v[1] = fmax(v[1], red[q][1][tid]);
-            v[2] = fmin(v[2], red[q][2][tid]);
-            if constexpr (W) v[3] += red[q][3][tid];
+        for (int q = 0; q < PANEL_WAVES; q += 4) {
+            const auto four = [&](int i) { return (red[q][i][tid] + red[q + 1][i][tid]) + (red[q + 2][i][tid] + red[q + 3][i][tid]); };
+            v[0] += four(0);
+            if constexpr (W) v[3] += four(3);
+#pragma unroll
+            for (int j = q; j < q + 4; ++j) {
+                v[1] = fmax(v[1], red[j][1][tid]);
+                v[2] = fmin(v[2], red[j][2][tid]);
+            }
         }
         const bool own = k >= first && k < K;  // (not the columns that a lane moved back shares with the one before it)
         if (own) out.column(k, N, v[0], v[1], v[2], v[3]);

@@ -276,3 +276,21 @@ def test_column_passes_are_exact_on_small_integers(dtype, cols, rows):
     S1, S2, S3 = vg.SA.cpu().numpy()
     T = 3 * np.abs(mean) * S1 + 2.5 * np.sqrt(3 * mean * mean * S2 + 9 * var * S3) + 2.5 * np.sqrt(3 * var * S2)
     assert np.all(np.abs(vg.T_col.cpu().numpy() * 2.0 ** 10 - T) <= 1e-6 * T)
+
+
+@pytest.mark.parametrize("weighted", [False, True])
+def test_column_passes_round_no_more_than_a_tree_of_sums(weighted):
+    """A lane sums 10 of 2500 rows of FP16, exact but for the last bits, and so are the sums of 16 lanes.  What the 16 wavefronts
+    have is added in pairs, these in pairs, and those one after the other.  A level of pairs adds c^2 (2^-24)^2 rows to the mean
+    square of the error, c^2 being 0.18 for roundings of normal values, n values one after the other (2 + .. + n) / n of that: 4.25
+    such terms, 0.87 2^-24 sqrt(rows); all one after the other it would be 8.4, 1.23.  Weighted, all additions round, with the sum
+    of the squares of the weights for rows: 5.4 terms in a lane and four levels of lanes more, 1.57 together; 1.79 otherwise."""
+    cols, rows = 1000, 2500
+    X = wl.rng(77, 42).standard_normal((rows, cols)).astype(np.float16)
+    vg = _session(3, rows, cols, "f16", 1)
+    dX = torch.from_numpy(X).cuda()
+    print(f"column passes, rounding errors, weighted {weighted}", flush=True)
+    vg.encode_weighted(dX) if weighted else vg.encode(dX)
+    w = np.arange(1, rows + 1, dtype=np.float64) if weighted else np.ones(rows)
+    error = (vg.Be2 if weighted else vg.Be).cpu().numpy() - w @ X.astype(np.float64)
+    assert np.sqrt(np.mean(error ** 2)) <= (1.57 if weighted else 1.0) * 2.0 ** -24 * np.sqrt(np.sum(w * w))
