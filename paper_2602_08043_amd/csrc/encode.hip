@@ -804,7 +804,7 @@ static void panel_launch(const void* src, int cols, int rows, int64_t ld, const 
     // 16-bit and FP8: half as wide for long columns, where the chip holds all panels at once (32 bytes of a row against 64:
     // BF16 1536 x 4096 9.7 against 12.5, 4096 x 512 8.4 / 7.2, 8192 x 4096 20.6 / 16.2; FP8 4096 x 2048 10.8 / 13.0, x 64
     // 8.0 / 7.0); FP8, with the most arithmetic to a byte, a quarter (16 bytes: 4096 x 4096 9.2 against 11.0 with the fold
-    // deferred, 4096 x 2048 with a fold of its own 11.3 / 10.6)
+    // deferred; but 4096 columns of 2048, with a fold of its own, 11.3 / 10.6)
     if constexpr (Elem<T>::vec == 16) {
         if (cols <= 256 * Panel<T, 1>::COLS && rows >= std::max(1024, cols / 4 * 3)) return launch(std::integral_constant<int, 1>());
     }
@@ -931,8 +931,6 @@ int threshold_dispatch(const vabft_problem* p, const void* dA, const void* d_Be,
 // the row of A, column k of A (M entries) plays the row of B, and M replaces N.
 // ---------------------------------------------------------------------------
 
-// Per column n of a K x N row-major B: fold the row-slab partials (sum, max, min, dot with c1 A) in slab
-// order and evaluate the column threshold.
 // Column threshold and expected column checksum from (sum, max, min, dot with c1 A) of a column of B
 template <typename acc_t> struct PanelThreshold {
     const acc_t* eA;
@@ -960,6 +958,8 @@ template <typename acc_t> struct PanelThreshold {
     }
 };
 
+// Per column n of a K x N row-major B: fold the row-slab partials (sum, max, min, dot with c1 A) in slab
+// order and evaluate the column threshold.
 template <typename acc_t>
 __global__ __launch_bounds__(256) void threshold_cols_finish_kernel(const acc_t* __restrict__ part, int nsplit,
                                                                     int N, int K, int M, const double* __restrict__ SA,

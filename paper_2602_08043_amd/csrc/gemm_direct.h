@@ -19,7 +19,7 @@
 // 8192 x 1024 x 1024 5.7e-7, now 2.9e-7).
 //
 // Where there are few tiles and a long K, several workgroups share the K of a tile (SPLIT): the last to arrive adds their tiles
-// up and goes on as if it had computed the sum alone.  FP32 93 x 345 x 5527 52 us, now 15.5.
+// up and goes on as if it had computed the sum alone.  FP32 93 x 345 x 5527 51 us, now 15.6 (fused call inside a HIP graph).
 //
 // Operands pass from global memory through registers into LDS rows of the wavefront's own and back as MFMA fragments.
 // Loading fragments straight into registers needs no LDS, but puts 16 rows side by side in a quarter of a wavefront,

@@ -2,8 +2,8 @@
 // any size but whole tiles -- laid out once for the GEMM behind: 16-bit elements (FP8 as FP16: exact), rows of whole 128-byte
 // lines, zeros behind their end.  What is read is a wavefront's pieces of 16 bytes in a row wherever they start; what is
 // written is aligned.  Bound by memory, and at a few MB by the launch: 1021 x 2047 and 2047 x 1531 BF16 4.4 us.  The direct
-// kernels read each such piece as two lines, once per tile: BF16 3708 x 1873 x 10496 354 us, with this pass and the tiled
-// kernel 165.
+// kernels read each such piece as two lines, once per tile: BF16 3708 x 1873 x 10496 352 us, with this pass and the tiled
+// kernel 151.
 //
 // With the A-side pass fused the rows of A, copied or not, give their statistics, expected checksum and threshold on the way
 // (row_threshold.h, the same bits as the pass by itself).

@@ -75,7 +75,8 @@ def test_place_of_the_a_side_pass():
 
 
 # measured fused calls, not shared / shared (us)
-SHARED = [("f32", 93, 345, 5527, 0), ("f64", 48, 192, 3840, 1), ("bf16", 78, 192, 6871, 0), ("bf16", 1280, 99, 6882, 1),  # 52 / 20, 40 / 11, 23 / 10, 29 / 21
+SHARED = [("f32", 93, 345, 5527, 0), ("f64", 48, 192, 3840, 1),  # 51 / 16, 39 / 11
+          ("bf16", 78, 192, 6871, 0), ("bf16", 1280, 99, 6882, 1),  # 23 / 10, 29 / 20
           ("f16", 4, 1681, 5803, 1), ("f16", 1, 107, 5065, 1), ("bf16", 1792, 80, 3169, 1)]  # 18.2 / 12.1, 13.3 / 9.8, 22.4 / 18.4
 NOT_SHARED = [("bf16", 40, 512, 1280, 1), ("f64", 683, 80, 231, 1), ("f8", 48, 6400, 9065, 1),  # 7.9 / 8.5, 12.0 / 12.8, 30 / 36
               ("f16", 30, 3584, 1974, 1)]  # 10.2 / 11.0
