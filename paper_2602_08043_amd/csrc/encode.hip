@@ -780,34 +780,21 @@ size_t encode_workspace_bytes(const vabft_problem* p) {
 // 13.7 / 13.7, 8661 x 4096 17.5 / 19.6; FP32 1536 x 1024 8.5 / 6.7, 4096 x 4096 19.7 / 15.3, 96 x 4096 8.3 / 8.7, 8301 x 7262
 // 56 / 78, 4890 x 2902 (306 panels) 20 / 23; FP64 96 x 1024 8.1 / 6.7, 4126 x 1024 (258 panels) 15.2 / 17.8.  600 problems of up
 // to 12000 x 11264 take 0.82 (BF16), 0.76 (FP8), 0.90 and 0.91 (FP64) of the time of two launches, six of them longer.
-// (With the matrix in a cache.  From memory, own fold and deferred: BF16 4080 x 4096 19.7 and 16.0 / 16.7 and 12.9, 2032 x 3584
-// 13.8 and 11.0 / 13.2 and 10.7, FP8 2032 x 4096 14.3 and 11.4 / 14.6 and 12.0, FP32 1008 x 2560 10.8 and 8.6 / 11.4 and 9.6.)
-// Rows at a pitch of whole 512 bytes meet in the same channels of the memory, and of a row a panel has 16 to 64 bytes: BF16 4096 x
-// 4096 18.7 and 14.5 / 18.6 and 16.5, x 3072 17.3 and 13.4 / 14.8 and 13.0, 3072 x 3584 16.2 and 12.5 / 17.0 and 15.0, x 2048 13.5
-// and 9.7 / 11.9 and 10.0; FP8 2048 x 4096 14.2 and 11.3 / 15.2 and 13.7, x 3072 13.2 and 10.2 / 12.2 and 10.3, 2560 x 4096 15.0
-// and 11.8 / 15.7 and 13.4, 4096 x 4096 17.7 and 13.5 / 16.1 and 14.1; FP32 1024 x 2048 10.4 and 8.2 / 11.0 and 9.6, x 1536 9.7 and
-// 7.7 / 9.2 and 7.5, 4096 x 4096 22.3 and 18.1 / 21.3 and 19.7; FP64 2048 x 2048 15.2 and 12.6 / 15.3 and 13.5; and with more panels
-// than units BF16 5120 x 3072 18.4 and 12.9 / 17.8 and 15.6, FP8 6144 x 4096 21.1 and 15.3 / 20.0 and 18.1, FP32 6144 x 2048 20.9 and
-// 14.8 / 20.5 and 18.6, but 8192 x 1536 24.6 and 17.1 / 18.0 and 14.8.  Both folds take the same launches, for the same bits: one
-// where the two together gain.
+// (With the matrix in a cache.  From memory rows at a pitch of whole 512 bytes meet in the same channels, and of a row a panel has
+// 16 to 64 bytes.  One launch in times of two, own fold and deferred, from memory / in a cache: BF16 1024 x 3072 1.18 and 1.29 / 0.87
+// and 0.83, 1536 x 3584 1.27 and 1.44 / 0.86 and 0.84, 2560 x 4096 1.26 and 1.45 / 0.82 and 0.77, but 4096 x 4096 1.00 and 1.13 / 0.74
+// and 0.65; FP8 2048 x 5120 1.23 and 1.34 / 0.89 and 0.87, x 4096 1.10 and 1.23 / 0.86 and 0.84; FP32 1536 x 2560 1.15 and 1.28 / 0.85
+// and 0.83, x 2048 1.06 and 1.19 / 0.85 and 0.81.  Both folds take the same launches, for the same bits: one where the four gain
+// together.  At other pitches they do up to the lines for a cache: BF16 4080 x 4096 0.85 and 0.80 from memory.)
 template <typename T> static bool panel_pays(int64_t cols, int64_t rows, int64_t ld) {
     constexpr int V = Elem<T>::vec;
-    int64_t most = 1024 + cols * 3 / 5, most_whole = most - 300;
-    if (V == 4) {
-        most = std::min(2048 + cols * 3 / 5, std::max<int64_t>(2048, 1536 + cols * 4 / 5));
-        most_whole = cols <= 1024 ? 2560 - cols : cols / 5;
-        if (cols > 1024 && cols <= 4096) most_whole = std::max(std::min<int64_t>(1024 + cols / 2, 2048), 2 * cols - 4608);
+    int64_t most = V == 4 ? 2048 + cols * 3 / 5 : 1024 + cols * 3 / 5;
+    if (V == 8) most = cols <= 4096 ? 2560 + cols * 7 / 10 : 3072;
+    if (V == 16) most = cols <= 4096 ? 4096 + cols * 4 / 5 : std::min<int64_t>(2048 + cols * 3 / 5, 5000);
+    if (V >= 4 && ld * Elem<T>::bytes >= 1536 && ld * Elem<T>::bytes % 512 == 0) {
+        const int64_t least = V == 4 ? 2048 : V == 8 ? 2560 : 4096, more = V == 4 ? 512 : V == 8 ? 1024 : 1536;
+        most = std::min(most, std::max(least, more + cols));
     }
-    if (V == 8) {
-        most = cols <= 4096 ? 2560 + cols * 7 / 10 : 3072;
-        most_whole = cols <= 4096 ? std::max(std::min<int64_t>(2560, 3072 - cols / 2), cols - 1024) : cols - 3072;
-    }
-    if (V == 16) {
-        most = std::min<int64_t>(2048 + cols * 3 / 5, 5000);
-        if (cols <= 4096) most = std::min(4096 + cols * 4 / 5, std::max(5632 - cols, 1536 + cols));
-        most_whole = cols <= 4096 ? std::max(5120 - cols, cols) : cols / 2 - 512;
-    }
-    if (ld * Elem<T>::bytes >= 1536 && ld * Elem<T>::bytes % 512 == 0) most = std::min(most, most_whole);
     if (cols > 8192) most = V >= 8 ? 1024 : 256;
     const int64_t panels = (cols - 1) / Panel<T, V == 2 ? 8 : 4>::COLS + 1, rounds = (panels + 255) / 256;
     const bool tail = rounds > 1 && 5 * 256 * rounds > (V == 2 ? 6 : 7) * panels && rows > 256;
