@@ -337,9 +337,11 @@ constexpr int LAUNCH_MOST = 1 << 22;
 // Folds the partial row sums of `rows` rows from row0 on and compares; SUB groups of R neighbouring threads share the
 // tile-columns of R rows, so that a wavefront reads whole pieces of lines: loads for other workgroups' partials pass the
 // caches by, one request per piece.  Against SUB neighbouring threads per row: 16 x 4096 x 4096 14.4 -> 11.7 us, 1024^3
-// 12.6 -> 12.0, 40 x 11008 x 4096 (three batches of loads) 23.6 -> 24.3.  This code runs once, at the end: a variant with
-// 32 loads in flight, twice the instructions to fetch, loses more than it saves (256^3 FP32 8.7 -> 9.8).  Returns the
-// number of flagged rows.
+// 12.6 -> 12.0.  This code runs once, at the end, in one workgroup: every instruction of it is time of the launch (1.3 ns, a taken
+// branch more), so it has no branch per load, a batch of loads of about the size that there are partials for, all in flight at
+// once, and one barrier for the fold.  With 16 guarded loads to a batch and a barrier per halving (fused calls in a graph):
+// FP32 256^3 8.3 -> 7.8 us, BF16 1024^3 10.9 -> 10.0, 7 x 1792 x 512 7.2 -> 6.3, 24 x 11008 x 4096 (172 partials to a row)
+// 20.3 -> 18.7.  Returns the number of flagged rows to the first wavefront.
 template <typename T, int R, int SUB>
 __device__ __forceinline__ int direct_compare(const DirectArgs& d, int row0, int rows, unsigned char* smem) {
     using acc_t = typename Elem<T>::acc_t;
@@ -348,41 +350,81 @@ __device__ __forceinline__ int direct_compare(const DirectArgs& d, int row0, int
     const bool act = r < rows, wsum = d.wsum != 0;
     const int gi = row0 + (act ? r : 0);
     // (with the partials in flight, not a round trip behind their fold)
-    const acc_t* ex = reinterpret_cast<const acc_t*>(g.expected) + gi;
-    const acc_t* th = reinterpret_cast<const acc_t*>(g.T) + gi;
-    const acc_t want = d.stat_blocks ? ld_agent(ex) : *ex, t = d.stat_blocks ? ld_agent(th) : *th;
+    const acc_t want = ld_agent(reinterpret_cast<const acc_t*>(g.expected) + gi);
+    const acc_t t = ld_agent(reinterpret_cast<const acc_t*>(g.T) + gi);
+    const int64_t step = (int64_t)SUB * g.M;
+    int64_t at = (int64_t)sub * g.M;  // of this thread's next partial, from its row's first
     acc_t s4[4] = {0, 0, 0, 0}, w4[4] = {0, 0, 0, 0};
-    for (int t0 = 0; t0 < g.tiles_n; t0 += 16 * SUB) {
-        acc_t v[16], v2[16];
+    const auto batch = [&](auto u_c, int t0) __attribute__((always_inline)) {
+        constexpr int U = decltype(u_c)::value;
+        int left = g.tiles_n - t0 - sub;  // (opaque, so that no other batch's conditions are worked out in front of this one)
+        asm volatile("" : "+v"(left));
+        const auto load = [&](const void* partials, acc_t* v) __attribute__((always_inline)) {
+            const acc_t* const row = reinterpret_cast<const acc_t*>(partials) + gi;
+            int64_t a = at;
 #pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            v[j] = v2[j] = 0;
-            if (t0 + j * SUB < g.tiles_n) {  // (the same for every thread)
-                const int64_t at = (int64_t)min(t0 + j * SUB + sub, g.tiles_n - 1) * g.M + gi;
-                v[j] = ld_agent(reinterpret_cast<const acc_t*>(g.rowpart) + at);
-                if (wsum) v2[j] = ld_agent(reinterpret_cast<const acc_t*>(g.rowpart2) + at);
-            }
+            for (int j = 0; j < U; ++j, a += step) v[j] = ld_agent(row + (j * SUB < left ? a : 0));
+        };
+        acc_t v[U], v2[U];
+        load(g.rowpart, v);
+        if (wsum) {
+            load(g.rowpart2, v2);
+#pragma unroll
+            for (int j = 0; j < U; ++j) w4[j & 3] += j * SUB < left ? v2[j] : (acc_t)0;
         }
 #pragma unroll
-        for (int j = 0; j < 16; ++j)
-            if (t0 + j * SUB + sub < g.tiles_n) {
-                s4[j & 3] += v[j];
-                w4[j & 3] += v2[j];
-            }
-    }
+        for (int j = 0; j < U; ++j) s4[j & 3] += j * SUB < left ? v[j] : (acc_t)0;
+        at += U * step;
+    };
+    // (as many as leave the kernel the registers that the product takes, and with them its wavefronts per SIMD: FP64 2048^3 with
+    // 24 281 us, with 8 272)
+    constexpr int MOST = sizeof(acc_t) == 8 || R * SUB > 256 ? 8 : R == 32 ? 24 : 16;
+    if (g.tiles_n <= 2 * SUB)
+        batch(std::integral_constant<int, 2>(), 0);
+    else if (MOST > 8 && g.tiles_n <= 8 * SUB)
+        batch(std::integral_constant<int, 8>(), 0);
+    else
+        for (int t0 = 0; t0 < g.tiles_n; t0 += MOST * SUB) batch(std::integral_constant<int, MOST>(), t0);
     acc_t s = (s4[0] + s4[1]) + (s4[2] + s4[3]), s2 = (w4[0] + w4[1]) + (w4[2] + w4[3]);
     if constexpr (SUB > 1) {
-        acc_t* const red = reinterpret_cast<acc_t*>(smem);  // [2][SUB][R]
-        red[threadIdx.x] = s;
-        red[SUB * R + threadIdx.x] = s2;
-        __syncthreads();
-#pragma unroll
-        for (int half = SUB / 2; half > 0; half /= 2) {
-            if (sub < half) {
-                red[threadIdx.x] = s += red[threadIdx.x + half * R];
-                red[SUB * R + threadIdx.x] = s2 += red[SUB * R + threadIdx.x + half * R];
+        // the groups of a wavefront, then the wavefronts (a power of two of them)
+        constexpr int NW = R * SUB / 64;
+        static_assert(R <= 64 && R >= 16, "");
+        const auto in_wave = [](acc_t q) {
+            acc_t a, b;
+            if constexpr (R <= 32) {
+                lane_exchange<32, WAVE>(q, a, b);
+                q = a + b;
             }
-            __syncthreads();
+            if constexpr (R <= 16) {
+                lane_exchange<16, WAVE>(q, a, b);
+                q = a + b;
+            }
+            return q;
+        };
+        acc_t* const red = reinterpret_cast<acc_t*>(smem);  // [2][NW][R]
+        const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
+        s = in_wave(s);
+        if (wsum) s2 = in_wave(s2);
+        if (wave > 0 && lane < R) {
+            red[wave * R + lane] = s;
+            if (wsum) red[(NW + wave) * R + lane] = s2;
+        }
+        __syncthreads();
+        if (wave == 0) {
+            const auto over_waves = [&](acc_t q, const acc_t* from) {
+                acc_t x[NW];
+                x[0] = q;
+#pragma unroll
+                for (int w = 1; w < NW; ++w) x[w] = from[w * R + r];
+#pragma unroll
+                for (int h = 1; h < NW; h *= 2)
+#pragma unroll
+                    for (int w = 0; w + h < NW; w += 2 * h) x[w] += x[w + h];
+                return x[0];
+            };
+            s = over_waves(s, red);
+            if (wsum) s2 = over_waves(s2, red + NW * R);
         }
     }
     int f = 0;
@@ -394,7 +436,7 @@ __device__ __forceinline__ int direct_compare(const DirectArgs& d, int row0, int
         reinterpret_cast<acc_t*>(g.E)[gi] = e;
         g.flags[gi] = f;
     }
-    return __syncthreads_count(f);
+    return SUB > 1 ? (int)__popcll(__ballot(f)) : __syncthreads_count(f);
 }
 
 // The last workgroup of tile-row bm to arrive (GEMM tiles and, with the A-side pass fused, its workgroups) compares the
@@ -409,9 +451,12 @@ __device__ __forceinline__ void direct_tile_row_check(const DirectArgs& d, int b
     const GemmArgs& g = d.g;
     constexpr int SHARE = S::NT / S::BM;  // tile-rows of a shared counter
     const bool shared = g.tiles_n <= 4 || (g.tiles_m * g.tiles_n <= 64 && g.M <= S::NT);
-    const int tile_rows = shared ? SHARE : 1, at = bm / tile_rows, row0 = at * tile_rows * S::BM;
-    const int counters = (g.tiles_m + tile_rows - 1) / tile_rows, rows = min(tile_rows * S::BM, g.M - row0);
-    const int arrivals = (rows + S::BM - 1) / S::BM * g.tiles_n + (d.stat_blocks ? (rows + d.stat_rows - 1) / d.stat_rows : 0);
+    static_assert((SHARE & (SHARE - 1)) == 0, "");
+    const int tile_rows = shared ? SHARE : 1, at = shared ? bm / SHARE : bm, row0 = at * tile_rows * S::BM;
+    const int counters = shared ? (g.tiles_m + SHARE - 1) / SHARE : g.tiles_m, rows = min(tile_rows * S::BM, g.M - row0);
+    // (a workgroup of the A-side pass has a power of two of rows)
+    const int arrivals = (rows + S::BM - 1) / S::BM * g.tiles_n +
+                         (d.stat_blocks ? (rows + d.stat_rows - 1) >> __builtin_ctz((unsigned)d.stat_rows) : 0);
     __builtin_amdgcn_s_waitcnt(0);  // this wavefront's partials are performed
     __syncthreads();
     int before = 0;
@@ -488,8 +533,13 @@ __device__ __forceinline__ void direct_stats(const DirectArgs& d, int block, dou
 // ANY: for rows so far apart that 32 bits do not hold a tile's byte offsets, and for rows of under 16 bytes.
 // D: steps in flight from global memory.
 // SPLIT: d.split workgroups share the K of a tile (kernels of their own: the code in the others, skipped, cost short calls 3 %).
+// Wavefronts to a SIMD that the compiler has to leave registers for: FP64 with K shared takes 128 of them (eight wavefronts, B N x K) or
+// 168, two more being a workgroup less on the compute unit.
+template <typename T, int TRANSB, int WVK, bool ANY, bool SPLIT> constexpr int direct_min_waves() {
+    return std::is_same<T, double>::value && WVK > 1 && !ANY && !SPLIT ? (WVK == 8 && TRANSB ? 4 : 3) : 2;
+}
 template <typename T, int TRANSB, int MF, int NF, int WVK, int WN, int D, bool ANY, bool SPLIT>
-__global__ __launch_bounds__(64 * WVK * WN, 2) void gemm_direct_kernel(const DirectArgs d) {
+__global__ __launch_bounds__(64 * WVK * WN, (direct_min_waves<T, TRANSB, WVK, ANY, SPLIT>())) void gemm_direct_kernel(const DirectArgs d) {
     using S = gd::Shape<T, TRANSB, MF, NF, WVK, WN>;
     using OFF = typename std::conditional<ANY, uint64_t, uint32_t>::type;
     using Tr = gd::Traits<T>;
@@ -757,12 +807,12 @@ __global__ __launch_bounds__(64 * WVK * WN, 2) void gemm_direct_kernel(const Dir
     // The column of C that column j of the tile holds, or -1.  With B stored K x N, a group of V columns that would
     // cross the end of the row was read from N - V on: its first columns repeat those of the group before.
     const bool nedge = col0 + S::BNW > g.N;  // wavefront-uniform
-    auto column_of = [&](int j) {
-        if (!nedge) return col0 + j;
+    auto edge_column = [&](int j) {  // (where nedge)
         if (TRANSB) return col0 + j < g.N ? col0 + j : -1;
         const int c = col0 + j / V * V, back = c - max(0, min(c, g.N - V));
         return j % V >= back && c - back + j % V < g.N ? c - back + j % V : -1;
     };
+    auto column_of = [&](int j) { return nedge ? edge_column(j) : col0 + j; };
     // first of the NF columns of a lane's results r (FP64 results sit at index lq + 4 r of the fragment, the others at
     // 4 lq + r)
     const auto frag_col = [&](int r) { return (sizeof(acc_t) == 8 ? lq + 4 * r : 4 * lq + r) * NF; };
@@ -925,17 +975,21 @@ __global__ __launch_bounds__(64 * WVK * WN, 2) void gemm_direct_kernel(const Dir
         if (verify) {
             acc_t x[EPT];
 #pragma unroll
-            for (int e = 0; e < EPT; ++e) x[e] = (!nedge || column_of(tc + e) >= 0) && gi < g.M ? v[0][e] : (acc_t)0;
+            for (int e = 0; e < EPT; ++e) x[e] = v[0][e];
+            if (nedge) {
+#pragma unroll
+                for (int e = 0; e < EPT; ++e) x[e] = edge_column(tc + e) >= 0 ? x[e] : (acc_t)0;
+            }
             if (csum) {
 #pragma unroll
-                for (int e = 0; e < EPT; ++e) src[e] = x[e];
+                for (int e = 0; e < EPT; ++e) src[e] = gi < g.M ? x[e] : (acc_t)0;
             }
             acc_t s2 = 0;
             if (wsum) {
                 // weights from the thread's first column on; that column's own weight goes with the plain sum below
 #pragma unroll
                 for (int e = 0; e < EPT; ++e)
-                    s2 = fma((acc_t)(nedge ? max(0, column_of(tc + e)) - (col0 + tc) : e), x[e], s2);
+                    s2 = fma((acc_t)(nedge ? max(0, edge_column(tc + e)) - (col0 + tc) : e), x[e], s2);
             }
 #pragma unroll
             for (int w = 1; w < EPT; w *= 2)
