@@ -197,6 +197,15 @@ int vabft_gemm_verified_fused(const vabft_problem* p, const void* dA, const void
                               vabft_inject_rec* d_injlog, int32_t* d_ninj, void* d_workspace,
                               size_t workspace_bytes, void* stream);
 
+/* vabft_encode and vabft_gemm_verified_fused behind each other, for a B that is new: S1..S3 are folded by the second
+ * launch, and written to d_S [3] unless that is NULL.  The bits are those of vabft_encode (d_S = NULL) and
+ * vabft_gemm_verified_fused (d_S = NULL). */
+int vabft_encode_gemm_fused(const vabft_problem* p, const void* dA, const void* dB, void* dC, void* d_Be,
+                            void* d_bstat, double* d_S, double e_max, double c_sigma, void* d_astat,
+                            void* d_expected, void* d_T, const vabft_inject* inj, void* d_rowsum, void* d_E,
+                            int32_t* d_flags, int32_t* d_nflag, vabft_inject_rec* d_injlog, int32_t* d_ninj,
+                            void* d_workspace, size_t workspace_bytes, void* stream);
+
 /* The fused call for callers that cannot allocate device memory: code under HIP graph capture, tight serving
  * loops, harnesses that forbid hipMalloc.  Same inputs and outputs as vabft_gemm_verified_fused, and the same results
  * bit for bit but for large products of 16-bit or FP8 rows that are not aligned to 16 bytes (FP8: of other sizes than

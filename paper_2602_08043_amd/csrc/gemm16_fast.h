@@ -773,7 +773,7 @@ __device__ __forceinline__ void gemm16_fast_tile(const GemmArgs& g, int bm, int 
             bek[j] = (j < n_slots && tid < 128) ? Be[128 * (bn + j * g.tiles_n) + tid] : 0.f;
         float* const s_scale = reinterpret_cast<float*>(smem + L::SCALE);
         // S1..S3 still in partials: every workgroup folds them here, under the latency of its first tile
-        if (!g.S) fold_s_partials_to_lds(g.s_partial, g.s_nparts, tid, reinterpret_cast<double*>(smem + L::S_RED));
+        if (g.s_nparts) fold_s_partials_to_lds(g.s_partial, g.s_nparts, tid, reinterpret_cast<double*>(smem + L::S_RED));
         // sigma = 2^(exponent(max |Be|) - 13): |Be / sigma| < 2^14 (BF16 shares FP32's exponent range: sigma = 1)
         float inv_sigma = 1.f;
         if constexpr (std::is_same<T, f16_t>::value) {

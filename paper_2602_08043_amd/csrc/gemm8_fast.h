@@ -208,7 +208,7 @@ __global__ __launch_bounds__(256) void gemm8_fast_kernel(const GemmArgs g) {
             cache[j * 256 + tid] = (k >= 0 && k < g.K) ? Be[k] : 0.f;
         }
         // S1..S3 still in partials: every workgroup folds them here, under the latency of its first tile
-        if (!g.S) fold_s_partials_to_lds(g.s_partial, g.s_nparts, tid, reinterpret_cast<double*>(smem + S_RED_OFFSET));
+        if (g.s_nparts) fold_s_partials_to_lds(g.s_partial, g.s_nparts, tid, reinterpret_cast<double*>(smem + S_RED_OFFSET));
     }
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();

@@ -514,13 +514,15 @@ __device__ __forceinline__ void direct_stats_rows(const DirectArgs& d, int block
 template <typename T, typename S>
 __device__ __forceinline__ void direct_stats(const DirectArgs& d, int block, double* s_red, int* s_last, unsigned char* smem) {
     const GemmArgs& g = d.g;
-    if (!g.S) {
+    const bool fold = g.s_nparts != 0;
+    if (fold) {
         fold_s_partials_to_lds(g.s_partial, g.s_nparts, threadIdx.x, s_red);
         __syncthreads();
+        if (block == 0 && threadIdx.x < 3 && g.S) g.S[threadIdx.x] = folded_s(s_red, threadIdx.x);
     }
     // (ahead of the row: not one more round trip behind it)
-    const double S1 = g.S ? g.S[0] : folded_s(s_red, 0), S2 = g.S ? g.S[1] : folded_s(s_red, 1),
-                 S3 = g.S ? g.S[2] : folded_s(s_red, 2);
+    const double S1 = fold ? folded_s(s_red, 0) : g.S[0], S2 = fold ? folded_s(s_red, 1) : g.S[1],
+                 S3 = fold ? folded_s(s_red, 2) : g.S[2];
     if (d.stat_rows == S::NW)
         direct_stats_rows<T, S, 64, 4>(d, block, S1, S2, S3);
     else if (d.stat_rows == 2 * S::NW)

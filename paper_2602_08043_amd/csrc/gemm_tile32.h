@@ -60,7 +60,7 @@ constexpr int LDS_BYTES_FUSED = S_RED_OFFSET + 128;
 // workgroup takes the tile-row's arrival ticket, and the last one to arrive combines the partials of all
 // tile-columns in a fixed order, evaluates Algorithm 1 in double precision (FUSED) and writes rowsum, E, flags
 // (section 2.2, Eq. abft-check); the last row block writes nflag.  gi = the row this thread owns; s_red = the
-// workgroup's fold of the S1..S3 partials in LDS (used when g.S is null).
+// workgroup's fold of the S1..S3 partials in LDS (used when g.s_nparts is not zero).
 template <bool WSUM, bool FUSED, bool EDGE = false>
 __device__ __forceinline__ void gemm_tile_row_check(const GemmArgs& g, unsigned char* smem, const double* s_red, int bm,
                                                     int gi_in, int tid) {
@@ -93,9 +93,15 @@ __device__ __forceinline__ void gemm_tile_row_check(const GemmArgs& g, unsigned 
         double S1 = 0, S2 = 0, S3 = 0;
         float expv = 0, thr = 0;
         if (FUSED) {
-            S1 = g.S ? g.S[0] : folded_s(s_red, 0);
-            S2 = g.S ? g.S[1] : folded_s(s_red, 1);
-            S3 = g.S ? g.S[2] : folded_s(s_red, 2);
+            const bool fold = g.s_nparts != 0;
+            S1 = fold ? folded_s(s_red, 0) : g.S[0];
+            S2 = fold ? folded_s(s_red, 1) : g.S[1];
+            S3 = fold ? folded_s(s_red, 2) : g.S[2];
+            if (fold && g.S && bm == 0 && tid == 0) {
+                g.S[0] = S1;
+                g.S[1] = S2;
+                g.S[2] = S3;
+            }
         } else {
             expv = reinterpret_cast<const float*>(g.expected)[gi];
             thr = reinterpret_cast<const float*>(g.T)[gi];

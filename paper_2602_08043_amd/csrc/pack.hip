@@ -14,7 +14,7 @@ namespace vabft {
 
 struct PackStats {  // the A-side pass; Be null: none
     const float* Be;
-    const double* S;  // null: fold s_partial[s_nparts][3]
+    double* S;  // with s_nparts > 0 an output, or null: the sums are folded from s_partial[s_nparts][3]
     const double* s_partial;
     int32_t s_nparts, N;
     double e_max, c_sigma;
@@ -98,12 +98,14 @@ template <typename T> __global__ __launch_bounds__(256) void pack_kernel(const P
     if ((int)blockIdx.x >= a.blocks) {
         pack_rows<T, false>(b, blockIdx.x - a.blocks, q, 0, 0, 0);
     } else if (q.Be) {
-        if (!q.S) {
+        const bool fold = q.s_nparts != 0;
+        if (fold) {
             fold_s_partials_to_lds(q.s_partial, q.s_nparts, threadIdx.x, s_red);
             __syncthreads();
+            if (blockIdx.x == 0 && threadIdx.x < 3 && q.S) q.S[threadIdx.x] = folded_s(s_red, threadIdx.x);
         }
-        const double S1 = q.S ? q.S[0] : folded_s(s_red, 0), S2 = q.S ? q.S[1] : folded_s(s_red, 1),
-                     S3 = q.S ? q.S[2] : folded_s(s_red, 2);
+        const double S1 = fold ? folded_s(s_red, 0) : q.S[0], S2 = fold ? folded_s(s_red, 1) : q.S[1],
+                     S3 = fold ? folded_s(s_red, 2) : q.S[2];
         pack_rows<T, true>(a, blockIdx.x, q, S1, S2, S3);
     } else {
         pack_rows<T, false>(a, blockIdx.x, q, 0, 0, 0);
@@ -125,9 +127,9 @@ int pack_dispatch(int dtype, const PackArgs& a0, const PackArgs& b0, const Fused
     PackStats q = {};
     if (fused) {
         q.Be = (const float*)fused->d_Be;
-        q.S = fused->d_S;
+        q.S = fused->d_S ? const_cast<double*>(fused->d_S) : fused->d_S_out;
         q.s_partial = s_partial;
-        q.s_nparts = s_nparts;
+        q.s_nparts = fused->d_S ? 0 : s_nparts;
         q.N = N;
         q.e_max = fused->e_max;
         q.c_sigma = fused->c_sigma;

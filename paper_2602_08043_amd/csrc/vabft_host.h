@@ -80,8 +80,8 @@ struct GemmArgs {
     // fused A-side statistics (Algorithm 1 for the rows of A, inside the GEMM)
     int32_t fused_stats;
     const void* Be;   // [K] acc
-    const double* S;  // [3]; null: fold s_partial[s_nparts][3] (left by an encode with a deferred fold)
-    const double* s_partial;
+    double* S;        // [3]; with s_nparts > 0 an output, or null: the sums are folded from s_partial
+    const double* s_partial;  // [s_nparts][3], left by an encode with a deferred fold
     int32_t s_nparts;
     double e_max, c_sigma;
     void* astat;      // [M][3] acc, output
@@ -105,7 +105,8 @@ struct GemmArgs {
 size_t gemm_workspace_bytes(const vabft_problem* p);
 struct FusedArgs {  // non-null d_Be selects the fused A-side path
     const void* d_Be;
-    const double* d_S;  // null: S1..S3 are still the partials of the preceding encode
+    const double* d_S;  // null: S1..S3 are still the partials of the preceding encode,
+    double* d_S_out;    // and what they fold to is wanted here (may be null)
     double e_max, c_sigma;
     void* d_astat;
 };

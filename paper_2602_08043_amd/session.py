@@ -150,10 +150,18 @@ class VerifiedGemm:
         self.gemm(A, B, 1, inj)
 
     def run_fused(self, A, B, e_max=None, c_sigma=2.5, inj=None, defer_S: bool = False):
-        """One pass of the whole path in two calls: encode, fused threshold + verified GEMM.
-        defer_S: S1..S3 travel as partials through the workspace and are folded inside the second call."""
-        self.encode(B, defer_S)
-        self.gemm_fused(A, B, e_max, c_sigma, inj, deferred_S=defer_S)
+        """One pass of the whole path: encode, fused threshold + verified GEMM.  S1..S3 travel as partials through the
+        workspace and are folded inside the second launch, to self.S as well unless defer_S."""
+        if e_max is None:
+            e_max = vb.vabft_default_emax(self.dtype, self.K, self.N)
+        self.e_max = e_max
+        vb.vabft_encode_gemm_fused(self.problem, A.data_ptr(), B.data_ptr(), self.C,
+                                   self.Be, self.bstat, None if defer_S else self.S, e_max,
+                                   c_sigma, self.astat, self.expected,
+                                   self.T, inj,
+                                   self.rowsum, self.E, self.flags,
+                                   self.nflag, self.injlog, self.ninj,
+                                   self.ws, self.ws_bytes, self._stream())
 
     # ---- weighted checksum, localisation, correction ---------------------------------
     def encode_weighted(self, B: torch.Tensor):
