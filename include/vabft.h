@@ -206,6 +206,16 @@ int vabft_encode_gemm_fused(const vabft_problem* p, const void* dA, const void* 
                             int32_t* d_flags, int32_t* d_nflag, vabft_inject_rec* d_injlog, int32_t* d_ninj,
                             void* d_workspace, size_t workspace_bytes, void* stream);
 
+/* vabft_encode_weighted, vabft_threshold_weighted, vabft_gemm_verified_weighted and vabft_locate_correct behind each
+ * other, without injector: what they compute, in two launches where C's rows are aligned to 8 bytes and the product
+ * runs on the kernels of small tiles. */
+int vabft_encode_gemm_weighted(const vabft_problem* p, const void* dA, const void* dB, void* dC, void* d_Be,
+                               void* d_Be2, void* d_bstat, double* d_S, double e_max, double c_sigma,
+                               void* d_astat, void* d_expected, void* d_expected2, void* d_T, void* d_rowsum,
+                               void* d_rowsum2, void* d_E, int32_t* d_flags, int32_t* d_nflag, int32_t correct,
+                               int32_t* d_loc, void* d_delta, int32_t* d_ncorrected, void* d_workspace,
+                               size_t workspace_bytes, void* stream);
+
 /* The fused call for callers that cannot allocate device memory: code under HIP graph capture, tight serving
  * loops, harnesses that forbid hipMalloc.  Same inputs and outputs as vabft_gemm_verified_fused, and the same results
  * bit for bit but for large products of 16-bit or FP8 rows that are not aligned to 16 bytes (FP8: of other sizes than

@@ -21,6 +21,7 @@ DTYPE_CODE = {"f64": VABFT_F64, "f32": VABFT_F32, "f16": VABFT_F16, "bf16": VABF
 
 EXPORTS = ("vabft_status_string", "vabft_workspace_bytes", "vabft_workspace_init", "vabft_default_emax",
            "vabft_encode", "vabft_threshold", "vabft_gemm_verified", "vabft_gemm_verified_fused", "vabft_encode_gemm_fused",
+           "vabft_encode_gemm_weighted",
            "vabft_encode_weighted", "vabft_threshold_weighted", "vabft_gemm_verified_weighted",
            "vabft_locate_correct", "vabft_default_emax_offline", "vabft_check_offline",
            "vabft_encode_a", "vabft_threshold_cols", "vabft_gemm_verified_rc",
@@ -103,6 +104,9 @@ def load(path: str | None = None):
                                             c_double, c_double, c_void_p, c_void_p, c_void_p, POINTER(Inject),
                                             c_void_p, c_void_p, c_void_p, c_void_p, c_void_p, c_void_p, c_void_p,
                                             c_size_t, c_void_p]
+    lib.vabft_encode_gemm_weighted.restype = ctypes.c_int
+    lib.vabft_encode_gemm_weighted.argtypes = ([POINTER(Problem)] + [c_void_p] * 7 + [c_double, c_double] + [c_void_p] * 9 +
+                                               [c_int32] + [c_void_p] * 4 + [c_size_t, c_void_p])
     lib.vabft_probe_read.restype = ctypes.c_int
     lib.vabft_probe_read.argtypes = [c_void_p, c_size_t, c_void_p, c_void_p]
     lib.vabft_probe_mfma.restype = ctypes.c_int
@@ -240,6 +244,15 @@ def vabft_encode_gemm_fused(p: Problem, dA, dB, dC, d_Be, d_bstat, d_S, e_max, c
                                        d_expected, d_T, inj, d_rowsum, d_E,
                                        d_flags, d_nflag, d_injlog, d_ninj, d_workspace, workspace_bytes, stream)
     return _check(rc, "vabft_encode_gemm_fused", check)
+
+
+def vabft_encode_gemm_weighted(p: Problem, dA, dB, dC, d_Be, d_Be2, d_bstat, d_S, e_max, c_sigma, d_astat, d_expected,
+                               d_expected2, d_T, d_rowsum, d_rowsum2, d_E, d_flags, d_nflag, correct, d_loc, d_delta,
+                               d_ncorrected, d_workspace, workspace_bytes, stream=None, check=True) -> int:
+    rc = load().call_encode_gemm_weighted(p, dA, dB, dC, d_Be, d_Be2, d_bstat, d_S, e_max, c_sigma, d_astat, d_expected,
+                                          d_expected2, d_T, d_rowsum, d_rowsum2, d_E, d_flags, d_nflag, int(correct), d_loc,
+                                          d_delta, d_ncorrected, d_workspace, workspace_bytes, stream)
+    return _check(rc, "vabft_encode_gemm_weighted", check)
 
 
 def vabft_probe_mfma(dtype: str, iters: int, d_out, stream=None) -> float:

@@ -14,7 +14,7 @@ OBJ = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libvabft.so")
 CALLS = os.path.join(PKG, "_calls.so")
 
-DIRECT = [f"gemm_direct_{t}.hip" for t in ("bf16", "f16", "f8", "bf8", "f32", "f64")]
+DIRECT = [f"gemm_direct_{w}{t}.hip" for t in ("bf16", "f16", "f8", "bf8", "f32", "f64") for w in ("", "w_")]
 SOURCES = DIRECT + ["gemm16_bf16_nn.hip", "gemm16_bf16_nt.hip", "gemm16_f16_nn.hip", "gemm16_f16_nt.hip",
                     "gemm8_f8_nt.hip", "gemm8_bf8_nt.hip", "api.hip", "encode.hip", "blocks.hip", "pack.hip", "probe.hip"]
 

@@ -221,6 +221,18 @@ template <typename T, bool STREAM, typename acc_t> __device__ __forceinline__ vo
         put<STREAM>(reinterpret_cast<v_t*>(p), x);
     }
 }
+// 8 bytes of stored elements from as many accumulator values
+template <typename T, typename acc_t> __device__ __forceinline__ uint64_t word8(const acc_t* v) {
+    uint64_t w;
+    if constexpr (std::is_same<T, double>::value || std::is_same<T, float>::value) {
+        __builtin_memcpy(&w, v, 8);
+    } else {
+        using h2 = typename std::conditional<std::is_same<T, bf16_t>::value, bf16x2_t, f16x2_t>::type;
+        const h2 x[2] = {__builtin_convertvector((f32x2_t{v[0], v[1]}), h2), __builtin_convertvector((f32x2_t{v[2], v[3]}), h2)};
+        __builtin_memcpy(&w, x, 8);
+    }
+    return w;
+}
 template <typename T, typename acc_t> __device__ __forceinline__ typename Traits<T>::out_t to_out(acc_t v) {
     if constexpr (std::is_same<T, double>::value || std::is_same<T, float>::value)
         return v;
@@ -342,12 +354,14 @@ constexpr int LAUNCH_MOST = 1 << 22;
 // once, and one barrier for the fold.  With 16 guarded loads to a batch and a barrier per halving (fused calls in a graph):
 // FP32 256^3 8.3 -> 7.8 us, BF16 1024^3 10.9 -> 10.0, 7 x 1792 x 512 7.2 -> 6.3, 24 x 11008 x 4096 (172 partials to a row)
 // 20.3 -> 18.7.  Returns the number of flagged rows to the first wavefront.
-template <typename T, int R, int SUB>
-__device__ __forceinline__ int direct_compare(const DirectArgs& d, int row0, int rows, unsigned char* smem) {
+// W: weighted sums too; with d.wsum == 2 flagged rows are localised and corrected here (locate_row), and corrected receives how
+// many.
+template <typename T, bool W, int R, int SUB>
+__device__ __forceinline__ int direct_compare(const DirectArgs& d, int row0, int rows, unsigned char* smem, int& corrected) {
     using acc_t = typename Elem<T>::acc_t;
     const GemmArgs& g = d.g;
     const int r = threadIdx.x % R, sub = threadIdx.x / R;
-    const bool act = r < rows, wsum = d.wsum != 0;
+    const bool act = r < rows;
     const int gi = row0 + (act ? r : 0);
     // (with the partials in flight, not a round trip behind their fold)
     const acc_t want = ld_agent(reinterpret_cast<const acc_t*>(g.expected) + gi);
@@ -367,7 +381,7 @@ __device__ __forceinline__ int direct_compare(const DirectArgs& d, int row0, int
         };
         acc_t v[U], v2[U];
         load(g.rowpart, v);
-        if (wsum) {
+        if constexpr (W) {
             load(g.rowpart2, v2);
 #pragma unroll
             for (int j = 0; j < U; ++j) w4[j & 3] += j * SUB < left ? v2[j] : (acc_t)0;
@@ -405,10 +419,10 @@ __device__ __forceinline__ int direct_compare(const DirectArgs& d, int row0, int
         acc_t* const red = reinterpret_cast<acc_t*>(smem);  // [2][NW][R]
         const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
         s = in_wave(s);
-        if (wsum) s2 = in_wave(s2);
+        if constexpr (W) s2 = in_wave(s2);
         if (wave > 0 && lane < R) {
             red[wave * R + lane] = s;
-            if (wsum) red[(NW + wave) * R + lane] = s2;
+            if constexpr (W) red[(NW + wave) * R + lane] = s2;
         }
         __syncthreads();
         if (wave == 0) {
@@ -424,18 +438,38 @@ __device__ __forceinline__ int direct_compare(const DirectArgs& d, int row0, int
                 return x[0];
             };
             s = over_waves(s, red);
-            if (wsum) s2 = over_waves(s2, red + NW * R);
+            if constexpr (W) s2 = over_waves(s2, red + NW * R);
         }
     }
-    int f = 0;
+    int f = 0, fixed = 0;
     if (act && sub == 0) {
         const acc_t e = want - s;
         f = !(fabs(e) <= t);
         reinterpret_cast<acc_t*>(g.rowsum)[gi] = s;
-        if (wsum) reinterpret_cast<acc_t*>(g.rowsum2)[gi] = s2;
+        if constexpr (W) reinterpret_cast<acc_t*>(g.rowsum2)[gi] = s2;
         reinterpret_cast<acc_t*>(g.E)[gi] = e;
         g.flags[gi] = f;
+        if constexpr (W) {
+            if (d.wsum == 2) {
+                int column = -1;
+                acc_t by = 0;
+                if (f) {
+                    const acc_t want2 = ld_agent(reinterpret_cast<const acc_t*>(g.w.expected2) + gi);
+                    column = locate_row<acc_t>(want, want2, s, s2, g.N, by);
+                    if (g.w.correct && column >= 0) {
+                        // (all of the row is in memory: its tiles were stored past the caches, before they arrived)
+                        using C = CElem<T>;
+                        auto* const c = reinterpret_cast<typename C::store_t*>(g.C) + (int64_t)gi * g.ldc + column;
+                        C::put_agent(c, C::get_agent(c) - by);
+                        fixed = 1;
+                    }
+                }
+                g.w.loc[gi] = column;
+                reinterpret_cast<acc_t*>(g.w.delta)[gi] = by;
+            }
+        }
     }
+    if constexpr (W) corrected = SUB > 1 ? (int)__popcll(__ballot(fixed)) : __syncthreads_count(fixed);
     return SUB > 1 ? (int)__popcll(__ballot(f)) : __syncthreads_count(f);
 }
 
@@ -446,7 +480,7 @@ __device__ __forceinline__ int direct_compare(const DirectArgs& d, int row0, int
 // Every thread of every workgroup calls this after its partials are written.  store_c
 // comes behind the arrival (in front of it, the wait for the partials would be one for the stores of C as well) and, in the
 // workgroup that compares, behind that.
-template <typename T, typename S, typename F>
+template <typename T, typename S, bool W, typename F>
 __device__ __forceinline__ void direct_tile_row_check(const DirectArgs& d, int bm, int* s_last, unsigned char* smem, F store_c) {
     const GemmArgs& g = d.g;
     constexpr int SHARE = S::NT / S::BM;  // tile-rows of a shared counter
@@ -463,19 +497,32 @@ __device__ __forceinline__ void direct_tile_row_check(const DirectArgs& d, int b
     if (threadIdx.x == 0 && arrivals > 1) before = atomicAdd(&g.tickets[at * g.ticket_stride], 1);
     // (workgroups that come by the thousand store C while the arrival is on its way; where there are few, the compare is
     // what the launch ends with and does not wait for the stores)
+    const bool stored = W && d.wsum == 2;  // C is in memory already
     if constexpr (S::OWN) store_c();
     if (threadIdx.x == 0) *s_last = before == arrivals - 1;
     __syncthreads();
     if (!*s_last) {
-        if constexpr (!S::OWN) store_c();
+        if constexpr (!S::OWN)
+            if (!stored) store_c();
         return;
     }
-    const int cnt = rows > S::BM ? direct_compare<T, S::NT, 1>(d, row0, rows, smem)
-                                 : direct_compare<T, S::BM, SHARE>(d, row0, rows, smem);
+    int fixed = 0;
+    const int cnt = rows > S::BM ? direct_compare<T, W, S::NT, 1>(d, row0, rows, smem, fixed)
+                                 : direct_compare<T, W, S::BM, SHARE>(d, row0, rows, smem, fixed);
     if (threadIdx.x == 0) {
         if (arrivals > 1) __hip_atomic_store(&g.tickets[at * g.ticket_stride], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (counters == 1) {
             *g.d_nflag = cnt;
+            if (stored) *g.w.ncorrected = fixed;
+        } else if (stored) {
+            // finished compares, corrected rows and flagged rows in one word (of 2^20 rows at most)
+            unsigned long long* done = done_counter(g);
+            const unsigned long long old = atomicAdd(done, (1ull << 42) | (unsigned long long)fixed << 21 | (unsigned long long)cnt);
+            if ((int)(old >> 42) == counters - 1) {
+                *g.d_nflag = (int)(old & 0x1fffff) + cnt;
+                *g.w.ncorrected = (int)(old >> 21 & 0x1fffff) + fixed;
+                __hip_atomic_store(done, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
         } else {
             // one 64-bit atomic counts the finished compares (high word) and the flagged rows (low word); whoever
             // completes the count publishes nflag and leaves the counter zero
@@ -487,19 +534,21 @@ __device__ __forceinline__ void direct_tile_row_check(const DirectArgs& d, int b
             }
         }
     }
-    if constexpr (!S::OWN) store_c();
+    if constexpr (!S::OWN)
+        if (!stored) store_c();
 }
 
 // The A-side pass inside the GEMM launch: d.stat_rows rows per workgroup, a wavefront or (short rows) 32 or 16 lanes of one
 // per row
-template <typename T, typename S, int LW, int NL>
+template <typename T, typename S, bool W, int LW, int NL>
 __device__ __forceinline__ void direct_stats_rows(const DirectArgs& d, int block, double S1, double S2, double S3) {
     using acc_t = typename Elem<T>::acc_t;
     const GemmArgs& g = d.g;
     const int lane = threadIdx.x % LW, m = block * d.stat_rows + threadIdx.x / LW;
     // (lanes behind the last row read it again: the exchanges need every lane)
     const char* row = reinterpret_cast<const char*>(g.A) + (int64_t)min(m, g.M - 1) * g.lda * Elem<T>::bytes;
-    const RowSums<acc_t> r = row_sums<T, false, NL, LW>(row, g.K, lane, reinterpret_cast<const acc_t*>(g.Be), nullptr);
+    const RowSums<acc_t> r = row_sums<T, W, NL, LW>(row, g.K, lane, reinterpret_cast<const acc_t*>(g.Be),
+                                                    W ? reinterpret_cast<const acc_t*>(g.w.Be2) : nullptr);
     if (lane == 0 && m < g.M) {
         double mu;
         const acc_t t = (acc_t)row_threshold(r, g.K, g.N, S1, S2, S3, g.e_max, g.c_sigma, mu);
@@ -509,9 +558,10 @@ __device__ __forceinline__ void direct_stats_rows(const DirectArgs& d, int block
         astat[2] = (acc_t)mu;
         st_agent(reinterpret_cast<acc_t*>(const_cast<void*>(g.expected)) + m, r.dot);
         st_agent(reinterpret_cast<acc_t*>(const_cast<void*>(g.T)) + m, t);
+        if constexpr (W) st_agent(reinterpret_cast<acc_t*>(g.w.expected2) + m, r.dot2);
     }
 }
-template <typename T, typename S>
+template <typename T, typename S, bool W>
 __device__ __forceinline__ void direct_stats(const DirectArgs& d, int block, double* s_red, int* s_last, unsigned char* smem) {
     const GemmArgs& g = d.g;
     const bool fold = g.s_nparts != 0;
@@ -524,24 +574,27 @@ __device__ __forceinline__ void direct_stats(const DirectArgs& d, int block, dou
     const double S1 = fold ? folded_s(s_red, 0) : g.S[0], S2 = fold ? folded_s(s_red, 1) : g.S[1],
                  S3 = fold ? folded_s(s_red, 2) : g.S[2];
     if (d.stat_rows == S::NW)
-        direct_stats_rows<T, S, 64, 4>(d, block, S1, S2, S3);
+        direct_stats_rows<T, S, W, 64, 4>(d, block, S1, S2, S3);
     else if (d.stat_rows == 2 * S::NW)
-        direct_stats_rows<T, S, 32, 1>(d, block, S1, S2, S3);
+        direct_stats_rows<T, S, W, 32, 1>(d, block, S1, S2, S3);
     else
-        direct_stats_rows<T, S, 16, 1>(d, block, S1, S2, S3);
-    direct_tile_row_check<T, S>(d, block * d.stat_rows / S::BM, s_last, smem, [] {});
+        direct_stats_rows<T, S, W, 16, 1>(d, block, S1, S2, S3);
+    direct_tile_row_check<T, S, W>(d, block * d.stat_rows / S::BM, s_last, smem, [] {});
 }
 
 // ANY: for rows so far apart that 32 bits do not hold a tile's byte offsets, and for rows of under 16 bytes.
 // D: steps in flight from global memory.
 // SPLIT: d.split workgroups share the K of a tile (kernels of their own: the code in the others, skipped, cost short calls 3 %).
-// Wavefronts to a SIMD that the compiler has to leave registers for: FP64 with K shared takes 128 of them (eight wavefronts, B N x K) or
-// 168, two more being a workgroup less on the compute unit.
-template <typename T, int TRANSB, int WVK, bool ANY, bool SPLIT> constexpr int direct_min_waves() {
-    return std::is_same<T, double>::value && WVK > 1 && !ANY && !SPLIT ? (WVK == 8 && TRANSB ? 4 : 3) : 2;
+// W: position-weighted row sums too (d.wsum; kernels of their own for the same reason).
+// Wavefronts to a SIMD that the compiler has to leave registers for: a few registers more would be a workgroup less on the compute
+// unit.
+template <typename T, int TRANSB, int MF, int WVK, bool ANY, bool SPLIT> constexpr int direct_min_waves() {
+    constexpr bool f64 = std::is_same<T, double>::value;
+    if (WVK == 8 && (MF == 1 || (f64 && TRANSB && !SPLIT))) return 4;
+    return f64 && WVK > 1 && !ANY && !SPLIT ? 3 : 2;
 }
-template <typename T, int TRANSB, int MF, int NF, int WVK, int WN, int D, bool ANY, bool SPLIT>
-__global__ __launch_bounds__(64 * WVK * WN, (direct_min_waves<T, TRANSB, WVK, ANY, SPLIT>())) void gemm_direct_kernel(const DirectArgs d) {
+template <typename T, int TRANSB, int MF, int NF, int WVK, int WN, int D, bool ANY, bool SPLIT, bool W>
+__global__ __launch_bounds__(64 * WVK * WN, (direct_min_waves<T, TRANSB, MF, WVK, ANY, SPLIT>())) void gemm_direct_kernel(const DirectArgs d) {
     using S = gd::Shape<T, TRANSB, MF, NF, WVK, WN>;
     using OFF = typename std::conditional<ANY, uint64_t, uint32_t>::type;
     using Tr = gd::Traits<T>;
@@ -570,7 +623,7 @@ __global__ __launch_bounds__(64 * WVK * WN, (direct_min_waves<T, TRANSB, WVK, AN
     }
     static_assert(!SPLIT || (!S::OWN && !ANY), "");
     if (block < d.stat_blocks) {
-        direct_stats<T, S>(d, block, s_red, s_last, smem);
+        direct_stats<T, S, W>(d, block, s_red, s_last, smem);
         return;
     }
     const int nth = block - d.stat_blocks;
@@ -867,7 +920,8 @@ __global__ __launch_bounds__(64 * WVK * WN, (direct_min_waves<T, TRANSB, WVK, AN
     }
 
     // ---- epilogue: a thread owns EPT consecutive columns of a row -----------------------------------------------
-    const bool wsum = d.wsum != 0, csum = d.csum != 0;
+    constexpr bool wsum = W;
+    const bool csum = d.csum != 0;
     using out_t = typename Tr::out_t;
     constexpr int EPT = S::EPT, PASSES = S::PASSES;
     static_assert(EPT * sizeof(acc_t) < 16 || EPT * sizeof(acc_t) % 16 == 0, "LDS vectors");
@@ -1005,7 +1059,7 @@ __global__ __launch_bounds__(64 * WVK * WN, (direct_min_waves<T, TRANSB, WVK, AN
     }
     if (verify && has_sum && row0 + srow < g.M) {
         st_agent(reinterpret_cast<acc_t*>(g.rowpart) + (int64_t)part * g.M + row0 + srow, rs);
-        if (wsum) st_agent(reinterpret_cast<acc_t*>(g.rowpart2) + (int64_t)part * g.M + row0 + srow, rs2);
+        if constexpr (W) st_agent(reinterpret_cast<acc_t*>(g.rowpart2) + (int64_t)part * g.M + row0 + srow, rs2);
     }
     if constexpr (S::OWN) {
         if (!inject) to_tile();
@@ -1016,6 +1070,29 @@ __global__ __launch_bounds__(64 * WVK * WN, (direct_min_waves<T, TRANSB, WVK, AN
 #pragma unroll
         for (int p = 0; p < PASSES; ++p) store_row(row0 + p * S::RPP + tr, v[p]);
     };
+    if constexpr (W && !S::OWN) {
+        // Flagged rows are corrected by the workgroup that compares them: C has to be in memory by then, not in this XCD's cache.
+        // (rows of C are aligned to 8 bytes; whole groups of them, and what the edge leaves by elements)
+        if (d.wsum == 2 && row0 + tr < g.M) {
+            out_t* const c = reinterpret_cast<out_t*>(g.C) + (int64_t)(row0 + tr) * g.ldc;
+            constexpr int G = 8 / (int)sizeof(out_t);
+#pragma unroll
+            for (int e = 0; e < EPT; e += G) {
+                if constexpr (EPT % G == 0) {
+                    if (!nedge) {
+                    __hip_atomic_store(reinterpret_cast<uint64_t*>(c + col0 + tc + e), gd::word8<T>(v[0] + e), __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_AGENT);
+                        continue;
+                    }
+                }
+#pragma unroll
+                for (int q = 0; q < G && e + q < EPT; ++q) {
+                    const int gj = column_of(tc + e + q);
+                    if (gj >= 0) CElem<T>::put_agent(reinterpret_cast<typename CElem<T>::store_t*>(c) + gj, v[0][e + q]);
+                }
+            }
+        }
+    }
     const bool check = verify && !g.block_mode;
     if (!check) store_c();
     if (!verify) return;
@@ -1031,15 +1108,15 @@ __global__ __launch_bounds__(64 * WVK * WN, (direct_min_waves<T, TRANSB, WVK, AN
                 reinterpret_cast<acc_t*>(g.colpart)[(int64_t)bm * g.N + gj] = (q[0] + q[1]) + (q[2] + q[3]);
         }
     }
-    if (check) direct_tile_row_check<T, S>(d, bm, s_last, smem, store_c);
+    if (check) direct_tile_row_check<T, S, W>(d, bm, s_last, smem, store_c);
 }
 
-template <typename T, int TRANSB, int MF, int NF, int WVK, int D, bool ANY = false, int WN = 1, bool SPLIT = false>
+template <bool W, typename T, int TRANSB, int MF, int NF, int WVK, int D, bool ANY = false, int WN = 1, bool SPLIT = false>
 static int gemm_direct_launch_shape(const DirectArgs& d, hipStream_t st) {
     using S = gd::Shape<T, TRANSB, MF, NF, WVK, WN>;
     if constexpr (!SPLIT && WVK > 1 && !ANY)
-        if (d.split > 1) return gemm_direct_launch_shape<T, TRANSB, MF, NF, WVK, D, ANY, WN, true>(d, st);
-    auto kern = gemm_direct_kernel<T, TRANSB, MF, NF, WVK, WN, D, ANY, SPLIT>;
+        if (d.split > 1) return gemm_direct_launch_shape<W, T, TRANSB, MF, NF, WVK, D, ANY, WN, true>(d, st);
+    auto kern = gemm_direct_kernel<T, TRANSB, MF, NF, WVK, WN, D, ANY, SPLIT, W>;
     if constexpr (S::LDS > 65536) {
         static bool attr_set = false;
         if (!attr_set) {
@@ -1059,26 +1136,26 @@ static int gemm_direct_launch_shape(const DirectArgs& d, hipStream_t st) {
 }
 
 // shape: see DirectShape.  Two steps are in flight from global memory where the registers allow it.
-template <typename T, int TRANSB> static int gemm_direct_launch_tb(const DirectArgs& d, int shape, hipStream_t st) {
+template <bool W, typename T, int TRANSB> static int gemm_direct_launch_tb(const DirectArgs& d, int shape, hipStream_t st) {
     constexpr int NS = TRANSB ? 2 : 4;  // a lane reads four columns of a K x N B
     switch (shape) {
-        case DIRECT_16: return gemm_direct_launch_shape<T, TRANSB, 1, NS, 8, TRANSB ? 2 : 1>(d, st);
-        case DIRECT_32: return gemm_direct_launch_shape<T, TRANSB, 2, NS, 8, TRANSB ? 2 : 1>(d, st);
-        case DIRECT_32W: return gemm_direct_launch_shape<T, TRANSB, 2, 4, 4, 1>(d, st);
-        case DIRECT_ANY: return gemm_direct_launch_shape<T, TRANSB, 2, 4, 4, 1, true>(d, st);
+        case DIRECT_16: return gemm_direct_launch_shape<W, T, TRANSB, 1, NS, 8, TRANSB ? 2 : 1>(d, st);
+        case DIRECT_32: return gemm_direct_launch_shape<W, T, TRANSB, 2, NS, 8, TRANSB ? 2 : 1>(d, st);
+        case DIRECT_32W: return gemm_direct_launch_shape<W, T, TRANSB, 2, 4, 4, 1>(d, st);
+        case DIRECT_ANY: return gemm_direct_launch_shape<W, T, TRANSB, 2, 4, 4, 1, true>(d, st);
         case DIRECT_64:
             if constexpr (!std::is_same<T, double>::value)
-                return gemm_direct_launch_shape<T, TRANSB, 4, 4, 4, std::is_same<T, float>::value || !TRANSB ? 1 : 2>(d, st);
+                return gemm_direct_launch_shape<W, T, TRANSB, 4, 4, 4, std::is_same<T, float>::value || !TRANSB ? 1 : 2>(d, st);
             break;
-        case DIRECT_OWN32: return gemm_direct_launch_shape<T, TRANSB, 2, 4, 1, 1, false, 4>(d, st);
+        case DIRECT_OWN32: return gemm_direct_launch_shape<W, T, TRANSB, 2, 4, 1, 1, false, 4>(d, st);
         case DIRECT_OWN64:
             if constexpr (!std::is_same<T, double>::value)
-                return gemm_direct_launch_shape<T, TRANSB, 4, 4, 1, 1, false, 4>(d, st);
+                return gemm_direct_launch_shape<W, T, TRANSB, 4, 4, 1, 1, false, 4>(d, st);
     }
     return VABFT_EINVAL;
 }
-template <typename T> static int gemm_direct_launch_t(const DirectArgs& d, int shape, int transB, hipStream_t st) {
-    return transB ? gemm_direct_launch_tb<T, 1>(d, shape, st) : gemm_direct_launch_tb<T, 0>(d, shape, st);
+template <bool W, typename T> static int gemm_direct_launch_t(const DirectArgs& d, int shape, int transB, hipStream_t st) {
+    return transB ? gemm_direct_launch_tb<W, T, 1>(d, shape, st) : gemm_direct_launch_tb<W, T, 0>(d, shape, st);
 }
 
 }  // namespace vabft

@@ -2,6 +2,6 @@
 #include "gemm_direct.h"
 namespace vabft {
 int gemm_direct_launch_f32(const DirectArgs& d, int shape, int transB, hipStream_t st) {
-    return gemm_direct_launch_t<float>(d, shape, transB, st);
+    return gemm_direct_launch_t<false, float>(d, shape, transB, st);
 }
 }  // namespace vabft

@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "vabft.h"
 
 namespace vabft {
@@ -220,6 +222,59 @@ __device__ __forceinline__ double folded_s(const double* s_red, int q) {
 #pragma unroll
     for (int w = 0; w < 4; ++w) v += s_red[q * 4 + w];
     return v;
+}
+
+// one stored element of C (FP16 for an FP8 problem), read and written in the accumulator type; _agent: past the caches
+template <typename STORE, typename T> struct CElemOf {
+    using store_t = STORE;
+    using acc_t = typename Elem<T>::acc_t;
+    static __device__ __forceinline__ acc_t from(store_t x) {
+        if constexpr (std::is_same<STORE, acc_t>::value)
+            return x;
+        else
+            return Elem<T>::to_acc(x);
+    }
+    static __device__ __forceinline__ store_t to(acc_t v) {
+        if constexpr (std::is_same<STORE, acc_t>::value)
+            return v;
+        else
+            return Elem<T>::from_acc(v);
+    }
+    static __device__ __forceinline__ acc_t get(const store_t* p) { return from(*p); }
+    static __device__ __forceinline__ void put(store_t* p, acc_t v) { *p = to(v); }
+    static __device__ __forceinline__ acc_t get_agent(const store_t* p) {
+        if constexpr (sizeof(store_t) == 2)
+            return from(__hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        else
+            return ld_agent(p);
+    }
+    static __device__ __forceinline__ void put_agent(store_t* p, acc_t v) {
+        if constexpr (sizeof(store_t) == 2)
+            __hip_atomic_store(p, to(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        else
+            st_agent(p, v);
+    }
+};
+template <typename T> struct CElem;
+template <> struct CElem<bf16_t> : CElemOf<uint16_t, bf16_t> {};
+template <> struct CElem<f16_t> : CElemOf<uint16_t, f16_t> {};
+template <> struct CElem<f8_t> : CElemOf<uint16_t, f16_t> {};
+template <> struct CElem<bf8_t> : CElemOf<uint16_t, f16_t> {};
+template <> struct CElem<float> : CElemOf<float, float> {};
+template <> struct CElem<double> : CElemOf<double, double> {};
+
+// The column of a flagged row's error under the single-error-per-row model (section 2.2): D1 = C^{r1'} - C^{r1}, D2 = C^{r2'} -
+// C^{r2}, column D2 / D1 - 1 for the linear weights w(k) = k + 1; -2 where that is not finite, further than 0.25 from an integer or
+// outside 0..N-1 (more than one error, or an error too close to the rounding noise of the weighted sums).  by: D1.
+template <typename acc_t>
+__device__ __forceinline__ int locate_row(acc_t expected, acc_t expected2, acc_t rowsum, acc_t rowsum2, int N, acc_t& by) {
+    const double d1 = (double)rowsum - (double)expected, d2 = (double)rowsum2 - (double)expected2;
+    by = (acc_t)d1;
+    if (d1 != 0.0 && isfinite(d1) && isfinite(d2)) {
+        const double q = d2 / d1 - 1.0, j = rint(q);
+        if (isfinite(q) && fabs(q - j) <= 0.25 && j >= 0.0 && j <= (double)(N - 1)) return (int)j;
+    }
+    return -2;
 }
 
 template <typename T> __device__ __forceinline__ T type_max();

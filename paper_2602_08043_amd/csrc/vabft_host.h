@@ -57,6 +57,18 @@ struct InjectArgs {
     int32_t* d_ninj;
 };
 
+// a weighted call of a direct kernel, in the injector's place (which is off): what its A-side pass forms too, and, with
+// DirectArgs::wsum == 2, what the localisation of flagged rows writes
+struct WeightedArgs {
+    int32_t mode;      // InjectArgs::mode: 0
+    int32_t correct;
+    const void* Be2;   // [K] acc
+    void* expected2;   // [M] acc
+    int32_t* loc;      // [M]
+    void* delta;       // [M] acc
+    int32_t* ncorrected;
+};
+
 struct GemmArgs {
     const void* A;
     const void* B;
@@ -66,7 +78,10 @@ struct GemmArgs {
     int32_t tiles_m, tiles_n;
     void* rowpart;    // [tiles_n][M] acc: per-tile-column partial row sums
     int32_t* d_nflag; // number of flagged rows
-    InjectArgs inj;
+    union {
+        InjectArgs inj;
+        WeightedArgs w;
+    };
     // in-kernel compare-and-flag (whole-tile kernels): the last workgroup to finish a
     // tile-row combines the partials of that row block
     const void* expected;  // [M] acc: input, or output when fused_stats
@@ -109,6 +124,7 @@ struct FusedArgs {  // non-null d_Be selects the fused A-side path
     double* d_S_out;    // and what they fold to is wanted here (may be null)
     double e_max, c_sigma;
     void* d_astat;
+    const WeightedArgs* w = nullptr;  // a weighted call that localises (and corrects) behind the check
 };
 // d_rowsum2 non-null selects the kernels that also form the position-weighted row sums; cols non-null those
 // that also form the column sums and compares them
@@ -156,7 +172,7 @@ enum DirectShape { DIRECT_NONE = -1, DIRECT_16 = 0, DIRECT_32 = 1, DIRECT_32W = 
                    DIRECT_OWN32 = 5, DIRECT_OWN64 = 6 };
 struct DirectArgs {
     GemmArgs g;
-    int8_t verify, wsum, csum;   // the check; with position-weighted row sums; with column sums
+    int8_t verify, wsum, csum;   // the check; with position-weighted row sums (2: localisation too); with column sums
     int8_t mirror;               // 0: the A-side pass's are the launch's first workgroups; -1: its last, the order being reversed
     int32_t stat_blocks;         // > 0: that many workgroups run that pass,
     int16_t stat_rows;           // of so many rows each: one, two or four per wavefront
@@ -174,6 +190,13 @@ int gemm_direct_launch_f8(const DirectArgs& d, int shape, int transB, hipStream_
 int gemm_direct_launch_bf8(const DirectArgs& d, int shape, int transB, hipStream_t st);
 int gemm_direct_launch_f32(const DirectArgs& d, int shape, int transB, hipStream_t st);
 int gemm_direct_launch_f64(const DirectArgs& d, int shape, int transB, hipStream_t st);
+// with position-weighted row sums (DirectArgs::wsum)
+int gemm_direct_launch_w_bf16(const DirectArgs& d, int shape, int transB, hipStream_t st);
+int gemm_direct_launch_w_f16(const DirectArgs& d, int shape, int transB, hipStream_t st);
+int gemm_direct_launch_w_f8(const DirectArgs& d, int shape, int transB, hipStream_t st);
+int gemm_direct_launch_w_bf8(const DirectArgs& d, int shape, int transB, hipStream_t st);
+int gemm_direct_launch_w_f32(const DirectArgs& d, int shape, int transB, hipStream_t st);
+int gemm_direct_launch_w_f64(const DirectArgs& d, int shape, int transB, hipStream_t st);
 
 // per-dtype launchers (one translation unit each, to compile in parallel)
 // mode: 0 plain, 1 check, 2 check + injector + weighted row sums + column sums, 3 check + weighted row

@@ -195,6 +195,15 @@ class VerifiedGemm:
     def run_weighted(self, A, B, e_max=None, c_sigma=2.5, inj=None, correct=1):
         """Detect, locate, correct: weighted encode, weighted threshold, weighted verified GEMM,
         then localisation (and correction of the stored C)."""
+        if inj is None:  # the pass over A and the localisation ride in the GEMM's launch where they can
+            if e_max is None:
+                e_max = vb.vabft_default_emax(self.dtype, self.K, self.N)
+            self.e_max = e_max
+            vb.vabft_encode_gemm_weighted(self.problem, A.data_ptr(), B.data_ptr(), self.C, self.Be, self.Be2, self.bstat,
+                                          self.S, e_max, c_sigma, self.astat, self.expected, self.expected2, self.T,
+                                          self.rowsum, self.rowsum2, self.E, self.flags, self.nflag, correct, self.loc,
+                                          self.delta, self.ncorrected, self.ws, self.ws_bytes, self._stream())
+            return
         self.encode_weighted(B)
         self.threshold_weighted(A, e_max, c_sigma)
         self.gemm_weighted(A, B, inj)
