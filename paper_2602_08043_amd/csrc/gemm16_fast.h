@@ -42,6 +42,7 @@
 // min of the row stay in the vector ALU, as packed 16-bit operations on the fragment registers.
 #pragma once
 #include "gemm_tile32.h"
+#include "row_threshold.h"
 
 namespace vabft {
 
@@ -1147,8 +1148,47 @@ __device__ __forceinline__ void gemm16_fast_tile(const GemmArgs& g, int bm, int 
     gemm16x_store_c<T, EDGE, NF>(g, acc, smem, row0, col0, lane, wm, wn, l16, lq);
 }
 
+// The A-side pass (Algorithm 1 for the rows of A) in workgroups of its own behind the tiles', on compute units that have no tile
+// of the last round: `share` of the -g.fused_stats of a tile-row, a wavefront per row at a time.  An arrival of its tile-row.
+template <typename T, bool EDGE> __device__ __forceinline__ void gemm16_stats(const GemmArgs& g, int bm, int share) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, w = -g.fused_stats;
+    double* const s_red = reinterpret_cast<double*>(smem);
+    const bool fold = g.s_nparts != 0;
+    if (fold) {
+        fold_s_partials_to_lds(g.s_partial, g.s_nparts, tid, s_red);
+        __syncthreads();
+        if (bm == 0 && share == 0 && tid < 3 && g.S) g.S[tid] = folded_s(s_red, tid);
+    }
+    const double S1 = fold ? folded_s(s_red, 0) : g.S[0], S2 = fold ? folded_s(s_red, 1) : g.S[1],
+                 S3 = fold ? folded_s(s_red, 2) : g.S[2];
+    const int rows = (256 + w - 1) / w, first = bm * 256 + share * rows, end = min(min(first + rows, bm * 256 + 256), g.M);
+    for (int m = first + wave; m < end; m += 4) {
+        const char* const row = reinterpret_cast<const char*>(g.A) + (int64_t)m * g.lda * 2;
+        const RowSums<float> r = row_sums<T, false, 4>(row, g.K, lane, reinterpret_cast<const float*>(g.Be), nullptr);
+        if (lane == 0) {
+            double mu;
+            const float t = (float)row_threshold(r, g.K, g.N, S1, S2, S3, g.e_max, g.c_sigma, mu);
+            float* const astat = reinterpret_cast<float*>(g.astat) + 3 * (int64_t)m;
+            astat[0] = r.mx;
+            astat[1] = r.mn;
+            astat[2] = (float)mu;
+            st_agent(reinterpret_cast<float*>(const_cast<void*>(g.expected)) + m, r.dot);
+            st_agent(reinterpret_cast<float*>(const_cast<void*>(g.T)) + m, t);
+        }
+    }
+    gemm_tile_row_check<false, false, EDGE>(g, smem, nullptr, bm, bm * 256 + tid, tid);
+}
+
 template <typename T, int TRANSB, int MODE, bool FUSED, bool EDGE, int NF, bool CHAINS = false>
 __global__ __launch_bounds__(256) void gemm16_fast_kernel(const GemmArgs g) {
+    if constexpr (MODE == 1 && !FUSED && !CHAINS) {
+        const int behind = (int)blockIdx.x - g.tiles_m * g.tiles_n;
+        if (behind >= 0) {
+            gemm16_stats<T, EDGE>(g, behind / -g.fused_stats, behind % -g.fused_stats);
+            return;
+        }
+    }
     int bm, bn;
     tile_of_block(blockIdx.x, g.tiles_m, g.tiles_n, bm, bn);
     gemm16_fast_tile<T, TRANSB, MODE, FUSED, EDGE, NF, CHAINS>(g, bm, bn, bm * 256, bn * 32 * NF);
@@ -1161,14 +1201,15 @@ template <typename KERN> static int gemm16_start(KERN kern, const GemmArgs& a, s
             return VABFT_EDEVICE;
         attr_set = true;
     }
-    kern<<<dim3(a.tiles_m * a.tiles_n), dim3(256), lds, st>>>(a);
+    const int behind = a.fused_stats < 0 ? -a.fused_stats * a.tiles_m : 0;
+    kern<<<dim3(a.tiles_m * a.tiles_n + behind), dim3(256), lds, st>>>(a);
     return hipGetLastError() == hipSuccess ? VABFT_OK : VABFT_EDEVICE;
 }
 
 // form: see Form16; the tile's width is 256, 192 or 128
 template <typename T, int TRANSB>
 static int gemm16_fast_launch_tb(const GemmArgs& a, int mode, int form, hipStream_t st) {
-    const int fused = a.fused_stats ? 1 : 0;
+    const int fused = a.fused_stats > 0 ? 1 : 0;
     const auto bytes = [&](auto l) { return (size_t)(fused ? decltype(l)::BYTES_FUSED : decltype(l)::BYTES); };
     using g16x::Lds16;
     const size_t lds = form >= FORM16_128 ? bytes(Lds16<4>{}) : form == FORM16_192 ? bytes(Lds16<6>{}) : bytes(Lds16<8>{});

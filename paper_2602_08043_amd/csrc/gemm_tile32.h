@@ -79,7 +79,8 @@ __device__ __forceinline__ void gemm_tile_row_check(const GemmArgs& g, unsigned 
     // shadow.
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
-    if (tid == 0) *s_last = (atomicAdd(&g.tickets[bm * g.ticket_stride], 1) == g.tiles_n - 1);
+    const int arrivals = g.tiles_n + (FUSED || g.fused_stats > 0 ? 0 : -g.fused_stats);
+    if (tid == 0) *s_last = (atomicAdd(&g.tickets[bm * g.ticket_stride], 1) == arrivals - 1);
     __syncthreads();
     if (*s_last) {
         // Combine the tile-column partials in tile order.  The device-scope loads are issued
@@ -103,8 +104,8 @@ __device__ __forceinline__ void gemm_tile_row_check(const GemmArgs& g, unsigned 
                 g.S[2] = S3;
             }
         } else {
-            expv = reinterpret_cast<const float*>(g.expected)[gi];
-            thr = reinterpret_cast<const float*>(g.T)[gi];
+            expv = ld_agent(reinterpret_cast<const float*>(g.expected) + gi);  // (of this launch, maybe)
+            thr = ld_agent(reinterpret_cast<const float*>(g.T) + gi);
         }
         for (int t0 = 0; t0 < g.tiles_n; t0 += 16) {
             float v[16][5];

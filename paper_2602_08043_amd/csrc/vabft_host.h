@@ -92,7 +92,8 @@ struct GemmArgs {
     int32_t* tickets;      // [tiles_m] arrival counters, then (8-byte aligned) one 64-bit word:
                            // finished row blocks << 32 | flagged rows; all zero between launches
     int32_t ticket_stride; // int32 from one tile-row's arrival counter to the next
-    // fused A-side statistics (Algorithm 1 for the rows of A, inside the GEMM)
+    // fused A-side statistics (Algorithm 1 for the rows of A, inside the GEMM).  Tiled kernels: 1 on the operand tiles, -w in w
+    // workgroups per tile-row of their own, the launch's last
     int32_t fused_stats;
     const void* Be;   // [K] acc
     double* S;        // [3]; with s_nparts > 0 an output, or null: the sums are folded from s_partial

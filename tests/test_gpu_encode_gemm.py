@@ -36,3 +36,26 @@ def test_same_bits_as_two_calls(dtype, M, N, K, transB):
             assert bool(((one.S - S).abs() <= K * 2.0 ** -53 * S).all())
         for n in ("Be", "bstat", "astat", "expected", "T", "rowsum", "E", "flags", "nflag", "C"):
             assert torch.equal(getattr(one, n), getattr(two, n)), (n, defer)
+
+
+@pytest.mark.parametrize("dtype,M,N,K,transB", [
+    ("f16", 1000, 3072, 1024, 1), ("bf16", 2048, 2048, 1024, 0), ("bf16", 1499, 2496, 1504, 1), ("f16", 2305, 2048, 1096, 0),
+    ("bf16", 2304, 3840, 512, 0), ("bf16", 1793, 4352, 1032, 0)])
+def test_pass_on_units_without_a_tile(dtype, M, N, K, transB):
+    """The A-side pass behind the tiles of the 16-bit kernels (whole and ragged tiles, any K): the bits of vabft_threshold, and
+    its checks see what the three calls see."""
+    td = {"bf16": torch.bfloat16, "f16": torch.float16}[dtype]
+    g = torch.Generator().manual_seed(4)
+    A = torch.randn(M, K, generator=g).to(td).cuda()
+    B = torch.randn((N, K) if transB else (K, N), generator=g).to(td).cuda()
+    one, three = VerifiedGemm(M, N, K, dtype, transB), VerifiedGemm(M, N, K, dtype, transB)
+    for e_max in (None, 1e-30, None):  # (1e-30: what rounding leaves of a row flags it)
+        three.encode(B)
+        three.threshold(A, e_max)
+        three.gemm(A, B)
+        one.encode(B)
+        one.gemm_fused(A, B, e_max)
+        torch.cuda.synchronize()
+        for n in ("astat", "expected", "T", "rowsum", "E", "flags", "nflag", "C"):
+            assert torch.equal(getattr(one, n), getattr(three, n)), (n, e_max)
+        assert (int(one.nflag.item()) > 0) == (e_max is not None)
