@@ -589,9 +589,9 @@ __device__ __forceinline__ void direct_stats(const DirectArgs& d, int block, dou
 // Wavefronts to a SIMD that the compiler has to leave registers for: a few registers more would be a workgroup less on the compute
 // unit.
 template <typename T, int TRANSB, int MF, int WVK, bool ANY, bool SPLIT> constexpr int direct_min_waves() {
-    constexpr bool f64 = std::is_same<T, double>::value;
-    if (WVK == 8 && (MF == 1 || (f64 && TRANSB && !SPLIT))) return 4;
-    return f64 && WVK > 1 && !ANY && !SPLIT ? 3 : 2;
+    if (WVK == 8 && TRANSB && MF == 1) return 4;  // (B stored K x N: LDS for one workgroup)
+    if (WVK == 4 && MF == 2 && !ANY) return 3;  // (BF16 1024^3 with two 12.0 us, with three 10.0)
+    return 2;
 }
 template <typename T, int TRANSB, int MF, int NF, int WVK, int WN, int D, bool ANY, bool SPLIT, bool W>
 __global__ __launch_bounds__(64 * WVK * WN, (direct_min_waves<T, TRANSB, MF, WVK, ANY, SPLIT>())) void gemm_direct_kernel(const DirectArgs d) {
@@ -638,11 +638,27 @@ __global__ __launch_bounds__(64 * WVK * WN, (direct_min_waves<T, TRANSB, MF, WVK
     const int rest = z == split - 1 ? g.K - steps * KSTEP : 0;  // k behind the last whole step
     const int row0 = bm * S::BM, col0 = bn * S::BN + wn * S::BNW;
 
+    // Rows of under 16 bytes (ANY) are read element by element, already finished (load_part)
+    const bool tiny = ANY && (g.K < V || (!TRANSB && g.N < V));
+    // Steps are dealt to the wavefronts in turn.  The k behind the last whole step are the end of a step that ends where K
+    // does: read like any other (all of it is inside the rows), first of its wavefront's, and the k before them cleared in both
+    // operands (clear_front).  With loads of its own for it, clamped and shifted, and the step's code a second time, its 500
+    // instructions ran with nothing in flight but the next step (fused calls, so / now): FP16 500 x 999 x 777 10.4 / 9.3 us,
+    // BF16 530 x 3584 x 283 (N x K) 16.2 / 14.0, FP32 1000 x 1200 x 1500 45.5 / 42.8, FP64 1777 x 1061 x 331 (N x K) 43.9 / 38.6;
+    // whole steps only, 256^3 in FP32 7.55 / 7.68, of 336 problems 4 more than 3 % slower.
+    const int whole = !tiny && full > wk ? (full - wk + WVK - 1) / WVK : 0;  // steps of this wavefront
+    const bool ends_here = rest > 0 && full % WVK == wk && g.K >= KSTEP;
+    // (64 rows: as a value that the compiler does not see through, or it keeps addresses for both cases and spills them)
+    const int tail = MF >= 4 ? __builtin_amdgcn_readfirstlane((int)ends_here) : (int)ends_here;
+    // k that the loads count from, this wavefront's first whole step.  Where it has none, its only step, which is read again behind
+    // itself: known late, so that the first loads do not wait for it, but with 64 rows, where a second base would be spilled.
+    const int kfirst = MF >= 4 && whole == 0 && g.K >= KSTEP ? g.K - KSTEP : (s0 + wk) * KSTEP;
+
     // ---- global memory -> registers ---------------------------------------------------------------------------
     // Row loads: load t covers LDS rows 8 t .. 8 t + 7, eight lanes each; the lane at position lane % 8 of row r
     // fetches chunk (lane % 8) ^ ((r >> 1) & 7), so that the 16 rows of a fragment read hit 16 distinct slots.
     const int lrow = lane >> 3;
-    const char* const abase = reinterpret_cast<const char*>(g.A) + ((int64_t)row0 * g.lda + (s0 + wk) * KSTEP) * ES;
+    const char* abase = reinterpret_cast<const char*>(g.A) + ((int64_t)row0 * g.lda + kfirst) * ES;
     OFF aoff[LA];
 #pragma unroll
     for (int t = 0; t < LA; ++t) {
@@ -652,7 +668,7 @@ __global__ __launch_bounds__(64 * WVK * WN, (direct_min_waves<T, TRANSB, MF, WVK
     const char* bbase;
     OFF boff[LB];
     if constexpr (TRANSB != 0) {
-        bbase = reinterpret_cast<const char*>(g.B) + ((int64_t)col0 * g.ldb + (s0 + wk) * KSTEP) * ES;
+        bbase = reinterpret_cast<const char*>(g.B) + ((int64_t)col0 * g.ldb + kfirst) * ES;
 #pragma unroll
         for (int t = 0; t < LB; ++t) {
             // LDS row ni * 16 + i holds column i * NF + ni of the tile
@@ -663,7 +679,7 @@ __global__ __launch_bounds__(64 * WVK * WN, (direct_min_waves<T, TRANSB, MF, WVK
         // LDS row k of RB bytes: the tile's columns of row k of the step, in groups of V; a group that would cross the
         // row's end starts at N - V instead (see column_of)
         const int c = max(0, min(col0 + lane * 16 % RB / ES, g.N - V));
-        bbase = reinterpret_cast<const char*>(g.B) + ((int64_t)((s0 + wk) * KSTEP) * g.ldb) * ES;
+        bbase = reinterpret_cast<const char*>(g.B) + ((int64_t)kfirst * g.ldb) * ES;
 #pragma unroll
         for (int t = 0; t < LB; ++t) boff[t] = (OFF)((t * 1024 + lane * 16) / RB) * (OFF)(g.ldb * ES) + (OFF)c * ES;
     }
@@ -671,9 +687,8 @@ __global__ __launch_bounds__(64 * WVK * WN, (direct_min_waves<T, TRANSB, MF, WVK
     struct Stage {
         gd::u32x4_t a[LA], b[LB];
     };
-    // Steps are dealt to the wavefronts in turn.  i: this wavefront's step number
-    auto load_step = [&](int i, Stage& st) __attribute__((always_inline)) {
-        const int64_t k0 = (int64_t)i * (WVK * KSTEP);
+    // k0: of the step, from kfirst
+    auto load_at = [&](int64_t k0, Stage& st) __attribute__((always_inline)) {
         // (base and offsets opaque, so that each load is scalar base + 32-bit lane offset and no sum of the two, nor
         // the offset widened to 64 bits, is kept across the loop)
         gd::gptr_t pa = (gd::gptr_t)(abase + k0 * ES);
@@ -688,10 +703,30 @@ __global__ __launch_bounds__(64 * WVK * WN, (direct_min_waves<T, TRANSB, MF, WVK
 #pragma unroll
         for (int t = 0; t < LB; ++t) st.b[t] = gd::load16g<ES>(pb + boff[t]);
     };
-    // Step i where only the first len < KSTEP k are inside K: rows along k are read where they still have 16 bytes
-    // and shifted by finish_part, rows along n past K are replaced by the last one and cleared by finish_part.
-    // Rows of under 16 bytes (ANY) are read element by element, already finished.
-    const bool tiny = ANY && (g.K < V || (!TRANSB && g.N < V));
+    // i: this wavefront's step number
+    auto load_step = [&](int i, Stage& st) __attribute__((always_inline)) { load_at((int64_t)i * (WVK * KSTEP), st); };
+    auto clear_front = [&](Stage& st) __attribute__((always_inline)) {
+        const int before = KSTEP - rest;
+        uint32_t keep[2][4];  // (of a lane's chunks in even and odd loads)
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const int bytes = (before - (((lane & 7) ^ ((4 * t + (lane >> 4)) & 7)) << 4) / ES) * ES;  // of the chunk to clear
+#pragma unroll
+            for (int q = 0; q < 4; ++q) keep[t][q] = bytes >= 4 * q + 4 ? 0u : ~0u << (8 * max(0, bytes - 4 * q) & 31);
+        }
+#pragma unroll
+        for (int t = 0; t < LA; ++t)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) st.a[t][q] &= keep[t & 1][q];
+#pragma unroll
+        for (int t = 0; t < LB; ++t) {
+            const uint32_t row = (t * 1024 + lane * 16) / RB < before ? 0u : ~0u;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) st.b[t][q] &= TRANSB ? keep[t & 1][q] : row;
+        }
+    };
+    // Step i where only the first len < KSTEP k are inside K (of a K of less than a step): rows along k are read where they still
+    // have 16 bytes and shifted by finish_part, rows along n past K are replaced by the last one and cleared by finish_part.
     auto beyond = [&](int t, int len) { return (((lane & 7) ^ ((4 * t + (lane >> 4)) & 7)) << 4) / ES + V - len; };
     auto load_part = [&](int i, int len, Stage& st) __attribute__((always_inline)) {
         const int64_t k0 = (int64_t)i * (WVK * KSTEP);
@@ -729,12 +764,14 @@ __global__ __launch_bounds__(64 * WVK * WN, (direct_min_waves<T, TRANSB, MF, WVK
     };
 
     accv_t acc[MF][NF];
+    const auto clear_acc = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    for (int mi = 0; mi < MF; ++mi)
+        for (int mi = 0; mi < MF; ++mi)
 #pragma unroll
-        for (int ni = 0; ni < NF; ++ni)
+            for (int ni = 0; ni < NF; ++ni)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) acc[mi][ni][r] = 0;
+                for (int r = 0; r < 4; ++r) acc[mi][ni][r] = 0;
+    };
     // ---- registers -> the wavefront's own LDS rows -> fragments -> MFMA ----------------------------------------
     // No other wavefront reads these rows and LDS operations of one wavefront complete in order, so one buffer and
     // no barrier will do.
@@ -754,86 +791,123 @@ __global__ __launch_bounds__(64 * WVK * WN, (direct_min_waves<T, TRANSB, MF, WVK
         __builtin_amdgcn_sched_barrier(0);
         reload();
         __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int u = 0; u < KU; ++u) {
+        // 16-bit, B stored K x N, K shared by the wavefronts: the second chunk's fragments are on their way while the first's are
+        // multiplied.  (Left to the compiler it comes out so or not: if not, BF16 and FP16 4 x 768 x 5376 9.8 us, not 8.5.)
+        constexpr bool AHEAD = TRANSB == 0 && ES == 2 && !S::OWN;
+        constexpr int HELD = AHEAD ? KU : 1;
+        raw16 af[HELD][MF], bf[NF];
+        uint32_t w[HELD][VK][CD];
+        const auto frag = [&](int f, int u) __attribute__((always_inline)) {
             // the lane's chunk: 16-byte slot and, for 8-byte chunks, its half
             const int at = CB == 16 ? ((4 * u + lq) ^ swz) << 4 : (((2 * u + (lq >> 1)) ^ swz) << 4) + 8 * (lq & 1);
-            auto frag = [&](int f) {
-                uint32_t w[Tr::CB / 4];
-                gd::copy_bytes<Tr::CB>(w, frag0 + f * 2048 + at);
-                return gd::to_frag<T>(w);
-            };
-            raw16 af[MF], bf[NF];
+            uint32_t c[Tr::CB / 4];
+            gd::copy_bytes<Tr::CB>(c, frag0 + f * 2048 + at);
+            return gd::to_frag<T>(c);
+        };
+        const auto fetch_b = [&](int u) __attribute__((always_inline)) {
             if constexpr (TRANSB != 0) {
 #pragma unroll
-                for (int ni = 0; ni < NF; ++ni) bf[ni] = frag(MF + ni);
+                for (int ni = 0; ni < NF; ++ni) bf[ni] = frag(MF + ni, u);
             } else {
-                uint32_t w[VK][CD];
 #pragma unroll
                 for (int e = 0; e < VK; ++e)
-                    gd::copy_bytes<4 * CD>(w[e], stage + LA * 1024 + (u * KC + lq * VK + e) * RB + l16 * NF * ES);
-#pragma unroll
-                for (int ni = 0; ni < NF; ++ni) bf[ni] = gd::to_frag_t<T, CD>(w, ni);
+                    gd::copy_bytes<4 * CD>(w[u % HELD][e], stage + LA * 1024 + (u * KC + lq * VK + e) * RB + l16 * NF * ES);
             }
+        };
+        const auto fetch_a = [&](int u) __attribute__((always_inline)) {
 #pragma unroll
-            for (int mi = 0; mi < MF; ++mi) af[mi] = frag(mi);
+            for (int mi = 0; mi < MF; ++mi) af[u % HELD][mi] = frag(mi, u);
+        };
+        const auto transpose = [&](int u) __attribute__((always_inline)) {
+            if constexpr (TRANSB == 0) {
+#pragma unroll
+                for (int ni = 0; ni < NF; ++ni) bf[ni] = gd::to_frag_t<T, CD>(w[u % HELD], ni);
+            }
+        };
+        const auto multiply = [&](int u) __attribute__((always_inline)) {
 #pragma unroll
             for (int j = 0; j < Tr::NJ; ++j)
 #pragma unroll
                 for (int mi = 0; mi < MF; ++mi)
 #pragma unroll
-                    for (int ni = 0; ni < NF; ++ni) acc[mi][ni] = gd::mfma<T>(bf[ni], af[mi], j, acc[mi][ni]);
+                    for (int ni = 0; ni < NF; ++ni) acc[mi][ni] = gd::mfma<T>(bf[ni], af[u % HELD][mi], j, acc[mi][ni]);
+        };
+        if constexpr (AHEAD) {
+            fetch_b(0);
+            fetch_a(0);
+            transpose(0);
+            __builtin_amdgcn_sched_barrier(0);
+            fetch_b(1);
+            fetch_a(1);
+            __builtin_amdgcn_sched_barrier(0);
+            multiply(0);
+            transpose(1);
+            multiply(1);
+        } else {
+#pragma unroll
+            for (int u = 0; u < KU; ++u) {
+                fetch_b(u);
+                transpose(u);
+                fetch_a(u);
+                multiply(u);
+            }
         }
         __builtin_amdgcn_sched_barrier(0);
     };
-    if (!S::OWN || col0 < g.N) {  // (of the last wavefronts of a tile-row some may have no columns)
-        const int cnt = !tiny && full > wk ? (full - wk + WVK - 1) / WVK : 0;  // whole steps of this wavefront
-        Stage sg[D];
-        if (rest > 0 && full % WVK == wk && !tiny) {
-            // the step that K ends in comes first, with the first whole step in flight behind it
-            Stage part;
-            load_part(full / WVK, rest, part);
-            if (cnt > 0) load_step(0, sg[0]);
-            __builtin_amdgcn_sched_barrier(0);
-            finish_part(rest, part);
-            compute(part, [] {});
-        } else if (cnt > 0) {
-            load_step(0, sg[0]);
+    const bool columns = !S::OWN || col0 < g.N;  // (of the last wavefronts of a tile-row some may have none)
+    const int cnt = columns && !tiny ? whole + tail : 0;
+    Stage sg[D];
+    // (as little as may be in front of the first loads: 1.3 ns an instruction)
+    if (cnt > 0) {
+        const int first = tail ? g.K - KSTEP - kfirst : 0;
+        load_at(first, sg[0]);
+        if (MF < 4 && whole == 0) {
+            abase += (int64_t)first * ES;
+            bbase += first * bstep;
         }
-        if (cnt > 0) {
-            static_for<1, D>([&](auto q_c) { load_step(min(decltype(q_c)::value, cnt - 1), sg[decltype(q_c)::value]); });
-            // OWN: K in four chains behind each other, as many as where wavefronts share it, for the same rounding error.
-            // (A loop per chain: with the change of chains inside one loop the accumulators went through scratch memory.)
-            accv_t done[S::OWN ? MF : 1][S::OWN ? NF : 1] = {};
-            const int chain = S::OWN ? (cnt + 3) / 4 : cnt;
-            for (int i = 0, end = chain;; end = min(end + chain, cnt)) {
-                for (;;) {  // (past the last step the last one is read again, and dropped)
-                    compute(sg[0], [&] { load_step(min(i + D, cnt - 1), sg[0]); });
+        const int last = __builtin_amdgcn_readfirstlane(whole > 0 ? whole - 1 : 0);
+        static_for<1, D>([&](auto q_c) { load_step(min(decltype(q_c)::value - tail, last), sg[decltype(q_c)::value]); });
+        __builtin_amdgcn_sched_barrier(0);
+        if (tail) clear_front(sg[0]);
+        clear_acc();
+        // OWN: K in four chains behind each other, as many as where wavefronts share it, for the same rounding error.
+        // (A loop per chain: with the change of chains inside one loop the accumulators went through scratch memory.)
+        accv_t done[S::OWN ? MF : 1][S::OWN ? NF : 1] = {};
+        const int chain = S::OWN ? (cnt + 3) / 4 : cnt;
+        for (int i = -tail, end = chain - tail;; end = min(end + chain, whole)) {  // (step -1: the one that K ends in)
+            for (;;) {  // (past the last step the last one is read again, and dropped)
+                compute(sg[0], [&] { load_step(min(i + D, last), sg[0]); });
+                if (++i == end) break;
+                if constexpr (D == 2) {
+                    compute(sg[1], [&] { load_step(min(i + D, last), sg[1]); });
                     if (++i == end) break;
-                    if constexpr (D == 2) {
-                        compute(sg[1], [&] { load_step(min(i + D, cnt - 1), sg[1]); });
-                        if (++i == end) break;
-                    }
                 }
-                if constexpr (!S::OWN) break;
-#pragma unroll
-                for (int f = 0; f < (S::OWN ? MF * NF : 0); ++f)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const acc_t sum = done[f / NF][f % NF][r] + acc[f / NF][f % NF][r];
-                        done[f / NF][f % NF][r] = sum;
-                        acc[f / NF][f % NF][r] = i == cnt ? sum : (acc_t)0;
-                    }
-                if (i == cnt) break;
             }
-        }
-        if constexpr (ANY) {
-            if (tiny)
-                for (int q = wk; q * KSTEP < g.K; q += WVK) {
-                    load_part(q / WVK, min(KSTEP, g.K - q * KSTEP), sg[0]);
-                    compute(sg[0], [] {});
+            if constexpr (!S::OWN) break;
+#pragma unroll
+            for (int f = 0; f < (S::OWN ? MF * NF : 0); ++f)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const acc_t sum = done[f / NF][f % NF][r] + acc[f / NF][f % NF][r];
+                    done[f / NF][f % NF][r] = sum;
+                    acc[f / NF][f % NF][r] = i == whole ? sum : (acc_t)0;
                 }
+            if (i == whole) break;
         }
+    } else {
+        clear_acc();
+        if (g.K < KSTEP && wk == 0 && !tiny && columns) {
+            load_part(0, rest, sg[0]);
+            finish_part(rest, sg[0]);
+            compute(sg[0], [] {});
+        }
+    }
+    if constexpr (ANY) {
+        if (tiny)
+            for (int q = wk; q * KSTEP < g.K; q += WVK) {
+                load_part(q / WVK, min(KSTEP, g.K - q * KSTEP), sg[0]);
+                compute(sg[0], [] {});
+            }
     }
 
     // ---- partial tiles of the WVK wavefronts -> LDS, as a tree ---------------------------------------------------
