@@ -37,7 +37,7 @@
 //
 // Loads need no alignment beyond the element's (the hardware takes unaligned global accesses).  Rows and columns past
 // the end are clamped and their results dropped; k past the end is zero in both operands.  FP16 1021 x 1531 x 2047,
-// nothing aligned: 36 us, against 530 with element-wise guarded loads into 256 x 256 tiles.
+// nothing aligned: 30 us, against 530 with element-wise guarded loads into 256 x 256 tiles.
 //
 // Check: the wavefronts' partial tiles are added in LDS as a fixed tree, the injector edits the sum, row sums (and
 // weighted and column sums) are taken from it before it is rounded to the output type, and the last workgroup of a
