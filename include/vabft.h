@@ -181,8 +181,8 @@ int vabft_gemm_verified(const vabft_problem* p, const void* dA, const void* dB, 
  * d_flags, d_nflag, dC, injection log (as vabft_gemm_verified).  Where a 16-bit or FP8 product is large
  * enough for the kernels of wide tiles, its operands' rows are 16-byte aligned and K is a multiple of 128 (FP8: of
  * 256, M and N too), the statistics ride on the operand tiles inside the GEMM kernel.  Elsewhere, and beside 16-bit
- * products whose last round of tiles leaves compute units idle, the A-side pass has workgroups of its own: in the same launch, or, with very many rows or beside the kernels of wide tiles, in
- * a launch in front of it, which also copies operands whose rows are not aligned for those kernels.  The route depends
+ * products whose last round of tiles leaves compute units idle, the A-side pass has workgroups of its own: in the same
+ * launch, or, with very many rows or beside other products on the kernels of wide tiles, in a launch in front of it, which also copies operands whose rows are not aligned for those kernels.  The route depends
  * on shape, type, layout and alignment, on whether the injector is on and on the room of the workspace (with that of
  * vabft_workspace_bytes or more it is the same), never on the data.  Another route sums K in another order: with the
  * injector on, large products of 16-bit and FP8 rows that the kernels of wide tiles take without it run on others, and

@@ -141,7 +141,8 @@ template <typename... A> PyObject* call(int (*f)(A...), const char* name, PyObje
     X(vabft_gemm_verified_fused_static) X(vabft_encode_weighted) X(vabft_threshold_weighted)                           \
     X(vabft_gemm_verified_weighted) X(vabft_locate_correct) X(vabft_check_offline) X(vabft_encode_a)                   \
     X(vabft_threshold_cols) X(vabft_gemm_verified_rc) X(vabft_encode_blocks) X(vabft_threshold_blocks)                 \
-    X(vabft_encode_gemm_fused) X(vabft_encode_gemm_weighted) X(vabft_gemm_verified_blocks) X(vabft_encode_blocks_k) X(vabft_threshold_blocks_k) X(vabft_gemm_verified_blocks_k)
+    X(vabft_gemm_verified_blocks) X(vabft_encode_blocks_k) X(vabft_threshold_blocks_k) X(vabft_gemm_verified_blocks_k) \
+    X(vabft_encode_gemm_fused) X(vabft_encode_gemm_weighted)
 ENTRIES(ENTRY)
 
 #define METHOD(NAME) {#NAME, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)(void)>(py_##NAME)), METH_FASTCALL, nullptr},

@@ -1154,8 +1154,8 @@ __global__ __launch_bounds__(64 * WVK * WN, (direct_min_waves<T, TRANSB, MF, WVK
             for (int e = 0; e < EPT; e += G) {
                 if constexpr (EPT % G == 0) {
                     if (!nedge) {
-                    __hip_atomic_store(reinterpret_cast<uint64_t*>(c + col0 + tc + e), gd::word8<T>(v[0] + e), __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_AGENT);
+                        __hip_atomic_store(reinterpret_cast<uint64_t*>(c + col0 + tc + e), gd::word8<T>(v[0] + e), __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_AGENT);
                         continue;
                     }
                 }
