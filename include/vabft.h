@@ -130,7 +130,9 @@ double vabft_default_emax(int32_t dtype, int32_t K, int32_t N);
  * vabft_encode_a) on that workspace, for GEMMs with any number of rows M (the workspace sized for the
  * largest of them; every region of the workspace that outlives a call sits at a place that depends on the
  * shape of B only, for up to a million rows), and
- * vabft_gemm_verified_fused called with d_S = NULL folds them itself (same order, same bits).
+ * vabft_gemm_verified_fused called with d_S = NULL folds them itself, in the same order.  The bits of d_Be and
+ * d_bstat are the same; those of S1..S3 are but for a B stored K x N with K > 4080, whose partials are then sums over
+ * other groups of rows k (each sum is within K units in the last place of the other).
  * This takes the arrival-counter round trips out of the encode's tail. */
 int vabft_encode(const vabft_problem* p, const void* dB, void* d_Be, void* d_bstat, double* d_S,
                  void* d_workspace, size_t workspace_bytes, void* stream);
@@ -182,9 +184,10 @@ int vabft_gemm_verified(const vabft_problem* p, const void* dA, const void* dB, 
  * enough for the kernels of wide tiles, its operands' rows are 16-byte aligned and K is a multiple of 128 (FP8: of
  * 256, M and N too), the statistics ride on the operand tiles inside the GEMM kernel.  Elsewhere, and beside 16-bit
  * products whose last round of tiles leaves compute units idle, the A-side pass has workgroups of its own: in the same
- * launch, or, with very many rows or beside other products on the kernels of wide tiles, in a launch in front of it, which also copies operands whose rows are not aligned for those kernels.  The route depends
- * on shape, type, layout and alignment, on whether the injector is on and on the room of the workspace (with that of
- * vabft_workspace_bytes or more it is the same), never on the data.  Another route sums K in another order: with the
+ * launch, or, with very many rows or beside other products on the kernels of wide tiles, in a launch in front of it,
+ * which also copies operands whose rows are not aligned for those kernels.  The route depends on shape, type, layout
+ * and alignment, on whether the injector is on and on the room of the workspace (with that of vabft_workspace_bytes or
+ * more it is the same), never on the data.  Another route sums K in another order: with the
  * injector on, large products of 16-bit and FP8 rows that the kernels of wide tiles take without it run on others, and
  * elements of C that no fault touched may differ in their last bits from a call's without it.  The
  * compare-and-flag step runs in the last workgroup of each row block.  The summation order of the A-side sums
@@ -197,9 +200,10 @@ int vabft_gemm_verified_fused(const vabft_problem* p, const void* dA, const void
                               vabft_inject_rec* d_injlog, int32_t* d_ninj, void* d_workspace,
                               size_t workspace_bytes, void* stream);
 
-/* vabft_encode and vabft_gemm_verified_fused behind each other, for a B that is new: S1..S3 are folded by the second
- * launch, and written to d_S [3] unless that is NULL.  The bits are those of vabft_encode (d_S = NULL) and
- * vabft_gemm_verified_fused (d_S = NULL). */
+/* vabft_encode and vabft_gemm_verified_fused behind each other, for a B that is new: S1..S3 are folded behind the encode,
+ * by the launch that holds the A-side pass or one in front of it, and written to d_S [3] unless that is NULL.  The bits
+ * are those of vabft_encode (d_S = NULL) and vabft_gemm_verified_fused (d_S = NULL).  All arguments are checked before
+ * the first launch. */
 int vabft_encode_gemm_fused(const vabft_problem* p, const void* dA, const void* dB, void* dC, void* d_Be,
                             void* d_bstat, double* d_S, double e_max, double c_sigma, void* d_astat,
                             void* d_expected, void* d_T, const vabft_inject* inj, void* d_rowsum, void* d_E,
@@ -207,8 +211,10 @@ int vabft_encode_gemm_fused(const vabft_problem* p, const void* dA, const void* 
                             void* d_workspace, size_t workspace_bytes, void* stream);
 
 /* vabft_encode_weighted, vabft_threshold_weighted, vabft_gemm_verified_weighted and vabft_locate_correct behind each
- * other, without injector: what they compute, in two launches where C's rows are aligned to 8 bytes and the product
- * runs on the kernels of small tiles. */
+ * other, without injector: what they compute, in as few as two launches (products of up to 6 MiB of C, FP64 2 MiB,
+ * with dC and the pitch of C's rows multiples of 8 bytes, on kernels of small tiles whose wavefronts share K; many long
+ * rows of A, larger products and B stored N x K in large matrices take further ones).  The fold of S1..S3 is as in
+ * vabft_encode_gemm_fused; all arguments are checked before the first launch. */
 int vabft_encode_gemm_weighted(const vabft_problem* p, const void* dA, const void* dB, void* dC, void* d_Be,
                                void* d_Be2, void* d_bstat, double* d_S, double e_max, double c_sigma,
                                void* d_astat, void* d_expected, void* d_expected2, void* d_T, void* d_rowsum,
@@ -220,9 +226,9 @@ int vabft_encode_gemm_weighted(const vabft_problem* p, const void* dA, const voi
  * loops, harnesses that forbid hipMalloc.  Same inputs and outputs as vabft_gemm_verified_fused, and the same results
  * bit for bit but for large products of 16-bit or FP8 rows that are not aligned to 16 bytes (FP8: of other sizes than
  * whole tiles, or B stored K x N), where a workspace has room for copies of them and this array has not: they take the
- * kernels that read rows as they lie, which sum K in another order.  There is no workspace argument: the partials and arrival counters live in a fixed array of
- * VABFT_STATIC_SCRATCH_BYTES (16 MiB) of device memory inside the library, one copy per GPU, held until the
- * process ends.  The call allocates nothing and frees nothing.
+ * kernels that read rows as they lie, which sum K in another order.  There is no workspace argument: the partials and
+ * arrival counters live in a fixed array of VABFT_STATIC_SCRATCH_BYTES (16 MiB) of device memory inside the library,
+ * one copy per GPU, held until the process ends.  The call allocates nothing and frees nothing.
  *   - d_S must not be NULL (no encode runs on this array, so there are no deferred partials to fold).
  *   - A problem whose partials and counters exceed the array returns VABFT_EWORKSPACE (the room for faster forms
  *     that vabft_workspace_bytes adds is not counted: they are taken where the array has it);

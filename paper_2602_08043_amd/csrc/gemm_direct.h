@@ -590,7 +590,7 @@ __device__ __forceinline__ void direct_stats(const DirectArgs& d, int block, dou
 // unit.
 template <typename T, int TRANSB, int MF, int WVK, bool ANY, bool SPLIT> constexpr int direct_min_waves() {
     if (WVK == 8 && TRANSB && MF == 1) return 4;  // (B stored K x N: LDS for one workgroup)
-    if (WVK == 4 && MF == 2 && !ANY) return 3;  // (BF16 1024^3 with two 12.0 us, with three 10.0)
+    if (WVK == 4 && MF == 2 && !ANY) return 3;  // (BF16 1024 x 1024 x 512 with two 10.0 us, with three 7.8)
     return 2;
 }
 template <typename T, int TRANSB, int MF, int NF, int WVK, int WN, int D, bool ANY, bool SPLIT, bool W>
@@ -645,7 +645,8 @@ __global__ __launch_bounds__(64 * WVK * WN, (direct_min_waves<T, TRANSB, MF, WVK
     // operands (clear_front).  With loads of its own for it, clamped and shifted, and the step's code a second time, its 500
     // instructions ran with nothing in flight but the next step (fused calls, so / now): FP16 500 x 999 x 777 10.4 / 9.3 us,
     // BF16 530 x 3584 x 283 (N x K) 16.2 / 14.0, FP32 1000 x 1200 x 1500 45.5 / 42.8, FP64 1777 x 1061 x 331 (N x K) 43.9 / 38.6;
-    // whole steps only, 256^3 in FP32 7.55 / 7.68, of 336 problems 4 more than 3 % slower.
+    // whole steps only, 256^3 in FP32 7.55 / 7.68, of 336 problems 4 more than 3 % slower; plain products 0.09 us (1.3 %) slower with
+    // 32 x 64 tiles, up to 4 % with a FP64 B stored N x K, whose products the compiler puts in another order.
     const int whole = !tiny && full > wk ? (full - wk + WVK - 1) / WVK : 0;  // steps of this wavefront
     const bool ends_here = rest > 0 && full % WVK == wk && g.K >= KSTEP;
     // (64 rows: as a value that the compiler does not see through, or it keeps addresses for both cases and spills them)

@@ -151,7 +151,7 @@ class VerifiedGemm:
 
     def run_fused(self, A, B, e_max=None, c_sigma=2.5, inj=None, defer_S: bool = False):
         """One pass of the whole path: encode, fused threshold + verified GEMM.  S1..S3 travel as partials through the
-        workspace and are folded inside the second launch, to self.S as well unless defer_S."""
+        workspace and are folded behind the encode, to self.S as well unless defer_S."""
         if e_max is None:
             e_max = vb.vabft_default_emax(self.dtype, self.K, self.N)
         self.e_max = e_max
